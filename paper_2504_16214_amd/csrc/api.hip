@@ -350,12 +350,18 @@ struct Fp8Plan { int bm, bn, splits, kb_per_split; };
 static bool fp8_plan(int M, int N, int K, Fp8Plan& pl) {
   const int KB = K / 128;
   int bm = M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : 128;
-  // 128 features per workgroup measured fastest at every token-tile height up to 128 (two or
-  // more workgroups per CU; 256 wide costs occupancy, 64 wide LDS traffic per matrix
-  // instruction).  Large problems take the 256 x 256 eight-wave tile (fewest LDS bytes per
-  // matrix instruction: 1.65-1.8 against 1.4-1.5 PFLOP/s) when it still yields two workgroups per CU.
+  // 128 features per workgroup measured fastest at every four-wave token-tile height up to 128 (two
+  // or more workgroups per CU; 256 wide costs occupancy, 64 wide LDS traffic per matrix instruction).
   int bn = 128;
-  if (M > 128 && N % 256 == 0 && (long long)((M + 255) / 256) * (N / 256) >= 512) { bm = 256; bn = 256; }
+  // More than 64 rows take the 256 x 256 two-group tile where its rounds over the 256 CUs are at
+  // least 60 % full: 4096 x 51200 x 5120 0.99 against 1.15 ms with the former 256 x 256 tile, 512 x
+  // 51200 151 against 205 us, 128 x 51200 61 against 76 us, 1024 x 10240 (160 tiles) 67 against 78 us;
+  // 320 tiles (62 %) tie, 80 tiles lose (200 x 20480: 60 against 44 us).  At 64 rows and fewer the
+  // small tiles stream the weights as fast with more workgroups in flight (64 x 65536 x 8192: 126
+  // against 134 us).
+  const long long tiles256 = (long long)((M + 255) / 256) * (N / 256);
+  const bool two_group = M > 64 && N % 256 == 0 && tiles256 * 5 >= 3 * 256 * ((tiles256 + 255) / 256);
+  if (two_group) { bm = 256; bn = 256; }
   // a few hundred rows: 64-token tiles when 128-token tiles would leave CUs without a second workgroup
   else if (M > 128 && N % 128 == 0 && (long long)((M + 127) / 128) * (N / 128) < 512) bm = 64;
   if (g_fp8_mt) { bm = 16 * g_fp8_mt; bn = 128; }
@@ -363,13 +369,13 @@ static bool fp8_plan(int M, int N, int K, Fp8Plan& pl) {
   const long long m_blocks = (M + bm - 1) / bm;
   while (bn > 64 && N % bn != 0) bn >>= 1;
   // small problems: narrower feature tiles first (more workgroups streaming weights) ...
-  while (bn > 64 && m_blocks * (N / bn) < 256) bn >>= 1;
+  while (bn > 64 && bm < 256 && m_blocks * (N / bn) < 256) bn >>= 1;
   if (g_fp8_nt) bn = 64 * g_fp8_nt;
   if ((bn != 64 && bn != 128 && bn != 256) || N % bn != 0 || (bm == 256 && bn == 64)) return false;
   const long long wgs = m_blocks * (N / bn);
   // ... then a split of the reduction, each split at least four blocks long
   int splits = 1;
-  if (wgs < 256) {
+  if (wgs < 256 && bm < 256) {
     splits = (int)((768 + wgs - 1) / wgs);
     if (splits > KB / 4) splits = KB / 4;
     if (splits > 16) splits = 16;
@@ -868,7 +874,8 @@ int fp8_blockwise_gemm(const uint8_t* A, const float* a_scale, const uint8_t* B,
   p.A = A; p.a_scale = a_scale; p.B = B; p.b_scale = b_scale;
   p.M = M; p.N = N; p.K = K;
   p.k_splits = pl.splits; p.kb_per_split = pl.kb_per_split; p.out_bf16 = out_dtype;
-  p.group_m = g_fp8_group_m ? g_fp8_group_m : 8;     // row blocks per tile group (4 ... 16 measured alike)
+  // row blocks per tile group: 4 for the 256 x 256 tile (8192^3 459 against 470 us at 8), 4 ... 16 alike elsewhere
+  p.group_m = g_fp8_group_m ? g_fp8_group_m : pl.bm == 256 ? 4 : 8;
   if (pl.splits > 1) {
     const size_t need = round_up((size_t)pl.splits * (size_t)M * (size_t)N * sizeof(float), 256);
     if (!workspace || workspace_bytes < need)
@@ -912,14 +919,17 @@ int fp8_moe_grouped_gemm(const uint8_t* A, const float* a_scale, int row_div, co
   if (rows_a * (unsigned long long)K >= (1ull << 32) || (unsigned long long)N * (unsigned long long)K >= (1ull << 32))
     return fail(MOE_UNSUPPORTED_SHAPE, "32-bit operand offsets: rows(A) * K and N * K must be below 2^32");
   const size_t cap = align_capacity(num_slots, E, block_m);
-  const int bn = N % 128 == 0 ? 128 : 64;
+  const int bn = block_m == 256 && N % 256 == 0 ? 256 : N % 128 == 0 ? 128 : 64;
   const long long grid = (long long)(cap / block_m) * (N / bn);
   if (cap > 0x7fffffffULL || grid > 0x7fffffffLL) return fail(MOE_UNSUPPORTED_SHAPE, "too many workgroups");
   fp8::GemmParams p = {};
   p.A = A; p.a_scale = a_scale; p.B = B; p.b_scale = b_scale; p.C = C;
   p.M = (int)cap; p.N = N; p.K = K;
   p.k_splits = 1; p.kb_per_split = K / 128; p.out_bf16 = out_dtype;
-  p.group_m = g_fp8_group_m ? g_fp8_group_m : 8;
+  // One row block at a time: an XCD then works on all feature tiles of one or two experts, whose
+  // rows of A stay in its L2 (256-expert layer at 4096 tokens 3.19 -> 3.07 ms against groups of
+  // eight, at 128 tokens 1.90 -> 1.88 ms).
+  p.group_m = g_fp8_group_m ? g_fp8_group_m : 1;
   p.sorted_slot_ids = sorted_slot_ids; p.block_expert_ids = block_expert_ids; p.num_padded = num_padded;
   p.num_slots = num_slots; p.row_div = row_div;
   p.b_expert_stride = (size_t)N * (size_t)K;
@@ -959,9 +969,19 @@ int fp8_silu_mul_quantize(const void* H, int S, int N, int dt, uint8_t* codes, f
 
 static thread_local int g_fp8_layer_block_m = 0;
 
-static int fp8_pick_block_m(long long S, int E) {
+static int fp8_pick_block_m(long long S, int E, int K, int N) {
   if (g_fp8_layer_block_m > 0) return g_fp8_layer_block_m;
   const long long avg = S / (E > 0 ? E : 1);
+  // 256-slot blocks (the two-group tile of fp8_moe_grouped_gemm, which skips a block's empty 32-row
+  // parts): every weight is fetched once per 256 rows.  From 64 rows per expert on if the smaller
+  // product's tiles fill their rounds over the CUs to 70 % (64 experts, K 2048, N 1408: 1000 tokens 197
+  // against 218 us, 3000 tokens 369 against 448; 8 experts, 144 tiles: 142 against 130), from 16 on
+  // in launches of many rounds (256 experts, K 7168, N 2048: 512 tokens 2.06 against 2.09 ms, 1024
+  // 2.25 against 2.49, 4096 3.07 against 3.95; at 8 rows per expert 32-slot blocks win by 1 %).
+  if (K % 256 == 0 && N % 128 == 0) {
+    const long long tiles = (S / 256 + (S < E ? S : E) / 2) * ((K < 2 * N ? K : 2 * N) / 256);
+    if (tiles >= 1024 ? avg >= 16 : avg >= 64 && tiles * 10 >= 7 * 256 * ((tiles + 255) / 256)) return 256;
+  }
   if (avg <= 32) return 32;      // measured: 32-token tiles stream the weights fastest at a few rows per expert
   if (avg >= 96) return 128;     // about one row block per expert: its weights are fetched once (measured +2 %)
   return 64;
@@ -1033,7 +1053,7 @@ int fp8_moe_layer(const void* X, const int32_t* topk_ids, const float* topk_weig
   uint8_t* aq = base + w.aq;
   float* sa = (float*)(base + w.sa);
   float* Y = (float*)(base + w.Y);
-  const int block_m = fp8_pick_block_m(S, E);
+  const int block_m = fp8_pick_block_m(S, E, K, N);
   const bool ev = g_nevents == 7;
   auto mark = [&](int i) { if (ev) (void)hipEventRecord((hipEvent_t)g_events[i], stream); };
 

@@ -37,19 +37,15 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ uint32_t to_bf16_bits(float x) {
-  uint32_t u = __float_as_uint(x);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0u;
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
-}
-__device__ __forceinline__ uint32_t to_f16_bits(float x) {
-  const _Float16 h = (_Float16)x;                 // round to nearest even
-  return (uint32_t)__builtin_bit_cast(uint16_t, h);
-}
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+// two float32 -> two 16-bit values in a word, round to nearest even (one v_cvt_pk_bf16_f32, or two
+// v_cvt_f16_f32 and a pack)
 template <int BF16>
 __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
-  return BF16 ? (to_bf16_bits(lo) | (to_bf16_bits(hi) << 16)) : (to_f16_bits(lo) | (to_f16_bits(hi) << 16));
+  if constexpr (BF16) return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
+  else return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), f16x2));
 }
 
 // Workgroup = WM x WN waves; wave (wm, wn) owns tokens [16 MT wm, 16 MT (wm + 1)) and features
@@ -318,6 +314,362 @@ fp8_blockwise_gemm_kernel(const GemmParams p) {
   }
 }
 
+// One token's 4 NT consecutive features in the output type (p.out_bf16: 0 fp16, 1 bf16, 2 float32).
+template <int NT>
+__device__ __forceinline__ void store_row(const GemmParams& p, size_t at, const f32x4 (&v)[NT]) {
+  if (p.k_splits > 1 || p.out_bf16 == 2) {      // a partial plane, or the result itself
+    float* dst = reinterpret_cast<float*>(p.C) + at;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<f32x4*>(dst + 4 * nt) = v[nt];
+    return;
+  }
+  uint16_t* dst = reinterpret_cast<uint16_t*>(p.C) + at;
+  uint32_t w[2 * NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    if (p.out_bf16 == 1) {
+      w[2 * nt] = pack2<1>(v[nt][0], v[nt][1]);
+      w[2 * nt + 1] = pack2<1>(v[nt][2], v[nt][3]);
+    } else {
+      w[2 * nt] = pack2<0>(v[nt][0], v[nt][1]);
+      w[2 * nt + 1] = pack2<0>(v[nt][2], v[nt][3]);
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < NT / 2; ++h)
+    *reinterpret_cast<u32x4*>(dst + 8 * h) = u32x4{w[4 * h], w[4 * h + 1], w[4 * h + 2], w[4 * h + 3]};
+}
+
+// ---- the 256 x 256 tile: two wave groups in turn on the matrix unit -------------------------------
+// Eight waves, two groups of four; a wave owns 64 features and every other 16-row sub-tile of the
+// workgroup's rows, waves w and w + 4 (one of each group) share a SIMD.  A reduction block is worked
+// off in clusters of two sub-tiles per wave (64 rows of the tile): a load phase (operand reads from
+// LDS, direct-to-LDS loads of later blocks) and a matrix phase (eight matrix instructions, each
+// followed by the scaled FMAs of the one three before it), a barrier after each.  The second group
+// runs one phase behind the first: on every SIMD one wave multiplies while the other loads.
+//
+// ML = live sub-tiles per wave (1 .. 8): rows past the matrix, or past an expert's slots, cost
+// nothing beyond the rounding to 32 rows.  The feature rows' operands stay in registers for a block.
+//
+// Why this shape.  Matrix instructions and the scaled FMAs (four per instruction) overlap fully when
+// they come from different waves of a SIMD or are three instructions apart; run in lockstep between
+// two barriers per block, as the former 256 x 256 tile did, the waves read LDS together, wait
+// together and sit in the wait states between an instruction and its own FMAs (matrix unit busy 41 %
+// of 4980 cycles per block).  In turns it is busy 57 % (8192^3, 2.14 GHz: the clock is power-limited).
+// Measured, former tile -> this one: 4096 x 51200 x 5120 1.19 -> 1.02 ms (1.81 -> 2.11 PFLOP/s), 8192^3
+// 0.51 -> 0.46 ms; FP8 layer of 256 experts at 4096 tokens (128-slot blocks on the 128 x 128 tile
+// before): gate/up product 2.44 -> 1.65 ms (4.5 TB/s of weights, each fetched once), layer 4.28 ->
+// 3.10 ms.  What is left: dense, the exposed stores of a round (110 of 1020 us) and power; grouped, HBM.
+template <int ML>
+struct PingGeom {
+  static constexpr int T = 512, BM = 256, BN = 256, NT = 4;
+  static constexpr int C = (ML + 1) / 2;                   // clusters per block
+  static constexpr int NBUF = C <= 2 ? 3 : 2;              // operand buffers
+  static constexpr int ROWS = C <= 2 ? 128 : 256;          // tile rows a buffer has room for
+  static constexpr int BOFF = ROWS * 128;
+  static constexpr int STAGE = BOFF + BN * 128;            // bytes per buffer: A rows, B rows
+  static constexpr int SR = ROWS / 32;                     // scale rows per wave and step
+  static constexpr int SOFF = NBUF * STAGE;                // activation scales: ring of four groups of four blocks
+  static constexpr int TOFF = SOFF + 4 * ROWS * 16;        // A row behind every tile row
+  static constexpr int LDS = TOFF + ROWS * 4;
+  static_assert(LDS <= 160 * 1024, "LDS");
+};
+constexpr int kPingLds = PingGeom<4>::LDS > PingGeom<8>::LDS ? PingGeom<4>::LDS : PingGeom<8>::LDS;
+
+#define FP8_PHASE_FENCE()                 \
+  {                                       \
+    __builtin_amdgcn_sched_barrier(0);    \
+    asm volatile("" ::: "memory");        \
+  }
+#define FP8_PHASE_BARRIER()               \
+  {                                       \
+    FP8_PHASE_FENCE()                     \
+    __builtin_amdgcn_s_barrier();         \
+    FP8_PHASE_FENCE()                     \
+  }
+// vmcnt(n) (six bits, split 4 + 2), lgkmcnt(0) if lg
+constexpr int waitcnt_imm(int vm, bool lg) { return (vm & 15) | ((vm >> 4) << 14) | 0x70 | (lg ? 0 : 0xF00); }
+
+// One tile.  row0: first row (dense) or first slot-table entry (grouped); B, bs: the tile's weight
+// matrix and block scales; [kb0, kb0 + nkb): its reduction blocks.
+template <int ML>
+__device__ __forceinline__ void
+ping_tile(const GemmParams& p, unsigned char* lds, int row0, int n0, const uint8_t* B, const float* bs, int kb0, int nkb,
+          int split) {
+  using G = PingGeom<ML>;
+  constexpr int NT = G::NT, C = G::C, NBUF = G::NBUF, BN = G::BN, SR = G::SR;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+  const int ln = lane & 15, lj = lane >> 4;
+  const bool grouped = p.sorted_slot_ids != nullptr;
+  const int KB = p.K >> 7;
+
+  // A row behind a tile row: dense = the row itself (rows past the matrix repeat its last row and are
+  // never stored); grouped = slot / row_div (padding rows read row 0)
+  int* const atab = reinterpret_cast<int*>(lds + G::TOFF);
+  if (tid < G::ROWS) {
+    int r;
+    if (grouped) {
+      const int slot = p.sorted_slot_ids[row0 + tid];
+      r = (slot >= 0 && slot < p.num_slots) ? slot / p.row_div : 0;
+    } else {
+      r = row0 + tid < p.M ? row0 + tid : p.M - 1;
+    }
+    atab[tid] = r;
+  }
+  __syncthreads();
+
+  // DMA sources: lane (8 lanes per row) at position sc of tile row r fetches chunk sc ^ (r & 7).  A wave
+  // sends rows of its own group only (cluster c: 64 c + 32 (wn >> 1) + 16 wm + 8 (wn & 1) + [0, 8)), so
+  // their buffer is free as soon as the group has read it.
+  const int srow = lane >> 3, sc = lane & 7;
+  const uint32_t chunk = 16u * (uint32_t)(sc ^ (srow & 7));
+  const int arow = 32 * (wn >> 1) + 16 * wm + 8 * (wn & 1);
+  uint32_t aoff[C], boff[4];
+#pragma unroll
+  for (int c = 0; c < C; ++c) aoff[c] = (uint32_t)atab[64 * c + arow + srow] * (uint32_t)p.K + chunk;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = 8 * wave + srow;      // LDS row 64 i + 16 nt + l holds feature 64 i + 16 (l >> 2) + 4 nt + (l & 3)
+    boff[i] = (uint32_t)(n0 + 64 * i + 16 * ((r >> 2) & 3) + 4 * (r >> 4) + (r & 3)) * (uint32_t)p.K + chunk;
+  }
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)p.A, 0, (int)0xffffffffu, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, (int)0xffffffffu, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)p.a_scale, 0, (int)0xffffffffu, 0x00020000);
+  const float* bssrc = bs + (size_t)((n0 + wn * 64) >> 7) * KB + kb0;
+  typedef __attribute__((address_space(3))) void* lptr_t;
+  // (block indices past the end are clamped: a valid block is loaded and never consumed, so every wave
+  // issues the same number of loads per block and the vmcnt arithmetic holds)
+  auto clampk = [&](int i) __attribute__((always_inline)) { return i < nkb ? i : nkb - 1; };
+  auto dma_a = [&](int base, int c, int kb) __attribute__((always_inline)) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lptr_t)(lds + base + (64 * c + arow) * 128), 16, (int)aoff[c], (kb0 + kb) * 128, 0, 0);
+  };
+  auto dma_b = [&](int base, int i, int kb) __attribute__((always_inline)) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lptr_t)(lds + base + G::BOFF + (64 * i + 8 * wave) * 128), 16, (int)boff[i], (kb0 + kb) * 128, 0, 0);
+  };
+  // Activation scales: four blocks at a time, so that a row's scales share a cache line (one 4-byte
+  // load per row and block touches 256 lines per block, half as many as the operands do).  Step t
+  // brings SR rows' scales of block group t / 4 per wave; four steps bring all.
+  auto scale_row = [&](int t) __attribute__((always_inline)) { return atab[((t & 3) * 8 + wave) * SR + ((lane >> 2) & (SR - 1))]; };
+  auto dma_s = [&](int t, int r) __attribute__((always_inline)) {
+    if (lane < 4 * SR) {
+      int k = (t & ~3) + (lane & 3);
+      if (k >= nkb) k = nkb - 1;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rs, (lptr_t)(lds + G::SOFF + ((t >> 2) & 3) * (G::ROWS * 16) + ((t & 3) * 8 + wave) * (SR * 16)), 4,
+          (r * KB + kb0 + k) * 4, 0, 0, 0);
+    }
+  };
+
+  // operand positions inside a buffer (sub-tile 2 mt + wm of the tile is the wave's mt)
+  const int xpos = (16 * wm + ln) * 128 + 16 * (lj ^ (ln & 7));                   // + 4096 mt
+  const int wpos = G::BOFF + (wn * 64 + ln) * 128 + 16 * (lj ^ (ln & 7));         // + 2048 nt
+  const int spos = G::SOFF + (16 * wm + ln) * 16;                                 // + 512 mt
+  auto read_op = [&](int at) __attribute__((always_inline)) -> i32x8 {
+    const i32x4 lo = *reinterpret_cast<const i32x4*>(lds + at);
+    const i32x4 hi = *reinterpret_cast<const i32x4*>(lds + (at ^ 64));
+    return i32x8{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+  };
+
+  f32x4 acc[ML][NT];
+#pragma unroll
+  for (int mt = 0; mt < ML; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  i32x8 wa[NT], xa[2];
+  f32x4 part[4];
+  float sp[2], spp[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) part[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  sp[0] = sp[1] = spp[0] = spp[1] = 0.f;
+  auto read_w = [&](int base, int nt) __attribute__((always_inline)) {
+    wa[nt] = read_op((base + wpos) + 2048 * nt);
+  };
+
+  // ---- when what is sent --------------------------------------------------------------------------
+  // C <= 2 (three buffers): load phase 0 of block kb sends all of block kb + 2 into the buffer of block
+  // kb - 1, which both groups have read; the block's feature operands are read in its load phase 0.
+  // C >= 3 (two buffers): block kb + 2 goes to the buffer of block kb while that is still being worked
+  // off: the feature rows once both groups hold them in registers (from load phase 1 on), a cluster's
+  // rows once its group has read them; the last cluster's rows follow in load phase 0 of block kb + 1.
+  // The next block's feature operands are read in the last matrix phase, each after its last use.
+  // Before the barrier at which a group first reads block kb + 1 every wave has waited for its part of
+  // it, in a load phase whose younger loads (kWait of them) may stay in flight.
+  constexpr bool REFILL = C >= 3;
+  constexpr int kWaitPhase = C >= 3 ? C - 2 : 0;
+  constexpr int kWait = C == 4 ? 1 + 3 + 4 : C == 3 ? 1 + 4 : 4 + C + 1;
+  auto send_prologue = [&](int base, int kb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dma_b(base, i, kb);
+#pragma unroll
+    for (int c = 0; c < (REFILL ? C - 1 : C); ++c) dma_a(base, c, kb);
+  };
+#pragma unroll
+  for (int t = 0; t < 8; ++t) dma_s(t, scale_row(t));
+  send_prologue(0, 0);
+  if constexpr (REFILL) dma_a(0, C - 1, 0);
+  send_prologue(G::STAGE, clampk(1));
+  __builtin_amdgcn_s_waitcnt(waitcnt_imm(REFILL ? 4 + C - 1 : 4 + C, true));      // block 0 has landed
+  FP8_PHASE_BARRIER()
+  if (wm == 1) FP8_PHASE_BARRIER()
+  if constexpr (REFILL) {
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) read_w(0, nt);
+  }
+
+  int srow_next = scale_row(0);      // the row behind the lane's next scale (step kb + 8)
+  float sb = bssrc[0];
+  int cur = 0, nxt = G::STAGE, far = NBUF == 3 ? 2 * G::STAGE : 0;      // buffers of blocks kb, kb + 1, kb + 2
+  for (int kb = 0; kb < nkb; ++kb) {
+    const int kn = clampk(kb + 1), kf = clampk(kb + 2);
+    const float sb_next = bssrc[kn];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int H = 2 * c + 1 < ML ? 2 : 1;                 // sub-tiles of this cluster
+      const int HP = c > 0 ? 2 : ((ML & 1) ? 1 : 2);        // ... of the previous one
+      const int cp = c > 0 ? c - 1 : C - 1;
+      // ---- load phase ----
+      if constexpr (!REFILL) {
+        if (c == 0) {
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) read_w(cur, nt);
+        }
+      }
+      float sa[2] = {0.f, 0.f};
+#pragma unroll
+      for (int h = 0; h < H; ++h) xa[h] = read_op((cur + xpos) + (2 * c + h) * 4096);
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+        sa[h] = *reinterpret_cast<const float*>(lds + spos + ((kb >> 2) & 3) * (G::ROWS * 16) + (kb & 3) * 4 + (2 * c + h) * 512);
+      if constexpr (C == 4) {
+        if (c == 0) dma_a(nxt, 3, kn);
+        if (c == 1) { dma_b(far, 0, kf); dma_b(far, 1, kf); dma_s(kb + 8, srow_next); }
+        if (c == 2) { dma_b(far, 2, kf); dma_b(far, 3, kf); dma_a(far, 0, kf); dma_a(far, 1, kf); }
+        if (c == 3) dma_a(far, 2, kf);
+      } else if constexpr (C == 3) {
+        if (c == 0) dma_a(nxt, 2, kn);
+        if (c == 1) { dma_b(far, 0, kf); dma_b(far, 1, kf); dma_s(kb + 8, srow_next); dma_a(far, 0, kf); }
+        if (c == 2) { dma_b(far, 2, kf); dma_b(far, 3, kf); dma_a(far, 1, kf); }
+      } else {
+        if (c == 0) { send_prologue(far, kf); dma_s(kb + 8, srow_next); }
+      }
+      if (c == (C > 1 ? 1 : 0)) srow_next = scale_row(kb + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      if (c == kWaitPhase) __builtin_amdgcn_s_waitcnt(waitcnt_imm(kWait, true));
+      else __builtin_amdgcn_s_waitcnt(waitcnt_imm(63, true));
+      FP8_PHASE_BARRIER()
+      // ---- matrix phase ----
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int h = 0; h < H; ++h) sp[h] = sa[h] * sb;
+#pragma unroll
+      for (int i = 0; i < 4 * H; ++i) {
+        const int nt = H == 2 ? i >> 1 : i, h = H == 2 ? i & 1 : 0;
+        part[i & 3] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wa[nt], xa[h], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        // fold in the product of three instructions ago (of the previous cluster for the first three)
+        if (i >= 3) {
+          const int j = i - 3, jn = H == 2 ? j >> 1 : j, jh = H == 2 ? j & 1 : 0;
+          acc[2 * c + jh][jn] += part[j & 3] * sp[jh];
+        } else {
+          const int j = i + 4 * HP - 3, jn = HP == 2 ? j >> 1 : j, jh = HP == 2 ? j & 1 : 0;
+          acc[2 * cp + jh][jn] += part[j & 3] * spp[jh];
+        }
+        if constexpr (REFILL) {
+          if (c == C - 1 && h == H - 1) read_w(nxt, nt);      // the operand's last use: fetch the next block's
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+      for (int h = 0; h < H; ++h) spp[h] = sp[h];
+      FP8_PHASE_BARRIER()
+    }
+    sb = sb_next;
+    const int t = cur;
+    cur = nxt; nxt = NBUF == 3 ? far : t; far = NBUF == 3 ? t : cur;
+  }
+  {
+    constexpr int HP = (ML & 1) ? 1 : 2;
+#pragma unroll
+    for (int j = 4 * HP - 3; j < 4 * HP; ++j) {
+      const int jn = HP == 2 ? j >> 1 : j, jh = HP == 2 ? j & 1 : 0;
+      acc[2 * (C - 1) + jh][jn] += part[j & 3] * spp[jh];
+    }
+  }
+  if (wm == 0) FP8_PHASE_BARRIER()
+  __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));      // no direct-to-LDS load outlives the workgroup
+
+  const int f0 = n0 + wn * 64 + 16 * lj;
+#pragma unroll
+  for (int mt = 0; mt < ML; ++mt) {
+    int t = row0 + 32 * mt + 16 * wm + ln;
+    if (grouped) {
+      t = p.sorted_slot_ids[t];
+      if (t < 0 || t >= p.num_slots) continue;
+    } else if (t >= p.M) {
+      continue;
+    }
+    store_row<NT>(p, ((size_t)split * p.M + t) * p.N + f0, acc[mt]);
+  }
+}
+
+__global__ void __launch_bounds__(512, 1)
+fp8_pingpong_kernel(const GemmParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  constexpr int BM = 256, BN = 256;
+  const bool grouped = p.sorted_slot_ids != nullptr;
+  const int n_blocks = p.N / BN;
+  const int m_blocks = grouped ? *p.num_padded / BM : (p.M + BM - 1) / BM;
+  const int total = grouped ? m_blocks * n_blocks : (int)gridDim.x;
+  int L;
+  {
+    const int id = blockIdx.x, q = total >> 3, r = total & 7, x = id & 7, idx = id >> 3;
+    if (idx >= q + (x < r ? 1 : 0)) return;       // (uniform over the workgroup: nobody reaches a barrier)
+    L = x * q + (x < r ? x : r) + idx;
+  }
+  const int split = L / (m_blocks * n_blocks);
+  L -= split * (m_blocks * n_blocks);
+  const int per_group = p.group_m * n_blocks;
+  const int grp = L / per_group;
+  const int rem = L - grp * per_group;
+  int m_in = m_blocks - grp * p.group_m;
+  if (m_in > p.group_m) m_in = p.group_m;
+  const int nb = rem / m_in, mb = grp * p.group_m + (rem - nb * m_in);
+  const int row0 = mb * BM, n0 = nb * BN;
+  const int KB = p.K >> 7, kb0 = split * p.kb_per_split;
+  const int nkb = KB - kb0 < p.kb_per_split ? KB - kb0 : p.kb_per_split;      // >= 1 by construction of the grid
+  const uint8_t* B = p.B;
+  const float* bs = p.b_scale;
+  // live rows: to the end of the matrix, or of the expert's slots (packed at the front of its blocks)
+  int live = p.M - row0 < BM ? p.M - row0 : BM;
+  if (grouped) {
+    const int e = p.block_expert_ids[mb];
+    if (e < 0) return;
+    B += (size_t)e * p.b_expert_stride;
+    bs += (size_t)e * p.bs_expert_stride;
+    live = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int slot = p.sorted_slot_ids[row0 + 32 * i];
+      live += (slot >= 0 && slot < p.num_slots) ? 32 : 0;
+    }
+  }
+  const int ml = __builtin_amdgcn_readfirstlane((live + 31) / 32);
+  switch (ml) {
+    case 1: ping_tile<1>(p, lds, row0, n0, B, bs, kb0, nkb, split); break;
+    case 2: ping_tile<2>(p, lds, row0, n0, B, bs, kb0, nkb, split); break;
+    case 3: ping_tile<3>(p, lds, row0, n0, B, bs, kb0, nkb, split); break;
+    case 4: ping_tile<4>(p, lds, row0, n0, B, bs, kb0, nkb, split); break;
+    case 5: ping_tile<5>(p, lds, row0, n0, B, bs, kb0, nkb, split); break;
+    case 6: ping_tile<6>(p, lds, row0, n0, B, bs, kb0, nkb, split); break;
+    case 7: ping_tile<7>(p, lds, row0, n0, B, bs, kb0, nkb, split); break;
+    case 8: ping_tile<8>(p, lds, row0, n0, B, bs, kb0, nkb, split); break;
+    default: break;
+  }
+}
+
 // Sum of the float32 planes in plane order, one rounding.  n4 = M * N / 4.
 __global__ void __launch_bounds__(256)
 fp8_split_reduce_kernel(const f32x4* __restrict__ planes, int k_splits, long long n4, void* __restrict__ C,
@@ -356,19 +708,38 @@ static int launch_one(const GemmParams& p, hipStream_t stream) {
 }
 
 // Tiles.  bm = tokens per workgroup in {16, 32, 64, 128, 256}, bn = features per workgroup in
-// {64, 128, 256}; bm = 256 runs eight waves (2 x 4), everything else four (1 x 4).  Returns a
+// {64, 128, 256}; bm = 256 runs eight waves (the two-group tile at bn = 256, 2 x 4 waves in step at
+// bn = 128), everything else four (1 x 4).  Returns a
 // hipError_t, or -1 for an unknown tile.  Measured and not compiled in: three LDS buffers (two
 // blocks in flight: no gain on the small tiles, -30 % on 128 x 128 where it costs the second
 // workgroup per CU) and the non-temporal cache policy on the weight loads (-18 % on streaming
 // shapes).
+static int launch_ping(const GemmParams& p, hipStream_t stream) {
+  auto kern = fp8_pingpong_kernel;
+  constexpr int kMaxDev = 64;
+  static bool allowed[kMaxDev] = {};
+  int dev = 0;
+  hipError_t err = hipGetDevice(&dev);
+  if (err != hipSuccess) return (int)err;
+  if (dev < 0 || dev >= kMaxDev || !allowed[dev]) {
+    err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kPingLds);
+    if (err != hipSuccess) return (int)err;
+    if (dev >= 0 && dev < kMaxDev) allowed[dev] = true;
+  }
+  const int grid = ((p.M + 255) / 256) * (p.N / 256) * p.k_splits;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(512), kPingLds, stream, p);
+  return (int)hipGetLastError();
+}
+
 int launch_fp8_gemm(const GemmParams& p, int bm, int bn, hipStream_t stream) {
+  if (bm == 256 && bn == 256) return launch_ping(p, stream);
 #define FP8_TILE(BMv, BNv, WMv, WNv, MTv, NTv, NSv)                                   \
   if (bm == BMv && bn == BNv) return launch_one<WMv, WNv, MTv, NTv, NSv>(p, stream);
   FP8_TILE(16, 64, 1, 4, 1, 1, 2)   FP8_TILE(16, 128, 1, 4, 1, 2, 2)   FP8_TILE(16, 256, 1, 4, 1, 4, 2)
   FP8_TILE(32, 64, 1, 4, 2, 1, 2)   FP8_TILE(32, 128, 1, 4, 2, 2, 2)   FP8_TILE(32, 256, 1, 4, 2, 4, 2)
   FP8_TILE(64, 64, 1, 4, 4, 1, 2)   FP8_TILE(64, 128, 1, 4, 4, 2, 2)   FP8_TILE(64, 256, 1, 4, 4, 4, 2)
   FP8_TILE(128, 64, 1, 4, 8, 1, 2)  FP8_TILE(128, 128, 1, 4, 8, 2, 2)  FP8_TILE(128, 256, 1, 4, 8, 4, 2)
-  FP8_TILE(256, 256, 2, 4, 8, 4, 2) FP8_TILE(256, 128, 2, 4, 8, 2, 2)
+  FP8_TILE(256, 128, 2, 4, 8, 2, 2)
 #undef FP8_TILE
   return -1;
 }

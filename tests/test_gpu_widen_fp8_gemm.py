@@ -347,3 +347,53 @@ def test_gemm_with_split_reduction_is_graph_capturable():
         assert torch.equal(out.view(torch.int16), eager.view(torch.int16)), f"replay {rep}"
         junk = torch.randn(1 << 16, device="cuda").sum().item()
         assert junk == junk
+
+
+# ------------------------------------------------------------------ the two-group 256 x 256 tile
+@pytest.mark.parametrize("Mr,kblocks,splits", [(1, 1, 1), (32, 2, 1), (33, 3, 1), (64, 9, 1), (65, 1, 1), (96, 4, 1),
+                                               (97, 5, 1), (128, 13, 1), (129, 2, 1), (160, 8, 1), (161, 6, 1),
+                                               (192, 1, 1), (193, 3, 1), (224, 10, 1), (225, 1, 1), (256, 17, 1),
+                                               (257, 7, 1), (500, 5, 2), (256, 2, 2), (70, 12, 3)])
+def test_two_group_tile_row_counts_and_block_counts(Mr, kblocks, splits):
+    """Every number of live 32-row parts (1 ... 8, full and ragged; each has a schedule of its own),
+    against reductions shorter than, equal to and beyond the loads in flight, split and unsplit."""
+    say(f"fp8 two-group tile M={Mr} blocks={kblocks} splits={splits}")
+    inp = make_fp8_inputs(Fp8GemmConfig("pp", M=Mr, N=512, K=128 * kblocks, seed=900 + Mr + kblocks))
+    M_.fp8_set_plan_override(16, 4, splits, 0)
+    try:
+        check(inp, what=f"two-group M={Mr} blocks={kblocks}")
+        if splits == 1 and kblocks < 4:
+            check(inp, dtype=torch.float16, what="fp16")
+    finally:
+        M_.fp8_set_plan_override(0, 0, 0, 0)
+
+
+@pytest.mark.parametrize("K,row_div_is_topk", [(128, True), (640, False), (1152, True)])
+def test_two_group_tile_grouped_row_counts(K, row_div_is_topk):
+    """256-slot blocks whose experts hold 1 ... 600 rows: every live-part count, a second and a third
+    block of one expert, an expert without rows, ignored ids."""
+    import gpu_util as U
+    counts = [1, 31, 32, 33, 70, 97, 128, 150, 0, 190, 200, 230, 256, 257, 600]
+    E, N, topk = len(counts), 256, 2
+    flat = np.repeat(np.arange(E, dtype=np.int32), counts)
+    flat = np.concatenate([flat, np.array([-1] * (2 + len(flat) % 2), np.int32)])
+    np.random.default_rng(5).shuffle(flat)
+    T = flat.size // topk
+    say(f"fp8 two-group grouped K={K} slots={flat.size}")
+    _, a, sa, b, sb = _grouped_case(T, topk, E, N, K, row_div_is_topk, seed=940 + K)
+    ids = flat.reshape(T, topk)
+    row_div, S = (topk if row_div_is_topk else 1), T * topk
+    al = U.run_align(torch.from_numpy(ids).cuda(), E, 256)
+    C = torch.full((S, N), float("nan"), dtype=torch.float32, device="cuda")
+    M_.fp8_moe_grouped_gemm(torch.from_numpy(a).cuda(), torch.from_numpy(sa).cuda(), row_div,
+                            torch.from_numpy(b).cuda(), torch.from_numpy(sb).cuda(),
+                            al["sorted_slot_ids"], al["block_expert_ids"], al["num_padded"], S, 256, C)
+    torch.cuda.synchronize()
+    got = C.to(torch.float64).cpu().numpy()
+    want, valid = F.grouped_blockwise_gemm(a, sa, row_div, b, sb, flat)
+    assert np.isnan(got[~valid]).all() and not np.isnan(got[valid]).any()
+    for e in range(E):
+        slots = np.nonzero(flat == e)[0]
+        if slots.size:
+            rows = slots // row_div
+            assert float((np.abs(got[slots] - want[slots]) / error_bound(want[slots], a[rows], sa[rows], b[e], sb[e])).max()) <= 1.0
