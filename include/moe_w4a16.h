@@ -292,14 +292,17 @@ int moe_w4a16_routed_layer(const void* X, const float* logits, const float* bias
  * moe_layer_block_m: the bucketing block size the layer picks for these sizes.
  *
  * moe_set_block_m_override: force the bucketing block of moe_w4a16_layer (16 ... 256) instead of
- * the built-in choice; 0 restores it.  Thread-local.
+ * the built-in choice; 0 restores it.  256 takes the two-group tile where the shapes admit it.
+ * Thread-local.
  *
  * moe_layer_block_m_for: the same with the layer's shapes known (group-128 layers with
  * K % 1024 == 0 and N % 1024 == 0 and more than 28 rows per expert take 128-slot blocks for
- * the eight-wave tile); honours moe_set_block_m_override.
+ * the eight-wave tile); honours moe_set_block_m_override.  It is the block to bucket by for the
+ * staged calls; large batches of such layers (see twogroup_pays in api.hip) bucket by 256 inside
+ * the layer call, for a tile that only the layer can use.
  *
- * moe_set_wide_tiles: 0 = use the eight-wave 128-token tile whenever block_m >= 128 and the shape
- * allows it (default), 1 = never (the four-wave tiles serve every block size).  Thread-local.
+ * moe_set_wide_tiles: 0 = use the eight-wave tiles (128 tokens, or 256 in the layer) whenever the block
+ * and the shape allow it (default), 1 = never (the four-wave tiles serve every block size).  Thread-local.
  *
  * moe_last_gemm_plan: what the last grouped / dense GEMM launch issued from this thread used:
  * plan9 (HOST pointer to 9 ints) = {mt, nt, ks, register_scales, tiles_per_workgroup,

@@ -10,6 +10,7 @@
 #include "../../include/moe_w4a16.h"
 #include "fp8_gemm.hpp"
 #include "gemm_kernel.hpp"
+#include "gemm_twogroup.hpp"
 
 
 namespace moe {
@@ -17,6 +18,7 @@ namespace moe {
 int launch_align(const int32_t*, int, int, int, int, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*,
                  hipStream_t);
 int launch_silu_mul(const void*, void*, long long, int, int, hipStream_t);
+int launch_prepare_rows(const void*, long long, int, int, void*, float*, hipStream_t);
 int launch_repack(const int32_t*, int, int, int, int, int32_t*, hipStream_t);
 int launch_awq_import(const int32_t*, const int32_t*, const void*, int, int, int, int, int32_t*, void*, uint8_t*,
                       hipStream_t);
@@ -317,10 +319,26 @@ static int pick_k_splits(long long S, int E, int K, int N, int block_m) {
   return want < 1 ? 1 : (int)want;
 }
 
+// Does the layer run on the two-group 256-slot tile (gemm_twogroup.hpp)?  It fetches and unpacks an
+// expert's weights once per 256 rows and keeps the matrix unit busier; below, the 32-slot and the
+// eight-wave 128-slot tiles stream the weights as fast or spread a small launch over more workgroups.
+// Measured (us, former choice -> two-group; 256 experts, K 7168, N 2048): fp16 512 tokens 1304 -> 1407,
+// 1024 1714 -> 1657, 1536 1991 -> 1915, 4096 4087 -> 3535; bf16, whose zero points cost the other
+// tiles a second matrix instruction, 512 tokens a tie, 717 1691 -> 1618, 1024 1933 -> 1810, 4096 5436
+// -> 4208.  Launches of few tiles lose by their last round: fp16 16 experts (K 4096, N 2048), 2048
+// tokens (768 tiles) 324 -> 359, 4096 tokens (1280) 562 -> 583, 8 experts (K 4096, N 14336), 1024
+// tokens (1536) 1008 -> 940; bf16 64 experts (K 2048, N 1024), 512 tokens (704) 113 -> 124, 1024
+// tokens (896) 186 -> 180, 16 experts, 2048 tokens (768) 440 -> 412.
+static bool twogroup_pays(long long S, int E, int K, int N, int dt) {
+  const long long avg = S / (E > 0 ? E : 1);
+  const long long tiles = (S / 256 + (S < E ? S : E) / 2) * ((2LL * N + K) / 256);      // of both products
+  return dt == MOE_BF16 ? avg >= 20 && tiles >= 750 : avg >= 29 && tiles >= 1400;
+}
+
 struct Workspace {
-  size_t counts, offsets, num_padded, sorted, blocks, act, Y, total;
+  size_t counts, offsets, num_padded, sorted, blocks, act, Y, base, rsum, total;
 };
-static Workspace carve(long long T, int K, int N, int E, int topk) {
+static Workspace carve(long long T, int K, int N, int E, int topk, int dt) {
   const long long S = T * topk;
   Workspace w;
   size_t o = 0;
@@ -333,6 +351,11 @@ static Workspace carve(long long T, int K, int N, int E, int topk) {
   // float32 (combined unrounded); one plane per reduction split (at most 8, small batches only)
   w.Y = o;           o += round_up((size_t)S * K * 4 * std::max(pick_k_splits(S, E, K, N, pick_block_m(S, E)),
                                                             pick_k_splits(S, E, K, N, pick_block_m(S, E, true))), 256);
+  w.base = o;        // what the layer cannot do without
+  // row sums of act for the bf16 operands of the two-group tile; a caller's workspace without them
+  // runs the layer on the eight-wave tile instead
+  w.rsum = o;
+  if (dt == MOE_BF16 && K % 1024 == 0 && N % 1024 == 0 && twogroup_pays(S, E, K, N, dt)) o += round_up((size_t)S * (N / 128) * 4, 256);
   w.total = o;
   return w;
 }
@@ -511,9 +534,8 @@ int moe_combine_masked(const void* Y, const float* topk_weights, const int32_t* 
 }
 
 size_t moe_w4a16_layer_workspace_bytes(int T, int K, int N, int E, int topk, moe_dtype dt) {
-  (void)dt;
   if (T < 0 || K < 1 || N < 1 || E < 1 || topk < 1) return 0;
-  return carve(T, K, N, E, topk).total;
+  return carve(T, K, N, E, topk, (int)dt).total;
 }
 
 int moe_layer_block_m(int T, int E, int topk) {
@@ -561,6 +583,34 @@ static int route_and_align(const RouteArgs& r, int T, int E, int topk, int block
   return MOE_OK;
 }
 
+// One product of the layer on the two-group tile.
+static int run_twogroup(const void* A, const float* bias_rows, int row_div, const int32_t* qw, const void* sc,
+                        const uint8_t* z, const int32_t* sorted, const int32_t* blocks, const int32_t* num_padded,
+                        int num_slots, int E, int N_out, int K_in, int dt, int fuse, int pre, void* C, hipStream_t stream) {
+  TwoGroupParams p;
+  p.A = A; p.bias_rows = bias_rows; p.row_div = row_div;
+  p.qweight = qw; p.scales = sc; p.zeros = z;
+  p.sorted_slot_ids = sorted; p.block_expert_ids = blocks; p.num_padded = num_padded;
+  p.num_slots = num_slots; p.E = E; p.N_out = N_out; p.K_in = K_in; p.C = C; p.pre = pre;
+  p.n_tiles = N_out / 256;
+  // Several tiles per workgroup where the reduction is short (a tile's start and end cost about as
+  // much as four stages), as long as a few rounds over the CUs remain.
+  const long long est_blocks = (num_slots + 255) / 256 + (num_slots < E ? num_slots : E) / 2;
+  int tpw = 56 / (K_in / 128);
+  if (tpw < 1) tpw = 1;
+  if (tpw > p.n_tiles) tpw = p.n_tiles;
+  while (tpw > 1 && (p.n_tiles % tpw != 0 || est_blocks * (p.n_tiles / tpw) < 1024)) --tpw;
+  if (g_force_tpw > 0) tpw = g_force_tpw < p.n_tiles ? g_force_tpw : p.n_tiles;
+  p.tiles_per_wg = tpw;
+  const long long grid = (long long)(align_capacity(num_slots, E, 256) / 256) * ((p.n_tiles + tpw - 1) / tpw);
+  if (grid > 0x7fffffffLL) return fail(MOE_UNSUPPORTED_SHAPE, "grid too large");
+  const int plan[9] = {16, 2, 128, 1, tpw, 1, K_in, fuse, 8};
+  for (int i = 0; i < 9; ++i) g_last_plan[i] = plan[i];
+  const int err = (dt == MOE_F16 ? launch_twogroup_f16 : launch_twogroup_bf16)(p, fuse, (int)grid, stream);
+  if (err != 0) return hip_fail(err, "two-group GEMM launch");
+  return MOE_OK;
+}
+
 static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_weights,
                       const int32_t* qw1, const void* s1, const uint8_t* z1,
                       const int32_t* qw2, const void* s2, const uint8_t* z2,
@@ -582,8 +632,8 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
     return fail(MOE_INVALID_ARGUMENT, "null pointer argument");
   if (((uintptr_t)workspace % 256) != 0) return fail(MOE_INVALID_ARGUMENT, "workspace must be 256-byte aligned");
   if (((uintptr_t)out % 16) != 0) return fail(MOE_INVALID_ARGUMENT, "out must be 16-byte aligned");
-  const Workspace w = carve(T, K, N, E, topk);
-  if (workspace_bytes < w.total)
+  const Workspace w = carve(T, K, N, E, topk, (int)dt);
+  if (workspace_bytes < w.base)
     return fail(MOE_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", workspace_bytes, w.total);
   const long long S = (long long)T * topk;
   if (S > 0x7fffffffLL / 2) return fail(MOE_UNSUPPORTED_SHAPE, "T*topk too large");
@@ -596,8 +646,17 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   int32_t* blocks = (int32_t*)(base + w.blocks);
   void* act = base + w.act;
   void* Y = base + w.Y;
+  // Two-group tile: its shapes, every tuning hook that asks for another kernel at rest, panels and
+  // words aligned for its loads, 32-bit offsets in range, room for the row sums (bf16).
+  const bool two_group =
+      layer_wide_ok(K, N, group_size) && g_scale_path != 1 && g_force_ksplit == 0 &&
+      (g_force_block_m == 256 || (g_force_block_m == 0 && twogroup_pays(S, E, K, N, (int)dt))) &&
+      (dt == MOE_F16 || workspace_bytes >= w.rsum + (size_t)S * (N / 128) * 4) &&
+      (((uintptr_t)X | (uintptr_t)qw1 | (uintptr_t)qw2) % 16) == 0 && (((uintptr_t)s1 | (uintptr_t)s2) % 8) == 0 &&
+      (((uintptr_t)z1 | (uintptr_t)z2) % 4) == 0 && (long long)N * K < (1LL << 31) &&
+      (long long)E * 2 * N * (K / 128) < (1LL << 31) && (long long)T * K * 2 < (1LL << 31) && S * N * 2 < (1LL << 31);
   // a forced bucketing block wins; a forced token tile (tuning hook) also fixes the block
-  const int block_m = g_force_block_m > 0 ? g_force_block_m
+  const int block_m = two_group ? 256 : g_force_block_m > 0 ? g_force_block_m
                       : (g_force_mt == 1 || g_force_mt == 2 || g_force_mt == 4 || g_force_mt == 8)
                           ? 16 * g_force_mt : pick_block_m(S, E, layer_wide_ok(K, N, group_size), !pre && layer_wide_ok(K, N, group_size));
   const bool ev = g_nevents == 5;
@@ -614,6 +673,27 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   }
 
   if (ev) (void)hipEventRecord((hipEvent_t)g_events[1], stream);
+  if (two_group) {
+    // the reordered rows of X and their sums live where Y will be written: Y is written last
+    float* const xsum = dt == MOE_BF16 ? (float*)((unsigned char*)Y + round_up((size_t)T * K * 2, 256)) : nullptr;
+    float* const asum = dt == MOE_BF16 ? (float*)(base + w.rsum) : nullptr;
+    err = launch_prepare_rows(X, T, K, (int)dt, Y, xsum, stream);
+    if (err != 0) return hip_fail(err, "activation reorder launch");
+    int st = run_twogroup(Y, xsum, topk, qw1, s1, z1, sorted, blocks, num_padded, (int)S, E, 2 * N, K, (int)dt, 1, pre, act, stream);
+    if (st != MOE_OK) return st;
+    if (ev) (void)hipEventRecord((hipEvent_t)g_events[2], stream);
+    if (asum) {
+      err = launch_prepare_rows(act, S, N, (int)dt, nullptr, asum, stream);
+      if (err != 0) return hip_fail(err, "row sum launch");
+    }
+    st = run_twogroup(act, asum, 1, qw2, s2, z2, sorted, blocks, num_padded, (int)S, E, K, N, (int)dt, 0, pre, Y, stream);
+    if (st != MOE_OK) return st;
+    if (ev) (void)hipEventRecord((hipEvent_t)g_events[3], stream);
+    err = launch_combine(Y, 1, 1, topk_weights, topk_ids, E, out, T, topk, K, (int)dt, stream);
+    if (err != 0) return hip_fail(err, "combine launch");
+    if (ev) (void)hipEventRecord((hipEvent_t)g_events[4], stream);
+    return MOE_OK;
+  }
   GemmArgs g1{X, topk, qw1, s1, z1, sorted, blocks, num_padded, (int)S, E, 2 * N, K, group_size, block_m,
               (int)dt, act, N, N, 0};
   g1.pre = pre;
@@ -694,7 +774,7 @@ int moe_w4a16_layer_noalloc(const void* X, const int32_t* topk_ids, const float*
                             void* stream) {
   if (T < 0 || K < 1 || N < 1 || E < 1 || topk < 1)
     return fail(MOE_INVALID_ARGUMENT, "need T >= 0 and positive K, N, E, topk, group_size");
-  const size_t need = carve(T, K, N, E, topk).total;
+  const size_t need = carve(T, K, N, E, topk, (int)dt).base;
   if (need > kStaticScratchBytes)
     return fail(MOE_WORKSPACE_TOO_SMALL,
                 "moe_w4a16_layer_noalloc: these sizes need %zu bytes of scratch, the built-in array holds %zu; "
