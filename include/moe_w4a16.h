@@ -250,7 +250,8 @@ int moe_route_align(const float* logits, const float* bias, int T, int E, int to
 
 /*
  * Router + layer on one stream: moe_route_align into tables held in the workspace, then the two
- * grouped GEMMs and the combine of moe_w4a16_layer (four launches up to 64 tokens, five beyond).
+ * grouped GEMMs and the combine of moe_w4a16_layer (four launches up to 64 tokens, five beyond; three
+ * for the few tokens that need no bucketing).
  * Arguments as for the two; `workspace` of at least moe_w4a16_routed_layer_workspace_bytes(...)
  * bytes, 256-byte aligned.
  */
@@ -267,7 +268,7 @@ int moe_w4a16_routed_layer(const void* X, const float* logits, const float* bias
  * moe_set_stage_events: while set (n == 5), moe_w4a16_layer records the given
  * hipEvent_t handles on its stream: events[0] before bucketing, [1] before the
  * first grouped GEMM, [2] before the second, [3] before the combine, [4] after
- * it.  Pass (NULL, 0) to clear.  Thread-local.
+ * it (a few tokens: nothing between [0] and [1] but the router, nor between [3] and [4]).  Pass (NULL, 0) to clear.  Thread-local.
  *
  * moe_set_tile_override: force the grouped GEMM tile (tokens per tile =
  * 16*mt, output features per workgroup = 64*nt) instead of the built-in
@@ -308,7 +309,8 @@ int moe_w4a16_routed_layer(const void* X, const float* logits, const float* bias
  * plan9 (HOST pointer to 9 ints) = {mt, nt, ks, register_scales, tiles_per_workgroup,
  * reduction_splits, reduction_indices_per_split, fused_silu, waves}.  A workgroup covers 16*mt
  * rows and tiles_per_workgroup consecutive tiles of 16*nt*waves features (half as many act
- * columns when fused).  Tests use it to aim samples at tile and tile-group borders.
+ * columns when fused).  All zeros after a layer call of a few tokens, which runs as vector products
+ * without a tile.  Tests use it to aim samples at tile and tile-group borders.
  */
 int moe_set_stage_events(void* const* events, int n);
 

@@ -8,6 +8,7 @@
 
 #include "../../include/fp8_blockwise_gemm.h"
 #include "../../include/moe_w4a16.h"
+#include "few_tokens.hpp"
 #include "fp8_gemm.hpp"
 #include "gemm_kernel.hpp"
 #include "gemm_twogroup.hpp"
@@ -611,6 +612,17 @@ static int run_twogroup(const void* A, const float* bias_rows, int row_div, cons
   return MOE_OK;
 }
 
+// The vector-product kernels (few_tokens.hip) have two launches instead of four, but read an expert's
+// weights once for every slot.  us, tiled / vector, f16, K x N, experts, slots:
+//   bytes of all slots: 7168x2048, 256:  8: 58.5 / 47   16: 88 / 88   32: 140 / 159    -> S N K up to 128 M
+//   slots that share an expert (about S^2 / 2E read again): 1024x1024, 8:  16: 21.7 / 17.2   32: 21.9 / 29.6;
+//     4096x4096, 4:  2: 33 / 21   4: 33.7 / 34.3   7: 37 / 57;   2048x2048, 2:  4: 24.2 / 17.1   8: 24.3 / 28.4;
+//     2048x1408, 64:  24: 39 / 35   48: 55 / 59                                     -> S^2 N K up to 40 M E
+//   256x512, 8:  32: 18.5 / 10.5   128: 21.3 / 28                                   -> S up to 32
+static bool few_tokens_pay(long long S, int E, int K, int N) {
+  const long long nk = (long long)N * K;
+  return S <= 32 && S * nk <= 128000000LL && S * S * nk <= 40000000LL * E;
+}
 static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_weights,
                       const int32_t* qw1, const void* s1, const uint8_t* z1,
                       const int32_t* qw2, const void* s2, const uint8_t* z2,
@@ -660,9 +672,33 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
                       : (g_force_mt == 1 || g_force_mt == 2 || g_force_mt == 4 || g_force_mt == 8)
                           ? 16 * g_force_mt : pick_block_m(S, E, layer_wide_ok(K, N, group_size), !pre && layer_wide_ok(K, N, group_size));
   const bool ev = g_nevents == 5;
+  auto mark = [&](int i) { if (ev) (void)hipEventRecord((hipEvent_t)g_events[i], stream); };
+  int err;
+  // A few tokens: vector products, unless a tuning hook asks for a tile; whole groups of 128, 16-byte
+  // aligned words and activations, 32-bit offsets into an expert.
+  const bool few = few_tokens_pay(S, E, K, N) && group_size == 128 && few_tokens_fit(topk, K, N) && g_force_block_m == 0 &&
+                   g_force_mt == 0 && g_force_nt == 0 && g_force_ksplit == 0 && g_scale_path == 0 && g_force_tpw == 0 && g_wide_mode == 0 &&
+                   (((uintptr_t)X | (uintptr_t)qw1 | (uintptr_t)qw2) % 16) == 0 && (((uintptr_t)s1 | (uintptr_t)s2) % 2) == 0 &&
+                   (long long)N * K < (1LL << 31);
+  if (few) {
+    mark(0);
+    if (route) {
+      err = launch_route_topk(route->logits, route->bias, T, E, topk, route->ids, route->weights, stream);
+      if (err != 0) return hip_fail(err, "router launch");
+    }
+    mark(1);
+    err = launch_few_gate_up(X, topk_ids, qw1, s1, z1, act, T, topk, E, K, N, (int)dt, pre, stream);
+    if (err != 0) return hip_fail(err, "few-token gate/up launch");
+    mark(2);
+    err = launch_few_down(act, topk_ids, topk_weights, qw2, s2, z2, out, T, topk, E, K, N, (int)dt, pre, stream);
+    if (err != 0) return hip_fail(err, "few-token down launch");
+    for (int& v : g_last_plan) v = 0;       // no tile
+    mark(3);
+    mark(4);
+    return MOE_OK;
+  }
 
   if (ev) (void)hipEventRecord((hipEvent_t)g_events[0], stream);
-  int err;
   if (route) {
     const int rst = route_and_align(*route, T, E, topk, block_m, counts, offsets, sorted, blocks, num_padded, stream);
     if (rst != MOE_OK) return rst;
