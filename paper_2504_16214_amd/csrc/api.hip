@@ -6,6 +6,8 @@
 #include <stdint.h>
 #include <stdio.h>
 
+#include <math.h>
+
 #include "../../include/fp8_blockwise_gemm.h"
 #include "../../include/moe_w4a16.h"
 #include "few_tokens.hpp"
@@ -370,6 +372,45 @@ static thread_local int g_fp8_mt = 0, g_fp8_nt = 0, g_fp8_splits = 0, g_fp8_grou
 
 struct Fp8Plan { int bm, bn, splits, kb_per_split; };
 
+// at least four blocks of the reduction in a split
+static int fp8_splits_for(int want, int most, int KB) {
+  int s = want < most ? want : most;
+  if (s > KB / 4) s = KB / 4;
+  return s < 1 ? 1 : s;
+}
+
+// 65 rows and more that do not fill the 256 x 256 tile: tile and split by the time they should take.  A
+// workgroup needs t microseconds for a block of 128 reduction indices with two workgroups on its CU (the
+// value depends little on the second one), about four blocks to start and end; a last round that
+// is partly full costs 0.4 of what is missing; a split costs a launch and 8 bytes an output.  Fitted to
+// 30 shapes of 65 to 1024 rows (N 2048 ... 10240, K 5120 ... 25600), it is within 12 % of the times of
+// the tiles that matter.  us, with the former rule (768 workgroups wanted, no split from 256 on) / now:
+//   128 x 10240 x 5120 29.9 / 22.2, 256 x 5120 x 8192 38.1 / 25.5, 200 x 5120 x 25600 107 / 51,
+//   512 x 5120 x 25600 126 / 89, 1024 x 2048 x 7168 39.3 / 31.6
+static void fp8_medium_plan(int M, int N, int KB, int& bm, int& bn, int& splits) {
+  static const struct { int bm, bn; double t; } kTiles[] = {{64, 128, 0.65}, {128, 128, 1.02}, {64, 64, 0.5}, {128, 64, 0.75}};
+  double best = -1;
+  for (const auto& c : kTiles) {
+    if (N % c.bn != 0 || (c.bm == 128 && c.bn == 64 && N % 128 == 0)) continue;
+    const double wgs = (double)((M + c.bm - 1) / c.bm) * (N / c.bn);
+    for (int s = 1; s <= fp8_splits_for(16, 16, KB); ++s) {
+      const double r = wgs * s / 512, full = ceil(r), f = r <= 1 ? 1 : r + 0.4 * (full - r);
+      const double us = f * ((KB + s - 1) / s + 4) * c.t + (s > 1 ? 4 + (double)s * M * N / 750e3 : 0);
+      if (best < 0 || us < best) { best = us; bm = c.bm; bn = c.bn; splits = s; }
+    }
+  }
+}
+
+// The splits whose planes a caller has to bring: a shape that needs none here runs unsplit, and one that
+// needs fewer than it would like runs with those it has room for.
+static int fp8_splits_needed(int M, int N, int K, int planned) {
+  const int bm = M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : M > 128 && N % 128 == 0 && (long long)((M + 127) / 128) * (N / 128) < 512 ? 64 : 128;
+  const long long mb = (M + bm - 1) / bm;
+  const long long wgs = N % 128 == 0 && mb * (N / 128) >= 256 ? mb * (N / 128) : mb * (N / 64);
+  const int had = wgs >= 256 ? 1 : fp8_splits_for((int)((768 + wgs - 1) / wgs), 16, K / 128);
+  return had < planned ? had : planned;
+}
+
 // false: the (forced) plan does not fit the shape
 static bool fp8_plan(int M, int N, int K, Fp8Plan& pl) {
   const int KB = K / 128;
@@ -384,26 +425,28 @@ static bool fp8_plan(int M, int N, int K, Fp8Plan& pl) {
   // small tiles stream the weights as fast with more workgroups in flight (64 x 65536 x 8192: 126
   // against 134 us).
   const long long tiles256 = (long long)((M + 255) / 256) * (N / 256);
-  const bool two_group = M > 64 && N % 256 == 0 && tiles256 * 5 >= 3 * 256 * ((tiles256 + 255) / 256);
+  // A reduction of fewer than four blocks does not hide its start and its write-out (4096 x 12800 x 256:
+  // 47 against 45 us).
+  const bool two_group = M > 64 && N % 256 == 0 && KB >= 4 && tiles256 * 5 >= 3 * 256 * ((tiles256 + 255) / 256);
   if (two_group) { bm = 256; bn = 256; }
-  // a few hundred rows: 64-token tiles when 128-token tiles would leave CUs without a second workgroup
-  else if (M > 128 && N % 128 == 0 && (long long)((M + 127) / 128) * (N / 128) < 512) bm = 64;
   if (g_fp8_mt) { bm = 16 * g_fp8_mt; bn = 128; }
   if (bm != 16 && bm != 32 && bm != 64 && bm != 128 && bm != 256) return false;
-  const long long m_blocks = (M + bm - 1) / bm;
-  while (bn > 64 && N % bn != 0) bn >>= 1;
-  // small problems: narrower feature tiles first (more workgroups streaming weights) ...
-  while (bn > 64 && bm < 256 && m_blocks * (N / bn) < 256) bn >>= 1;
-  if (g_fp8_nt) bn = 64 * g_fp8_nt;
-  if ((bn != 64 && bn != 128 && bn != 256) || N % bn != 0 || (bm == 256 && bn == 64)) return false;
-  const long long wgs = m_blocks * (N / bn);
-  // ... then a split of the reduction, each split at least four blocks long
   int splits = 1;
-  if (wgs < 256 && bm < 256) {
-    splits = (int)((768 + wgs - 1) / wgs);
-    if (splits > KB / 4) splits = KB / 4;
-    if (splits > 16) splits = 16;
-    if (splits < 1) splits = 1;
+  if (M > 64 && !two_group && !g_fp8_mt && !g_fp8_nt) {
+    fp8_medium_plan(M, N, KB, bm, bn, splits);
+  } else {
+    const long long m_blocks = (M + bm - 1) / bm;
+    while (bn > 64 && N % bn != 0) bn >>= 1;
+    // small problems: narrower feature tiles first (more workgroups streaming weights) ...
+    while (bn > 64 && bm < 256 && m_blocks * (N / bn) < 256) bn >>= 1;
+    if (g_fp8_nt) bn = 64 * g_fp8_nt;
+    if ((bn != 64 && bn != 128 && bn != 256) || N % bn != 0 || (bm == 256 && bn == 64)) return false;
+    // ... then a split of the reduction up to two workgroups per CU, each split at least four blocks
+    // long.  A split costs 8 bytes an output and a workgroup beyond the second per CU a second round:
+    // 64 x 10240 x 5120 20.5 us at 5 splits (800 workgroups), 16.7 at 3; 16 x 5120 x 8192 14.1 at 10, 12.1 at 6;
+    // 64 x 2048 x 7168 13.5 at 14, 10.4 at 8.
+    const long long wgs = m_blocks * (N / bn);
+    if (wgs < 256 && bm < 256) splits = fp8_splits_for(512 / (int)wgs, wgs < 32 ? 16 : 8, KB);
   }
   if (g_fp8_splits) splits = g_fp8_splits;
   if (splits < 1 || splits > KB) return false;
@@ -978,11 +1021,25 @@ int fp8_blockwise_gemm(const uint8_t* A, const float* a_scale, const uint8_t* B,
   if (((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) % 16 != 0 || ((uintptr_t)a_scale | (uintptr_t)b_scale) % 4 != 0)
     return fail(MOE_INVALID_ARGUMENT, "A, B, C must be 16-byte aligned, the scales 4-byte aligned");
   if (C == (const void*)A || C == (const void*)B) return fail(MOE_INVALID_ARGUMENT, "C must not alias an input");
+  const size_t plane = (size_t)M * (size_t)N * sizeof(float);
   Fp8Plan pl;
   if (!fp8_plan(M, N, K, pl)) return fail(MOE_UNSUPPORTED_SHAPE, "the forced FP8 plan does not fit M=%d N=%d K=%d", M, N, K);
   if ((unsigned long long)M * (unsigned long long)K >= (1ull << 32) ||
       (unsigned long long)N * (unsigned long long)K >= (1ull << 32))
     return fail(MOE_UNSUPPORTED_SHAPE, "the FP8 GEMM addresses A and B with 32-bit offsets: M * K and N * K must be below 2^32");
+  if (pl.splits > 1 && !g_fp8_mt && !g_fp8_nt && !g_fp8_splits) {
+    const size_t have = workspace && (uintptr_t)workspace % 256 == 0 ? workspace_bytes : 0;
+    const int least = fp8_splits_needed(M, N, K, pl.splits);
+    if (have < round_up((size_t)pl.splits * plane, 256) && (least == 1 || have >= round_up((size_t)least * plane, 256))) {
+      const int KB = K / 128;
+      int fit = (int)(have / plane);
+      if (fit < 1) fit = 1;
+      if (fit > pl.splits) fit = pl.splits;
+      pl.kb_per_split = (KB + fit - 1) / fit;
+      pl.splits = (KB + pl.kb_per_split - 1) / pl.kb_per_split;
+      if (pl.splits > 1 && have < round_up((size_t)pl.splits * plane, 256)) { pl.splits = 1; pl.kb_per_split = KB; }
+    }
+  }
   const long long m_blocks = (M + pl.bm - 1) / pl.bm;
   const long long grid = m_blocks * (N / pl.bn) * pl.splits;
   if (grid > 0x7fffffffLL) return fail(MOE_UNSUPPORTED_SHAPE, "too many workgroups");
@@ -993,7 +1050,7 @@ int fp8_blockwise_gemm(const uint8_t* A, const float* a_scale, const uint8_t* B,
   // row blocks per tile group: 4 for the 256 x 256 tile (8192^3 459 against 470 us at 8), 4 ... 16 alike elsewhere
   p.group_m = g_fp8_group_m ? g_fp8_group_m : pl.bm == 256 ? 4 : 8;
   if (pl.splits > 1) {
-    const size_t need = round_up((size_t)pl.splits * (size_t)M * (size_t)N * sizeof(float), 256);
+    const size_t need = round_up((size_t)pl.splits * plane, 256);
     if (!workspace || workspace_bytes < need)
       return fail(MOE_WORKSPACE_TOO_SMALL, "FP8 GEMM workspace: need %zu bytes, got %zu", need, workspace_bytes);
     if ((uintptr_t)workspace % 256 != 0) return fail(MOE_INVALID_ARGUMENT, "workspace must be 256-byte aligned");

@@ -397,3 +397,37 @@ def test_two_group_tile_grouped_row_counts(K, row_div_is_topk):
         if slots.size:
             rows = slots // row_div
             assert float((np.abs(got[slots] - want[slots]) / error_bound(want[slots], a[rows], sa[rows], b[e], sb[e])).max()) <= 1.0
+
+
+@pytest.mark.parametrize("Mr,N,K", [(16, 640, 8192), (65, 128, 512), (100, 192, 1152), (129, 640, 5248), (260, 448, 4096),
+                                    (1030, 384, 896)])
+def test_split_choice_from_a_few_to_a_thousand_rows(Mr, N, K):
+    """The default tile and split on either side of 64 rows: feature counts in 64s and in 128s,
+    splits that do not divide the reduction, a ragged last row block."""
+    say(f"fp8 gemm split choice M={Mr} N={N} K={K}")
+    check(make_fp8_inputs(Fp8GemmConfig("s", M=Mr, N=N, K=K, seed=Mr + N)), what=f"M={Mr} N={N} K={K}")
+
+
+def test_a_shape_that_can_do_without_planes_takes_any_workspace():
+    """700 x 1536 x 8192 likes three planes but runs without: no workspace, a misaligned one and one of
+    two planes are accepted; a shape that cannot do without its planes still refuses."""
+    Mr, N, K = 700, 1536, 8192
+    say(f"fp8 gemm without planes M={Mr} N={N} K={K}")
+    plane, full = Mr * N * 4, M_.fp8_blockwise_gemm_workspace_bytes(Mr, N, K)
+    assert full >= 2 * plane
+    inp = make_fp8_inputs(Fp8GemmConfig("w", M=Mr, N=N, K=K, seed=8))
+    want = F.blockwise_gemm(inp.a_codes, inp.a_scale, inp.b_codes, inp.b_scale, "bf16")
+    bound = error_bound(want, inp.a_codes, inp.a_scale, inp.b_codes, inp.b_scale)
+    A, sa, B, sb = (torch.from_numpy(x).cuda() for x in (inp.a_codes, inp.a_scale, inp.b_codes, inp.b_scale))
+    buf = torch.full((full + 256,), 255, dtype=torch.uint8, device="cuda")
+    for ws in (None, buf[:plane], buf[:2 * plane + 256], buf[16:full + 16], buf[:full]):
+        C = torch.full((Mr, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        M_.fp8_blockwise_gemm(A, sa, B, sb, C, ws)
+        torch.cuda.synchronize()
+        got = C.to(torch.float64).cpu().numpy()
+        assert not np.isnan(got).any() and float((np.abs(got - want) / bound).max()) <= 1.0
+    small = make_fp8_inputs(Fp8GemmConfig("w2", M=16, N=128, K=2048, seed=9))
+    A, sa, B, sb = (torch.from_numpy(x).cuda() for x in (small.a_codes, small.a_scale, small.b_codes, small.b_scale))
+    C = torch.empty(16, 128, dtype=torch.bfloat16, device="cuda")
+    with pytest.raises(RuntimeError, match="workspace"):
+        M_.fp8_blockwise_gemm(A, sa, B, sb, C, buf[:M_.fp8_blockwise_gemm_workspace_bytes(16, 128, 2048) - 256])
