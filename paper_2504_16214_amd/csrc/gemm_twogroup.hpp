@@ -67,7 +67,8 @@ struct TwoGroupGeom {
   static constexpr int SR = RROWS / 32;                     // row sums: rows per wave and step
   static constexpr int ROFF = NBUF * STAGE;                 // ring of four groups of four stages
   static constexpr int TOFF = ROFF + 4 * RROWS * 16;        // slot of every tile row
-  static constexpr int WOFF = TOFF + 256 * 4;               // STREAM: three buffers of 256 rows x 128 bytes
+  static constexpr int ZOFF = TOFF + 256 * 4;               // zeros, as large as one group of the ring
+  static constexpr int WOFF = ZOFF + RROWS * 16;            // STREAM: three buffers of 256 rows x 128 bytes
   static constexpr int LDS = WOFF + (STREAM ? 3 * 32768 : 0);
   static_assert(LDS <= 160 * 1024, "LDS");
 };
@@ -136,6 +137,7 @@ tg_tile(const TwoGroupParams& p, unsigned char* lds, int row0, int e, int tile0,
     const int s = tid < 32 * ML ? p.sorted_slot_ids[row0 + tid] : -1;
     slots[tid] = s >= 0 && s < p.num_slots ? s : -1;
   }
+  if (DT == kBF16 && tid < G::RROWS) *reinterpret_cast<u32x4*>(lds + G::ZOFF + tid * 16) = u32x4{0, 0, 0, 0};
   __syncthreads();
   auto arow_of = [&](int r) __attribute__((always_inline)) { const int s = slots[r]; return s < 0 ? 0 : s / p.row_div; };
 
@@ -332,10 +334,15 @@ tg_tile(const TwoGroupParams& p, unsigned char* lds, int row0, int e, int tile0,
     }
     const float sc = from_bits16<DT>((uint16_t)sb);
     if (__builtin_expect(__ballot(sc == 0.f) != 0ull, 0)) {
-      // rare: a group with scale 0 contributes nothing (q == z everywhere); a real branch
+      // rare: a group with scale 0 contributes exactly nothing; a real branch.  fp16: q == z everywhere.
+      // bf16: operands 0.0, and the caller takes no row sums away (47 * sum from the matrix unit and
+      // from the row sums are not added in the same order, so they would not cancel)
       asm volatile("" ::: "memory");
-      const uint32_t zw = zz * 0x11111111u;
-      if (sc == 0.f) w[0] = w[1] = u32x4{zw, zw, zw, zw};
+      const uint32_t zw = DT == kF16 ? zz * 0x11111111u : 0u;
+      if (sc == 0.f) {
+        w[0] = w[1] = u32x4{zw, zw, zw, zw};
+        if constexpr (DT == kBF16) ctx.c0 = 0u;
+      }
     }
     return sc;
   };
@@ -352,15 +359,16 @@ tg_tile(const TwoGroupParams& p, unsigned char* lds, int row0, int e, int tile0,
       (([&] {
          constexpr int r = Rs;
          float rs = 1.f;
-         // bf16: 47 * (row sum) of the lane's 16 rows of a sub-tile
+         // bf16: 47 * (row sum) of the lane's 16 rows of a sub-tile, from `sums` on (zeros: scale 0)
          floatx4_t nr[4];
+         int sums = 0;
          auto load_sums = [&](int mt) __attribute__((always_inline)) {
            if constexpr (DT == kBF16) {
 #pragma unroll
              for (int c4 = 0; c4 < 4; ++c4) {
                const int row = mt * 32 + 8 * c4 + 4 * lh;
                nr[c4] = *reinterpret_cast<const floatx4_t*>(
-                   lds + G::ROFF + ((gst >> 2) & 3) * (G::RROWS * 16) + (row / SR) * (SR * 16) + r * (SR * 4) + (row & (SR - 1)) * 4);
+                   lds + sums + (row / SR) * (SR * 16) + r * (SR * 4) + (row & (SR - 1)) * 4);
              }
            }
          };
@@ -405,6 +413,7 @@ tg_tile(const TwoGroupParams& p, unsigned char* lds, int row0, int e, int tile0,
              const float sc = group_ctx(s_cur, z_cur, r, ctx, w);
              rs = sc == 0.f ? 1.f : unit * __builtin_amdgcn_rcpf(sc);
              unit = sc == 0.f ? unit : sc;
+             if constexpr (DT == kBF16) sums = sc == 0.f ? G::ZOFF : G::ROFF + ((gst >> 2) & 3) * (G::RROWS * 16);
            }
 #pragma unroll
            for (int i = 0; i < WPP; ++i) bw[i] = tg_unpack<DT>(w[(i0 + i) >> 2][(i0 + i) & 3], ctx, uk);

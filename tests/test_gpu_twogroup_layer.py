@@ -92,6 +92,29 @@ def test_every_live_part_count(dtype, K, N, zero_scales):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_a_zero_scale_contributes_exactly_nothing(dtype):
+    """Every live-part count.  A down row whose scales are all zero gives exact zeros; one whose only scale
+    is its last group's 2^-20 gives the product of that group alone, which anything left behind by the seven
+    groups before it would drown (their products are expressed in units of 1: one float32 rounding of
+    them is as large as the whole result).  Bound in the 2-norm: two 16-bit roundings (activation, output)."""
+    inp = _inputs(dtype, 1024, 1024, [1, 33, 70, 100, 150, 170, 200, 256], seed=803)
+    c = inp.cfg
+    inp.s2_bits[:, 16, :] = 0
+    inp.s2_bits[:, 32, :] = 0
+    inp.s2_bits[:, 32, -1] = O.encode_bits(np.array([2.0 ** -20]), dtype)[0]
+    print(f"two-group layer {dtype}, rows of zero scales", flush=True)
+    got = U.dev_to_f64(_layer(inp))
+    assert np.all(got[:, 16] == 0)
+    want = O.layer(O.decode_bits(inp.x_bits, dtype), inp.topk_ids, inp.topk_weights, inp.qw1,
+                   O.decode_bits(inp.s1_bits, dtype), inp.z1, inp.qw2, O.decode_bits(inp.s2_bits, dtype),
+                   inp.z2, c.group, dtype)
+    # (fp16: an output of 2^-15 is subnormal and rounds to a multiple of 2^-24)
+    abs_step = 2.0 ** -25 if dtype == "f16" else 0.0
+    rms = np.sqrt(np.mean((got[:, 32] - want[:, 32]) ** 2))
+    assert rms <= 2.0 ** -7 * np.sqrt(np.mean(want[:, 32] ** 2)) + 2 * abs_step
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("tiles", [1, 3, 8])
 def test_tiles_per_workgroup(dtype, tiles):
     """Walking several feature tiles with one load pipeline gives the same bits as one tile each."""
