@@ -642,7 +642,7 @@ fp8_pingpong_kernel(const GemmParams p) {
   const int nkb = KB - kb0 < p.kb_per_split ? KB - kb0 : p.kb_per_split;      // >= 1 by construction of the grid
   const uint8_t* B = p.B;
   const float* bs = p.b_scale;
-  // live rows: to the end of the matrix, or of the expert's slots (packed at the front of its blocks)
+  // live rows: to the end of the matrix, or to the last slot in the block's table (in whole 32-row parts)
   int live = p.M - row0 < BM ? p.M - row0 : BM;
   if (grouped) {
     const int e = p.block_expert_ids[mb];
@@ -651,9 +651,10 @@ fp8_pingpong_kernel(const GemmParams p) {
     bs += (size_t)e * p.bs_expert_stride;
     live = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int slot = p.sorted_slot_ids[row0 + 32 * i];
-      live += (slot >= 0 && slot < p.num_slots) ? 32 : 0;
+    for (int i = 0; i < 4; ++i) {
+      const int slot = p.sorted_slot_ids[row0 + 64 * i + (threadIdx.x & 63)];
+      const unsigned long long any = __ballot(slot >= 0 && slot < p.num_slots);
+      if (any) live = 64 * i + (any >> 32 ? 64 : 32);
     }
   }
   const int ml = __builtin_amdgcn_readfirstlane((live + 31) / 32);

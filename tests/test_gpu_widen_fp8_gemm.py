@@ -399,6 +399,34 @@ def test_two_group_tile_grouped_row_counts(K, row_div_is_topk):
             assert float((np.abs(got[slots] - want[slots]) / error_bound(want[slots], a[rows], sa[rows], b[e], sb[e])).max()) <= 1.0
 
 
+@pytest.mark.parametrize("front", [1, 31, 32, 130, 254])
+def test_two_group_tile_reads_the_whole_table_of_a_block(front):
+    """A block's table may hold ignored entries anywhere, not only behind its slots: `front` of them
+    first, then every third one."""
+    import gpu_util as U
+    E, N, K, S = 3, 256, 512, 150
+    say(f"fp8 two-group table with {front} ignored entries in front")
+    _, a, sa, b, sb = _grouped_case(S, 1, E, N, K, True, seed=960)
+    flat = np.full(S, -1, np.int32)
+    table, nxt = np.full(256 * E, S, np.int32), 0
+    for e in range(E):
+        for i in range(front, 256):
+            if i % 3 and nxt < 50 * (e + 1):
+                table[256 * e + i], flat[nxt] = nxt, e
+                nxt += 1
+    C = torch.full((S, N), float("nan"), dtype=torch.float32, device="cuda")
+    M_.fp8_moe_grouped_gemm(torch.from_numpy(a).cuda(), torch.from_numpy(sa).cuda(), 1, torch.from_numpy(b).cuda(),
+                            torch.from_numpy(sb).cuda(), U.i32(table), U.i32(np.arange(E)), U.i32([256 * E]), S, 256, C)
+    torch.cuda.synchronize()
+    got = C.to(torch.float64).cpu().numpy()
+    want, valid = F.grouped_blockwise_gemm(a, sa, 1, b, sb, flat)
+    assert np.isnan(got[~valid]).all() and not np.isnan(got[valid]).any()
+    for e in range(E):
+        s = np.nonzero(flat == e)[0]
+        if s.size:
+            assert float((np.abs(got[s] - want[s]) / error_bound(want[s], a[s], sa[s], b[e], sb[e])).max()) <= 1.0
+
+
 @pytest.mark.parametrize("Mr,N,K", [(16, 640, 8192), (65, 128, 512), (100, 192, 1152), (129, 640, 5248), (260, 448, 4096),
                                     (1030, 384, 896)])
 def test_split_choice_from_a_few_to_a_thousand_rows(Mr, N, K):
