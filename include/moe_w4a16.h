@@ -206,7 +206,8 @@ int moe_w4a16_layer_noalloc(const void* X, const int32_t* topk_ids, const float*
  *
  * moe_w4a16_layer_prepacked: moe_w4a16_layer with qw1p = repack(W1, paired 0) and
  * qw2p = repack(W2, paired 1); scales and zero points stay in their original layout.
- * Needs group_size == 128, K % 1024 == 0, N % 1024 == 0.  Same results bit for bit.
+ * Needs group_size == 128, K % 1024 == 0, N % 1024 == 0, scales 16-byte and zero points 8-byte aligned
+ * (any T; otherwise MOE_UNSUPPORTED_SHAPE).  Same results bit for bit.
  */
 int moe_repack_qweight(const int32_t* qweight, int E, int N_out, int K_in, int paired, int32_t* out, void* stream);
 int moe_w4a16_layer_prepacked(const void* X, const int32_t* topk_ids, const float* topk_weights,

@@ -692,6 +692,15 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
     return fail(MOE_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", workspace_bytes, w.total);
   const long long S = (long long)T * topk;
   if (S > 0x7fffffffLL / 2) return fail(MOE_UNSUPPORTED_SHAPE, "T*topk too large");
+  // Operand-order weights: the same shapes and alignments at every token number, whichever kernel runs.
+  if (pre) {
+    if ((((uintptr_t)X | (uintptr_t)qw1 | (uintptr_t)qw2) % 16) != 0 || (((uintptr_t)s1 | (uintptr_t)s2) % 2) != 0)
+      return fail(MOE_INVALID_ARGUMENT, "X and the packed weights must be 16-byte, scales 2-byte aligned");
+    if (group_size != 128 || K % 1024 != 0 || N % 1024 != 0 || (((uintptr_t)s1 | (uintptr_t)s2) % 16) != 0 ||
+        (((uintptr_t)z1 | (uintptr_t)z2) % 8) != 0 || (long long)E * 2 * N * (K / 128) >= (1LL << 31))
+      return fail(MOE_UNSUPPORTED_SHAPE, "operand-order weights need group_size 128, K %% 1024 == 0, N %% 1024 == 0, "
+                  "16-byte aligned scales and 8-byte aligned zero points");
+  }
 
   unsigned char* base = (unsigned char*)workspace;
   int32_t* counts = (int32_t*)(base + w.counts);

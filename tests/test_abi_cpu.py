@@ -105,6 +105,22 @@ def test_validation_before_launch_returns_status(binding):
     assert lib.moe_set_tile_override(0, 0) == 0
 
 
+@pytest.mark.parametrize("T", [1, 4, 64, 4096])
+@pytest.mark.parametrize("what", ["K", "N", "group", "scales", "zeros"])
+def test_prepacked_layer_refuses_the_same_weights_at_every_token_number(binding, T, what):
+    """Refused before any launch (the dummy pointers are never dereferenced), also where a few tokens
+    run on kernels that could read the weights."""
+    lib = binding.load_library()
+    K, N, E, topk, g = (1152 if what == "K" else 1024), (640 if what == "N" else 1024), 8, 2, (64 if what == "group" else 128)
+    p, ws = 0x10000, binding.moe_w4a16_layer_workspace_bytes(T, K, N, E, topk, 0)
+    s, z = p + (2 if what == "scales" else 0), p + (4 if what == "zeros" else 0)
+    for order in ((s, z, p, p), (p, p, s, z)):
+        s1, z1, s2, z2 = order
+        assert lib.moe_w4a16_layer_prepacked(p, p, p, p, s1, z1, p, s2, z2, p, T, K, N, E, topk, g, 0, p, ws, None) == 2
+        if what in ("K", "N", "group"):
+            break
+
+
 def test_fp8_gemm_host_logic(binding):
     """Workspace sizing and every check that happens before a launch (no kernel runs: the dummy
     pointers are never dereferenced)."""
