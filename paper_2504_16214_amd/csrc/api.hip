@@ -401,14 +401,20 @@ static void fp8_medium_plan(int M, int N, int KB, int& bm, int& bn, int& splits)
   }
 }
 
-// The splits whose planes a caller has to bring: a shape that needs none here runs unsplit, and one that
-// needs fewer than it would like runs with those it has room for.
-static int fp8_splits_needed(int M, int N, int K, int planned) {
-  const int bm = M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : M > 128 && N % 128 == 0 && (long long)((M + 127) / 128) * (N / 128) < 512 ? 64 : 128;
+// The splits a workspace was sized for before the tiles and splits above were chosen by time: up to 768
+// workgroups of the four-wave tiles.  A caller who brings planes for them, by a size kept from an earlier
+// release, still runs: a shape that needed none unsplit, one that needed fewer than it is now given
+// with those it has room for.
+static int fp8_four_wave_rows(int M, int N) {
+  return M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : M > 128 && N % 128 == 0 && (long long)((M + 127) / 128) * (N / 128) < 512 ? 64 : 128;
+}
+static int fp8_splits_needed(int M, int N, int K) {
+  const int bm = fp8_four_wave_rows(M, N), KB = K / 128;
   const long long mb = (M + bm - 1) / bm;
   const long long wgs = N % 128 == 0 && mb * (N / 128) >= 256 ? mb * (N / 128) : mb * (N / 64);
-  const int had = wgs >= 256 ? 1 : fp8_splits_for((int)((768 + wgs - 1) / wgs), 16, K / 128);
-  return had < planned ? had : planned;
+  if (wgs >= 256) return 1;
+  const int want = fp8_splits_for((int)((768 + wgs - 1) / wgs), 16, KB), per = (KB + want - 1) / want;
+  return (KB + per - 1) / per;                         // no empty split
 }
 
 // false: the (forced) plan does not fit the shape
@@ -1036,17 +1042,14 @@ int fp8_blockwise_gemm(const uint8_t* A, const float* a_scale, const uint8_t* B,
   if ((unsigned long long)M * (unsigned long long)K >= (1ull << 32) ||
       (unsigned long long)N * (unsigned long long)K >= (1ull << 32))
     return fail(MOE_UNSUPPORTED_SHAPE, "the FP8 GEMM addresses A and B with 32-bit offsets: M * K and N * K must be below 2^32");
-  if (pl.splits > 1 && !g_fp8_mt && !g_fp8_nt && !g_fp8_splits) {
-    const size_t have = workspace && (uintptr_t)workspace % 256 == 0 ? workspace_bytes : 0;
-    const int least = fp8_splits_needed(M, N, K, pl.splits);
-    if (have < round_up((size_t)pl.splits * plane, 256) && (least == 1 || have >= round_up((size_t)least * plane, 256))) {
-      const int KB = K / 128;
-      int fit = (int)(have / plane);
-      if (fit < 1) fit = 1;
-      if (fit > pl.splits) fit = pl.splits;
-      pl.kb_per_split = (KB + fit - 1) / fit;
+  if (!g_fp8_mt && !g_fp8_nt && !g_fp8_splits) {
+    const int KB = K / 128, least = fp8_splits_needed(M, N, K);
+    const bool misaligned = (uintptr_t)workspace % 256 != 0;
+    if (least > 1 && misaligned) return fail(MOE_INVALID_ARGUMENT, "workspace must be 256-byte aligned");
+    const int fit = workspace && !misaligned ? (int)std::min<size_t>(workspace_bytes / plane, 16) : 0;
+    if (fit < pl.splits && fit >= (least > 1 ? least : 0)) {
+      pl.kb_per_split = fit > 1 ? (KB + fit - 1) / fit : KB;
       pl.splits = (KB + pl.kb_per_split - 1) / pl.kb_per_split;
-      if (pl.splits > 1 && have < round_up((size_t)pl.splits * plane, 256)) { pl.splits = 1; pl.kb_per_split = KB; }
     }
   }
   const long long m_blocks = (M + pl.bm - 1) / pl.bm;

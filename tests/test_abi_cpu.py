@@ -154,6 +154,23 @@ def test_fp8_gemm_host_logic(binding):
     assert lib.fp8_probe_mfma(None, 4, None) == 1
 
 
+@pytest.mark.parametrize("M,N,K,planes", [(154, 1152, 21376, 14), (532, 384, 23168, 14), (143, 1152, 21504, 14), (166, 1408, 14080, 11),
+                                          (700, 1536, 8192, 0)])
+def test_fp8_gemm_takes_the_planes_it_used_to_ask_for(binding, M, N, K, planes):
+    """A workspace of as many planes as the size query named before the splits were chosen by time is
+    enough.  (Without a device the launch itself then fails: status 4, not 3.)"""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("would launch on dummy pointers")
+    call, p = binding.load_library().fp8_blockwise_gemm, 0x10000
+    nbytes = planes * M * N * 4
+    assert binding.fp8_blockwise_gemm_workspace_bytes(M, N, K) > nbytes
+    assert call(p, p, p, p, 2 * p, M, N, K, 1, p if planes else None, nbytes, None) == 4
+    if planes:
+        assert call(p, p, p, p, 2 * p, M, N, K, 1, p, nbytes - 256, None) == 3
+        assert call(p, p, p, p, 2 * p, M, N, K, 1, p + 16, nbytes, None) == 1      # misaligned
+
+
 def test_product_path_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2504_16214_amd")
     for dirpath, _, files in os.walk(pkg):

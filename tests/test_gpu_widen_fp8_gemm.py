@@ -436,6 +436,26 @@ def test_split_choice_from_a_few_to_a_thousand_rows(Mr, N, K):
     check(make_fp8_inputs(Fp8GemmConfig("s", M=Mr, N=N, K=K, seed=Mr + N)), what=f"M={Mr} N={N} K={K}")
 
 
+def test_a_workspace_for_fewer_splits_than_planned():
+    """154 x 1152 x 21376 likes 16 planes and runs with the 14 it was once given; with 13 it refuses."""
+    Mr, N, K = 154, 1152, 21376
+    say(f"fp8 gemm with 14 planes M={Mr} N={N} K={K}")
+    plane = Mr * N * 4
+    assert M_.fp8_blockwise_gemm_workspace_bytes(Mr, N, K) > 14 * plane
+    inp = make_fp8_inputs(Fp8GemmConfig("w14", M=Mr, N=N, K=K, seed=10))
+    want = F.blockwise_gemm(inp.a_codes, inp.a_scale, inp.b_codes, inp.b_scale, "bf16")
+    bound = error_bound(want, inp.a_codes, inp.a_scale, inp.b_codes, inp.b_scale)
+    A, sa, B, sb = (torch.from_numpy(x).cuda() for x in (inp.a_codes, inp.a_scale, inp.b_codes, inp.b_scale))
+    buf = torch.full((14 * plane,), 255, dtype=torch.uint8, device="cuda")
+    C = torch.full((Mr, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    M_.fp8_blockwise_gemm(A, sa, B, sb, C, buf)
+    torch.cuda.synchronize()
+    got = C.to(torch.float64).cpu().numpy()
+    assert not np.isnan(got).any() and float((np.abs(got - want) / bound).max()) <= 1.0
+    with pytest.raises(RuntimeError, match="workspace"):
+        M_.fp8_blockwise_gemm(A, sa, B, sb, C, buf[:13 * plane])
+
+
 def test_a_shape_that_can_do_without_planes_takes_any_workspace():
     """700 x 1536 x 8192 likes three planes but runs without: no workspace, a misaligned one and one of
     two planes are accepted; a shape that cannot do without its planes still refuses."""
