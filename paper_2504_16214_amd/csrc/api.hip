@@ -420,7 +420,7 @@ static int fp8_splits_needed(int M, int N, int K) {
 // false: the (forced) plan does not fit the shape
 static bool fp8_plan(int M, int N, int K, Fp8Plan& pl) {
   const int KB = K / 128;
-  int bm = M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : 128;
+  int bm = fp8_four_wave_rows(M, N);
   // 128 features per workgroup measured fastest at every four-wave token-tile height up to 128 (two
   // or more workgroups per CU; 256 wide costs occupancy, 64 wide LDS traffic per matrix instruction).
   int bn = 128;
@@ -433,18 +433,21 @@ static bool fp8_plan(int M, int N, int K, Fp8Plan& pl) {
   const long long tiles256 = (long long)((M + 255) / 256) * (N / 256);
   // A reduction of fewer than four blocks does not hide its start and its write-out (4096 x 12800 x 256:
   // 47 against 45 us).
-  const bool two_group = M > 64 && N % 256 == 0 && KB >= 4 && tiles256 * 5 >= 3 * 256 * ((tiles256 + 255) / 256);
-  if (two_group) { bm = 256; bn = 256; }
-  if (g_fp8_mt) { bm = 16 * g_fp8_mt; bn = 128; }
+  const bool two_group = !g_fp8_mt && !g_fp8_nt && M > 64 && N % 256 == 0 && KB >= 4 &&
+                         tiles256 * 5 >= 3 * 256 * ((tiles256 + 255) / 256);
+  if (g_fp8_mt) bm = 16 * g_fp8_mt;
+  else if (g_fp8_nt && M > 128 && N % 256 == 0 && tiles256 >= 512) bm = 256;      // (a forced width picks its height)
   if (bm != 16 && bm != 32 && bm != 64 && bm != 128 && bm != 256) return false;
   int splits = 1;
-  if (M > 64 && !two_group && !g_fp8_mt && !g_fp8_nt) {
+  if (two_group) {
+    bm = bn = 256;
+  } else if (M > 64 && !g_fp8_mt && !g_fp8_nt) {
     fp8_medium_plan(M, N, KB, bm, bn, splits);
   } else {
     const long long m_blocks = (M + bm - 1) / bm;
     while (bn > 64 && N % bn != 0) bn >>= 1;
     // small problems: narrower feature tiles first (more workgroups streaming weights) ...
-    while (bn > 64 && bm < 256 && m_blocks * (N / bn) < 256) bn >>= 1;
+    while (bn > 64 && m_blocks * (N / bn) < 256) bn >>= 1;
     if (g_fp8_nt) bn = 64 * g_fp8_nt;
     if ((bn != 64 && bn != 128 && bn != 256) || N % bn != 0 || (bm == 256 && bn == 64)) return false;
     // ... then a split of the reduction up to two workgroups per CU, each split at least four blocks

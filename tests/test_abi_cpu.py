@@ -171,6 +171,22 @@ def test_fp8_gemm_takes_the_planes_it_used_to_ask_for(binding, M, N, K, planes):
         assert call(p, p, p, p, 2 * p, M, N, K, 1, p + 16, nbytes, None) == 1      # misaligned
 
 
+def test_fp8_forced_widths_and_heights_keep_their_plans(binding):
+    """A forced feature width takes the row count it always took (no 256-row tile below 512 tiles of it),
+    and a 256-row tile that would have to be 64 wide is refused."""
+    wsb, call, p = binding.fp8_blockwise_gemm_workspace_bytes, binding.load_library().fp8_blockwise_gemm, 0x10000
+    set_plan = binding.load_library().fp8_set_plan_override
+    try:
+        for M, N, K, nt, splits, planes in ((467, 10496, 22912, 4, 0, 0), (246, 13696, 10880, 2, 0, 0), (1553, 8704, 3840, 1, 5, 5)):
+            assert set_plan(0, nt, splits, 0) == 0
+            assert wsb(M, N, K) == planes * M * N * 4
+        for M, N, K in ((4, 2560, 10496), (2821, 1280, 1920), (2, 13696, 12160)):
+            assert set_plan(16, 0, 0, 0) == 0
+            assert call(p, p, p, p, 2 * p, M, N, K, 1, None, 0, None) == 2
+    finally:
+        assert set_plan(0, 0, 0, 0) == 0
+
+
 def test_product_path_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2504_16214_amd")
     for dirpath, _, files in os.walk(pkg):
