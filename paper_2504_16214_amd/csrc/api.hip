@@ -719,14 +719,15 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   int32_t* blocks = (int32_t*)(base + w.blocks);
   void* act = base + w.act;
   void* Y = base + w.Y;
-  // Two-group tile: its shapes, every tuning hook that asks for another kernel at rest, panels and
-  // words aligned for its loads, 32-bit offsets in range, room for the row sums (bf16).
+  // Two-group tile: its shapes, every tuning hook that asks for another kernel at rest, 32-bit offsets
+  // in range, room for the row sums (bf16), and the alignment of the other register-scale tiles, so
+  // that scales and zero points of less are taken or refused alike at every token number.
   const bool two_group =
       layer_wide_ok(K, N, group_size) && g_scale_path != 1 && g_force_ksplit == 0 &&
       (g_force_block_m == 256 || (g_force_block_m == 0 && twogroup_pays(S, E, K, N, (int)dt))) &&
       (dt == MOE_F16 || workspace_bytes >= w.rsum + (size_t)S * (N / 128) * 4) &&
-      (((uintptr_t)X | (uintptr_t)qw1 | (uintptr_t)qw2) % 16) == 0 && (((uintptr_t)s1 | (uintptr_t)s2) % 8) == 0 &&
-      (((uintptr_t)z1 | (uintptr_t)z2) % 4) == 0 && (long long)N * K < (1LL << 31) &&
+      (((uintptr_t)X | (uintptr_t)qw1 | (uintptr_t)qw2) % 16) == 0 && (((uintptr_t)s1 | (uintptr_t)s2) % 16) == 0 &&
+      (((uintptr_t)z1 | (uintptr_t)z2) % 8) == 0 && (long long)N * K < (1LL << 31) &&
       (long long)E * 2 * N * (K / 128) < (1LL << 31) && (long long)T * K * 2 < (1LL << 31) && S * N * 2 < (1LL << 31);
   // a forced bucketing block wins; a forced token tile (tuning hook) also fixes the block
   const int block_m = two_group ? 256 : g_force_block_m > 0 ? g_force_block_m

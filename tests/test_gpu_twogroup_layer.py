@@ -139,3 +139,30 @@ def test_small_workspace_falls_back():
     finally:
         M.moe_set_block_m_override(0)
     _check(inp, out, "fallback")
+
+
+def test_scales_of_less_alignment_take_the_tiles_that_read_them():
+    """8-byte aligned scale rows: the layer runs on a tile with a scale table, and asking for scales in
+    registers is refused, as at every other token number."""
+    inp = _inputs("f16", 1024, 1024, [100, 260], seed=804)
+    print("two-group layer, 8-byte aligned scales", flush=True)
+    d, c = U.DevInputs(inp), inp.cfg
+    for name in ("s1", "s2"):
+        t = getattr(d, name)
+        room = torch.empty(t.numel() + 4, dtype=t.dtype, device="cuda")
+        moved = room[4:].view(t.shape)
+        moved.copy_(t)
+        setattr(d, name, moved)
+    assert d.s1.data_ptr() % 16 == 8
+    M.moe_set_block_m_override(256)
+    try:
+        out = U.run_layer(d)
+        assert M.moe_last_gemm_plan()["mt"] == 8 and M.moe_last_gemm_plan()["register_scales"] == 0
+        M.moe_set_scale_path(2)
+        with pytest.raises(M.MoEError) as e:
+            U.run_layer(d)
+        assert e.value.status == 2
+    finally:
+        M.moe_set_scale_path(0)
+        M.moe_set_block_m_override(0)
+    _check(inp, out, "8-byte aligned scales")
