@@ -664,16 +664,35 @@ static int run_twogroup(const void* A, const float* bias_rows, int row_div, cons
   return MOE_OK;
 }
 
-// The vector-product kernels (few_tokens.hip) have two launches instead of four, but read an expert's
-// weights once for every slot.  us, tiled / vector, f16, K x N, experts, slots:
-//   bytes of all slots: 7168x2048, 256:  8: 58.5 / 47   16: 88 / 88   32: 140 / 159    -> S N K up to 128 M
-//   slots that share an expert (about S^2 / 2E read again): 1024x1024, 8:  16: 21.7 / 17.2   32: 21.9 / 29.6;
-//     4096x4096, 4:  2: 33 / 21   4: 33.7 / 34.3   7: 37 / 57;   2048x2048, 2:  4: 24.2 / 17.1   8: 24.3 / 28.4;
-//     2048x1408, 64:  24: 39 / 35   48: 55 / 59                                     -> S^2 N K up to 40 M E
-//   256x512, 8:  32: 18.5 / 10.5   128: 21.3 / 28                                   -> S up to 32
-static bool few_tokens_pay(long long S, int E, int K, int N) {
-  const long long nk = (long long)N * K;
-  return S <= 32 && S * nk <= 128000000LL && S * S * nk <= 40000000LL * E;
+// Do the vector-product kernels (few_tokens.hip) take the call?  They have two launches instead of four, but
+// read an expert's weights once for every slot, and their down launch has a workgroup of eight waves for
+// every token and 16 columns (one fits a CU), whose waves idle where a token has few (slot, part)
+// pairs.  So up to 32 slots, and by the time both sides should take, in us with weights that are not in a
+// cache: fitted to 1331 calls of 1 to 32 tokens, K 256 ... 7168, N 512 ... 14336, 8 to 256 experts, top 1 to 8,
+// within 7 % (vector) and 5 % (tiled) on average; operand-order weights suit the tiles better and have a fit of
+// their own (598 calls).  Of 1791 calls near the crossing that the fits had not seen it takes 115 that are slower
+// than on the tiles, cached or not, by 12 % at most; of those it was fitted to, it leaves 34 on the tiles that
+// would be 3 to 18 % faster.  Tiled / vector, weights in memory (in the cache):
+//   7168x2048, 256 experts, top 8: 1 token 59.7 / 48.9 (57.8 / 46.2);   top 1: 4 tokens 48.4 / 43.8 (47.3 / 40.4), 6 52.1 / 66.8
+//   4096x14336, 8, top 2: 1 token 55.7 / 49.1 (54.3 / 44.2);   2048x1408, 64, top 6: 4 tokens 42.1 / 39.6, 5 46.1 / 46.2
+//   2048x2048, 64: top 1, 6 tokens 27.9 / 24.2, 8 28.4 / 28.9, 16 35.6 / 49.7;   top 4, 6 tokens 45.6 / 45.6
+//   1024x1024, 64: top 2, 12 tokens 27.0 / 24.6, 16 27.6 / 29.4;   256x512, 8, top 2: 16 tokens 19.4 / 10.1
+// The other limits keep slots that share an expert (about S^2 / 2E reads more than the tiles have) and
+// large weights, where nothing is left to gain, on the tiles.
+static bool few_tokens_pay(int T, int topk, int E, int K, int N, int dt, int pre) {
+  const long long S = (long long)T * topk, nk = (long long)N * K;
+  if (S > 32 || S * nk > 128000000LL || S * S * nk > 40000000LL * E) return false;
+  const int parts = few_down_parts(topk, N), panels = (N + 1023) / 1024;
+  const double mw = nk / 1e6;                                  // a million weights of one of an expert's three matrices
+  const int serial = (topk * parts + 7) / 8 * ((panels + parts - 1) / parts);        // panels that a down wave works off
+  const double w = (double)T * K / 4096, full = ceil(w), rounds = w <= 1 ? 1 : w + 0.4 * (full - w);      // of down workgroups
+  const double experts = E * (1 - pow(1 - (topk < E ? (double)topk / E : 1.0), T));  // that the batch meets
+  const bool f16 = dt == MOE_F16;
+  if (pre)
+    return 9.7 + 0.331 * S * mw + rounds * (0.92 + (f16 ? 1.92 : 1.49) * serial) < 19.1 + 0.252 * experts * mw + (f16 ? 1.35e-3 : 1.55e-3) * K;
+  // (a reduction that is no multiple of 1024 runs without register scales and splits on the tiles)
+  return 8.5 + (f16 ? 0.331 : 0.303) * S * mw + rounds * (0.68 + 2.06 * serial) <
+         19.1 + 0.271 * experts * mw + (f16 ? 1.58e-3 : 1.87e-3) * K + (K % 1024 ? 1.04e-3 * K : 0) + (N % 1024 ? 1.71e-3 * N : 0);
 }
 static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_weights,
                       const int32_t* qw1, const void* s1, const uint8_t* z1,
@@ -738,7 +757,7 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   int err;
   // A few tokens: vector products, unless a tuning hook asks for a tile; whole groups of 128, 16-byte
   // aligned words and activations, 32-bit offsets into an expert.
-  const bool few = few_tokens_pay(S, E, K, N) && group_size == 128 && few_tokens_fit(topk, K, N) && g_force_block_m == 0 &&
+  const bool few = few_tokens_pay(T, topk, E, K, N, (int)dt, pre) && group_size == 128 && few_tokens_fit(topk, K, N) && g_force_block_m == 0 &&
                    g_force_mt == 0 && g_force_nt == 0 && g_force_ksplit == 0 && g_scale_path == 0 && g_force_tpw == 0 && g_wide_mode == 0 &&
                    (((uintptr_t)X | (uintptr_t)qw1 | (uintptr_t)qw2) % 16) == 0 && (((uintptr_t)s1 | (uintptr_t)s2) % 2) == 0 &&
                    (long long)N * K < (1LL << 31);

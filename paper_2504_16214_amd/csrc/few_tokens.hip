@@ -300,6 +300,11 @@ bool few_tokens_fit(int topk, int K, int N) {
   return K % 128 == 0 && N % 128 == 0 && (size_t)vec_total(K) <= kFewLds && (size_t)topk * (vec_total(N) + 8 * 64) <= kFewLds;
 }
 
+int few_down_parts(int topk, int N) {
+  const int parts = topk >= 8 ? 1 : topk >= 4 ? 2 : topk >= 2 ? 4 : 8, panels = (N + 1023) / 1024;
+  return parts < panels ? parts : panels;
+}
+
 int launch_few_gate_up(const void* X, const int32_t* ids, const int32_t* qw, const void* s, const uint8_t* z, void* act, int T,
                        int topk, int E, int K, int N, int dt, int pre, hipStream_t stream) {
   const dim3 grid((N + 31) / 32, T * topk), block(256);
@@ -315,9 +320,7 @@ int launch_few_gate_up(const void* X, const int32_t* ids, const int32_t* qw, con
 
 int launch_few_down(const void* act, const int32_t* ids, const float* w, const int32_t* qw, const void* s, const uint8_t* z,
                     void* out, int T, int topk, int E, int K, int N, int dt, int pre, hipStream_t stream) {
-  // about eight (slot, part) pairs for the eight waves
-  int parts = topk >= 8 ? 1 : topk >= 4 ? 2 : topk >= 2 ? 4 : 8;
-  if (parts > (N + 1023) / 1024) parts = (N + 1023) / 1024;
+  const int parts = few_down_parts(topk, N);
   const dim3 grid(K / 16, T), block(512);
   const size_t lds = (size_t)topk * (vec_total(N) + parts * 64);
   if (dt == kF16)

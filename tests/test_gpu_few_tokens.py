@@ -58,6 +58,15 @@ def test_the_rule_ends_where_slots_share_experts():
         assert ran_without_a_tile() == few
 
 
+@pytest.mark.parametrize("T,few", [(8, True), (24, False)])
+def test_the_rule_ends_where_many_tokens_have_few_slots(T, few):
+    """One expert a token: the down launch has a workgroup for every token, most of whose waves idle."""
+    cfg = MoEConfig("few_top1", T=T, K=1024, N=1024, E=24, topk=1, group=128, dtype="f16", seed=T)
+    say(f"edge of the rule {cfg}")
+    check_case(make_inputs(cfg), str(cfg))
+    assert ran_without_a_tile() == few
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_few_tokens_in_operand_order_are_the_same_bits(dtype):
     cfg = MoEConfig("few_pre", T=2, K=2048, N=1024, E=6, topk=3, group=128, dtype=dtype, seed=5)
