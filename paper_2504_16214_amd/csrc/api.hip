@@ -450,12 +450,15 @@ static bool fp8_plan(int M, int N, int K, Fp8Plan& pl) {
     while (bn > 64 && m_blocks * (N / bn) < 256) bn >>= 1;
     if (g_fp8_nt) bn = 64 * g_fp8_nt;
     if ((bn != 64 && bn != 128 && bn != 256) || N % bn != 0 || (bm == 256 && bn == 64)) return false;
-    // ... then a split of the reduction up to two workgroups per CU, each split at least four blocks
-    // long.  A split costs 8 bytes an output and a workgroup beyond the second per CU a second round:
-    // 64 x 10240 x 5120 20.5 us at 5 splits (800 workgroups), 16.7 at 3; 16 x 5120 x 8192 14.1 at 10, 12.1 at 6;
-    // 64 x 2048 x 7168 13.5 at 14, 10.4 at 8.
+    // ... then a split of the reduction, each split at least four blocks long: up to two workgroups per CU, or
+    // for 32 rows and fewer, whose planes (8 bytes an output and split) are small and whose workgroups
+    // have less to load, about 2.75.  us by splits, weights in memory (in the cache):
+    //   64 x 10240 x 5120 (160 workgroups a split) 3: 24.7 (16.7), 4: 27.2 (19.1), 5: 28.9 (20.3);  64 x 5120 x 25600 (80) 6: 44 (29), 10: 52 (35)
+    //   16 x 10240 x 5120 3: 19.1 (13.3), 4: 17.9 (13.6), 5: 18.8 (14.8);  1 x 5120 x 25600 6: 36 (24), 8: 31 (23), 10: 31 (25)
+    //   32 x 14336 x 4096 (224) 2: 21.3 (14.6), 3: 19.2 (14.7), 4: 20.1 (15.9);  1 x 2048 x 7168 (32) 8: 11.3 (7.4), 12: 11.0 (8.3), 14: 10.8 (8.6)
     const long long wgs = m_blocks * (N / bn);
-    if (wgs < 256 && bm < 256) splits = fp8_splits_for(512 / (int)wgs, wgs < 32 ? 16 : 8, KB);
+    if (wgs < 256 && bm < 256)
+      splits = bm <= 32 ? fp8_splits_for((704 + (int)wgs / 2) / (int)wgs, wgs < 32 ? 16 : 12, KB) : fp8_splits_for(512 / (int)wgs, wgs < 32 ? 16 : 8, KB);
   }
   if (g_fp8_splits) splits = g_fp8_splits;
   if (splits < 1 || splits > KB) return false;

@@ -171,6 +171,14 @@ def test_fp8_gemm_takes_the_planes_it_used_to_ask_for(binding, M, N, K, planes):
         assert call(p, p, p, p, 2 * p, M, N, K, 1, p + 16, nbytes, None) == 1      # misaligned
 
 
+@pytest.mark.parametrize("M,N,K,wgs,planes", [(1, 5120, 25600, 80, 9), (16, 10240, 5120, 160, 4), (32, 14336, 4096, 224, 3),
+                                              (64, 5120, 25600, 80, 6), (64, 10240, 5120, 160, 3)])
+def test_fp8_gemm_splits_of_few_rows(binding, M, N, K, wgs, planes):
+    """About 2.75 workgroups per CU up to 32 rows (256 CUs), two beyond."""
+    assert binding.fp8_blockwise_gemm_workspace_bytes(M, N, K) == planes * M * N * 4
+    assert (576 if M <= 32 else 448) <= planes * wgs <= (832 if M <= 32 else 512)
+
+
 def test_fp8_forced_widths_and_heights_keep_their_plans(binding):
     """A forced feature width takes the row count it always took (no 256-row tile below 512 tiles of it),
     and a 256-row tile that would have to be 64 wide is refused."""
