@@ -332,10 +332,22 @@ static int pick_k_splits(long long S, int E, int K, int N, int block_m) {
 // tokens (768 tiles) 324 -> 359, 4096 tokens (1280) 562 -> 583, 8 experts (K 4096, N 14336), 1024
 // tokens (1536) 1008 -> 940; bf16 64 experts (K 2048, N 1024), 512 tokens (704) 113 -> 124, 1024
 // tokens (896) 186 -> 180, 16 experts, 2048 tokens (768) 440 -> 412.
-static bool twogroup_pays(long long S, int E, int K, int N, int dt) {
-  const long long avg = S / (E > 0 ? E : 1);
-  const long long tiles = (S / 256 + (S < E ? S : E) / 2) * ((2LL * N + K) / 256);      // of both products
-  return dt == MOE_BF16 ? avg >= 20 && tiles >= 750 : avg >= 29 && tiles >= 1400;
+// Two more conditions come from 24000 layer calls on the former tiles and on this one (8 to 256 experts, K and N
+// 1024 ... 14336, 8 to 192 rows per expert, uniform and power-law routing, both weight layouts):
+//   * Skewed routing packs the rows into far fewer blocks than uniform routing, and the host does not know which
+//     it is.  So even if every block were full there have to be some rounds of tiles (`packed`), or so many
+//     rows per expert that the 128-slot tile needs a second block.  Former time over this one's, geometric mean
+//     (share of calls more than 5 % slower) of the calls these conditions keep / take away: bf16 uniform 1.09 (3 %) /
+//     0.98 (33 %), skewed 1.12 (12 %) / 0.92 (56 %); fp16 uniform 1.07 (4 %) / 1.03 (12 %), skewed 0.96 (39 %) / 0.87 (80 %).
+//   * Operand-order weights run on 64-slot four-wave tiles otherwise, which lose less at few rows: bf16 20 to 26
+//     rows per expert 4 to 7 % faster there (256 experts, K 7168, N 2048), 28 a tie, 32 17 % slower.  Kept / taken
+//     away: bf16 uniform 1.15 (6 %) / 0.96 (53 %), skewed 1.03 (31 %) / 0.82 (77 %); fp16 1.12 (3 %) / 1.01 (29 %) and
+//     0.96 (45 %) / 0.81 (94 %).
+static bool twogroup_pays(long long S, int E, int K, int N, int dt, int pre) {
+  const long long avg = S / (E > 0 ? E : 1), feat = (2LL * N + K) / 256;
+  const long long tiles = (S / 256 + (S < E ? S : E) / 2) * feat, packed = S / 256 * feat;      // of both products
+  if (dt == MOE_BF16) return avg >= (pre ? 28 : 20) && tiles >= 750 && (packed >= 600 || avg >= 112);
+  return avg >= 29 && tiles >= 1400 && (packed >= 1000 || avg >= 112);
 }
 
 struct Workspace {
@@ -358,7 +370,7 @@ static Workspace carve(long long T, int K, int N, int E, int topk, int dt) {
   // row sums of act for the bf16 operands of the two-group tile; a caller's workspace without them
   // runs the layer on the eight-wave tile instead
   w.rsum = o;
-  if (dt == MOE_BF16 && K % 1024 == 0 && N % 1024 == 0 && twogroup_pays(S, E, K, N, dt)) o += round_up((size_t)S * (N / 128) * 4, 256);
+  if (dt == MOE_BF16 && K % 1024 == 0 && N % 1024 == 0 && twogroup_pays(S, E, K, N, dt, 0)) o += round_up((size_t)S * (N / 128) * 4, 256);
   w.total = o;
   return w;
 }
@@ -746,7 +758,7 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   // that scales and zero points of less are taken or refused alike at every token number.
   const bool two_group =
       layer_wide_ok(K, N, group_size) && g_scale_path != 1 && g_force_ksplit == 0 &&
-      (g_force_block_m == 256 || (g_force_block_m == 0 && twogroup_pays(S, E, K, N, (int)dt))) &&
+      (g_force_block_m == 256 || (g_force_block_m == 0 && twogroup_pays(S, E, K, N, (int)dt, pre))) &&
       (dt == MOE_F16 || workspace_bytes >= w.rsum + (size_t)S * (N / 128) * 4) &&
       (((uintptr_t)X | (uintptr_t)qw1 | (uintptr_t)qw2) % 16) == 0 && (((uintptr_t)s1 | (uintptr_t)s2) % 16) == 0 &&
       (((uintptr_t)z1 | (uintptr_t)z2) % 8) == 0 && (long long)N * K < (1LL << 31) &&

@@ -70,6 +70,21 @@ def test_workspace_covers_tables_and_intermediates(binding):
     assert S * N * 2 + 2 * S * K * 4 <= need <= S * N * 2 + 8 * S * K * 4 + (1 << 20)
 
 
+@pytest.mark.parametrize("T,K,N,E,topk,row_sums", [
+    (717, 7168, 2048, 256, 8, True),          # 22 rows an expert, 968 tiles even if every block were full
+    (4096, 7168, 2048, 256, 8, True),
+    (512, 7168, 2048, 256, 8, False),         # 16 rows an expert
+    (1024, 2048, 1024, 64, 4, False),         # 768 tiles if the routing is even, 256 if it is not
+    (3200, 1024, 1024, 64, 4, True),
+    (2048, 4096, 4096, 16, 1, True),          # 128 rows an expert
+])
+def test_row_sums_are_reserved_where_the_two_group_tile_is_chosen(binding, T, K, N, E, topk, row_sums):
+    """bf16 only: the size query adds them where the layer chooses the tile by itself."""
+    wsb, S = binding.moe_w4a16_layer_workspace_bytes, T * topk
+    extra = wsb(T, K, N, E, topk, 1) - wsb(T, K, N, E, topk, 0)
+    assert extra == (-(-S * (N // 128) * 4 // 256) * 256 if row_sums else 0)
+
+
 def test_layer_block_choice_tracks_rows_per_expert(binding):
     assert binding.moe_layer_block_m(128, 256, 8) == 16      # about 4 rows per expert
     assert binding.moe_layer_block_m(64, 8, 2) == 32         # 16 rows per expert
