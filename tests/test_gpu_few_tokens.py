@@ -10,6 +10,7 @@ import pytest
 import torch
 
 from moe_workloads import MoEConfig, make_inputs
+from oracle import moe_oracle as O
 from test_gpu_random_shapes import check_case, say
 
 pytestmark = pytest.mark.gpu
@@ -119,3 +120,28 @@ def test_an_infinite_activation_stays_in_its_token(dtype):
         M.moe_set_block_m_override(0)
     assert np.array_equal(got[[0, 2]], clean[[0, 2]])
     assert np.array_equal(np.isfinite(got), np.isfinite(tiled)) and not np.isfinite(got[1]).any()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("with_bias", [False, True])
+def test_routed_layer_of_a_few_tokens(dtype, with_bias):
+    """Router and vector products behind one call: the oracle chain, and the bits of the plain entry."""
+    cfg = MoEConfig("few_routed", T=16, K=256, N=512, E=8, topk=2, group=128, dtype=dtype, seed=21)
+    say(f"routed, few tokens {cfg} bias={with_bias}")
+    inp = make_inputs(cfg)
+    bias = np.linspace(1.0, -1.0, cfg.E).astype(np.float32) if with_bias else None
+    inp.topk_ids, w = O.route_topk(inp.logits, cfg.topk, bias=bias)
+    inp.topk_weights = w.astype(np.float32)
+    d = U.DevInputs(inp)
+    logits, bd = torch.from_numpy(inp.logits).cuda(), None if bias is None else torch.from_numpy(bias).cuda()
+    ws = torch.full((M.moe_w4a16_routed_layer_workspace_bytes(cfg.T, cfg.K, cfg.N, cfg.E, cfg.topk,
+                                                              M.MOE_F16 if dtype == "f16" else M.MOE_BF16),),
+                    255, dtype=torch.uint8, device="cuda")
+    out = torch.full((cfg.T, cfg.K), float("nan"), dtype=U.TORCH_DT[dtype], device="cuda")
+    M.moe_w4a16_routed_layer(d.X, logits, bd, d.qw1, d.s1, d.z1, d.qw2, d.s2, d.z2, out, cfg.topk, cfg.group, ws)
+    torch.cuda.synchronize()
+    assert ran_without_a_tile()
+    check_case(inp, str(cfg))
+    assert ran_without_a_tile()
+    M.moe_route_topk(logits, bd, d.ids, d.w)
+    assert torch.equal(out, U.run_layer(d))

@@ -166,3 +166,38 @@ def test_scales_of_less_alignment_take_the_tiles_that_read_them():
         M.moe_set_scale_path(0)
         M.moe_set_block_m_override(0)
     _check(inp, out, "8-byte aligned scales")
+
+
+def test_automatic_choice_through_the_three_entries():
+    """bf16, several slots a token (the row sums of X are gathered by token, not by slot), the workspace of
+    the size query and no override: the plain layer against the oracle, the prepacked and the routed one
+    with the same bits."""
+    cfg = MoEConfig("tg_auto", T=3200, K=1024, N=1024, E=64, topk=4, group=128, dtype="bf16", seed=805)
+    print(f"two-group layer, automatic choice {cfg}", flush=True)
+    inp = make_inputs(cfg)
+    d = U.DevInputs(inp)
+    logits = torch.from_numpy(inp.logits).cuda()
+    M.moe_route_topk(logits, None, d.ids, d.w)
+    inp.topk_ids, inp.topk_weights = d.ids.cpu().numpy(), d.w.cpu().numpy()
+
+    def on_two_group():
+        plan = M.moe_last_gemm_plan()
+        return plan["mt"] == 16 and plan["waves"] == 8
+
+    got = U.run_layer(d)
+    assert on_two_group()
+    _check(inp, got, "plain entry")
+    sizes = (cfg.T, cfg.K, cfg.N, cfg.E, cfg.topk, M.MOE_BF16)
+    p1, p2 = torch.empty_like(d.qw1), torch.empty_like(d.qw2)
+    M.moe_repack_qweight(d.qw1, False, p1)
+    M.moe_repack_qweight(d.qw2, True, p2)
+    out = torch.full_like(got, float("nan"))
+    ws = torch.full((M.moe_w4a16_layer_workspace_bytes(*sizes),), 255, dtype=torch.uint8, device="cuda")
+    M.moe_w4a16_layer_prepacked(d.X, d.ids, d.w, p1, d.s1, d.z1, p2, d.s2, d.z2, out, cfg.group, ws)
+    torch.cuda.synchronize()
+    assert on_two_group() and torch.equal(out.view(torch.int16), got.view(torch.int16))
+    out = torch.full_like(got, float("nan"))
+    ws = torch.full((M.moe_w4a16_routed_layer_workspace_bytes(*sizes),), 255, dtype=torch.uint8, device="cuda")
+    M.moe_w4a16_routed_layer(d.X, logits, None, d.qw1, d.s1, d.z1, d.qw2, d.s2, d.z2, out, cfg.topk, cfg.group, ws)
+    torch.cuda.synchronize()
+    assert on_two_group() and torch.equal(out.view(torch.int16), got.view(torch.int16))
