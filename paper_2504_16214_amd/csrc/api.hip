@@ -1198,9 +1198,12 @@ static int fp8_pick_block_m(long long S, int E, int K, int N) {
   // against 218 us, 3000 tokens 369 against 448; 8 experts, 144 tiles: 142 against 130), from 16 on
   // in launches of many rounds (256 experts, K 7168, N 2048: 512 tokens 2.06 against 2.09 ms, 1024
   // 2.25 against 2.49, 4096 3.07 against 3.95; at 8 rows per expert 32-slot blocks win by 1 %).
+  // Skewed routing packs the rows into fewer blocks; the second case also asks for 100 tiles if every block were
+  // full (former time over this tile's below / at 100 ... 160 / from 260 on, geometric mean: even routing 1.04 / 1.15 /
+  // 1.15, power law 0.85 / 0.96 / 1.09).
   if (K % 256 == 0 && N % 128 == 0) {
-    const long long tiles = (S / 256 + (S < E ? S : E) / 2) * ((K < 2 * N ? K : 2 * N) / 256);
-    if (tiles >= 1024 ? avg >= 16 : avg >= 64 && tiles * 10 >= 7 * 256 * ((tiles + 255) / 256)) return 256;
+    const long long per_block = (K < 2 * N ? K : 2 * N) / 256, tiles = (S / 256 + (S < E ? S : E) / 2) * per_block;
+    if (tiles >= 1024 ? avg >= 16 : avg >= 64 && tiles * 10 >= 7 * 256 * ((tiles + 255) / 256) && S / 256 * per_block >= 100) return 256;
   }
   if (avg <= 32) return 32;      // measured: 32-token tiles stream the weights fastest at a few rows per expert
   if (avg >= 96) return 128;     // about one row block per expert: its weights are fetched once (measured +2 %)
