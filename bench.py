@@ -136,6 +136,12 @@ def main():
         step()
     torch.cuda.synchronize()
 
+    # what the layer runs on for these sizes: 16 = two-group tile (256-slot blocks), 0 = vector products, else a grouped tile
+    tile = M.moe_last_gemm_plan()["mt"]
+    kernel = {16: "w4a16_twogroup_kernel", 0: "few_gate_up_kernel"}.get(tile, "w4a16_gemm_kernel")
+    block_m = {16: 256, 0: None}.get(tile, M.moe_layer_block_m(cfg.T, cfg.E, cfg.topk) if args.prepacked else
+                                     M.moe_layer_block_m_for(cfg.T, cfg.K, cfg.N, cfg.E, cfg.topk, cfg.group))
+
     # per-step stage events, created (and first recorded) before the timed region
     K_steps = args.steps
     evs = [[torch.cuda.Event(enable_timing=True) for _ in range(5)] for _ in range(K_steps)]
@@ -183,7 +189,7 @@ def main():
     # such run was recorded for the configuration)
     roofline["traffic_source"] = ("profiles/hbm_traffic.json (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, separate run)"
                                   if traffic is not None else None)
-    roofline["kernel"] = "w4a16_gemm_kernel (gate/up projection + SiLU-and-multiply)"
+    roofline["kernel"] = f"{kernel} (gate/up projection + SiLU-and-multiply)"
     roofline["kernel_ms"] = round(float(stage_avg[1]), 4)
 
     result = {
@@ -196,8 +202,7 @@ def main():
                                f"g={cfg.group} {cfg.dtype}, seed {cfg.seed}",
                    "tokens_override": bool(args.tokens),
                    "active_experts": E_act, "algorithmic_bytes": layer_bytes, "flop": flops,
-                   "block_m": (M.moe_layer_block_m(cfg.T, cfg.E, cfg.topk) if args.prepacked else
-                               M.moe_layer_block_m_for(cfg.T, cfg.K, cfg.N, cfg.E, cfg.topk, cfg.group)), "tile_override": args.tile or None,
+                   "block_m": block_m, "tile_override": args.tile or None,
                    "weights": "operand-order repack (offline)" if args.prepacked else "as stated: [E, rows, K/8] int32"},
         "tflops": round(tflops, 2), "hbm_frac": round(gbs / HBM_PEAK_GBS, 4),
         "mfma_frac": round(tflops / MFMA_PEAK_TFLOPS, 4),
@@ -321,7 +326,8 @@ def fp8_main(args, cfg):
         ach = flops / (k_ms * 1e-3) / 1e12
         roofline = {"bound": "mfma", "achieved": round(ach, 1), "peak": FP8_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(ach / FP8_MFMA_PEAK_TFLOPS, 4), "traffic": None}
-    roofline["kernel"] = "fp8_blockwise_gemm_kernel" + (" + fp8_split_reduce_kernel" if nbytes else "")
+    # (above 64 rows the 256 x 256 tile, fp8_pingpong_kernel, where its tiles fill the chip)
+    roofline["kernel"] = "fp8_blockwise_gemm" + (" with fp8_split_reduce_kernel" if nbytes else "")
     roofline["kernel_ms"] = round(k_ms, 4)
     tpath = os.path.join(ROOT, "profiles", "hbm_traffic.json")
     if os.path.exists(tpath):
@@ -429,7 +435,7 @@ def fp8_moe_main(args, cfg):
         ach = 4.0 * K * N * S / (g1_ms * 1e-3) / 1e12
         roofline = {"bound": "mfma", "achieved": round(ach, 1), "peak": FP8_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(ach / FP8_MFMA_PEAK_TFLOPS, 4), "traffic": None}
-    roofline["kernel"] = "fp8_blockwise_gemm_kernel (grouped gate/up product)"
+    roofline["kernel"] = "fp8_moe_grouped_gemm (gate/up product)"
     roofline["kernel_ms"] = round(g1_ms, 4)
     result = {
         "metric": "FP8 MoE layer TFLOP/s + HBM GB/s (% of MI355X roofline), 1 GPU",

@@ -176,12 +176,14 @@ int moe_w4a16_layer(const void* X, const int32_t* topk_ids, const float* topk_we
 /*
  * moe_w4a16_layer for callers that cannot allocate device memory or carry a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments
- * (minus the workspace), same kernels and same results bit for bit.  The bucketing tables, the
+ * (minus the workspace), same kernels and same results bit for bit (but see below).  The bucketing tables, the
  * activation between the two GEMMs and the float32 down-projection planes live in a fixed
  * 64 MiB device array inside the library (one copy per GPU, held until the process ends); the
  * call performs no allocation of any kind.  Sizes for which
  * moe_w4a16_layer_workspace_bytes(...) exceeds 64 MiB return MOE_WORKSPACE_TOO_SMALL (the
- * DeepSeek-shaped decode batch of 128 tokens needs 33 MiB).  The array's address is resolved on
+ * DeepSeek-shaped decode batch of 128 tokens needs 33 MiB); a bf16 batch that exceeds it by no more than the
+ * row sums of the two-group tile (T * topk * N / 32 bytes) runs on another tile instead, with the same
+ * accuracy but other roundings than moe_w4a16_layer with its full workspace.  The array's address is resolved on
  * the first call on each device (make that call outside a graph capture).  All calls on one GPU
  * share the array: calls that overlap on one GPU (different streams or threads) race; calls
  * ordered on one stream, or serialised by the caller, are safe.
@@ -251,8 +253,8 @@ int moe_route_align(const float* logits, const float* bias, int T, int E, int to
 
 /*
  * Router + layer on one stream: moe_route_align into tables held in the workspace, then the two
- * grouped GEMMs and the combine of moe_w4a16_layer (four launches up to 64 tokens, five beyond; three
- * for the few tokens that need no bucketing).
+ * grouped GEMMs and the combine of moe_w4a16_layer: four launches up to 64 tokens, five beyond, one (fp16) or
+ * two (bf16) more for large batches on the two-group tile, three for the few tokens that need no bucketing.
  * Arguments as for the two; `workspace` of at least moe_w4a16_routed_layer_workspace_bytes(...)
  * bytes, 256-byte aligned.
  */
@@ -268,8 +270,10 @@ int moe_w4a16_routed_layer(const void* X, const float* logits, const float* bias
  *
  * moe_set_stage_events: while set (n == 5), moe_w4a16_layer records the given
  * hipEvent_t handles on its stream: events[0] before bucketing, [1] before the
- * first grouped GEMM, [2] before the second, [3] before the combine, [4] after
- * it (a few tokens: nothing between [0] and [1] but the router, nor between [3] and [4]).  Pass (NULL, 0) to clear.  Thread-local.
+ * first grouped GEMM, [2] after it, [3] before the combine, [4] after it.  Large
+ * batches on the two-group tile: [0] to [1] includes the reorder of X and, in bf16,
+ * [2] to [3] the row sums of the second operand.  A few tokens: nothing between [0]
+ * and [1] but the router, nor between [3] and [4].  Pass (NULL, 0) to clear.  Thread-local.
  *
  * moe_set_tile_override: force the grouped GEMM tile (tokens per tile =
  * 16*mt, output features per workgroup = 64*nt) instead of the built-in
@@ -291,7 +295,7 @@ int moe_w4a16_routed_layer(const void* X, const float* logits, const float* bias
  * number of 1024-index scale panels; ignored by kernels without register-resident scales.
  * Thread-local.
  *
- * moe_layer_block_m: the bucketing block size the layer picks for these sizes.
+ * moe_layer_block_m: the bucketing block size the layer picks for these sizes (see moe_layer_block_m_for).
  *
  * moe_set_block_m_override: force the bucketing block of moe_w4a16_layer (16 ... 256) instead of
  * the built-in choice; 0 restores it.  256 takes the two-group tile where the shapes admit it.

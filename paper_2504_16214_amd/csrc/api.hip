@@ -794,7 +794,7 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
     return MOE_OK;
   }
 
-  if (ev) (void)hipEventRecord((hipEvent_t)g_events[0], stream);
+  mark(0);
   if (route) {
     const int rst = route_and_align(*route, T, E, topk, block_m, counts, offsets, sorted, blocks, num_padded, stream);
     if (rst != MOE_OK) return rst;
@@ -804,35 +804,36 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
     if (err != 0) return hip_fail(err, "align launch");
   }
 
-  if (ev) (void)hipEventRecord((hipEvent_t)g_events[1], stream);
   if (two_group) {
     // the reordered rows of X and their sums live where Y will be written: Y is written last
     float* const xsum = dt == MOE_BF16 ? (float*)((unsigned char*)Y + round_up((size_t)T * K * 2, 256)) : nullptr;
     float* const asum = dt == MOE_BF16 ? (float*)(base + w.rsum) : nullptr;
     err = launch_prepare_rows(X, T, K, (int)dt, Y, xsum, stream);
     if (err != 0) return hip_fail(err, "activation reorder launch");
+    mark(1);
     int st = run_twogroup(Y, xsum, topk, qw1, s1, z1, sorted, blocks, num_padded, (int)S, E, 2 * N, K, (int)dt, 1, pre, act, stream);
     if (st != MOE_OK) return st;
-    if (ev) (void)hipEventRecord((hipEvent_t)g_events[2], stream);
+    mark(2);
     if (asum) {
       err = launch_prepare_rows(act, S, N, (int)dt, nullptr, asum, stream);
       if (err != 0) return hip_fail(err, "row sum launch");
     }
     st = run_twogroup(act, asum, 1, qw2, s2, z2, sorted, blocks, num_padded, (int)S, E, K, N, (int)dt, 0, pre, Y, stream);
     if (st != MOE_OK) return st;
-    if (ev) (void)hipEventRecord((hipEvent_t)g_events[3], stream);
+    mark(3);
     err = launch_combine(Y, 1, 1, topk_weights, topk_ids, E, out, T, topk, K, (int)dt, stream);
     if (err != 0) return hip_fail(err, "combine launch");
-    if (ev) (void)hipEventRecord((hipEvent_t)g_events[4], stream);
+    mark(4);
     return MOE_OK;
   }
+  mark(1);
   GemmArgs g1{X, topk, qw1, s1, z1, sorted, blocks, num_padded, (int)S, E, 2 * N, K, group_size, block_m,
               (int)dt, act, N, N, 0};
   g1.pre = pre;
   int st = run_gemm(g1, stream);
   if (st != MOE_OK) return st;
 
-  if (ev) (void)hipEventRecord((hipEvent_t)g_events[2], stream);
+  mark(2);
   GemmArgs g2{act, 1, qw2, s2, z2, sorted, blocks, num_padded, (int)S, E, K, N, group_size, block_m,
               (int)dt, Y, K, 0, 1};
   // reduction splits: as many partial planes as the caller's workspace holds
@@ -846,10 +847,10 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   st = run_gemm(g2, stream);
   if (st != MOE_OK) return st;
 
-  if (ev) (void)hipEventRecord((hipEvent_t)g_events[3], stream);
+  mark(3);
   err = launch_combine(Y, 1, planes, topk_weights, topk_ids, E, out, T, topk, K, (int)dt, stream);
   if (err != 0) return hip_fail(err, "combine launch");
-  if (ev) (void)hipEventRecord((hipEvent_t)g_events[4], stream);
+  mark(4);
   return MOE_OK;
 }
 
