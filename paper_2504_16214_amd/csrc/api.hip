@@ -326,9 +326,9 @@ static int pick_k_splits(long long S, int E, int K, int N, int block_m) {
 // expert's weights once per 256 rows and keeps the matrix unit busier; below, the 32-slot and the
 // eight-wave 128-slot tiles stream the weights as fast or spread a small launch over more workgroups.
 // Measured (us, former choice -> two-group; 256 experts, K 7168, N 2048): fp16 512 tokens 1304 -> 1407,
-// 1024 1714 -> 1657, 1536 1991 -> 1915, 4096 4087 -> 3535; bf16, whose zero points cost the other
-// tiles a second matrix instruction, 512 tokens a tie, 717 1691 -> 1618, 1024 1933 -> 1810, 4096 5436
-// -> 4208.  Launches of few tiles lose by their last round: fp16 16 experts (K 4096, N 2048), 2048
+// 1024 1714 -> 1657, 1536 1991 -> 1915, 4096 4026 -> 3596; bf16, whose zero points cost the other
+// tiles a second matrix instruction, 512 tokens a tie, 717 1723 -> 1690, 1024 1933 -> 1912, 4096 5436
+// -> 4258.  Launches of few tiles lose by their last round: fp16 16 experts (K 4096, N 2048), 2048
 // tokens (768 tiles) 324 -> 359, 4096 tokens (1280) 562 -> 583, 8 experts (K 4096, N 14336), 1024
 // tokens (1536) 1008 -> 940; bf16 64 experts (K 2048, N 1024), 512 tokens (704) 113 -> 124, 1024
 // tokens (896) 186 -> 180, 16 experts, 2048 tokens (768) 440 -> 412.

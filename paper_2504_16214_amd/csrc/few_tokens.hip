@@ -5,13 +5,15 @@
 // 256 experts, top 8: 118 MB of gate/up weights in 29 us); bucketing and combine are two more launches
 // of 5 to 6 us that hardly use the chip.  Here every slot is a vector product of its own: gate/up with
 // SiLU-and-multiply is one kernel over (slot, columns), the down projection of all of a token's slots
-// with the weighted combine another over (token, columns).  Measured, us, tiled then vector: that token
-// 58.5 / 47 (bf16 60 / 45), one token of 4096 x 14336 with 8 experts 53.5 / 44, of 2048 x 1408 with 64 28.5 / 17,
-// 16 tokens of 256 x 512 with 8 18.5 / 10.5.
+// with the weighted combine another over (token, columns).  Measured, us, tiled then vector, with the weights in
+// the last-level cache (in memory): that token 57.3 / 45.9 (59.7 / 48.8), bf16 60.6 / 43.8 (63.3 / 48.3); one token of
+// 4096 x 14336 with 8 experts, top 2, 53.7 / 44.1 (55.9 / 49.3); of 2048 x 1408 with 64, top 6, groups of 128, 29.6 / 17.5
+// (31.1 / 21.3); 16 tokens of 256 x 512 with 8, top 2, 18.7 / 9.4 (19.4 / 9.8).
 //
-// What bounds it: two launches (9 us), then the vector unit (77 instructions a wave and 1 KB of weights,
-// about 5 TB/s); matrix instructions on 4 x 4 x 4 blocks in place of the dot products measured 5 to 10 %
-// slower, they issue from the same port.
+// What bounds it: two launches (9 us); in the gate/up launch the vector unit (77 instructions a wave and
+// 1 KB of weights, 118 MB in 26 us: 4.5 TB/s), matrix instructions on 4 x 4 x 4 blocks in place of the dot products
+// measured 5 to 10 % slower, they issue from the same port; in the down launch (59 MB in 24 us) every workgroup
+// stages all act vectors of its token, 36 KB at top 8, for 16 columns.
 //
 // A wave covers 16 weight rows; 8 lanes share a row, lane i takes reduction indices 256 c + 32 i + [0, 32)
 // (16 bytes) of step c: 128 contiguous bytes of a row, or 128-byte runs of the offline repack's blocks
@@ -19,8 +21,8 @@
 // of four steps (1024 indices, eight groups of 128) is loaded while the previous one is multiplied; lane i
 // fetches the scale and zero point of the panel's group i and passes them round.  The order in which a
 // row is summed is the same in both weight layouts.  Weights go through the caches: slots that share
-// an expert find them there, and a layer that fits the last-level cache stays in it (2048 x 1408: 17 us
-// against 21 with non-temporal loads, the 256-expert layer the same).
+// an expert find them there, and a layer that fits the last-level cache stays in it (2048 x 1408 called again
+// and again: 17 us against 21 with non-temporal loads, the 256-expert layer the same).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -34,7 +36,8 @@ namespace moe {
 // different banks.  Behind the values one float32 per chunk.
 //   fp16: the unit of the chunk.  The dot product takes subnormal operands as zero, so a chunk is moved up
 //         by the power of two that brings its largest value to [2^15, 2^16); values below 2^-29 of
-//         that largest one are lost, which is less than a rounding of its float32 sum.
+//         that largest one (possible only from 64 on) are lost, which is less than a rounding of its float32
+//         sum unless that value's weight is exactly zero.
 //   bf16: the sum of its values, which takes the bias of the weights (128 + z) out again.
 __host__ __device__ __forceinline__ int vec_bytes(int k) { return 2 * k + (k >> 7) * 16; }
 __host__ __device__ __forceinline__ int vec_total(int k) { return vec_bytes(k) + (k >> 5) * 4; }

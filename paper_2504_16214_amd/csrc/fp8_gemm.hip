@@ -364,11 +364,13 @@ __device__ __forceinline__ void store_row(const GemmParams& p, size_t at, const 
 // they come from different waves of a SIMD or are three instructions apart; run in lockstep between
 // two barriers per block, as the former 256 x 256 tile did, the waves read LDS together, wait
 // together and sit in the wait states between an instruction and its own FMAs (matrix unit busy 41 %
-// of 4980 cycles per block).  In turns it is busy 57 % (8192^3, 2.14 GHz: the clock is power-limited).
-// Measured, former tile -> this one: 4096 x 51200 x 5120 1.19 -> 1.02 ms (1.81 -> 2.11 PFLOP/s), 8192^3
+// of 4980 cycles per block).  In turns it is busy 57 % (8192^3, 2.14 GHz) and 51 % (4096 x 51200 x 5120, 1.84 GHz):
+// the clock is power-limited.
+// Measured, former tile -> this one: 4096 x 51200 x 5120 1.18 -> 1.00 ms (1.82 -> 2.15 PFLOP/s), 8192^3
 // 0.51 -> 0.46 ms; FP8 layer of 256 experts at 4096 tokens (128-slot blocks on the 128 x 128 tile
-// before): gate/up product 2.44 -> 1.65 ms (4.5 TB/s of weights, each fetched once), layer 4.28 ->
-// 3.10 ms.  What is left: dense, the exposed stores of a round (110 of 1020 us) and power; grouped, HBM.
+// before): gate/up product 2.44 -> 1.65 ms (4.5 TB/s of weights, each fetched once), layer 4.21 ->
+// 3.09 ms.  What is left: dense, the exposed stores of a round (110 of 1020 us) and power; grouped, loads (half
+// of the wave cycles wait, 2.1 GHz, matrix unit busy 25 %).
 template <int ML>
 struct PingGeom {
   static constexpr int T = 512, BM = 256, BN = 256, NT = 4;

@@ -16,12 +16,14 @@
 //
 // The kernel is specialised on the live 32-slot parts of a block (ML), so that a block costs what its
 // rows cost; 256-slot blocks then fetch and unpack an expert's weights once per 256 rows.  Up to 64 rows
-// it is bound by the weight stream (STREAM below), above by power: at 128 rows the matrix unit is busy
-// 57 % of the cycles at 1.73 GHz (2.4 nominal); without the fragment reads from LDS the cycles stay
-// the same and the clock rises to 2.0 GHz (1860 -> 1558 us), without weight loads likewise (1607 us).
+// its loads come as whole lines through LDS (STREAM below); at 22 rows per expert (bf16, K 7168, N 2048) neither
+// side is at its limit: 4.7 TB/s fetched, matrix unit busy 21 % of the cycles, vector unit 49 %.  Above it is
+// bound by power: at 128 rows the matrix unit is busy 56 % of the cycles at 1.77 GHz (2.4 nominal); without the
+// fragment reads from LDS the cycles stay the same and the clock rises to 2.0 GHz (1860 -> 1558 us), without
+// weight loads likewise (1607 us).
 // Measured, eight-wave 128-slot tile -> this one, gate/up product of 256 experts (K 7168, N 2048), fp16:
-// 128 rows per expert 2.09 -> 1.87 ms (1.03 PFLOP/s), 160 rows 2.87 -> 2.22, 192 rows 3.23 -> 2.54, 64 rows
-// 1.32 -> 1.17; layer at 4096 tokens fp16 4.09 -> 3.54 ms, bf16 5.44 -> 4.2 ms.
+// 128 rows per expert 2.09 -> 1.87 ms (even counts; 2.06 with drawn routing), 160 rows 2.87 -> 2.22, 192 rows
+// 3.23 -> 2.54, 64 rows 1.32 -> 1.17; layer at 4096 tokens fp16 4.03 -> 3.60 ms, bf16 5.44 -> 4.26 ms.
 #pragma once
 #include "gemm_kernel.hpp"
 

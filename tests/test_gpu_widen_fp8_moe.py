@@ -284,8 +284,8 @@ def test_fp8_layer_full_size_decode_sampled_tokens():
 
 
 def test_fp8_layer_full_size_prefill_sampled_tokens():
-    """The DeepSeek-shaped prefill batch (T = 4096, about 128 rows per expert: 128-slot blocks, most
-    experts own one full block and a second, partly filled one): the first and the last token plus
+    """The DeepSeek-shaped prefill batch (T = 4096, about 128 rows per expert: 256-slot blocks, most
+    experts own one half-full block): the first and the last token plus
     tokens chosen to cover many experts, in the launch configuration the benchmark times."""
     cfg = FP8_MOE_CONFIGS["fp8_moe_prefill"]
     say(f"fp8 layer full size {cfg}: generating")
