@@ -469,7 +469,7 @@ static bool fp8_plan(int M, int N, int K, Fp8Plan& pl) {
     //   16 x 10240 x 5120 3: 19.1 (13.3), 4: 17.9 (13.6), 5: 18.8 (14.8);  1 x 5120 x 25600 6: 36 (24), 8: 31 (23), 10: 31 (25)
     //   32 x 14336 x 4096 (224) 2: 21.3 (14.6), 3: 19.2 (14.7), 4: 20.1 (15.9);  1 x 2048 x 7168 (32) 8: 11.3 (7.4), 12: 11.0 (8.3), 14: 10.8 (8.6)
     const long long wgs = m_blocks * (N / bn);
-    if (wgs < 256 && bm < 256)
+    if (wgs < 256)
       splits = bm <= 32 ? fp8_splits_for((704 + (int)wgs / 2) / (int)wgs, wgs < 32 ? 16 : 12, KB) : fp8_splits_for(512 / (int)wgs, wgs < 32 ? 16 : 8, KB);
   }
   if (g_fp8_splits) splits = g_fp8_splits;
