@@ -399,6 +399,33 @@ def test_two_group_tile_grouped_row_counts(K, row_div_is_topk):
             assert float((np.abs(got[slots] - want[slots]) / error_bound(want[slots], a[rows], sa[rows], b[e], sb[e])).max()) <= 1.0
 
 
+@pytest.mark.parametrize("block_m,N", [(16, 192), (32, 384), (256, 768)])
+@pytest.mark.parametrize("blocks", [[1] * 11, [3, 1, 1, 1, 1, 1, 1, 1, 1, 2], [9, 0, 8, 1]])
+def test_grouped_tile_order_with_and_without_shared_experts(block_m, N, blocks):
+    """Groups of eight row blocks whose experts all differ, of which two or three are alike, and of one expert,
+    and a last group of fewer, over several feature blocks: every tile is done, and once."""
+    import gpu_util as U
+    counts, K = [max(b * block_m - 5, 0) for b in blocks], 256
+    flat = np.repeat(np.arange(len(counts), dtype=np.int32), counts)
+    np.random.default_rng(6).shuffle(flat)
+    S, E = flat.size, len(counts)
+    say(f"fp8 grouped order block_m={block_m} N={N} blocks={blocks}")
+    _, a, sa, b, sb = _grouped_case(S, 1, E, N, K, True, seed=970 + block_m)
+    al = U.run_align(torch.from_numpy(flat.reshape(S, 1)).cuda(), E, block_m)
+    C = torch.full((S, N), float("nan"), dtype=torch.float32, device="cuda")
+    M_.fp8_moe_grouped_gemm(torch.from_numpy(a).cuda(), torch.from_numpy(sa).cuda(), 1, torch.from_numpy(b).cuda(),
+                            torch.from_numpy(sb).cuda(), al["sorted_slot_ids"], al["block_expert_ids"], al["num_padded"],
+                            S, block_m, C)
+    torch.cuda.synchronize()
+    got = C.to(torch.float64).cpu().numpy()
+    want, _ = F.grouped_blockwise_gemm(a, sa, 1, b, sb, flat)
+    assert not np.isnan(got).any()
+    for e in range(E):
+        s = np.nonzero(flat == e)[0]
+        if s.size:
+            assert float((np.abs(got[s] - want[s]) / error_bound(want[s], a[s], sa[s], b[e], sb[e])).max()) <= 1.0
+
+
 @pytest.mark.parametrize("front", [1, 31, 32, 130, 254])
 def test_two_group_tile_reads_the_whole_table_of_a_block(front):
     """A block's table may hold ignored entries anywhere, not only behind its slots: `front` of them
