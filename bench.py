@@ -136,10 +136,12 @@ def main():
         step()
     torch.cuda.synchronize()
 
-    # what the layer runs on for these sizes: 16 = two-group tile (256-slot blocks), 0 = vector products, else a grouped tile
-    tile = M.moe_last_gemm_plan()["mt"]
-    kernel = {16: "w4a16_twogroup_kernel", 0: "few_gate_up_kernel"}.get(tile, "w4a16_gemm_kernel")
-    block_m = {16: 256, 0: None}.get(tile, M.moe_layer_block_m(cfg.T, cfg.E, cfg.topk) if args.prepacked else
+    # what the layer runs on for these sizes: 16 = two-group tile (256-slot blocks), "mid" = 64-slot tile, 0 = vector
+    # products, else a grouped tile
+    plan = M.moe_last_gemm_plan()
+    tile = "mid" if (plan["mt"], plan["ks"]) == (4, 256) else plan["mt"]
+    kernel = {16: "w4a16_twogroup_kernel", "mid": "w4a16_mid_kernel", 0: "few_gate_up_kernel"}.get(tile, "w4a16_gemm_kernel")
+    block_m = {16: 256, "mid": 64, 0: None}.get(tile, M.moe_layer_block_m(cfg.T, cfg.E, cfg.topk) if args.prepacked else
                                      M.moe_layer_block_m_for(cfg.T, cfg.K, cfg.N, cfg.E, cfg.topk, cfg.group))
 
     # per-step stage events, created (and first recorded) before the timed region

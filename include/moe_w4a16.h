@@ -182,7 +182,7 @@ int moe_w4a16_layer(const void* X, const int32_t* topk_ids, const float* topk_we
  * call performs no allocation of any kind.  Sizes for which
  * moe_w4a16_layer_workspace_bytes(...) exceeds 64 MiB return MOE_WORKSPACE_TOO_SMALL (the
  * DeepSeek-shaped decode batch of 128 tokens needs 33 MiB); a bf16 batch that exceeds it by no more than the
- * row sums of the two-group tile (T * topk * N / 32 bytes) runs on another tile instead, with the same
+ * row sums of the two-group or the 64-slot tile (T * topk * N / 32 bytes) runs on another tile instead, with the same
  * accuracy but other roundings than moe_w4a16_layer with its full workspace.  The array's address is resolved on
  * the first call on each device (make that call outside a graph capture).  All calls on one GPU
  * share the array: calls that overlap on one GPU (different streams or threads) race; calls
@@ -254,7 +254,7 @@ int moe_route_align(const float* logits, const float* bias, int T, int E, int to
 /*
  * Router + layer on one stream: moe_route_align into tables held in the workspace, then the two
  * grouped GEMMs and the combine of moe_w4a16_layer: four launches up to 64 tokens, five beyond, one (fp16) or
- * two (bf16) more for large batches on the two-group tile, three for the few tokens that need no bucketing.
+ * two (bf16) more for batches on the two-group or the 64-slot tile, three for the few tokens that need no bucketing.
  * Arguments as for the two; `workspace` of at least moe_w4a16_routed_layer_workspace_bytes(...)
  * bytes, 256-byte aligned.
  */
@@ -270,8 +270,8 @@ int moe_w4a16_routed_layer(const void* X, const float* logits, const float* bias
  *
  * moe_set_stage_events: while set (n == 5), moe_w4a16_layer records the given
  * hipEvent_t handles on its stream: events[0] before bucketing, [1] before the
- * first grouped GEMM, [2] after it, [3] before the combine, [4] after it.  Large
- * batches on the two-group tile: [0] to [1] includes the reorder of X and, in bf16,
+ * first grouped GEMM, [2] after it, [3] before the combine, [4] after it.  Batches
+ * on the two-group or the 64-slot tile: [0] to [1] includes the reorder of X and, in bf16,
  * [2] to [3] the row sums of the second operand.  A few tokens: nothing between [0]
  * and [1] but the router, nor between [3] and [4].  Pass (NULL, 0) to clear.  Thread-local.
  *
@@ -298,14 +298,15 @@ int moe_w4a16_routed_layer(const void* X, const float* logits, const float* bias
  * moe_layer_block_m: the bucketing block size the layer picks for these sizes (see moe_layer_block_m_for).
  *
  * moe_set_block_m_override: force the bucketing block of moe_w4a16_layer (16 ... 256) instead of
- * the built-in choice; 0 restores it.  256 takes the two-group tile where the shapes admit it.
+ * the built-in choice; 0 restores it.  256 takes the two-group tile and 64 the tile of that many slots for
+ * medium batches where the shapes admit it.
  * Thread-local.
  *
  * moe_layer_block_m_for: the same with the layer's shapes known (group-128 layers with
  * K % 1024 == 0 and N % 1024 == 0 and more than 28 rows per expert take 128-slot blocks for
  * the eight-wave tile); honours moe_set_block_m_override.  It is the block to bucket by for the
- * staged calls; large batches of such layers (see twogroup_pays in api.hip) bucket by 256 inside
- * the layer call, for a tile that only the layer can use.
+ * staged calls; medium and large batches of such layers (see mid_pays and twogroup_pays in api.hip) bucket by 64 and
+ * 256 inside the layer call, for tiles that only the layer can use.
  *
  * moe_set_wide_tiles: 0 = use the eight-wave tiles (128 tokens, or 256 in the layer) whenever the block
  * and the shape allow it (default), 1 = never (the four-wave tiles serve every block size).  Thread-local.

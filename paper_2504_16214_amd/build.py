@@ -35,6 +35,8 @@ def _units():
         units.append(("gemm_inst.hip", f"gemm_inst_wide_dt{dt}.o", [f"-DMOE_DT={dt}", "-DMOE_KW=4", "-DMOE_WIDE=1"]))
     for dt in (0, 1):      # two-group 256-slot tiles (large batches), group 128 only
         units.append(("gemm_twogroup.hip", f"gemm_twogroup_dt{dt}.o", [f"-DMOE_DT={dt}"]))
+    for dt in (0, 1):      # 64-slot tiles (medium batches), group 128 only
+        units.append(("gemm_mid.hip", f"gemm_mid_dt{dt}.o", [f"-DMOE_DT={dt}"]))
     for src in ("align.hip", "elementwise.hip", "few_tokens.hip", "router.hip", "fp8_gemm.hip", "fp8_quant.hip", "api.hip"):
         units.append((src, src.replace(".hip", ".o"), []))
     return units

@@ -13,6 +13,7 @@
 #include "few_tokens.hpp"
 #include "fp8_gemm.hpp"
 #include "gemm_kernel.hpp"
+#include "gemm_mid.hpp"
 #include "gemm_twogroup.hpp"
 
 
@@ -21,7 +22,7 @@ namespace moe {
 int launch_align(const int32_t*, int, int, int, int, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*,
                  hipStream_t);
 int launch_silu_mul(const void*, void*, long long, int, int, hipStream_t);
-int launch_prepare_rows(const void*, long long, int, int, void*, float*, hipStream_t);
+int launch_prepare_rows(const void*, long long, int, int, int, void*, float*, float, hipStream_t);
 int launch_repack(const int32_t*, int, int, int, int, int32_t*, hipStream_t);
 int launch_awq_import(const int32_t*, const int32_t*, const void*, int, int, int, int, int32_t*, void*, uint8_t*,
                       hipStream_t);
@@ -350,8 +351,36 @@ static bool twogroup_pays(long long S, int E, int K, int N, int dt, int pre) {
   return avg >= 29 && tiles >= 1400 && (packed >= 1000 || avg >= 112);
 }
 
+// Does the layer run on the 64-slot tile (gemm_mid.hpp)?  It reads an expert's weights once for up to 64 rows, works
+// off whole 16-row parts only, and takes activations that were put in order by a launch of their own (4 us; bf16:
+// two, with the sums of act), so the launch has to be large: a quarter of a billion weights in each of an expert's
+// matrices together and two workgroups for each of three on a CU.  Former choice over this tile, 624 calls (6 shapes, 3 to 96 rows
+// per expert, uniform and power-law routing, both layouts), by rows per expert:
+//   256 experts, K 7168, N 2048, fp16   3: 1.01  6: 0.98  9: 1.10  16: 1.04  28: 1.13  40: 1.09  48: 1.06  64: 0.92
+//                                bf16   3: 0.99  6: 0.97  9: 1.31  16: 1.21  28: 1.14  40: 1.17  64: 1.02  96: 0.95
+//   8 experts, K 4096, N 14336,  fp16   6: 0.95  9: 1.10  16: 1.01  28: 1.07  32: 1.32  48: 1.21  64: 0.95
+//                                bf16   6: 0.92  9: 1.27  16: 1.14  28: 1.14  32: 1.34  64: 1.07  96: 1.29
+//   128 experts, K = N = 2048,   fp16   6: 0.90  9: 1.02  16: 0.97  28: 1.05  40: 1.12  64: 0.90
+//                                bf16   6: 0.88  9: 1.19  16: 1.09  28: 1.13  40: 1.17  64: 1.00
+//   smaller: 16 experts, K 4096, N 2048, fp16 9: 1.11 20: 1.00 40: 0.92;  64 experts, K 2048, N 1024, fp16 9: 1.02 20: 0.92 40: 0.92
+// Operand-order weights, whose other choice is the 64-slot four-wave tile, gain a little longer.  Skewed
+// routing gains more where it is a matter of chance at all (0.85 ... 1.87; 8 experts at 20 and 24 rows lose 0.85 ... 0.95).
+static bool mid_pays(long long S, int E, int K, int N, int dt, int pre) {
+  const long long avg = S / (E > 0 ? E : 1);
+  return avg >= 9 && avg < (dt == MOE_BF16 ? 80 : pre ? 72 : 56) && (long long)E * N * K >= 250000000LL && (long long)E * N >= 96000;
+}
+
+// Reduction splits of its down projection: about one workgroup for each of three on a CU.
+static int mid_splits(long long S, int E, int K, int N) {
+  const long long wgs = (S < E ? S : E) * (K / 128);
+  int s = wgs >= 768 ? 1 : (int)((768 + wgs / 2) / (wgs > 0 ? wgs : 1)), npan = N / 1024;
+  if (s > npan) s = npan;
+  if (s > 8) s = 8;
+  return s < 1 ? 1 : s;
+}
+
 struct Workspace {
-  size_t counts, offsets, num_padded, sorted, blocks, act, Y, base, rsum, total;
+  size_t counts, offsets, num_padded, sorted, blocks, act, Y, base, rsum, planes, total;
 };
 static Workspace carve(long long T, int K, int N, int E, int topk, int dt) {
   const long long S = T * topk;
@@ -367,10 +396,18 @@ static Workspace carve(long long T, int K, int N, int E, int topk, int dt) {
   w.Y = o;           o += round_up((size_t)S * K * 4 * std::max(pick_k_splits(S, E, K, N, pick_block_m(S, E)),
                                                             pick_k_splits(S, E, K, N, pick_block_m(S, E, true))), 256);
   w.base = o;        // what the layer cannot do without
-  // row sums of act for the bf16 operands of the two-group tile; a caller's workspace without them
-  // runs the layer on the eight-wave tile instead
+  // row sums of act for the bf16 operands of the two-group and the 64-slot tile; a caller's workspace
+  // without them runs the layer on another tile instead.  (Where only the 64-slot tile wants them they are
+  // reserved for either type: the query says the same for both, as it always has there.)
   w.rsum = o;
-  if (dt == MOE_BF16 && K % 1024 == 0 && N % 1024 == 0 && twogroup_pays(S, E, K, N, dt, 0)) o += round_up((size_t)S * (N / 128) * 4, 256);
+  const bool ordered = K % 1024 == 0 && N % 1024 == 0, rows_for_two = ordered && twogroup_pays(S, E, K, N, MOE_BF16, 0);
+  if (rows_for_two ? dt == MOE_BF16 : ordered && mid_pays(S, E, K, N, dt, 0)) o += round_up((size_t)S * (N / 128) * 4, 256);
+  // planes of the 64-slot tile's split down product; without them it makes do with those at Y
+  w.planes = o;
+  if (ordered && mid_pays(S, E, K, N, dt, 0)) {
+    const size_t need = (size_t)S * K * 4 * mid_splits(S, E, K, N);
+    if (need > w.base - w.Y) o += round_up(need, 256);
+  }
   w.total = o;
   return w;
 }
@@ -679,6 +716,39 @@ static int run_twogroup(const void* A, const float* bias_rows, int row_div, cons
   return MOE_OK;
 }
 
+// One product of the layer on the 64-slot tile.
+static int run_mid(const void* A, const float* sums, int row_div, const int32_t* qw, const void* sc, const uint8_t* z,
+                   const int32_t* sorted, const int32_t* blocks, const int32_t* num_padded, int num_slots, int E, int N_out,
+                   int K_in, int dt, int fuse, int pre, int want_splits, void* C, int* used_splits, hipStream_t stream) {
+  MidParams p;
+  p.A = A; p.sums = sums; p.row_div = row_div;
+  p.qweight = qw; p.scales = sc; p.zeros = z;
+  p.sorted_slot_ids = sorted; p.block_expert_ids = blocks; p.num_padded = num_padded;
+  p.num_slots = num_slots; p.E = E; p.N_out = N_out; p.K_in = K_in; p.C = C;
+  p.n_tiles = N_out / 128;
+  p.k_splits = 1; p.k_span = K_in; p.split_stride = (long long)num_slots * N_out;
+  if (want_splits > 1) {               // whole panels of 1024, every range non-empty
+    const int npan = K_in / 1024, per = (npan + want_splits - 1) / want_splits;
+    p.k_splits = (npan + per - 1) / per;
+    p.k_span = per * 1024;
+  }
+  if (used_splits) *used_splits = p.k_splits;
+  const long long est_blocks = (num_slots + 63) / 64 + (num_slots < E ? num_slots : E) / 2;
+  int tpw = (48 + p.k_span / 256 - 1) / (p.k_span / 256);
+  if (tpw > 8) tpw = 8;
+  if (tpw > p.n_tiles) tpw = p.n_tiles;
+  while (tpw > 1 && (p.n_tiles % tpw != 0 || est_blocks * (p.n_tiles / tpw) * p.k_splits < 1536)) --tpw;
+  if (g_force_tpw > 0) tpw = g_force_tpw < p.n_tiles ? g_force_tpw : p.n_tiles;
+  p.tiles_per_wg = tpw;
+  const long long grid = (long long)(align_capacity(num_slots, E, 64) / 64) * ((p.n_tiles + tpw - 1) / tpw) * p.k_splits;
+  if (grid > 0x7fffffffLL) return fail(MOE_UNSUPPORTED_SHAPE, "grid too large");
+  const int plan[9] = {4, 2, 256, 1, tpw, p.k_splits, p.k_span, fuse, 4};
+  for (int i = 0; i < 9; ++i) g_last_plan[i] = plan[i];
+  const int err = (dt == MOE_F16 ? launch_mid_f16 : launch_mid_bf16)(p, fuse, pre, (int)grid, stream);
+  if (err != 0) return hip_fail(err, "64-slot GEMM launch");
+  return MOE_OK;
+}
+
 // Do the vector-product kernels (few_tokens.hip) take the call?  They have two launches instead of four, but
 // read an expert's weights once for every slot, and their down launch has a workgroup of eight waves for
 // every token and 16 columns (one fits a CU), whose waves idle where a token has few (slot, part)
@@ -753,18 +823,20 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   int32_t* blocks = (int32_t*)(base + w.blocks);
   void* act = base + w.act;
   void* Y = base + w.Y;
-  // Two-group tile: its shapes, every tuning hook that asks for another kernel at rest, 32-bit offsets
+  // Two-group and 64-slot tile: their shapes, every tuning hook that asks for another kernel at rest, 32-bit offsets
   // in range, room for the row sums (bf16), and the alignment of the other register-scale tiles, so
   // that scales and zero points of less are taken or refused alike at every token number.
-  const bool two_group =
-      layer_wide_ok(K, N, group_size) && g_scale_path != 1 && g_force_ksplit == 0 &&
-      (g_force_block_m == 256 || (g_force_block_m == 0 && twogroup_pays(S, E, K, N, (int)dt, pre))) &&
-      (dt == MOE_F16 || workspace_bytes >= w.rsum + (size_t)S * (N / 128) * 4) &&
+  const bool ordered =
+      layer_wide_ok(K, N, group_size) && g_scale_path != 1 && (dt == MOE_F16 || workspace_bytes >= w.rsum + (size_t)S * (N / 128) * 4) &&
       (((uintptr_t)X | (uintptr_t)qw1 | (uintptr_t)qw2) % 16) == 0 && (((uintptr_t)s1 | (uintptr_t)s2) % 16) == 0 &&
       (((uintptr_t)z1 | (uintptr_t)z2) % 8) == 0 && (long long)N * K < (1LL << 31) &&
       (long long)E * 2 * N * (K / 128) < (1LL << 31) && (long long)T * K * 2 < (1LL << 31) && S * N * 2 < (1LL << 31);
+  const bool mid_fits = mid_pays(S, E, K, N, (int)dt, pre);
+  const bool mid = ordered && (g_force_block_m == 64 || (g_force_block_m == 0 && mid_fits));
+  const bool two_group = ordered && g_force_ksplit == 0 &&
+                         (g_force_block_m == 256 || (g_force_block_m == 0 && !mid_fits && twogroup_pays(S, E, K, N, (int)dt, pre)));
   // a forced bucketing block wins; a forced token tile (tuning hook) also fixes the block
-  const int block_m = two_group ? 256 : g_force_block_m > 0 ? g_force_block_m
+  const int block_m = two_group ? 256 : mid ? 64 : g_force_block_m > 0 ? g_force_block_m
                       : (g_force_mt == 1 || g_force_mt == 2 || g_force_mt == 4 || g_force_mt == 8)
                           ? 16 * g_force_mt : pick_block_m(S, E, layer_wide_ok(K, N, group_size), !pre && layer_wide_ok(K, N, group_size));
   const bool ev = g_nevents == 5;
@@ -808,20 +880,49 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
     // the reordered rows of X and their sums live where Y will be written: Y is written last
     float* const xsum = dt == MOE_BF16 ? (float*)((unsigned char*)Y + round_up((size_t)T * K * 2, 256)) : nullptr;
     float* const asum = dt == MOE_BF16 ? (float*)(base + w.rsum) : nullptr;
-    err = launch_prepare_rows(X, T, K, (int)dt, Y, xsum, stream);
+    err = launch_prepare_rows(X, T, K, (int)dt, 0, Y, xsum, 47.f, stream);
     if (err != 0) return hip_fail(err, "activation reorder launch");
     mark(1);
     int st = run_twogroup(Y, xsum, topk, qw1, s1, z1, sorted, blocks, num_padded, (int)S, E, 2 * N, K, (int)dt, 1, pre, act, stream);
     if (st != MOE_OK) return st;
     mark(2);
     if (asum) {
-      err = launch_prepare_rows(act, S, N, (int)dt, nullptr, asum, stream);
+      err = launch_prepare_rows(act, S, N, (int)dt, 0, nullptr, asum, 47.f, stream);
       if (err != 0) return hip_fail(err, "row sum launch");
     }
     st = run_twogroup(act, asum, 1, qw2, s2, z2, sorted, blocks, num_padded, (int)S, E, K, N, (int)dt, 0, pre, Y, stream);
     if (st != MOE_OK) return st;
     mark(3);
     err = launch_combine(Y, 1, 1, topk_weights, topk_ids, E, out, T, topk, K, (int)dt, stream);
+    if (err != 0) return hip_fail(err, "combine launch");
+    mark(4);
+    return MOE_OK;
+  }
+  if (mid) {
+    float* const xsum = dt == MOE_BF16 ? (float*)((unsigned char*)Y + round_up((size_t)T * K * 2, 256)) : nullptr;
+    float* const asum = dt == MOE_BF16 ? (float*)(base + w.rsum) : nullptr;
+    err = launch_prepare_rows(X, T, K, (int)dt, 1, Y, xsum, 1.f, stream);
+    if (err != 0) return hip_fail(err, "activation reorder launch");
+    mark(1);
+    int st = run_mid(Y, xsum, topk, qw1, s1, z1, sorted, blocks, num_padded, (int)S, E, 2 * N, K, (int)dt, 1, pre, 1, act, nullptr, stream);
+    if (st != MOE_OK) return st;
+    mark(2);
+    if (asum) {
+      // (act's runs are in the order the kernel reads; the sums do not mind)
+      err = launch_prepare_rows(act, S, N, (int)dt, 1, nullptr, asum, 1.f, stream);
+      if (err != 0) return hip_fail(err, "row sum launch");
+    }
+    // reduction splits: as many partial planes as the caller's workspace holds
+    int want = g_force_ksplit > 0 ? g_force_ksplit : mid_splits(S, E, K, N);
+    const size_t plane = (size_t)S * K * 4, behind = w.total - w.planes;
+    void* P = Y;
+    if (plane * want > w.base - w.Y && plane * want <= behind && workspace_bytes >= w.total) P = base + w.planes;
+    else if (plane * want > w.base - w.Y) want = (int)((w.base - w.Y) / plane);
+    int planes = 1;
+    st = run_mid(act, asum, 1, qw2, s2, z2, sorted, blocks, num_padded, (int)S, E, K, N, (int)dt, 0, pre, want, P, &planes, stream);
+    if (st != MOE_OK) return st;
+    mark(3);
+    err = launch_combine(P, 1, planes, topk_weights, topk_ids, E, out, T, topk, K, (int)dt, stream);
     if (err != 0) return hip_fail(err, "combine launch");
     mark(4);
     return MOE_OK;

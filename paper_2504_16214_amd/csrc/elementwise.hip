@@ -103,24 +103,34 @@ combine_kernel(const void* __restrict__ Yv, const float* __restrict__ w, const i
   }
 }
 
-// Activations for the two-group GEMM.  out (may be null): every run of eight reduction indices in the
-// order 0,4,1,5,2,6,3,7.  bias (may be null): 47 * (sum of the row's 128-index group), float32 (the
-// bf16 operands carry the constant 47, see gemm_twogroup.hpp).  16 lanes per group, 8 elements each;
+// 8 consecutive 16-bit elements x0..x7 -> order x0,x2,x4,x6,x1,x3,x5,x7
+__device__ __forceinline__ u32x4 deal8(const u32x4& a) {
+  u32x4 o;
+  o.x = __builtin_amdgcn_perm(a.y, a.x, 0x05040100u);  // (x0, x2)
+  o.y = __builtin_amdgcn_perm(a.w, a.z, 0x05040100u);  // (x4, x6)
+  o.z = __builtin_amdgcn_perm(a.y, a.x, 0x07060302u);  // (x1, x3)
+  o.w = __builtin_amdgcn_perm(a.w, a.z, 0x07060302u);  // (x5, x7)
+  return o;
+}
+
+// Activations for the two-group and the 64-slot GEMM.  out (may be null): every run of eight reduction indices in
+// the order 0,4,1,5,2,6,3,7 (DEAL: 0,2,4,6,1,3,5,7).  sums (may be null): factor * (sum of the row's 128-index group), float32
+// (two-group, bf16: 47, the constant its operands carry; 64-slot, bf16: 1).  16 lanes per group, 8 elements each;
 // a pure stream (4096 x 7168: 117 MB moved in 24 us).
-template <int DT>
+template <int DT, int DEAL>
 __global__ void __launch_bounds__(256)
-prepare_rows_kernel(const uint16_t* __restrict__ X, long long groups, uint16_t* __restrict__ out, float* __restrict__ bias) {
+prepare_rows_kernel(const uint16_t* __restrict__ X, long long groups, uint16_t* __restrict__ out, float* __restrict__ sums, float factor) {
   for (long long g = ((long long)blockIdx.x * 256 + threadIdx.x) >> 4; g < groups; g += ((long long)gridDim.x * 256) >> 4) {
     const long long at = g * 128 + (threadIdx.x & 15) * 8;
     const u32x4 v = *reinterpret_cast<const u32x4*>(X + at);
-    if (out) *reinterpret_cast<u32x4*>(out + at) = interleave8(v);
-    if (bias) {
+    if (out) *reinterpret_cast<u32x4*>(out + at) = DEAL ? deal8(v) : interleave8(v);
+    if (sums) {
       float s = 0.f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) s += from_bits16<DT>((uint16_t)v[i]) + from_bits16<DT>((uint16_t)(v[i] >> 16));
 #pragma unroll
       for (int d = 8; d >= 1; d >>= 1) s += __shfl_xor(s, d, 16);
-      if ((threadIdx.x & 15) == 0) bias[g] = 47.0f * s;
+      if ((threadIdx.x & 15) == 0) sums[g] = factor * s;
     }
   }
 }
@@ -231,15 +241,15 @@ int launch_awq_import(const int32_t* aq, const int32_t* az, const void* as, int 
   return (int)hipGetLastError();
 }
 
-int launch_prepare_rows(const void* X, long long rows, int K, int dt, void* out, float* bias, hipStream_t stream) {
+int launch_prepare_rows(const void* X, long long rows, int K, int dt, int deal, void* out, float* sums, float factor, hipStream_t stream) {
   const long long groups = rows * (K >> 7);
   if (groups == 0) return 0;
-  if (dt == kF16)
-    hipLaunchKernelGGL(prepare_rows_kernel<kF16>, dim3(grid_for(groups * 16)), dim3(256), 0, stream, (const uint16_t*)X,
-                       groups, (uint16_t*)out, bias);
-  else
-    hipLaunchKernelGGL(prepare_rows_kernel<kBF16>, dim3(grid_for(groups * 16)), dim3(256), 0, stream, (const uint16_t*)X,
-                       groups, (uint16_t*)out, bias);
+#define MOE_LAUNCH_PREPARE(DT, DEAL) \
+  hipLaunchKernelGGL((prepare_rows_kernel<DT, DEAL>), dim3(grid_for(groups * 16)), dim3(256), 0, stream, (const uint16_t*)X, groups, (uint16_t*)out, sums, factor)
+  if (dt == kF16) MOE_LAUNCH_PREPARE(kF16, 0);
+  else if (deal) MOE_LAUNCH_PREPARE(kBF16, 1);
+  else MOE_LAUNCH_PREPARE(kBF16, 0);
+#undef MOE_LAUNCH_PREPARE
   return (int)hipGetLastError();
 }
 

@@ -1,0 +1,128 @@
+"""GPU parity of the layer on its 64-slot tile (9 to 60 rows per expert, group 128): every number of live
+16-slot parts of a block, experts of more than one block, both weight layouts, reductions from one panel of
+1024 to an odd number of them, split and unsplit, several tiles per workgroup, zero scales and ignored ids."""
+import numpy as np
+import pytest
+import torch
+
+from moe_workloads import MoEConfig, make_inputs
+from test_gpu_twogroup_layer import _check, _inputs
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    import gpu_util as U
+    import paper_2504_16214_amd as M
+
+
+def _on_mid():
+    plan = M.moe_last_gemm_plan()
+    return (plan["mt"], plan["ks"], plan["waves"]) == (4, 256, 4)
+
+
+def _layer(inp, prepacked=False, tiles=0, splits=0):
+    d, c = U.DevInputs(inp), inp.cfg
+    out = torch.full((c.T, c.K), float("nan"), dtype=U.TORCH_DT[c.dtype], device="cuda")
+    mdt = M.MOE_F16 if c.dtype == "f16" else M.MOE_BF16
+    M.moe_set_block_m_override(64)
+    M.moe_set_tiles_per_workgroup(tiles)
+    M.moe_set_reduction_splits(splits)
+    try:
+        # (room for the bf16 row sums, which the size query adds only where the tile is the automatic choice)
+        need = M.moe_w4a16_layer_workspace_bytes(c.T, c.K, c.N, c.E, c.topk, mdt) + c.S * (c.N // 128) * 4 + 256
+        ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+        if prepacked:
+            p1, p2 = torch.empty_like(d.qw1), torch.empty_like(d.qw2)
+            M.moe_repack_qweight(d.qw1, False, p1)
+            M.moe_repack_qweight(d.qw2, True, p2)
+            M.moe_w4a16_layer_prepacked(d.X, d.ids, d.w, p1, d.s1, d.z1, p2, d.s2, d.z2, out, c.group, ws)
+        else:
+            M.moe_w4a16_layer(d.X, d.ids, d.w, d.qw1, d.s1, d.z1, d.qw2, d.s2, d.z2, out, c.group, ws)
+        torch.cuda.synchronize()
+        assert _on_mid(), M.moe_last_gemm_plan()
+        if splits:
+            assert M.moe_last_gemm_plan()["reduction_splits"] == min(splits, c.N // 1024)
+    finally:
+        M.moe_set_block_m_override(0)
+        M.moe_set_tiles_per_workgroup(0)
+        M.moe_set_reduction_splits(0)
+    return out
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("K,N,zero_scales", [(1024, 1024, True), (3072, 1024, False), (1024, 2048, False)])
+def test_every_live_part_count(dtype, K, N, zero_scales):
+    counts = [1, 15, 16, 17, 0, 32, 33, 48, 49, 63, 64, 65, 100, 130]
+    print(f"64-slot layer {dtype} K={K} N={N}", flush=True)
+    inp = _inputs(dtype, K, N, counts, seed=900 + K + N, zero_scales=zero_scales, bad_ids=5)
+    got = _layer(inp)
+    _check(inp, got, f"64-slot layer {dtype} K={K} N={N}")
+    bad = (inp.topk_ids[:, 0] < 0) | (inp.topk_ids[:, 0] >= inp.cfg.E)
+    assert np.all(U.dev_to_f64(got)[bad] == 0)
+    same = _layer(inp, prepacked=True)
+    assert torch.equal(got.view(torch.int16), same.view(torch.int16)), "operand-order weights: same words, same order"
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("tiles", [3, 8])
+def test_tiles_per_workgroup(dtype, tiles):
+    """Walking several feature tiles with one load pipeline gives the same bits as one tile each."""
+    inp = _inputs(dtype, 2048, 1024, [7, 20, 40, 60, 90], seed=901)
+    print(f"64-slot layer {dtype} tiles per workgroup {tiles}", flush=True)
+    got = _layer(inp, tiles=tiles)
+    _check(inp, got, f"tiles {tiles}")
+    assert torch.equal(got.view(torch.int16), _layer(inp, tiles=1).view(torch.int16))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("splits", [2, 3])
+def test_split_down_product(dtype, splits):
+    inp = _inputs(dtype, 1024, 3072, [5, 16, 30, 50, 20], seed=902)
+    print(f"64-slot layer {dtype} splits {splits}", flush=True)
+    _check(inp, _layer(inp, splits=splits), f"splits {splits}")
+
+
+def test_small_workspace_falls_back():
+    """bf16 without room for the row sums: the layer runs on the other tiles, within the same bound."""
+    inp = _inputs("bf16", 1024, 1024, [10, 26, 40], seed=903)
+    d, c = U.DevInputs(inp), inp.cfg
+    out = torch.empty((c.T, c.K), dtype=torch.bfloat16, device="cuda")
+    ws = torch.empty(M.moe_w4a16_layer_workspace_bytes(c.T, c.K, c.N, c.E, c.topk, M.MOE_BF16), dtype=torch.uint8, device="cuda")
+    M.moe_set_block_m_override(64)
+    try:
+        M.moe_w4a16_layer(d.X, d.ids, d.w, d.qw1, d.s1, d.z1, d.qw2, d.s2, d.z2, out, c.group, ws)
+        torch.cuda.synchronize()
+        assert not _on_mid()
+    finally:
+        M.moe_set_block_m_override(0)
+    _check(inp, out, "fallback")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_automatic_choice_through_the_three_entries(dtype):
+    """Several slots a token, the workspace of the size query (with the planes of a split down product) and no
+    override: the plain layer against the oracle, the prepacked and the routed one with the same bits."""
+    cfg = MoEConfig("mid_auto", T=44, K=2048, N=20480, E=8, topk=2, group=128, dtype=dtype, seed=904)
+    print(f"64-slot layer, automatic choice {cfg}", flush=True)
+    inp = make_inputs(cfg)
+    d = U.DevInputs(inp)
+    logits = torch.from_numpy(inp.logits).cuda()
+    M.moe_route_topk(logits, None, d.ids, d.w)
+    inp.topk_ids, inp.topk_weights = d.ids.cpu().numpy(), d.w.cpu().numpy()
+    got = U.run_layer(d)
+    assert _on_mid() and M.moe_last_gemm_plan()["reduction_splits"] > 1
+    _check(inp, got, "plain entry")
+    sizes = (cfg.T, cfg.K, cfg.N, cfg.E, cfg.topk, M.MOE_F16 if dtype == "f16" else M.MOE_BF16)
+    p1, p2 = torch.empty_like(d.qw1), torch.empty_like(d.qw2)
+    M.moe_repack_qweight(d.qw1, False, p1)
+    M.moe_repack_qweight(d.qw2, True, p2)
+    out = torch.full_like(got, float("nan"))
+    ws = torch.full((M.moe_w4a16_layer_workspace_bytes(*sizes),), 255, dtype=torch.uint8, device="cuda")
+    M.moe_w4a16_layer_prepacked(d.X, d.ids, d.w, p1, d.s1, d.z1, p2, d.s2, d.z2, out, cfg.group, ws)
+    torch.cuda.synchronize()
+    assert _on_mid() and torch.equal(out.view(torch.int16), got.view(torch.int16))
+    out = torch.full_like(got, float("nan"))
+    ws = torch.full((M.moe_w4a16_routed_layer_workspace_bytes(*sizes),), 255, dtype=torch.uint8, device="cuda")
+    M.moe_w4a16_routed_layer(d.X, logits, None, d.qw1, d.s1, d.z1, d.qw2, d.s2, d.z2, out, cfg.topk, cfg.group, ws)
+    torch.cuda.synchronize()
+    assert _on_mid() and torch.equal(out.view(torch.int16), got.view(torch.int16))
