@@ -254,7 +254,7 @@ int moe_route_align(const float* logits, const float* bias, int T, int E, int to
 /*
  * Router + layer on one stream: moe_route_align into tables held in the workspace, then the two
  * grouped GEMMs and the combine of moe_w4a16_layer: four launches up to 64 tokens, five beyond, one (fp16) or
- * two (bf16) more for batches on the two-group or the 64-slot tile, three for the few tokens that need no bucketing.
+ * two (bf16) more for batches on the two-group or the 64-slot tile, two (at most 64 experts, 16 a token) or three for the few tokens that need no bucketing.
  * Arguments as for the two; `workspace` of at least moe_w4a16_routed_layer_workspace_bytes(...)
  * bytes, 256-byte aligned.
  */
@@ -273,7 +273,7 @@ int moe_w4a16_routed_layer(const void* X, const float* logits, const float* bias
  * first grouped GEMM, [2] after it, [3] before the combine, [4] after it.  Batches
  * on the two-group or the 64-slot tile: [0] to [1] includes the reorder of X and, in bf16,
  * [2] to [3] the row sums of the second operand.  A few tokens: nothing between [0]
- * and [1] but the router, nor between [3] and [4].  Pass (NULL, 0) to clear.  Thread-local.
+ * and [1] but the router where it is a launch of its own, nor between [3] and [4].  Pass (NULL, 0) to clear.  Thread-local.
  *
  * moe_set_tile_override: force the grouped GEMM tile (tokens per tile =
  * 16*mt, output features per workgroup = 64*nt) instead of the built-in

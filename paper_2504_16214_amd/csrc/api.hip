@@ -850,15 +850,17 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
                    (long long)N * K < (1LL << 31);
   if (few) {
     mark(0);
-    if (route) {
+    const FewRoute inside{route ? route->logits : nullptr, route ? route->bias : nullptr, route ? route->ids : nullptr, route ? route->weights : nullptr};
+    const bool fused = route && E <= kFewRouteE && topk <= kFewRouteTopk;
+    if (route && !fused) {
       err = launch_route_topk(route->logits, route->bias, T, E, topk, route->ids, route->weights, stream);
       if (err != 0) return hip_fail(err, "router launch");
     }
     mark(1);
-    err = launch_few_gate_up(X, topk_ids, qw1, s1, z1, act, T, topk, E, K, N, (int)dt, pre, stream);
+    err = launch_few_gate_up(X, fused ? &inside : nullptr, topk_ids, qw1, s1, z1, act, (float*)Y, T, topk, E, K, N, (int)dt, pre, stream);
     if (err != 0) return hip_fail(err, "few-token gate/up launch");
     mark(2);
-    err = launch_few_down(act, topk_ids, topk_weights, qw2, s2, z2, out, T, topk, E, K, N, (int)dt, pre, stream);
+    err = launch_few_down(act, (const float*)Y, topk_ids, topk_weights, qw2, s2, z2, out, T, topk, E, K, N, (int)dt, pre, stream);
     if (err != 0) return hip_fail(err, "few-token down launch");
     for (int& v : g_last_plan) v = 0;       // no tile
     mark(3);

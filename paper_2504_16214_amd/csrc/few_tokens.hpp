@@ -12,11 +12,20 @@ constexpr size_t kFewLds = 64 * 1024;      // LDS either kernel may take (no att
 bool few_tokens_fit(int topk, int K, int N);
 // Parts of the reduction that a slot's down product is cut into: about eight (slot, part) pairs for the eight waves.
 int few_down_parts(int topk, int N);
-// act [T * topk, N] (runs of eight reordered), then out [T, K]; ids outside [0, E) contribute zero.  Group
-// 128; X, act, out and the packed words 16-byte aligned; pre: the words are in operand order.
-int launch_few_gate_up(const void* X, const int32_t* ids, const int32_t* qw, const void* s, const uint8_t* z, void* act, int T,
-                       int topk, int E, int K, int N, int dt, int pre, hipStream_t stream);
-int launch_few_down(const void* act, const int32_t* ids, const float* w, const int32_t* qw, const void* s, const uint8_t* z,
+// Routing inside the gate/up launch: up to kFewRouteE experts and 16 experts a token; fills ids and weights [T, topk].
+constexpr int kFewRouteE = 64, kFewRouteTopk = 16;
+struct FewRoute {
+  const float* logits;
+  const float* bias;         // may be null
+  int32_t* ids;
+  float* weights;
+};
+// act [T * topk, N] as vectors of the down kernel (16-byte aligned) with their chunks' floats in units [T * topk, N / 32],
+// then out [T, K]; ids outside [0, E) contribute zero.  route (may be null): the ids come from there.  Group 128; X, act, out
+// and the packed words 16-byte aligned; pre: the words are in operand order.
+int launch_few_gate_up(const void* X, const FewRoute* route, const int32_t* ids, const int32_t* qw, const void* s, const uint8_t* z, void* act,
+                       float* units, int T, int topk, int E, int K, int N, int dt, int pre, hipStream_t stream);
+int launch_few_down(const void* act, const float* units, const int32_t* ids, const float* w, const int32_t* qw, const void* s, const uint8_t* z,
                     void* out, int T, int topk, int E, int K, int N, int dt, int pre, hipStream_t stream);
 
 }  // namespace moe

@@ -98,12 +98,13 @@ __device__ __forceinline__ unsigned long long row_max_u64(unsigned long long v) 
 
 constexpr int kRouter16MaxE = 256, kRouter16MaxTopk = 16;
 
+template <int KEYS = 16>      // keys a lane holds: E <= 16 KEYS
 __device__ __forceinline__ void route_token_row16(const float* __restrict__ row, const float* __restrict__ bias, int E,
                                                   int topk, int lane, int32_t* ids_out, float* w_out) {
   const int l16 = lane & 15;
-  unsigned long long key[16];
+  unsigned long long key[KEYS];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
+  for (int i = 0; i < KEYS; ++i) {
     const int e = l16 + 16 * i;
     key[i] = 0ull;
     if (e < E) {
@@ -121,7 +122,7 @@ __device__ __forceinline__ void route_token_row16(const float* __restrict__ row,
   for (int j = 0; j < topk; ++j) {
     unsigned long long best = 0ull;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) best = key[i] > best ? key[i] : best;
+    for (int i = 0; i < KEYS; ++i) best = key[i] > best ? key[i] : best;
     best = row_max_u64(best);
     const uint32_t e = 0xffffffffu - (uint32_t)(best & 0xffffffffull);
     uint32_t u = (uint32_t)(best >> 32);
@@ -129,7 +130,7 @@ __device__ __forceinline__ void route_token_row16(const float* __restrict__ row,
     my_val = l16 == j ? __uint_as_float(u) : my_val;
     my_id = l16 == j ? (int)e : my_id;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) key[i] = ((int)e == l16 + 16 * i) ? 0ull : key[i];
+    for (int i = 0; i < KEYS; ++i) key[i] = ((int)e == l16 + 16 * i) ? 0ull : key[i];
   }
   const float m = __shfl(my_val, 0, 16);
   const float p = l16 < topk ? expf(my_val - m) : 0.f;

@@ -145,3 +145,24 @@ def test_routed_layer_of_a_few_tokens(dtype, with_bias):
     assert ran_without_a_tile()
     M.moe_route_topk(logits, bd, d.ids, d.w)
     assert torch.equal(out, U.run_layer(d))
+
+
+@pytest.mark.parametrize("E,topk,T", [(64, 6, 4), (65, 6, 4), (17, 16, 1), (17, 17, 1), (5, 5, 6)])
+def test_routing_inside_the_gate_up_launch(E, topk, T):
+    """Either side of the limits (64 experts, 16 a token), with ties and signed zeros among the logits: the bits of
+    the plain entry on the ids and weights of the stand-alone router."""
+    cfg = MoEConfig("few_route_in", T=T, K=256, N=512, E=E, topk=topk, group=128, dtype="f16", seed=E + topk)
+    say(f"routing inside {cfg}")
+    inp = make_inputs(cfg)
+    inp.logits[:] = np.round(inp.logits)              # many ties
+    inp.logits[0, :3] = [0.0, -0.0, 0.0]
+    d = U.DevInputs(inp)
+    logits = torch.from_numpy(inp.logits).cuda()
+    M.moe_route_topk(logits, None, d.ids, d.w)
+    want = U.run_layer(d)
+    assert ran_without_a_tile()
+    ws = torch.full((M.moe_w4a16_routed_layer_workspace_bytes(T, cfg.K, cfg.N, E, topk, M.MOE_F16),), 255, dtype=torch.uint8, device="cuda")
+    out = torch.full((T, cfg.K), float("nan"), dtype=torch.float16, device="cuda")
+    M.moe_w4a16_routed_layer(d.X, logits, None, d.qw1, d.s1, d.z1, d.qw2, d.s2, d.z2, out, topk, cfg.group, ws)
+    torch.cuda.synchronize()
+    assert ran_without_a_tile() and torch.equal(out, want)
