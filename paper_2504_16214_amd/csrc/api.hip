@@ -269,10 +269,17 @@ static int run_gemm(const GemmArgs& a, hipStream_t stream) {
     // prefer a count that divides the tiles of a block evenly (no short last group)
     for (int t = tpw; t <= tpw + 2 && t <= 8 && t <= p.n_tiles; ++t)
       if (p.n_tiles % t == 0) { tpw = t; break; }
+    // Enough workgroups for the chip: with a few rows per expert (16-row blocks) a workgroup is all
+    // weight streaming and three rounds of the 768 that are resident even out the tail; with more rows
+    // two are enough.  A count that leaves a short last group is lowered to the next that does not, if
+    // that costs less than half of it.  Down projection of 256 experts, 2048 -> 7168 (56 tiles), f16:
+    // 128 tokens 4 or 7 tiles 358 us, 10 379, 12 403; 37 tokens on repacked weights 2 tiles 222 us,
+    // 4 228, 6 (what 1536 workgroups alone gave) 235.  The whole layer at 24 .. 96 tokens: 1 to 2 % less.
     const long long est_blocks = (a.num_slots + 16 * mt - 1) / (16 * mt) + (a.num_slots < a.E ? a.num_slots : a.E) / 2;
-    // (measured on the 256-expert decode shape: seven or eight 8-stage tiles per workgroup beat five,
-    // as long as about 1500 workgroups remain)
-    while (tpw > 1 && est_blocks * ((p.n_tiles + tpw - 1) / tpw) * ksp < 1536) --tpw;
+    const long long least = mt == 1 ? 2304 : 1536;
+    while (tpw > 1 && est_blocks * ((p.n_tiles + tpw - 1) / tpw) * ksp < least) --tpw;
+    for (int t = tpw; mt == 1 && 2 * t > tpw; --t)
+      if (p.n_tiles % t == 0) { tpw = t; break; }
   }
   if (g_force_tpw > 0) tpw = szr ? (g_force_tpw < p.n_tiles ? g_force_tpw : p.n_tiles) : 1;
   p.tiles_per_wg = tpw;
