@@ -127,7 +127,8 @@ constexpr int kMaxGroups = 512;
 
 static size_t gemm_lds_bytes(int mt, int nt, int ks, int G, int szr) {
   const size_t M_T = 16 * mt, NW = 16 * nt;
-  return kXBufs(mt, ks) * M_T * (ks * 2 + kXRowPad) + 4 * NW * (ks / 2 + kWRowPad(ks)) + (szr ? 0 : (size_t)G * 64 * nt * 4) + M_T * 4;
+  const int xbufs = mt == 4 ? 2 : kXBufs(mt, nt, ks, szr);    // (the 64x128 tile takes one of the two: same limit on K_in / group_size)
+  return xbufs * M_T * (ks * 2 + kXRowPad) + 4 * NW * (ks / 2 + kWRowPad(ks)) + (szr ? 0 : (size_t)G * 64 * nt * 4) + M_T * 4;
 }
 
 // The eight-wave 128-token tile serves 128-slot blocks of register-scale shapes in the stated

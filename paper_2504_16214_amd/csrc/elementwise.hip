@@ -103,16 +103,6 @@ combine_kernel(const void* __restrict__ Yv, const float* __restrict__ w, const i
   }
 }
 
-// 8 consecutive 16-bit elements x0..x7 -> order x0,x2,x4,x6,x1,x3,x5,x7
-__device__ __forceinline__ u32x4 deal8(const u32x4& a) {
-  u32x4 o;
-  o.x = __builtin_amdgcn_perm(a.y, a.x, 0x05040100u);  // (x0, x2)
-  o.y = __builtin_amdgcn_perm(a.w, a.z, 0x05040100u);  // (x4, x6)
-  o.z = __builtin_amdgcn_perm(a.y, a.x, 0x07060302u);  // (x1, x3)
-  o.w = __builtin_amdgcn_perm(a.w, a.z, 0x07060302u);  // (x5, x7)
-  return o;
-}
-
 // Activations for the two-group and the 64-slot GEMM.  out (may be null): every run of eight reduction indices in
 // the order 0,4,1,5,2,6,3,7 (DEAL: 0,2,4,6,1,3,5,7).  sums (may be null): factor * (sum of the row's 128-index group), float32
 // (two-group, bf16: 47, the constant its operands carry; 64-slot, bf16: 1).  16 lanes per group, 8 elements each;

@@ -14,7 +14,7 @@ namespace moe {
 template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE, int WV>
 int launch_w4a16_gemm(const GemmParams& p, int grid, hipStream_t stream) {
   auto kern = w4a16_gemm_kernel<DT, MT, NT, KS, KW, FUSE, SZR, PRE, WV>;
-  const size_t lds = TileGeom<MT, NT, KS, WV>::lds_bytes(p.G, SZR, PRE);
+  const size_t lds = TileGeom<MT, NT, KS, SZR, WV>::lds_bytes(p.G, PRE);
   if (lds > 64 * 1024) {
     // Raise the dynamic LDS limit of this kernel, once per device and size (the attribute is
     // per device; remembering it per device keeps a second GPU of the process correct).

@@ -102,7 +102,8 @@ __device__ __forceinline__ floatx16_t mfma32x32x16(const u32x4& a, const u32x4& 
 //     -(bias + z) subtracts bias and zero point inside the fp32 accumulation.
 //   ZM = 0 (fp16): one packed subtract per nibble pair yields the exact integers q - z.
 // Either way the group scale is applied in fp32 (to the partial sum of a chunk-step, or by
-// keeping the accumulator in units of the current group's scale: see RS in the kernel).
+// keeping the accumulator in units of the current group's scale: see RS in the kernel).  The bf16
+// 64x128 tile with its scales in LDS takes the plain q and the zero points by row sums: see ZS.
 //
 // fp16: nibbles 0/4 of a word are ORed into the mantissa of 1024.0 (ulp 1: value 1024 + q);
 //       nibbles 1/5 sit four bits higher and are ORed into the mantissa of 64.0 (ulp 1/16,
@@ -244,6 +245,26 @@ __device__ __forceinline__ u32x4 interleave8(const u32x4& a) {
   return o;
 }
 
+// the same -> order x0,x2,x4,x6,x1,x3,x5,x7
+__device__ __forceinline__ u32x4 deal8(const u32x4& a) {
+  u32x4 o;
+  o.x = __builtin_amdgcn_perm(a.y, a.x, 0x05040100u);  // (x0, x2)
+  o.y = __builtin_amdgcn_perm(a.w, a.z, 0x05040100u);  // (x4, x6)
+  o.z = __builtin_amdgcn_perm(a.y, a.x, 0x07060302u);  // (x1, x3)
+  o.w = __builtin_amdgcn_perm(a.w, a.z, 0x07060302u);  // (x5, x7)
+  return o;
+}
+
+// One packed word -> eight exact bf16 integers q in the order 0,2,4,6,1,3,5,7.  The byte 0x0q is the
+// e4m3 code of q / 512 (subnormal below 8), so the scaled conversion by 512 yields q itself: 7 VALU ops.
+__device__ __forceinline__ u32x4 nibbles_bf16(uint32_t w) {
+  const uint32_t lo = w & 0x0F0F0F0Fu, hi = (w >> 4) & 0x0F0F0F0Fu;
+  return u32x4{__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 512.f, false)),
+               __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 512.f, true)),
+               __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 512.f, false)),
+               __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 512.f, true))};
+}
+
 // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Map the hardware
 // block id to a logical tile index so that every XCD walks a contiguous range of tiles:
 // tiles that share an activation tile (same slot block, neighbouring feature tiles) or the
@@ -301,10 +322,19 @@ __device__ __forceinline__ WordVec<KW> lds_read_words(const unsigned char* p) {
 // few percent of the kernel.)
 constexpr int kXRowPad = 32;
 constexpr int kWRowPad(int ks) { return ks >= 512 ? 16 : 32; }   // 512-k stages: LDS room for three workgroups
-// activation tile buffers in LDS per token-tile size (see TileGeom::XBUFS)
-constexpr int kXBufs(int mt, int ks, int wv = 4) { return wv == 8 ? 3 : (mt == 2 || ks >= 512) ? 1 : 2; }
+// Activation tile buffers in LDS.  Two (one barrier per stage) by default; three rotate in the
+// eight-wave tile's skewed pipeline.  One (two barriers per stage) where that lets a third workgroup
+// fit on a CU: the 32-slot tiles, and the 64x128 tile with its scales in LDS (65 -> 47 KB at 32
+// groups).  That tile waits for its LDS reads and barriers, not for a unit that is full: 64 experts,
+// K 2048, N 1408, 1024 tokens of top-6 with half the rows on three experts, group 64, layer with two
+// buffers / one / one and the stage's words read ahead (AHEAD): f16 247 / 229 / 225 us, bf16 (with
+// ZS) 312 / 282 / 276.  Where scales leave room for one workgroup either way (K 7168, group 64) one
+// buffer costs 2 to 5 % and AHEAD gives 5 to 6 % back.
+constexpr int kXBufs(int mt, int nt, int ks, int szr, int wv = 4) {
+  return wv == 8 ? 3 : (mt == 2 || (mt == 4 && nt == 2 && !szr) || ks >= 512) ? 1 : 2;
+}
 
-template <int MT, int NT, int KS, int WV = 4>
+template <int MT, int NT, int KS, int SZR, int WV = 4>
 struct TileGeom {
   static constexpr int THREADS = 64 * WV;    // WV wavefronts per workgroup (4, or 8 for the widest tiles)
   static constexpr int M_T = 16 * MT;        // slots per workgroup tile
@@ -319,12 +349,9 @@ struct TileGeom {
   static constexpr int RPI = 64 / LPR;       // weight rows per wave load instruction
   static constexpr int WPASS = NW / RPI;     // weight load instructions per stage per wave
   static_assert(XPASS >= 1 && WPASS >= 1, "tile too small for the load mapping");
-  // Activation tile buffers: two (one barrier per stage) except for 32-slot tiles, where a single
-  // buffer (two barriers per stage) is what lets a third workgroup fit on a CU, and for the
-  // eight-wave tile, whose skewed pipeline rotates three.
-  static constexpr int XBUFS = kXBufs(MT, KS, WV);
-  static size_t lds_bytes(int G, int szr, int pre = 0) {
-    return (size_t)XBUFS * M_T * XP + (pre ? 0 : (size_t)WV * NW * WP) + (szr ? 0 : (size_t)G * N_T * 4) +
+  static constexpr int XBUFS = kXBufs(MT, NT, KS, SZR, WV);
+  static size_t lds_bytes(int G, int pre = 0) {
+    return (size_t)XBUFS * M_T * XP + (pre ? 0 : (size_t)WV * NW * WP) + (SZR ? 0 : (size_t)G * N_T * 4) +
            (size_t)M_T * 4;
   }
 };
@@ -376,12 +403,12 @@ template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE = 0
 // compiler keeps them in accumulation registers, which VALU instructions cannot address, and
 // every rescale of an accumulator becomes read + multiply + write back (the 64-row tile without
 // register scales spent a quarter of its VALU instructions on those copies).
-__global__ void __launch_bounds__(64 * WV, (WV == 8 ? 1 : ((MT * NT <= 4 || (MT * NT <= 8 && MT <= 4) || (SZR && MT <= 4) || (PRE == 2 && NT <= 2)) ? 2 : 1)))
+__global__ void __launch_bounds__(64 * WV, (WV == 8 ? 1 : (MT == 4 && NT == 2 && !SZR) ? 3 : ((MT * NT <= 4 || (MT * NT <= 8 && MT <= 4) || (SZR && MT <= 4) || (PRE == 2 && NT <= 2)) ? 2 : 1)))
 w4a16_gemm_kernel(const GemmParams p) {
   static_assert(SZR == 0 || KW == 4, "register-resident scales need 128-k chunk-steps (group 128)");
   static_assert(PRE == 0 || (SZR == 1 && (FUSE == 1 || NT >= 2)), "operand-order weights: register-scale, paired tiles");
   static_assert(WV == 4 || (WV == 8 && SZR == 1), "eight-wave workgroups: register-scale kernels only");
-  using G_ = TileGeom<MT, NT, KS, WV>;
+  using G_ = TileGeom<MT, NT, KS, SZR, WV>;
   constexpr int THREADS = G_::THREADS;
   constexpr int M_T = G_::M_T, NW = G_::NW, N_T = G_::N_T, XP = G_::XP, WP = G_::WP;
   constexpr int CPR = G_::CPR, RPP = G_::RPP, XPASS = G_::XPASS;
@@ -402,7 +429,18 @@ w4a16_gemm_kernel(const GemmParams p) {
   // accumulator registers, which is what lets 64x256 tiles run two workgroups per CU.  Each
   // rescale is one fp32 rounding (and a 1-ulp reciprocal): about 1e-6 relative over a row.
   // A zero scale keeps the unit and zeroes the group's operand instead.
-  constexpr int RS = MT >= 4 ? 1 : 0;
+  // ZS = 1 (the bf16 64x128 tile with scales in LDS): zero points by row sums.  ZM's second MFMA per
+  // operand doubles the matrix work of a tile that is bound by matrix plus VALU issue.  Here the
+  // operand holds the plain integers q, and sum s z x is subtracted as -(s z) times the activations'
+  // sum over the chunk-step.  Wave w sums rows [16w, 16w+16) with one MFMA per packed word against
+  // ones (a quarter of the rows each; ZM issues four per packed word and sub-tile); the sums of a
+  // trip sit in the padding of the activation rows, and one float32 16x16x4 MFMA per accumulator
+  // subtracts four chunk-steps.  Partial sums have room beside the accumulator, so RS is not needed.
+  // The plain integers lose less than the biased ones did: rms error 1.1e-7 -> 6.1e-8 of the sum of
+  // magnitudes (K 2048, group 64, sums that cancel; 5e-8 .. 1.6e-7 over groups 32 .. 128, K 512 .. 2816).
+  // (In time it is worth 2 % at group 64, 3 % at 128: see kXBufs for what bounds the tile.)
+  constexpr int ZS = DT == kBF16 && SZR == 0 && MT == 4 && NT == 2 && WV == 4 ? 1 : 0;
+  constexpr int RS = MT >= 4 && !ZS ? 1 : 0;
 
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* xs = smem;                                        // [2][M_T][XP]
@@ -574,7 +612,7 @@ w4a16_gemm_kernel(const GemmParams p) {
     }                                                                                           \
     _Pragma("unroll") for (int ps = 0; ps < XLIVE; ++ps)                                        \
         *reinterpret_cast<u32x4*>((XBUF) + (ps * RPP + xr_row) * XP + xw_pos * 16) =            \
-            interleave8(XV[ps]);                                                                \
+            ZS ? deal8(XV[ps]) : interleave8(XV[ps]);                                           \
   }
 
   // Flattened step index over (tile, stage).  nst_pad rounds the stages of a tile up to whole
@@ -734,6 +772,12 @@ w4a16_gemm_kernel(const GemmParams p) {
 #pragma unroll
   for (int s = 0; s < NT; ++s) unit[s] = 1.f;
 
+#define MOE_AREAD(MT_, OFF_) *reinterpret_cast<const u32x4*>(xbuf + ((MT_) * 16 + ln) * XP + 16 * (OFF_))
+  // ZS: row sums of the trip's chunk-steps, floats in the padding of the activation rows.  Trips take turns
+  // with the two halves of the padding, so the next trip does not overwrite sums that a wave still reads (by
+  // its third step two barriers have passed); where a trip fills the padding (32-k chunk-steps) a barrier
+  // separates them.
+  unsigned char* rsums = xs + KS * 2;
   u32x4 wcur[WPASS];      // PRE: the weight words of the stage being computed (copied out of the ring)
   auto compute_stage = [&](int st, const unsigned char* xbuf, auto rc) __attribute__((always_inline)) {
     constexpr int R = decltype(rc)::value;       // step index inside the unrolled trip
@@ -741,6 +785,24 @@ w4a16_gemm_kernel(const GemmParams p) {
     // (the run-time bound also keeps the chunk-steps apart for the scheduler: with a constant bound
     // it interleaves them and needs ~40 more registers, which costs a workgroup per CU)
     const int nu = left < UCH ? left : UCH;   // SZR: whole panels, no partial or dead stage
+    // the stage's packed words and scale entries are read before its first product, so a chunk-step
+    // does not begin with a wait for them (see kXBufs)
+    constexpr int AHEAD = MT == 4 && NT == 2 && !SZR;
+    WordVec<KW> w_st[AHEAD ? UCH : 1][NT];
+    uint32_t e_st[AHEAD ? UCH : 1][NT];
+    if constexpr (AHEAD) {
+      if (left <= 0) return;
+#pragma unroll
+      for (int u = 0; u < UCH; ++u) {
+        const int cc = st * UCH + (u < nu ? u : 0);
+        const int gi = p.cpg == 1 ? cc : cc / p.cpg;
+#pragma unroll
+        for (int s = 0; s < NT; ++s) {
+          e_st[u][s] = sz[gi * N_T + wave * NW + s * 16 + ln];
+          w_st[u][s] = lds_read_words<KW>(wsw + (s * 16 + ln) * WP + 16 * KW * u + 4 * KW * lj);
+        }
+      }
+    }
 #pragma unroll
     for (int u = 0; u < UCH; ++u) {
       if (u >= nu) break;
@@ -753,15 +815,57 @@ w4a16_gemm_kernel(const GemmParams p) {
         if constexpr (SZR) {
           const int gp = (UCH * R + u) % PG;   // group inside the panel: constant after unrolling
           ctx[s] = DeqCtx<DT, ZM>::from_panel(gp, s_cur[s][gp >> 1], z_cur[s][gp >> 2], z4_cur[s][gp >> 2], uk);
+        } else if constexpr (AHEAD) {
+          ctx[s] = DeqCtx<DT, ZM>(e_st[u][s]);
         } else {
           ctx[s] = DeqCtx<DT, ZM>(sz[gi * N_T + wave * NW + s * 16 + ln]);
         }
         if constexpr (PRE) {
           const u32x4 t = wcur[s * UCH + u];      // the lane's four operand words, straight from the ring
           wv[s].w[0] = t.x; wv[s].w[1] = t.y; wv[s].w[2] = t.z; wv[s].w[3] = t.w;
+        } else if constexpr (AHEAD) {
+          wv[s] = w_st[u][s];
         } else {
           wv[s] = lds_read_words<KW>(wsw + (s * 16 + ln) * WP + 16 * KW * u + 4 * KW * lj);
         }
+      }
+      if constexpr (ZS) {
+        u32x4 a_nxt[ML];
+#pragma unroll
+        for (int mt = 0; mt < ML; ++mt) a_nxt[mt] = MOE_AREAD(mt, 4 * KW * u + lj);
+        floatx4_t part[ML][NT], own = floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < KW; ++i) {
+          u32x4 a_cur[ML];
+#pragma unroll
+          for (int mt = 0; mt < ML; ++mt) a_cur[mt] = a_nxt[mt];
+          if (i + 1 < KW) {
+#pragma unroll
+            for (int mt = 0; mt < ML; ++mt) a_nxt[mt] = MOE_AREAD(mt, 4 * KW * u + lj + 4 * (i + 1));
+          }
+          const u32x4 a_own = MOE_AREAD(wave, 4 * KW * u + lj + 4 * i);
+          u32x4 b[NT];
+#pragma unroll
+          for (int s = 0; s < NT; ++s) b[s] = nibbles_bf16(wv[s].w[i]);
+#pragma unroll
+          for (int mt = 0; mt < ML; ++mt)
+#pragma unroll
+            for (int s = 0; s < NT; ++s)
+              part[mt][s] = mfma16x16x32<DT>(a_cur[mt], b[s], i == 0 ? floatx4_t{0.f, 0.f, 0.f, 0.f} : part[mt][s]);
+          own = mfma16x16x32<DT>(a_own, u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u}, own);
+        }
+        if (ln == 0) {         // every column of `own` holds the sums; row 4 lj + c in element c
+          unsigned char* const at = rsums + (wave * 16 + 4 * lj) * XP + 4 * (R * UCH + u);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) *reinterpret_cast<float*>(at + c * XP) = own[c];
+        }
+#pragma unroll
+        for (int s = 0; s < NT; ++s)
+#pragma unroll
+          for (int mt = 0; mt < ML; ++mt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[mt][s][i] = __builtin_fmaf(ctx[s].s, part[mt][s][i], acc[mt][s][i]);
+        continue;
       }
       u32x4 zop[NT];
       float scl[NT];
@@ -797,7 +901,6 @@ w4a16_gemm_kernel(const GemmParams p) {
         // word i+1 are in flight while word i multiplies), so the LDS latency is not exposed
         // MT times per word
         u32x4 a_nxt[ML];
-#define MOE_AREAD(MT_, OFF_) *reinterpret_cast<const u32x4*>(xbuf + ((MT_) * 16 + ln) * XP + 16 * (OFF_))
 #pragma unroll
         for (int mt = 0; mt < ML; ++mt)
           a_nxt[mt] = MOE_AREAD(mt, 4 * KW * u + lj);
@@ -860,6 +963,30 @@ w4a16_gemm_kernel(const GemmParams p) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[mt][s][i] = __builtin_fmaf(scl[s], part[mt][s][i], acc[mt][s][i]);
         }
+      }
+    }
+  };
+
+  // ZS, after the barrier that ends a trip: lane (n, j) holds, as A, row n's sum of chunk-step 4q + j and,
+  // as B, -(s z) of its feature there; chunk-steps past the end have no sum and count as zero.
+  auto subtract_zero_points = [&](int st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < (UNR * UCH + 3) / 4; ++q) {
+      const int cc = st * UCH + 4 * q + lj;
+      const bool live_step = 4 * q + lj < UNR * UCH && cc < K_ext / CK;
+      const int gi = live_step ? (p.cpg == 1 ? cc : cc / p.cpg) : 0;
+      float a[ML];
+#pragma unroll
+      for (int mt = 0; mt < ML; ++mt) {
+        const float v = *reinterpret_cast<const float*>(rsums + (mt * 16 + ln) * XP + 4 * (4 * q + lj));
+        a[mt] = live_step ? v : 0.f;
+      }
+#pragma unroll
+      for (int s = 0; s < NT; ++s) {
+        const uint32_t en = sz[gi * N_T + wave * NW + s * 16 + ln];
+        const float b = live_step ? -(__builtin_bit_cast(float, en & 0xffff0000u) * (float)(en & 0xffu)) : 0.f;
+#pragma unroll
+        for (int mt = 0; mt < ML; ++mt) acc[mt][s] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt], b, acc[mt][s], 0, 0, 0);
       }
     }
   };
@@ -1103,6 +1230,11 @@ w4a16_gemm_kernel(const GemmParams p) {
         for (int i = 0; i < PG / 2; ++i) s_cur[s][i] = s_nxt[s][i];
       }
       adopt_zero_points(z_nxt);
+    }
+    if constexpr (ZS) {
+      subtract_zero_points(c_st);
+      if constexpr (UNR * UCH * 4 * 2 > kXRowPad) __syncthreads();
+      else rsums = rsums == xs + KS * 2 ? rsums + UNR * UCH * 4 : xs + KS * 2;
     }
     c_st += UNR;
     if (c_st == nst_pad) {

@@ -133,6 +133,21 @@ def test_every_gemm_tile_variant(tile, dtype, group):
     staged_gemm_case(cfg, 128, "w1", tile=tile)
 
 
+@pytest.mark.parametrize("K,N,group", [(32, 96, 32), (128, 128, 32), (288, 96, 32), (544, 544, 32), (192, 192, 96), (64, 64, 64),
+                                       (448, 192, 64), (704, 320, 64), (128, 256, 128), (640, 384, 128), (768, 256, 256)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("which", ["w1", "w2"])
+def test_64_slot_tile_with_scale_table(K, N, group, dtype, which):
+    """One to nine 128-k stages, an even and an odd number of them (the pipeline takes two a turn), partial last
+    stages of every chunk-step width, experts with one row, a partial block and several blocks and
+    ignored ids."""
+    cfg = MoEConfig(name="t64", T=150, K=K, N=N, E=3, topk=2, group=group, dtype=dtype, seed=21)
+    say(f"64-slot tile, scale table: {which} K={K} N={N} group={group} {dtype}")
+    staged_gemm_case(cfg, 64, which, corrupt_ids=True, tile=(4, 2))
+    plan = M.moe_last_gemm_plan()
+    assert (plan["mt"], plan["nt"], plan["ks"], plan["register_scales"]) == (4, 2, 128, 0), plan
+
+
 @pytest.mark.parametrize("tile", [(1, 1), (1, 2), (1, 4), (2, 1), (2, 2)])
 @pytest.mark.parametrize("dtype,K", [("f16", 1024), ("bf16", 3072)])
 @pytest.mark.parametrize("which", ["w1", "w2"])
