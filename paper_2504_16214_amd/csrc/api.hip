@@ -337,7 +337,7 @@ static int pick_k_splits(long long S, int E, int K, int N, int block_m) {
 // Measured (us, former choice -> two-group; 256 experts, K 7168, N 2048): fp16 512 tokens 1304 -> 1407,
 // 1024 1714 -> 1657, 1536 1991 -> 1915, 4096 4026 -> 3596; bf16, whose zero points cost the other
 // tiles a second matrix instruction, 512 tokens a tie, 717 1723 -> 1690, 1024 1933 -> 1912, 4096 5436
-// -> 4258.  Launches of few tiles lose by their last round: fp16 16 experts (K 4096, N 2048), 2048
+// -> 4258 (the 64-slot tile, asked first, now has the 717 and 1024: 1407 and 1570 in bf16, 1510 in fp16).  Launches of few tiles lose by their last round: fp16 16 experts (K 4096, N 2048), 2048
 // tokens (768 tiles) 324 -> 359, 4096 tokens (1280) 562 -> 583, 8 experts (K 4096, N 14336), 1024
 // tokens (1536) 1008 -> 940; bf16 64 experts (K 2048, N 1024), 512 tokens (704) 113 -> 124, 1024
 // tokens (896) 186 -> 180, 16 experts, 2048 tokens (768) 440 -> 412.
@@ -770,6 +770,8 @@ static int run_mid(const void* A, const float* sums, int row_div, const int32_t*
 //   4096x14336, 8, top 2: 1 token 55.7 / 49.1 (54.3 / 44.2);   2048x1408, 64, top 6: 4 tokens 42.1 / 39.6, 5 46.1 / 46.2
 //   2048x2048, 64: top 1, 6 tokens 27.9 / 24.2, 8 28.4 / 28.9, 16 35.6 / 49.7;   top 4, 6 tokens 45.6 / 45.6
 //   1024x1024, 64: top 2, 12 tokens 27.0 / 24.6, 16 27.6 / 29.4;   256x512, 8, top 2: 16 tokens 19.4 / 10.1
+// (The vector figures are from before the gate/up launch wrote act as chunk vectors: one token is now 45.0 for 49.1, the
+// 256x512 layer 17.5 for 20.2 with its router, so calls near the crossing may still be better off there.)
 // The other limits keep slots that share an expert (about S^2 / 2E reads more than the tiles have) and
 // large weights, where nothing is left to gain, on the tiles.
 static bool few_tokens_pay(int T, int topk, int E, int K, int N, int dt, int pre) {

@@ -17,7 +17,8 @@
 // The kernel is specialised on the live 32-slot parts of a block (ML), so that a block costs what its
 // rows cost; 256-slot blocks then fetch and unpack an expert's weights once per 256 rows.  Up to 64 rows
 // its loads come as whole lines through LDS (STREAM below); at 22 rows per expert (bf16, K 7168, N 2048) neither
-// side is at its limit: 4.7 TB/s fetched, matrix unit busy 21 % of the cycles, vector unit 49 %.  Above it is
+// side is at its limit: 4.7 TB/s fetched, matrix unit busy 21 % of the cycles, vector unit 49 % (such batches of large
+// weights run on the 64-slot tile).  Above it is
 // bound by power: at 128 rows the matrix unit is busy 56 % of the cycles at 1.77 GHz (2.4 nominal); without the
 // fragment reads from LDS the cycles stay the same and the clock rises to 2.0 GHz (1860 -> 1558 us), without
 // weight loads likewise (1607 us).
