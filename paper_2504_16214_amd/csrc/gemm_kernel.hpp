@@ -785,9 +785,12 @@ w4a16_gemm_kernel(const GemmParams p) {
     // (the run-time bound also keeps the chunk-steps apart for the scheduler: with a constant bound
     // it interleaves them and needs ~40 more registers, which costs a workgroup per CU)
     const int nu = left < UCH ? left : UCH;   // SZR: whole panels, no partial or dead stage
-    // the stage's packed words and scale entries are read before its first product, so a chunk-step
-    // does not begin with a wait for them (see kXBufs)
-    constexpr int AHEAD = MT == 4 && NT == 2 && !SZR;
+    // The stage's packed words and scale entries are read before its first product, so a chunk-step
+    // does not begin with a wait for them (see kXBufs).  In the 32-row tile it pays in fp16 with more than
+    // one group per 128 k (two to eight chunk-steps a stage hold four to eight waits): 24 rows per expert, groups of 64,
+    // layer K 7168, N 2048, 32 experts 303 -> 288 us, K 4096, N 7168, 8 experts 151 -> 143, K 2048, N 1408, 64
+    // experts 130 -> 127, groups of 32 the same; at group 128 it costs 1 %, in bf16 and in the 16-row tile it gives nothing.
+    constexpr int AHEAD = !SZR && ((MT == 4 && NT == 2) || (MT == 2 && DT == kF16 && KW < 4));
     WordVec<KW> w_st[AHEAD ? UCH : 1][NT];
     uint32_t e_st[AHEAD ? UCH : 1][NT];
     if constexpr (AHEAD) {
