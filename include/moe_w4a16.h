@@ -181,8 +181,9 @@ int moe_w4a16_layer(const void* X, const int32_t* topk_ids, const float* topk_we
  * 64 MiB device array inside the library (one copy per GPU, held until the process ends); the
  * call performs no allocation of any kind.  Sizes for which
  * moe_w4a16_layer_workspace_bytes(...) exceeds 64 MiB return MOE_WORKSPACE_TOO_SMALL (the
- * DeepSeek-shaped decode batch of 128 tokens needs 33 MiB); a bf16 batch that exceeds it by no more than the
- * row sums of the two-group or the 64-slot tile (T * topk * N / 32 bytes) runs on another tile instead, with the same
+ * DeepSeek-shaped decode batch of 128 tokens needs 33 MiB), but those that exceed it by no more than the
+ * row sums of the two-group or the 64-slot tile (T * topk * N / 32 bytes) run: an fp16 batch, which has no use for
+ * them, with the same bits, a bf16 batch on another tile, with the same
  * accuracy but other roundings than moe_w4a16_layer with its full workspace.  The array's address is resolved on
  * the first call on each device (make that call outside a graph capture).  All calls on one GPU
  * share the array: calls that overlap on one GPU (different streams or threads) race; calls

@@ -387,9 +387,16 @@ static int mid_splits(long long S, int E, int K, int N) {
   return s < 1 ? 1 : s;
 }
 
+// Scratch inside the library, for the layer call that carries no workspace.
+constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
+
 struct Workspace {
-  size_t counts, offsets, num_padded, sorted, blocks, act, Y, base, rsum, planes, total;
+  size_t counts, offsets, num_padded, sorted, blocks, act, Y, base, sums, mid_splits, total;
 };
+// Bytes up to the end of `planes` partial planes at Y; the row sums of act lie there.
+static size_t end_of_planes(const Workspace& w, size_t plane, size_t planes) {
+  return std::max(w.base, w.Y + round_up(plane * planes, 256));
+}
 static Workspace carve(long long T, int K, int N, int E, int topk, int dt) {
   const long long S = T * topk;
   Workspace w;
@@ -407,16 +414,20 @@ static Workspace carve(long long T, int K, int N, int E, int topk, int dt) {
   // row sums of act for the bf16 operands of the two-group and the 64-slot tile; a caller's workspace
   // without them runs the layer on another tile instead.  (Where only the 64-slot tile wants them they are
   // reserved for either type: the query says the same for both, as it always has there.)
-  w.rsum = o;
   const bool ordered = K % 1024 == 0 && N % 1024 == 0, rows_for_two = ordered && twogroup_pays(S, E, K, N, MOE_BF16, 0);
-  if (rows_for_two ? dt == MOE_BF16 : ordered && mid_pays(S, E, K, N, dt, 0)) o += round_up((size_t)S * (N / 128) * 4, 256);
-  // planes of the 64-slot tile's split down product; without them it makes do with those at Y
-  w.planes = o;
-  if (ordered && mid_pays(S, E, K, N, dt, 0)) {
-    const size_t need = (size_t)S * K * 4 * mid_splits(S, E, K, N);
-    if (need > w.base - w.Y) o += round_up(need, 256);
-  }
-  w.total = o;
+  const bool mid = ordered && mid_pays(S, E, K, N, dt, 0);
+  const size_t row_sums = (size_t)S * (N / 128) * 4;
+  w.sums = dt == MOE_BF16 ? row_sums : 0;
+  if (rows_for_two ? dt == MOE_BF16 : mid) o += round_up(row_sums, 256);
+  // Planes of the 64-slot tile's split down product.  A workspace without them runs it in fewer splits, whose sums are
+  // rounded in another order, so sizes that the built-in array serves get no more of them than it holds: the two
+  // calls then have the same bits.
+  const size_t plane = (size_t)S * K * 4;
+  auto with_planes = [&](size_t planes) { return end_of_planes(w, plane, planes) + round_up(w.sums, 256); };
+  const size_t most = w.base <= kStaticScratchBytes ? std::max(kStaticScratchBytes, with_planes(0)) : ~(size_t)0;
+  w.mid_splits = mid_splits(S, E, K, N);
+  while (w.mid_splits > 1 && (mid ? with_planes(w.mid_splits) > most : w.Y + plane * w.mid_splits > w.base)) --w.mid_splits;
+  w.total = mid ? std::max(o, with_planes(w.mid_splits)) : o;
   return w;
 }
 
@@ -837,7 +848,7 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   // in range, room for the row sums (bf16), and the alignment of the other register-scale tiles, so
   // that scales and zero points of less are taken or refused alike at every token number.
   const bool ordered =
-      layer_wide_ok(K, N, group_size) && g_scale_path != 1 && (dt == MOE_F16 || workspace_bytes >= w.rsum + (size_t)S * (N / 128) * 4) &&
+      layer_wide_ok(K, N, group_size) && g_scale_path != 1 && workspace_bytes >= w.base + w.sums &&
       (((uintptr_t)X | (uintptr_t)qw1 | (uintptr_t)qw2) % 16) == 0 && (((uintptr_t)s1 | (uintptr_t)s2) % 16) == 0 &&
       (((uintptr_t)z1 | (uintptr_t)z2) % 8) == 0 && (long long)N * K < (1LL << 31) &&
       (long long)E * 2 * N * (K / 128) < (1LL << 31) && (long long)T * K * 2 < (1LL << 31) && S * N * 2 < (1LL << 31);
@@ -891,7 +902,7 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   if (two_group) {
     // the reordered rows of X and their sums live where Y will be written: Y is written last
     float* const xsum = dt == MOE_BF16 ? (float*)((unsigned char*)Y + round_up((size_t)T * K * 2, 256)) : nullptr;
-    float* const asum = dt == MOE_BF16 ? (float*)(base + w.rsum) : nullptr;
+    float* const asum = dt == MOE_BF16 ? (float*)(base + w.base) : nullptr;
     err = launch_prepare_rows(X, T, K, (int)dt, 0, Y, xsum, 47.f, stream);
     if (err != 0) return hip_fail(err, "activation reorder launch");
     mark(1);
@@ -912,7 +923,11 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   }
   if (mid) {
     float* const xsum = dt == MOE_BF16 ? (float*)((unsigned char*)Y + round_up((size_t)T * K * 2, 256)) : nullptr;
-    float* const asum = dt == MOE_BF16 ? (float*)(base + w.rsum) : nullptr;
+    // reduction splits of the down product: as many partial planes as the caller's workspace holds
+    const size_t plane = (size_t)S * K * 4;
+    size_t want = g_force_ksplit > 0 ? (size_t)g_force_ksplit : w.mid_splits;
+    while (want > 1 && end_of_planes(w, plane, want) + w.sums > workspace_bytes) --want;
+    float* const asum = dt == MOE_BF16 ? (float*)(base + end_of_planes(w, plane, want)) : nullptr;
     err = launch_prepare_rows(X, T, K, (int)dt, 1, Y, xsum, 1.f, stream);
     if (err != 0) return hip_fail(err, "activation reorder launch");
     mark(1);
@@ -924,17 +939,11 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
       err = launch_prepare_rows(act, S, N, (int)dt, 1, nullptr, asum, 1.f, stream);
       if (err != 0) return hip_fail(err, "row sum launch");
     }
-    // reduction splits: as many partial planes as the caller's workspace holds
-    int want = g_force_ksplit > 0 ? g_force_ksplit : mid_splits(S, E, K, N);
-    const size_t plane = (size_t)S * K * 4, behind = w.total - w.planes;
-    void* P = Y;
-    if (plane * want > w.base - w.Y && plane * want <= behind && workspace_bytes >= w.total) P = base + w.planes;
-    else if (plane * want > w.base - w.Y) want = (int)((w.base - w.Y) / plane);
     int planes = 1;
-    st = run_mid(act, asum, 1, qw2, s2, z2, sorted, blocks, num_padded, (int)S, E, K, N, (int)dt, 0, pre, want, P, &planes, stream);
+    st = run_mid(act, asum, 1, qw2, s2, z2, sorted, blocks, num_padded, (int)S, E, K, N, (int)dt, 0, pre, (int)want, Y, &planes, stream);
     if (st != MOE_OK) return st;
     mark(3);
-    err = launch_combine(P, 1, planes, topk_weights, topk_ids, E, out, T, topk, K, (int)dt, stream);
+    err = launch_combine(Y, 1, planes, topk_weights, topk_ids, E, out, T, topk, K, (int)dt, stream);
     if (err != 0) return hip_fail(err, "combine launch");
     mark(4);
     return MOE_OK;
@@ -991,7 +1000,6 @@ int moe_w4a16_layer_prepacked(const void* X, const int32_t* topk_ids, const floa
 // Same kernels as moe_w4a16_layer; the bucketing tables, `act` and the float32 down-projection
 // planes live in a fixed device array of this module instead of a caller workspace.  Every GPU
 // the library runs on holds its own copy of the array (at its own address) until the process ends.
-constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 // Device address of `scratch` on the current device, resolved once per device.  (In host code the

@@ -126,3 +126,67 @@ def test_automatic_choice_through_the_three_entries(dtype):
     M.moe_w4a16_routed_layer(d.X, logits, None, d.qw1, d.s1, d.z1, d.qw2, d.s2, d.z2, out, cfg.topk, cfg.group, ws)
     torch.cuda.synchronize()
     assert _on_mid() and torch.equal(out.view(torch.int16), got.view(torch.int16))
+
+
+def _drawn_layer(K, N, E, T, topk, dtype, seed):
+    """Arguments of a large layer, drawn on the device."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    tdt = U.TORCH_DT[dtype]
+
+    def weight(rows, red):
+        q = torch.randint(-2 ** 31, 2 ** 31, (E, rows, red // 8), generator=g, device="cuda", dtype=torch.int32)
+        s = (torch.rand(E, rows, red // 128, generator=g, device="cuda") * 0.018 + 0.002).to(tdt)
+        z = torch.randint(0, 16, (E, rows, red // 128), generator=g, device="cuda", dtype=torch.uint8)
+        return q, s, z
+
+    X = (0.5 * torch.randn(T, K, generator=g, device="cuda")).to(tdt)
+    top, ids = torch.topk(torch.randn(T, E, generator=g, device="cuda"), topk, dim=1)
+    return [X, ids.int().contiguous(), torch.softmax(top, dim=1), *weight(2 * N, K), *weight(K, N)]
+
+
+@pytest.mark.parametrize("N,T,topk,dtype,splits", [(6144, 552, 2, "bf16", 2),      # two planes and the row sums: within the array of 64 MiB
+                                                  (13312, 447, 2, "f16", 2),      # within it as well
+                                                  (14336, 552, 2, "bf16", 1)])    # two planes would not be
+def test_the_call_without_a_workspace_has_the_same_bits(N, T, topk, dtype, splits):
+    """16 experts of K 4096, whose down product wants two splits: the entry without a workspace runs in as
+    many as the one with the workspace of the size query."""
+    K, E = 4096, 16
+    print(f"64-slot layer without a workspace N={N} T={T} {dtype}", flush=True)
+    args = _drawn_layer(K, N, E, T, topk, dtype, 905)
+    need = M.moe_w4a16_layer_workspace_bytes(T, K, N, E, topk, M.MOE_F16 if dtype == "f16" else M.MOE_BF16)
+    assert need <= 64 << 20
+    got, want = (torch.full((T, K), float("nan"), dtype=U.TORCH_DT[dtype], device="cuda") for _ in range(2))
+    M.moe_w4a16_layer(*args, want, 128, torch.full((need,), 255, dtype=torch.uint8, device="cuda"))
+    assert _on_mid() and M.moe_last_gemm_plan()["reduction_splits"] == splits
+    M.moe_w4a16_layer_noalloc(*args, got, 128)
+    torch.cuda.synchronize()
+    assert _on_mid() and M.moe_last_gemm_plan()["reduction_splits"] == splits
+    assert torch.isfinite(want).all() and torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_workspace_without_room_for_all_planes(dtype):
+    """A workspace from what the layer cannot do without (with the row sums) up to the size query: as many splits as
+    it has planes for, within the bound, and nothing written behind it."""
+    cfg = MoEConfig("mid_planes", T=120, K=2048, N=20480, E=8, topk=2, group=128, dtype=dtype, seed=906)
+    print(f"64-slot layer, planes {cfg}", flush=True)
+    inp = make_inputs(cfg)
+    d = U.DevInputs(inp)
+    need = M.moe_w4a16_layer_workspace_bytes(cfg.T, cfg.K, cfg.N, cfg.E, cfg.topk, M.MOE_F16 if dtype == "f16" else M.MOE_BF16)
+    seen = set()
+    for planes in range(7):
+        size = need - planes * cfg.S * cfg.K * 4
+        buf = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+        out = torch.full((cfg.T, cfg.K), float("nan"), dtype=U.TORCH_DT[dtype], device="cuda")
+        try:
+            M.moe_w4a16_layer(d.X, d.ids, d.w, d.qw1, d.s1, d.z1, d.qw2, d.s2, d.z2, out, cfg.group, buf[:size])
+        except M.MoEError as e:
+            assert e.status == 3 and planes > 0
+            break
+        torch.cuda.synchronize()
+        assert bool((buf[size:] == 255).all()), "written behind the workspace"
+        if _on_mid():
+            seen.add(M.moe_last_gemm_plan()["reduction_splits"])
+        _check(inp, out, f"{planes} planes less")
+    assert len(seen) > 1
