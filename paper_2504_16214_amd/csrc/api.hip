@@ -759,7 +759,7 @@ static int run_mid(const void* A, const float* sums, int row_div, const int32_t*
   while (tpw > 1 && (p.n_tiles % tpw != 0 || est_blocks * (p.n_tiles / tpw) * p.k_splits < 1536)) --tpw;
   if (g_force_tpw > 0) tpw = g_force_tpw < p.n_tiles ? g_force_tpw : p.n_tiles;
   p.tiles_per_wg = tpw;
-  const long long grid = (long long)(align_capacity(num_slots, E, 64) / 64) * ((p.n_tiles + tpw - 1) / tpw) * p.k_splits;
+  const long long grid = mid_grid(align_capacity(num_slots, E, 64) / 64, (p.n_tiles + tpw - 1) / tpw * p.k_splits);
   if (grid > 0x7fffffffLL) return fail(MOE_UNSUPPORTED_SHAPE, "grid too large");
   const int plan[9] = {4, 2, 256, 1, tpw, p.k_splits, p.k_span, fuse, 4};
   for (int i = 0; i < 9; ++i) g_last_plan[i] = plan[i];

@@ -22,6 +22,7 @@
 // and 64 rows), unpacking between the matrix instructions instead of before them (the same).
 #pragma once
 #include "gemm_kernel.hpp"
+#include "mid_order.hpp"
 
 namespace moe {
 
@@ -423,13 +424,11 @@ __global__ void __launch_bounds__(256, 3)
 w4a16_mid_kernel(const MidParams p) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int tgroups = (p.n_tiles + p.tiles_per_wg - 1) / p.tiles_per_wg;
-  int L = xcd_contiguous_index(blockIdx.x, (*p.num_padded / kMidRows) * tgroups * p.k_splits);
-  if (L < 0) return;
-  const int split = L % p.k_splits;
-  L /= p.k_splits;
-  const int tile0 = (L % tgroups) * p.tiles_per_wg;
+  const int nwork = tgroups * p.k_splits;
+  int blk, work;
+  if (!mid_work(blockIdx.x, *p.num_padded / kMidRows, nwork, blk, work)) return;
+  const int row0 = blk * kMidRows, split = work % p.k_splits, tile0 = work / p.k_splits * p.tiles_per_wg;
   const int ntl = p.n_tiles - tile0 < p.tiles_per_wg ? p.n_tiles - tile0 : p.tiles_per_wg;
-  const int blk = L / tgroups, row0 = blk * kMidRows;
   const int e = p.block_expert_ids[blk];
   if (e < 0 || e >= p.E) return;
   const int slot = p.sorted_slot_ids[row0 + (threadIdx.x & 63)];
