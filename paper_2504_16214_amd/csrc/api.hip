@@ -413,9 +413,9 @@ static Workspace carve(long long T, int K, int N, int E, int topk, int dt) {
   w.base = o;        // what the layer cannot do without
   // row sums of act for the bf16 operands of the two-group and the 64-slot tile; a caller's workspace
   // without them runs the layer on another tile instead.  (Where only the 64-slot tile wants them they are
-  // reserved for either type: the query says the same for both, as it always has there.)
+  // reserved for either type, so that as a rule the query says the same for both.)
   const bool ordered = K % 1024 == 0 && N % 1024 == 0, rows_for_two = ordered && twogroup_pays(S, E, K, N, MOE_BF16, 0);
-  const bool mid = ordered && mid_pays(S, E, K, N, dt, 0);
+  const bool mid = ordered && (mid_pays(S, E, K, N, dt, 0) || mid_pays(S, E, K, N, dt, 1));     // (the query does not know the layout)
   const size_t row_sums = (size_t)S * (N / 128) * 4;
   w.sums = dt == MOE_BF16 ? row_sums : 0;
   if (rows_for_two ? dt == MOE_BF16 : mid) o += round_up(row_sums, 256);

@@ -295,3 +295,12 @@ def test_split_planes_stay_within_the_built_in_array(binding, T, K, N, E, topk, 
     S = T * topk
     assert S * N * 2 + S * K * 4 + S * (N // 128) * 4 + (1 << 20) < 64 << 20
     assert binding.moe_w4a16_layer_workspace_bytes(T, K, N, E, topk, dt) <= 64 << 20
+
+
+@pytest.mark.parametrize("avg", [40, 55, 56, 64, 71])
+def test_split_planes_are_reserved_for_operand_order_weights(binding, avg):
+    """fp16 operand-order weights run on the 64-slot tile up to 71 rows per expert, stated ones up to 55; the query is one for
+    both: four planes of the down product, 24 x 8 workgroups each."""
+    K, N, E = 3072, 12288, 8
+    S = avg * E
+    assert binding.moe_w4a16_layer_workspace_bytes(S, K, N, E, 1, 0) >= S * N * 2 + 4 * S * K * 4

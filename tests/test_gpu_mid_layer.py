@@ -190,3 +190,27 @@ def test_workspace_without_room_for_all_planes(dtype):
             seen.add(M.moe_last_gemm_plan()["reduction_splits"])
         _check(inp, out, f"{planes} planes less")
     assert len(seen) > 1
+
+
+@pytest.mark.parametrize("avg", [40, 64])
+def test_operand_order_weights_split_with_the_queried_workspace(avg):
+    """fp16 operand-order weights take this tile up to 71 rows per expert, stated ones up to 55: the splits of the down
+    product do not drop in between, and the bits are those of the stated layout on the same tile."""
+    K, N, E, T = 3072, 12288, 8, 4 * avg
+    print(f"64-slot layer, operand order, {avg} rows per expert", flush=True)
+    X, ids, w, q1, s1, z1, q2, s2, z2 = _drawn_layer(K, N, E, T, 2, "f16", 907)
+    p1, p2 = torch.empty_like(q1), torch.empty_like(q2)
+    M.moe_repack_qweight(q1, False, p1)
+    M.moe_repack_qweight(q2, True, p2)
+    ws = torch.full((M.moe_w4a16_layer_workspace_bytes(T, K, N, E, 2, M.MOE_F16),), 255, dtype=torch.uint8, device="cuda")
+    got, want = (torch.full((T, K), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2))
+    M.moe_w4a16_layer_prepacked(X, ids, w, p1, s1, z1, p2, s2, z2, got, 128, ws)
+    assert _on_mid() and M.moe_last_gemm_plan()["reduction_splits"] == 4
+    M.moe_set_block_m_override(64)
+    try:
+        M.moe_w4a16_layer(X, ids, w, q1, s1, z1, q2, s2, z2, want, 128, ws)
+        assert _on_mid() and M.moe_last_gemm_plan()["reduction_splits"] == 4
+    finally:
+        M.moe_set_block_m_override(0)
+    torch.cuda.synchronize()
+    assert torch.isfinite(got).all() and torch.equal(got, want)
