@@ -362,20 +362,30 @@ static bool twogroup_pays(long long S, int E, int K, int N, int dt, int pre) {
 // Does the layer run on the 64-slot tile (gemm_mid.hpp)?  It reads an expert's weights once for up to 64 rows, works
 // off whole 16-row parts only, and takes activations that were put in order by a launch of their own (4 us; bf16:
 // two, with the sums of act), so the launch has to be large: a quarter of a billion weights in each of an expert's
-// matrices together and two workgroups for each of three on a CU.  Former choice over this tile, 624 calls (6 shapes, 3 to 96 rows
-// per expert, uniform and power-law routing, both layouts), by rows per expert:
-//   256 experts, K 7168, N 2048, fp16   3: 1.01  6: 0.98  9: 1.10  16: 1.04  28: 1.13  40: 1.09  48: 1.06  64: 0.92
-//                                bf16   3: 0.99  6: 0.97  9: 1.31  16: 1.21  28: 1.14  40: 1.17  64: 1.02  96: 0.95
-//   8 experts, K 4096, N 14336,  fp16   6: 0.95  9: 1.10  16: 1.01  28: 1.07  32: 1.32  48: 1.21  64: 0.95
-//                                bf16   6: 0.92  9: 1.27  16: 1.14  28: 1.14  32: 1.34  64: 1.07  96: 1.29
-//   128 experts, K = N = 2048,   fp16   6: 0.90  9: 1.02  16: 0.97  28: 1.05  40: 1.12  64: 0.90
-//                                bf16   6: 0.88  9: 1.19  16: 1.09  28: 1.13  40: 1.17  64: 1.00
-//   smaller: 16 experts, K 4096, N 2048, fp16 9: 1.11 20: 1.00 40: 0.92;  64 experts, K 2048, N 1024, fp16 9: 1.02 20: 0.92 40: 0.92
-// Operand-order weights, whose other choice is the 64-slot four-wave tile, gain a little longer.  Skewed
-// routing gains more where it is a matter of chance at all (0.85 ... 1.87; 8 experts at 20 and 24 rows lose 0.85 ... 0.95).
+// matrices together and two workgroups for each of three on a CU.  Former choice over this tile, lower of two draws, by rows per
+// expert: even routing / experts weighted as 1 / rank / as rank ** -2.4 (2900 calls, 11 shapes, both layouts), stated layout:
+//   256 experts, K 7168, N 2048,  fp16  9: 1.18/1.28/1.12  16: 1.09/1.23/1.23  28: 1.14/1.27/1.28  40: 1.12/1.56/0.97  54: 0.99/1.41/0.93
+//                                 bf16  9: 1.39/1.49/1.43  16: 1.26/1.47/1.38  28: 1.19/1.84/1.09  48: 1.13/1.63/1.01  60: 1.00/1.50/0.96  72: 0.93/1.48/0.93
+//   64 experts, K 7168, N 2048,   fp16  9: 1.15/1.16/1.22  16: 1.04/1.16/1.19  28: 1.07/1.27/1.24  40: 1.16/1.63/1.35  54: 1.07/1.48/1.25
+//                                 bf16  9: 1.35/1.41/1.38  16: 1.23/1.32/1.37  28: 1.22/1.52/1.45  48: 1.16/1.97/1.65  60: 1.09/1.90/1.64  72: 0.90/1.64/1.25
+//   8 experts, K 4096, N 14336,   fp16  9: 1.23/1.20/1.24  16: 1.04/1.26/1.21  20: 1.05/1.15/1.07  28: 1.15/1.24/1.22  40: 1.44/1.90/1.92
+//                                 bf16  9: 1.39/1.36/1.34  16: 1.19/1.39/1.36  20: 1.15/1.21/1.14  48: 1.45/2.25/2.29  60: 1.40/2.01/1.98  72: 1.05/1.81/1.79
+//   16 experts, K 5120, N 8192,   fp16  9: 1.10/1.05/1.04  20: 0.95/1.18/1.25  28: 1.03/1.24/1.24  40: 1.25/1.85/1.12;  bf16  60: 1.13/1.95/1.38  78: 0.88/1.77/1.70
+//   64 experts, K = N = 2048,     fp16  9: 1.13/1.12/1.04  20: 0.94/1.10/1.15  28: 0.99/1.12/1.20  40: 1.06/1.44/1.35;  bf16  60: 0.95/1.76/1.40  72: 0.82/1.70/1.44
+//   32 experts, K 2048, N 4096,   fp16  9: 1.04/1.15/1.11  20: 0.93/1.15/1.18  28: 1.03/1.17/1.27  48: 0.99/1.43/1.22;  bf16  60: 0.95/1.88/1.35  72: 0.83/1.95/1.17
+//   8 experts, K 2048, N 20480,   fp16  9: 1.12/1.14/1.21  20: 0.99/1.05/1.17  28: 1.06/1.12/1.23  48: 1.69/2.36/2.35;  bf16  60: 1.73/2.59/2.61  72: 1.38/2.39/2.39
+// What the numbers set.  fp16 below half a billion weights: from 28 rows on; below that only where the former choice splits
+// a short down product or unpacks operand-order words, and the reduction is not the shortest (8 experts, K 1024, N 31744,
+// operand order, 16 rows 0.91).  The end is where even routing turns (from 64 rows on half the experts need a second block); later,
+// bf16, where the down product had too few tiles before (E * K), or for operand-order weights that are not on the
+// two-group tile (72 rows 1.09 ... 1.36).  Not used: 8 experts, K 4096, N 14336 gain up to 96 rows (1.1 ... 1.3 in runs of blocks).
 static bool mid_pays(long long S, int E, int K, int N, int dt, int pre) {
-  const long long avg = S / (E > 0 ? E : 1);
-  return avg >= 9 && avg < (dt == MOE_BF16 ? 80 : pre ? 72 : 56) && (long long)E * N * K >= 250000000LL && (long long)E * N >= 96000;
+  const long long avg = S / (E > 0 ? E : 1), weights = (long long)E * N * K;
+  if (avg < 9 || weights < 250000000LL || (long long)E * N < 96000) return false;
+  const bool two_group = twogroup_pays(S, E, K, N, dt, pre);
+  if (dt == MOE_F16)
+    return avg < (!pre ? 56 : two_group ? 64 : 72) && (weights >= 500000000LL || avg >= 28 || (K >= 2048 && (pre || (long long)E * K <= 50000)));
+  return avg < ((long long)E * K <= 40000 || (pre && !two_group) ? 80 : 64);
 }
 
 // Reduction splits of its down projection: about one workgroup for each of three on a CU.

@@ -287,7 +287,7 @@ def test_binding_rejects_short_tables_and_mismatched_outputs(binding):
                             torch.zeros(4, 64, dtype=torch.float16))
 
 
-@pytest.mark.parametrize("T,K,N,E,topk,dt", [(447, 4096, 13312, 16, 2, 0), (432, 4096, 14336, 16, 2, 0), (552, 4096, 6144, 16, 2, 1), (552, 4096, 14336, 16, 2, 1),
+@pytest.mark.parametrize("T,K,N,E,topk,dt", [(447, 4096, 13312, 16, 2, 0), (432, 4096, 14336, 16, 2, 0), (504, 4096, 14336, 16, 2, 1), (504, 4096, 17408, 16, 2, 1),
                                              (880, 2048, 8192, 32, 2, 0)])
 def test_split_planes_stay_within_the_built_in_array(binding, T, K, N, E, topk, dt):
     """Sizes that the entry without a workspace serves (act, one plane and the tables below its 64 MiB) ask for no more

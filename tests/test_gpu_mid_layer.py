@@ -145,9 +145,9 @@ def _drawn_layer(K, N, E, T, topk, dtype, seed):
     return [X, ids.int().contiguous(), torch.softmax(top, dim=1), *weight(2 * N, K), *weight(K, N)]
 
 
-@pytest.mark.parametrize("N,T,topk,dtype,splits", [(6144, 552, 2, "bf16", 2),      # two planes and the row sums: within the array of 64 MiB
+@pytest.mark.parametrize("N,T,topk,dtype,splits", [(14336, 504, 2, "bf16", 2),     # two planes and the row sums: within the array of 64 MiB
                                                   (13312, 447, 2, "f16", 2),      # within it as well
-                                                  (14336, 552, 2, "bf16", 1)])    # two planes would not be
+                                                  (17408, 504, 2, "bf16", 1)])    # two planes would not be
 def test_the_call_without_a_workspace_has_the_same_bits(N, T, topk, dtype, splits):
     """16 experts of K 4096, whose down product wants two splits: the entry without a workspace runs in as
     many as the one with the workspace of the size query."""
@@ -214,3 +214,23 @@ def test_operand_order_weights_split_with_the_queried_workspace(avg):
         M.moe_set_block_m_override(0)
     torch.cuda.synchronize()
     assert torch.isfinite(got).all() and torch.equal(got, want)
+
+
+@pytest.mark.parametrize("dtype,pre,K,N,E,avg,on", [
+    ("f16", False, 2048, 4096, 32, 20, False), ("f16", False, 2048, 4096, 32, 28, True),      # small layers
+    ("f16", True, 2048, 4096, 32, 20, True), ("f16", True, 1024, 4096, 64, 20, False),
+    ("f16", False, 4096, 4096, 32, 20, True), ("f16", False, 4096, 4096, 32, 56, False),
+    ("f16", True, 4096, 4096, 32, 71, True),
+    ("bf16", False, 4096, 4096, 32, 63, True), ("bf16", False, 4096, 4096, 32, 64, False),    # half the experts need a second block
+    ("bf16", True, 4096, 4096, 32, 72, True), ("bf16", False, 4096, 12288, 8, 72, True),
+])
+def test_where_the_tile_is_chosen(dtype, pre, K, N, E, avg, on):
+    """Either side of the rule's lines: where even routing on this tile takes longer than before it, the layer runs on another."""
+    print(f"64-slot layer, choice {dtype} K={K} N={N} E={E} avg={avg} pre={pre}", flush=True)
+    T = avg * E
+    args = _drawn_layer(K, N, E, T, 1, dtype, 908)        # (any words stand for repacked ones: only the choice is looked at)
+    ws = torch.empty(M.moe_w4a16_layer_workspace_bytes(T, K, N, E, 1, M.MOE_F16 if dtype == "f16" else M.MOE_BF16), dtype=torch.uint8, device="cuda")
+    out = torch.empty(T, K, dtype=U.TORCH_DT[dtype], device="cuda")
+    (M.moe_w4a16_layer_prepacked if pre else M.moe_w4a16_layer)(*args, out, 128, ws)
+    torch.cuda.synchronize()
+    assert _on_mid() == on, M.moe_last_gemm_plan()
