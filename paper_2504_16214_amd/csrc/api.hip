@@ -874,8 +874,9 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   auto mark = [&](int i) { if (ev) (void)hipEventRecord((hipEvent_t)g_events[i], stream); };
   int err;
   // A few tokens: vector products, unless a tuning hook asks for a tile; whole groups of 128, 16-byte
-  // aligned words and activations, 32-bit offsets into an expert.
+  // aligned words and activations, 32-bit offsets into an expert, room for the chunks' floats (4 bytes for 32 columns of act) in Y.
   const bool few = few_tokens_pay(T, topk, E, K, N, (int)dt, pre) && group_size == 128 && few_tokens_fit(topk, K, N) && g_force_block_m == 0 &&
+                   (size_t)S * (N / 32) * 4 <= w.base - w.Y &&
                    g_force_mt == 0 && g_force_nt == 0 && g_force_ksplit == 0 && g_scale_path == 0 && g_force_tpw == 0 && g_wide_mode == 0 &&
                    (((uintptr_t)X | (uintptr_t)qw1 | (uintptr_t)qw2) % 16) == 0 && (((uintptr_t)s1 | (uintptr_t)s2) % 2) == 0 &&
                    (long long)N * K < (1LL << 31);
