@@ -939,7 +939,7 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
     size_t want = g_force_ksplit > 0 ? (size_t)g_force_ksplit : w.mid_splits;
     while (want > 1 && end_of_planes(w, plane, want) + w.sums > workspace_bytes) --want;
     float* const asum = dt == MOE_BF16 ? (float*)(base + end_of_planes(w, plane, want)) : nullptr;
-    err = launch_prepare_rows(X, T, K, (int)dt, 1, Y, xsum, 1.f, stream);
+    err = launch_prepare_rows(X, T, K, (int)dt, 1, Y, xsum, kZeroUnit, stream);
     if (err != 0) return hip_fail(err, "activation reorder launch");
     mark(1);
     int st = run_mid(Y, xsum, topk, qw1, s1, z1, sorted, blocks, num_padded, (int)S, E, 2 * N, K, (int)dt, 1, pre, 1, act, nullptr, stream);
@@ -947,7 +947,7 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
     mark(2);
     if (asum) {
       // (act's runs are in the order the kernel reads; the sums do not mind)
-      err = launch_prepare_rows(act, S, N, (int)dt, 1, nullptr, asum, 1.f, stream);
+      err = launch_prepare_rows(act, S, N, (int)dt, 1, nullptr, asum, kZeroUnit, stream);
       if (err != 0) return hip_fail(err, "row sum launch");
     }
     int planes = 1;

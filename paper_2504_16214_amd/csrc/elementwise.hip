@@ -105,7 +105,7 @@ combine_kernel(const void* __restrict__ Yv, const float* __restrict__ w, const i
 
 // Activations for the two-group and the 64-slot GEMM.  out (may be null): every run of eight reduction indices in
 // the order 0,4,1,5,2,6,3,7 (DEAL: 0,2,4,6,1,3,5,7).  sums (may be null): factor * (sum of the row's 128-index group), float32
-// (two-group, bf16: 47, the constant its operands carry; 64-slot, bf16: 1).  16 lanes per group, 8 elements each;
+// (two-group, bf16: 47, the constant its operands carry; 64-slot, bf16: 16, kZeroUnit).  16 lanes per group, 8 elements each;
 // a pure stream (4096 x 7168: 117 MB moved in 24 us).
 template <int DT, int DEAL>
 __global__ void __launch_bounds__(256)

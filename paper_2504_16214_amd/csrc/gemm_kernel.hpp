@@ -255,6 +255,11 @@ __device__ __forceinline__ u32x4 deal8(const u32x4& a) {
   return o;
 }
 
+// Zero points that leave by row sums: the sums are taken times 16 and the zero points divided by it, so that scale * z
+// does not leave the float32 range where the scale itself is within bf16's.  Powers of two: no rounding.
+constexpr float kZeroUnit = 16.f;
+constexpr uint32_t kZeroUnitBf16x2 = 0x41804180u;
+
 // One packed word -> eight exact bf16 integers q in the order 0,2,4,6,1,3,5,7.  The byte 0x0q is the
 // e4m3 code of q / 512 (subnormal below 8), so the scaled conversion by 512 yields q itself: 7 VALU ops.
 __device__ __forceinline__ u32x4 nibbles_bf16(uint32_t w) {
@@ -433,7 +438,7 @@ w4a16_gemm_kernel(const GemmParams p) {
   // operand doubles the matrix work of a tile that is bound by matrix plus VALU issue.  Here the
   // operand holds the plain integers q, and sum s z x is subtracted as -(s z) times the activations'
   // sum over the chunk-step.  Wave w sums rows [16w, 16w+16) with one MFMA per packed word against
-  // ones (a quarter of the rows each; ZM issues four per packed word and sub-tile); the sums of a
+  // a constant (a quarter of the rows each; ZM issues four per packed word and sub-tile); the sums of a
   // trip sit in the padding of the activation rows, and one float32 16x16x4 MFMA per accumulator
   // subtracts four chunk-steps.  Partial sums have room beside the accumulator, so RS is not needed.
   // The plain integers lose less than the biased ones did: rms error 1.1e-7 -> 6.1e-8 of the sum of
@@ -855,7 +860,7 @@ w4a16_gemm_kernel(const GemmParams p) {
 #pragma unroll
             for (int s = 0; s < NT; ++s)
               part[mt][s] = mfma16x16x32<DT>(a_cur[mt], b[s], i == 0 ? floatx4_t{0.f, 0.f, 0.f, 0.f} : part[mt][s]);
-          own = mfma16x16x32<DT>(a_own, u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u}, own);
+          own = mfma16x16x32<DT>(a_own, u32x4{kZeroUnitBf16x2, kZeroUnitBf16x2, kZeroUnitBf16x2, kZeroUnitBf16x2}, own);
         }
         if (ln == 0) {         // every column of `own` holds the sums; row 4 lj + c in element c
           unsigned char* const at = rsums + (wave * 16 + 4 * lj) * XP + 4 * (R * UCH + u);
@@ -987,7 +992,7 @@ w4a16_gemm_kernel(const GemmParams p) {
 #pragma unroll
       for (int s = 0; s < NT; ++s) {
         const uint32_t en = sz[gi * N_T + wave * NW + s * 16 + ln];
-        const float b = live_step ? -(__builtin_bit_cast(float, en & 0xffff0000u) * (float)(en & 0xffu)) : 0.f;
+        const float b = live_step ? -(__builtin_bit_cast(float, en & 0xffff0000u) * ((float)(en & 0xffu) * (1.f / kZeroUnit))) : 0.f;
 #pragma unroll
         for (int mt = 0; mt < ML; ++mt) acc[mt][s] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[mt], b, acc[mt][s], 0, 0, 0);
       }

@@ -28,7 +28,7 @@ namespace moe {
 
 struct MidParams {
   const void* A;             // [rows, K_in] 16-bit, runs of eight reordered (mid_unpack)
-  const float* sums;         // bf16: [rows, K_in / 128] sums of the row's groups; fp16: unused
+  const float* sums;         // bf16: [rows, K_in / 128] 16 times the sums of the row's groups (kZeroUnit); fp16: unused
   int row_div;
   const int32_t* qweight;
   const void* scales;
@@ -398,12 +398,12 @@ __device__ __forceinline__ void mid_tile(const MidParams& p, unsigned char* lds,
        ...);
     }(std::make_integer_sequence<int, 4 * XSTEPS>{});
     if constexpr (DT == kBF16) {
-      // the panel's zero points: four groups per instruction, float32 operands
+      // the panel's zero points: four groups per instruction, float32 operands (scale * z / 16 stays in range, see kZeroUnit)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-          const float sz = -__builtin_bit_cast(float, h ? sp[s] & 0xffff0000u : sp[s] << 16) * (float)((zp[s] >> (8 * h)) & 15u);
+          const float sz = -__builtin_bit_cast(float, h ? sp[s] & 0xffff0000u : sp[s] << 16) * ((float)((zp[s] >> (8 * h)) & 15u) * (1.f / kZeroUnit));
 #pragma unroll
           for (int mt = 0; mt < ML; ++mt) acc[mt][s] = __builtin_amdgcn_mfma_f32_16x16x4f32(rsum[mt][h], sz, acc[mt][s], 0, 0, 0);
         }

@@ -234,3 +234,48 @@ def test_where_the_tile_is_chosen(dtype, pre, K, N, E, avg, on):
     (M.moe_w4a16_layer_prepacked if pre else M.moe_w4a16_layer)(*args, out, 128, ws)
     torch.cuda.synchronize()
     assert _on_mid() == on, M.moe_last_gemm_plan()
+
+
+def _other_tile(inp):
+    """The layer on 16-slot blocks."""
+    M.moe_set_block_m_override(16)
+    try:
+        return U.run_layer(U.DevInputs(inp))
+    finally:
+        M.moe_set_block_m_override(0)
+
+
+def _block_64(inp):
+    """The layer in blocks of 64: this tile for group 128, the 64 x 128 tile with its scales in LDS otherwise."""
+    if inp.cfg.group == 128:
+        return _layer(inp)
+    M.moe_set_block_m_override(64)
+    try:
+        out = U.run_layer(U.DevInputs(inp))
+        plan = M.moe_last_gemm_plan()
+        assert (plan["mt"], plan["nt"], plan["ks"], plan["register_scales"]) == (4, 2, 128, 0), plan
+        return out
+    finally:
+        M.moe_set_block_m_override(0)
+
+
+@pytest.mark.parametrize("group", [128, 64, 32])
+def test_the_largest_bf16_scales(group):
+    """Scales up to the type's largest value on activations that are small in proportion: no product of a scale and a zero point
+    leaves the float32 range by itself.  Tolerance: two bf16 roundings (act, output) of sums that agree to 2^-9 of
+    their magnitude."""
+    cfg = MoEConfig("mid_big", T=75, K=1024, N=1024, E=3, topk=1, group=group, dtype="bf16", seed=910)
+    print(f"blocks of 64, largest scales {cfg}", flush=True)
+    inp = make_inputs(cfg)
+    s1 = inp.s1_bits.copy()
+    s1 -= 20 << 7                                   # 2^-20: act of about 2^-40
+    inp.s1_bits = s1
+    inp.s2_bits = inp.s2_bits.copy()
+    inp.s2_bits[:, ::3, 1::2] = 0x7F7F              # 3.39e38
+    inp.s2_bits[:, 1::3, ::2] = 0x7E80              # 8.5e37
+    inp.z2 = inp.z2.copy()
+    inp.z2[:, ::5] = 15
+    got, tiled = U.dev_to_f64(_block_64(inp)), U.dev_to_f64(_other_tile(inp))
+    assert np.isfinite(tiled).all() and np.isfinite(got).all()
+    rms = np.sqrt((tiled ** 2).mean(axis=0))        # by column: its scales
+    assert (np.abs(got - tiled) <= 2.0 ** -6 * (np.abs(tiled) + rms)).all()
