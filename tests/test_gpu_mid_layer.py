@@ -260,6 +260,26 @@ def _block_64(inp):
 
 
 @pytest.mark.parametrize("group", [128, 64, 32])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("what", ["infinity", "NaN"])
+def test_an_infinite_activation_stays_in_its_token(group, dtype, what):
+    """Also where the zero points leave by sums over rows that share an instruction: every other token has the bits it
+    had, and that token is as on the 16-slot tile."""
+    cfg = MoEConfig("mid_inf", T=75, K=1024, N=1024, E=3, topk=1, group=group, dtype=dtype, seed=909)
+    print(f"blocks of 64, {what} {cfg}", flush=True)
+    inp = make_inputs(cfg)
+    clean = U.dev_to_f64(_block_64(inp))
+    bits = inp.x_bits.copy()
+    for t, k in ((0, 0), (20, 77), (74, 1023)):
+        bits[t, k] = {("f16", "infinity"): 0x7C00, ("bf16", "infinity"): 0xFF80, ("f16", "NaN"): 0x7E01, ("bf16", "NaN"): 0x7FC1}[dtype, what]
+    inp.x_bits = bits
+    got, tiled = U.dev_to_f64(_block_64(inp)), U.dev_to_f64(_other_tile(inp))
+    others = np.setdiff1d(np.arange(cfg.T), [0, 20, 74])
+    assert np.isfinite(clean).all() and np.array_equal(got[others], clean[others])
+    assert np.array_equal(np.isfinite(got), np.isfinite(tiled)) and not np.isfinite(got[[0, 20, 74]]).any()
+
+
+@pytest.mark.parametrize("group", [128, 64, 32])
 def test_the_largest_bf16_scales(group):
     """Scales up to the type's largest value on activations that are small in proportion: no product of a scale and a zero point
     leaves the float32 range by itself.  Tolerance: two bf16 roundings (act, output) of sums that agree to 2^-9 of
