@@ -62,11 +62,14 @@ namespace moe {
 #define MOE_TILE_WIDE(MT, NT, KS, WV) MOE_DECL_WIDE(0, MT, NT, KS, 0, WV) MOE_DECL_WIDE(1, MT, NT, KS, 0, WV)
 #define MOE_TILE_WIDE_FUSE(MT, NT, KS, WV) MOE_DECL_WIDE(0, MT, NT, KS, 1, WV) MOE_DECL_WIDE(1, MT, NT, KS, 1, WV)
 #include "gemm_variants_wide.def"
+#define MOE_ONE_BUFFER(M, F) M(0, 1, F) M(0, 2, F) M(0, 4, F) M(1, 1, F) M(1, 2, F) M(1, 4, F)
+#define MOE_DECL_ONE(DT, KW, F) extern template int launch_w4a16_gemm<DT, 4, 2, 128, KW, F, 0, 0, 4, 1>(const GemmParams&, int, hipStream_t);
+MOE_ONE_BUFFER(MOE_DECL_ONE, 0) MOE_ONE_BUFFER(MOE_DECL_ONE, 1)
 
 typedef int (*GemmLaunchFn)(const GemmParams&, int, hipStream_t);
 // pre: 0 = weight tile staged in LDS, 1 = operand-order (repacked) weights, 2 = row-major weights
-// loaded in operand order; wv = wavefronts per workgroup
-struct GemmVariant { int dt, mt, nt, ks, kw, fuse, szr, pre, wv; GemmLaunchFn fn; };
+// loaded in operand order; wv = wavefronts per workgroup; one = with one activation buffer where the tile has two
+struct GemmVariant { int dt, mt, nt, ks, kw, fuse, szr, pre, wv; GemmLaunchFn fn; int one = 0; };
 #define MOE_ENTRY(DT, MT, NT, KS, KW, F, Z) {DT, MT, NT, KS, KW, F, Z, 0, 4, &launch_w4a16_gemm<DT, MT, NT, KS, KW, F, Z, 0, 4>},
 #define MOE_ENTRY_PRE(DT, MT, NT, KS, F) {DT, MT, NT, KS, 4, F, 1, 1, 4, &launch_w4a16_gemm<DT, MT, NT, KS, 4, F, 1, 1, 4>},
 #define MOE_ENTRY_WIDE(DT, MT, NT, KS, F, WV) {DT, MT, NT, KS, 4, F, 1, 2, WV, &launch_w4a16_gemm<DT, MT, NT, KS, 4, F, 1, 2, WV>},
@@ -83,12 +86,14 @@ static const GemmVariant kVariants[] = {
 #define MOE_TILE_WIDE(MT, NT, KS, WV) MOE_ENTRY_WIDE(0, MT, NT, KS, 0, WV) MOE_ENTRY_WIDE(1, MT, NT, KS, 0, WV)
 #define MOE_TILE_WIDE_FUSE(MT, NT, KS, WV) MOE_ENTRY_WIDE(0, MT, NT, KS, 1, WV) MOE_ENTRY_WIDE(1, MT, NT, KS, 1, WV)
 #include "gemm_variants_wide.def"
+#define MOE_ENTRY_ONE(DT, KW, F) {DT, 4, 2, 128, KW, F, 0, 0, 4, &launch_w4a16_gemm<DT, 4, 2, 128, KW, F, 0, 0, 4, 1>, 1},
+  MOE_ONE_BUFFER(MOE_ENTRY_ONE, 0) MOE_ONE_BUFFER(MOE_ENTRY_ONE, 1)
 };
 
-static const GemmVariant* find_variant(int dt, int mt, int nt, int kw, int fuse, int szr, int pre = 0, int wv = 4) {
+static const GemmVariant* find_variant(int dt, int mt, int nt, int kw, int fuse, int szr, int pre = 0, int wv = 4, int one = 0) {
   for (const GemmVariant& v : kVariants)
     if (v.dt == dt && v.mt == mt && v.nt == nt && v.kw == kw && v.fuse == fuse && v.szr == szr && v.pre == pre &&
-        v.wv == wv)
+        v.wv == wv && v.one == one)
       return &v;
   return nullptr;
 }
@@ -127,8 +132,7 @@ constexpr int kMaxGroups = 512;
 
 static size_t gemm_lds_bytes(int mt, int nt, int ks, int G, int szr) {
   const size_t M_T = 16 * mt, NW = 16 * nt;
-  const int xbufs = mt == 4 ? 2 : kXBufs(mt, nt, ks, szr);    // (the 64x128 tile takes one of the two: same limit on K_in / group_size)
-  return xbufs * M_T * (ks * 2 + kXRowPad) + 4 * NW * (ks / 2 + kWRowPad(ks)) + (szr ? 0 : (size_t)G * 64 * nt * 4) + M_T * 4;
+  return kXBufs(mt, ks) * M_T * (ks * 2 + kXRowPad) + 4 * NW * (ks / 2 + kWRowPad(ks)) + (szr ? 0 : (size_t)G * 64 * nt * 4) + M_T * 4;
 }
 
 // The eight-wave 128-token tile serves 128-slot blocks of register-scale shapes in the stated
@@ -175,6 +179,21 @@ static int choose_tile(int num_slots, int E, int feat, int G, int block_m, int f
     if (nt == min_nt) return -1;
     nt >>= 1;
   }
+}
+
+// Does the 64x128 tile with its scales in LDS run with one activation buffer?  One frees 18 KB of LDS, for a third
+// workgroup on a CU (where many groups fill the LDS, for a second), and costs a second barrier per stage.  So the
+// launch has to have more than two and a half workgroups (one and a quarter) for every CU, and more than a few stages.  Layer,
+// time with two buffers over time with one, 600 shapes, mean (worst), by workgroups of the larger product up to 512 /
+// 512 ... 768 / above 1500: fp16, chunk-steps of 32 and 64 k 0.99 (0.97) / 1.06 (0.97) / 1.16 (0.98), 128 k 0.98 (0.96) / 0.99
+// (0.97) / 1.07 (0.98); bf16, 32 and 64 k 0.99 (0.95) / 1.06 (0.98) / 1.15 (0.97).  Reductions of 128 ... 320 with 1000 workgroups
+// 0.95 ... 0.97.  bf16, 128 k: always, its row sums (ZS) outweigh the barrier, 1.02 (1.00) / 1.07 (1.02) / 1.14 (1.00).
+static bool one_buffer_pays(int num_slots, int E, int feat, int fuse, int K_in, int G, int dt, int kw) {
+  if (dt == MOE_BF16 && kw == 4) return true;
+  const size_t two = gemm_lds_bytes(4, 2, 128, G, 0), one = two - 64 * (128 * 2 + kXRowPad), cu = 160 * 1024;
+  const int fit_two = (int)std::min<size_t>(2, cu / two), fit_one = (int)std::min<size_t>(3, cu / one);
+  const long long blocks = (num_slots + 63) / 64 + (num_slots < E ? num_slots : E) / 2, n_tiles = (feat + (fuse ? 63 : 127)) / (fuse ? 64 : 128);
+  return fit_one > fit_two && K_in >= 512 && blocks * n_tiles > 320 * fit_two;
 }
 
 struct GemmArgs {
@@ -229,7 +248,8 @@ static int run_gemm(const GemmArgs& a, hipStream_t stream) {
     return fail(MOE_UNSUPPORTED_SHAPE, "no GEMM tile fits (K_in/group_size = %d, block_m = %d, override %d/%d)",
                 G, a.block_m, g_force_mt, g_force_nt);
   }
-  const GemmVariant* v = find_variant(a.dt, mt, nt, kw, fuse, szr, pre, wv);
+  const int one = mt == 4 && nt == 2 && !szr && one_buffer_pays(a.num_slots, a.E, feat, fuse, a.K_in, G, a.dt, kw);
+  const GemmVariant* v = find_variant(a.dt, mt, nt, kw, fuse, szr, pre, wv, one);
   if (!v) return fail(MOE_UNSUPPORTED_SHAPE, "GEMM variant mt=%d nt=%d kw=%d fuse=%d szr=%d is not compiled", mt, nt, kw, fuse, szr);
 
   GemmParams p;

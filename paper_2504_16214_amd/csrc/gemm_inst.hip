@@ -11,10 +11,10 @@
 
 namespace moe {
 
-template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE, int WV>
+template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE, int WV, int XB>
 int launch_w4a16_gemm(const GemmParams& p, int grid, hipStream_t stream) {
-  auto kern = w4a16_gemm_kernel<DT, MT, NT, KS, KW, FUSE, SZR, PRE, WV>;
-  const size_t lds = TileGeom<MT, NT, KS, SZR, WV>::lds_bytes(p.G, PRE);
+  auto kern = w4a16_gemm_kernel<DT, MT, NT, KS, KW, FUSE, SZR, PRE, WV, XB>;
+  const size_t lds = TileGeom<MT, NT, KS, SZR, WV, XB>::lds_bytes(p.G, PRE);
   if (lds > 64 * 1024) {
     // Raise the dynamic LDS limit of this kernel, once per device and size (the attribute is
     // per device; remembering it per device keeps a second GPU of the process correct).
@@ -40,6 +40,9 @@ int launch_w4a16_gemm(const GemmParams& p, int grid, hipStream_t stream) {
 #define MOE_TILE_FUSE(MT, NT, KS) \
   template int launch_w4a16_gemm<MOE_DT, MT, NT, KS, MOE_KW, 1, 0, 0, 4>(const GemmParams&, int, hipStream_t);
 #include "gemm_variants.def"
+// one activation buffer
+template int launch_w4a16_gemm<MOE_DT, 4, 2, 128, MOE_KW, 0, 0, 0, 4, 1>(const GemmParams&, int, hipStream_t);
+template int launch_w4a16_gemm<MOE_DT, 4, 2, 128, MOE_KW, 1, 0, 0, 4, 1>(const GemmParams&, int, hipStream_t);
 
 // register-resident scale variants: group 128 only (KW == 4), small token tiles
 #if MOE_KW == 4

@@ -103,7 +103,7 @@ __device__ __forceinline__ floatx16_t mfma32x32x16(const u32x4& a, const u32x4& 
 //   ZM = 0 (fp16): one packed subtract per nibble pair yields the exact integers q - z.
 // Either way the group scale is applied in fp32 (to the partial sum of a chunk-step, or by
 // keeping the accumulator in units of the current group's scale: see RS in the kernel).  The bf16
-// 64x128 tile with its scales in LDS takes the plain q and the zero points by row sums: see ZS.
+// 64x128 tile with one activation buffer takes the plain q and the zero points by row sums: see ZS.
 //
 // fp16: nibbles 0/4 of a word are ORed into the mantissa of 1024.0 (ulp 1: value 1024 + q);
 //       nibbles 1/5 sit four bits higher and are ORed into the mantissa of 64.0 (ulp 1/16,
@@ -328,18 +328,15 @@ __device__ __forceinline__ WordVec<KW> lds_read_words(const unsigned char* p) {
 constexpr int kXRowPad = 32;
 constexpr int kWRowPad(int ks) { return ks >= 512 ? 16 : 32; }   // 512-k stages: LDS room for three workgroups
 // Activation tile buffers in LDS.  Two (one barrier per stage) by default; three rotate in the
-// eight-wave tile's skewed pipeline.  One (two barriers per stage) where that lets a third workgroup
-// fit on a CU: the 32-slot tiles, and the 64x128 tile with its scales in LDS (65 -> 47 KB at 32
-// groups).  That tile waits for its LDS reads and barriers, not for a unit that is full: 64 experts,
+// eight-wave tile's skewed pipeline; one (two barriers per stage) in the 32-slot tiles, where it lets a
+// third workgroup fit on a CU.  The 64x128 tile with its scales in LDS is compiled with two and with one (65 and
+// 47 KB at 32 groups): XB.  It waits for its LDS reads and barriers, not for a unit that is full: 64 experts,
 // K 2048, N 1408, 1024 tokens of top-6 with half the rows on three experts, group 64, layer with two
 // buffers / one / one and the stage's words read ahead (AHEAD): f16 247 / 229 / 225 us, bf16 (with
-// ZS) 312 / 282 / 276.  Where scales leave room for one workgroup either way (K 7168, group 64) one
-// buffer costs 2 to 5 % and AHEAD gives 5 to 6 % back.
-constexpr int kXBufs(int mt, int nt, int ks, int szr, int wv = 4) {
-  return wv == 8 ? 3 : (mt == 2 || (mt == 4 && nt == 2 && !szr) || ks >= 512) ? 1 : 2;
-}
+// ZS) 312 / 282 / 276.  Where the launch has no third workgroup for each CU the second barrier is all it gives (see run_gemm).
+constexpr int kXBufs(int mt, int ks, int wv = 4) { return wv == 8 ? 3 : (mt == 2 || ks >= 512) ? 1 : 2; }
 
-template <int MT, int NT, int KS, int SZR, int WV = 4>
+template <int MT, int NT, int KS, int SZR, int WV = 4, int XB = kXBufs(MT, KS, WV)>
 struct TileGeom {
   static constexpr int THREADS = 64 * WV;    // WV wavefronts per workgroup (4, or 8 for the widest tiles)
   static constexpr int M_T = 16 * MT;        // slots per workgroup tile
@@ -354,7 +351,7 @@ struct TileGeom {
   static constexpr int RPI = 64 / LPR;       // weight rows per wave load instruction
   static constexpr int WPASS = NW / RPI;     // weight load instructions per stage per wave
   static_assert(XPASS >= 1 && WPASS >= 1, "tile too small for the load mapping");
-  static constexpr int XBUFS = kXBufs(MT, NT, KS, SZR, WV);
+  static constexpr int XBUFS = XB;
   static size_t lds_bytes(int G, int pre = 0) {
     return (size_t)XBUFS * M_T * XP + (pre ? 0 : (size_t)WV * NW * WP) + (SZR ? 0 : (size_t)G * N_T * 4) +
            (size_t)M_T * 4;
@@ -402,18 +399,19 @@ __device__ __forceinline__ void feature_of(int n_tile, int wave, int sub, int n,
 //
 // WV = 8: eight wavefronts per workgroup (two per SIMD) share one activation tile; wave w owns
 // features [w*16*NT, (w+1)*16*NT) of a tile of 128*NT features.
-template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE = 0, int WV = 4>
+template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE = 0, int WV = 4, int XB = kXBufs(MT, KS, WV)>
 // Minimum workgroups per CU: two wherever the tile's registers fit 256 per lane.  Besides the
 // occupancy this decides where the accumulators live: with a budget above 256 registers the
 // compiler keeps them in accumulation registers, which VALU instructions cannot address, and
 // every rescale of an accumulator becomes read + multiply + write back (the 64-row tile without
 // register scales spent a quarter of its VALU instructions on those copies).
-__global__ void __launch_bounds__(64 * WV, (WV == 8 ? 1 : (MT == 4 && NT == 2 && !SZR) ? 3 : ((MT * NT <= 4 || (MT * NT <= 8 && MT <= 4) || (SZR && MT <= 4) || (PRE == 2 && NT <= 2)) ? 2 : 1)))
+__global__ void __launch_bounds__(64 * WV, (WV == 8 ? 1 : (MT == 4 && XB == 1) ? 3 : ((MT * NT <= 4 || (MT * NT <= 8 && MT <= 4) || (SZR && MT <= 4) || (PRE == 2 && NT <= 2)) ? 2 : 1)))
 w4a16_gemm_kernel(const GemmParams p) {
   static_assert(SZR == 0 || KW == 4, "register-resident scales need 128-k chunk-steps (group 128)");
   static_assert(PRE == 0 || (SZR == 1 && (FUSE == 1 || NT >= 2)), "operand-order weights: register-scale, paired tiles");
   static_assert(WV == 4 || (WV == 8 && SZR == 1), "eight-wave workgroups: register-scale kernels only");
-  using G_ = TileGeom<MT, NT, KS, SZR, WV>;
+  static_assert(XB == kXBufs(MT, KS, WV) || (XB == 1 && MT == 4 && NT == 2 && KS == 128 && SZR == 0 && WV == 4), "one activation buffer: the 64x128 tile with its scales in LDS");
+  using G_ = TileGeom<MT, NT, KS, SZR, WV, XB>;
   constexpr int THREADS = G_::THREADS;
   constexpr int M_T = G_::M_T, NW = G_::NW, N_T = G_::N_T, XP = G_::XP, WP = G_::WP;
   constexpr int CPR = G_::CPR, RPP = G_::RPP, XPASS = G_::XPASS;
@@ -434,7 +432,7 @@ w4a16_gemm_kernel(const GemmParams p) {
   // accumulator registers, which is what lets 64x256 tiles run two workgroups per CU.  Each
   // rescale is one fp32 rounding (and a 1-ulp reciprocal): about 1e-6 relative over a row.
   // A zero scale keeps the unit and zeroes the group's operand instead.
-  // ZS = 1 (the bf16 64x128 tile with scales in LDS): zero points by row sums.  ZM's second MFMA per
+  // ZS = 1 (the bf16 64x128 tile with one activation buffer, chunk-steps of 64 k and more): zero points by row sums.  ZM's second MFMA per
   // operand doubles the matrix work of a tile that is bound by matrix plus VALU issue.  Here the
   // operand holds the plain integers q, and sum s z x is subtracted as -(s z) times the activations'
   // sum over the chunk-step.  Wave w sums rows [16w, 16w+16) with one MFMA per packed word against
@@ -443,8 +441,9 @@ w4a16_gemm_kernel(const GemmParams p) {
   // subtracts four chunk-steps.  Partial sums have room beside the accumulator, so RS is not needed.
   // The plain integers lose less than the biased ones did: rms error 1.1e-7 -> 6.1e-8 of the sum of
   // magnitudes (K 2048, group 64, sums that cancel; 5e-8 .. 1.6e-7 over groups 32 .. 128, K 512 .. 2816).
-  // (In time it is worth 2 % at group 64, 3 % at 128: see kXBufs for what bounds the tile.)
-  constexpr int ZS = DT == kBF16 && SZR == 0 && MT == 4 && NT == 2 && WV == 4 ? 1 : 0;
+  // Layer, time with two buffers and without ZS over time with one and: without ZS / with ZS, launches of more than 768 workgroups,
+  // geometric mean: chunk-steps of 32 k 1.16 / 1.11 (a sum and a barrier more for every 32 k), 64 k 1.08 / 1.11, 128 k 1.06 / 1.14.
+  constexpr int ZS = DT == kBF16 && SZR == 0 && MT == 4 && XB == 1 && KW >= 2 ? 1 : 0;
   constexpr int RS = MT >= 4 && !ZS ? 1 : 0;
 
   extern __shared__ __align__(16) unsigned char smem[];
@@ -780,8 +779,7 @@ w4a16_gemm_kernel(const GemmParams p) {
 #define MOE_AREAD(MT_, OFF_) *reinterpret_cast<const u32x4*>(xbuf + ((MT_) * 16 + ln) * XP + 16 * (OFF_))
   // ZS: row sums of the trip's chunk-steps, floats in the padding of the activation rows.  Trips take turns
   // with the two halves of the padding, so the next trip does not overwrite sums that a wave still reads (by
-  // its third step two barriers have passed); where a trip fills the padding (32-k chunk-steps) a barrier
-  // separates them.
+  // its third step two barriers have passed).
   unsigned char* rsums = xs + KS * 2;
   u32x4 wcur[WPASS];      // PRE: the weight words of the stage being computed (copied out of the ring)
   auto compute_stage = [&](int st, const unsigned char* xbuf, auto rc) __attribute__((always_inline)) {
@@ -1241,8 +1239,8 @@ w4a16_gemm_kernel(const GemmParams p) {
     }
     if constexpr (ZS) {
       subtract_zero_points(c_st);
-      if constexpr (UNR * UCH * 4 * 2 > kXRowPad) __syncthreads();
-      else rsums = rsums == xs + KS * 2 ? rsums + UNR * UCH * 4 : xs + KS * 2;
+      static_assert(UNR * UCH * 4 * 2 <= kXRowPad, "the sums of two trips fit in the padding");
+      rsums = rsums == xs + KS * 2 ? rsums + UNR * UCH * 4 : xs + KS * 2;
     }
     c_st += UNR;
     if (c_st == nst_pad) {
@@ -1279,7 +1277,7 @@ w4a16_gemm_kernel(const GemmParams p) {
 }
 
 // Host-side launcher, one per instantiation.  Returns hipError_t as int.
-template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE = 0, int WV = 4>
+template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE, int WV, int XB = kXBufs(MT, KS, WV)>
 int launch_w4a16_gemm(const GemmParams& p, int grid, hipStream_t stream);
 
 }  // namespace moe

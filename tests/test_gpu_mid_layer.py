@@ -1,6 +1,9 @@
 """GPU parity of the layer on its 64-slot tile (9 to 60 rows per expert, group 128): every number of live
 16-slot parts of a block, experts of more than one block, both weight layouts, reductions from one panel of
 1024 to an odd number of them, split and unsplit, several tiles per workgroup, zero scales and ignored ids."""
+import copy
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -246,8 +249,8 @@ def _other_tile(inp):
 
 
 def _block_64(inp):
-    """The layer in blocks of 64: this tile for group 128, the 64 x 128 tile with its scales in LDS otherwise."""
-    if inp.cfg.group == 128:
+    """The layer in blocks of 64: this tile where the shapes admit it, else the 64 x 128 tile with its scales in LDS."""
+    if inp.cfg.group == 128 and inp.cfg.K % 1024 == 0 and inp.cfg.N % 1024 == 0:
         return _layer(inp)
     M.moe_set_block_m_override(64)
     try:
@@ -259,32 +262,36 @@ def _block_64(inp):
         M.moe_set_block_m_override(0)
 
 
-@pytest.mark.parametrize("group", [128, 64, 32])
+# this tile; the 64 x 128 tile with its scales in LDS: row sums in bf16 at any size and in large launches only, former zero points
+BLOCKS_OF_64 = [(128, 1024, 75), (256, 1024, 75), (64, 512, 5200), (32, 1024, 75)]
+
+
+@pytest.mark.parametrize("group,N,T", BLOCKS_OF_64)
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("what", ["infinity", "NaN"])
-def test_an_infinite_activation_stays_in_its_token(group, dtype, what):
+def test_an_infinite_activation_stays_in_its_token(group, N, T, dtype, what):
     """Also where the zero points leave by sums over rows that share an instruction: every other token has the bits it
     had, and that token is as on the 16-slot tile."""
-    cfg = MoEConfig("mid_inf", T=75, K=1024, N=1024, E=3, topk=1, group=group, dtype=dtype, seed=909)
+    cfg = MoEConfig("mid_inf", T=T, K=1024, N=N, E=3, topk=1, group=group, dtype=dtype, seed=909)
     print(f"blocks of 64, {what} {cfg}", flush=True)
     inp = make_inputs(cfg)
     clean = U.dev_to_f64(_block_64(inp))
     bits = inp.x_bits.copy()
-    for t, k in ((0, 0), (20, 77), (74, 1023)):
+    for t, k in ((0, 0), (20, 77), (T - 1, 1023)):
         bits[t, k] = {("f16", "infinity"): 0x7C00, ("bf16", "infinity"): 0xFF80, ("f16", "NaN"): 0x7E01, ("bf16", "NaN"): 0x7FC1}[dtype, what]
     inp.x_bits = bits
     got, tiled = U.dev_to_f64(_block_64(inp)), U.dev_to_f64(_other_tile(inp))
-    others = np.setdiff1d(np.arange(cfg.T), [0, 20, 74])
+    others = np.setdiff1d(np.arange(T), [0, 20, T - 1])
     assert np.isfinite(clean).all() and np.array_equal(got[others], clean[others])
-    assert np.array_equal(np.isfinite(got), np.isfinite(tiled)) and not np.isfinite(got[[0, 20, 74]]).any()
+    assert np.array_equal(np.isfinite(got), np.isfinite(tiled)) and not np.isfinite(got[[0, 20, T - 1]]).any()
 
 
-@pytest.mark.parametrize("group", [128, 64, 32])
-def test_the_largest_bf16_scales(group):
-    """Scales up to the type's largest value on activations that are small in proportion: no product of a scale and a zero point
+@pytest.mark.parametrize("group,N,T", BLOCKS_OF_64[:3])
+def test_the_largest_bf16_scales(group, N, T):
+    """Zero points by row sums: scales up to the type's largest value on activations that are small in proportion: no product of a scale and a zero point
     leaves the float32 range by itself.  Tolerance: two bf16 roundings (act, output) of sums that agree to 2^-9 of
     their magnitude."""
-    cfg = MoEConfig("mid_big", T=75, K=1024, N=1024, E=3, topk=1, group=group, dtype="bf16", seed=910)
+    cfg = MoEConfig("mid_big", T=T, K=1024, N=N, E=3, topk=1, group=group, dtype="bf16", seed=910)
     print(f"blocks of 64, largest scales {cfg}", flush=True)
     inp = make_inputs(cfg)
     s1 = inp.s1_bits.copy()
@@ -299,3 +306,20 @@ def test_the_largest_bf16_scales(group):
     assert np.isfinite(tiled).all() and np.isfinite(got).all()
     rms = np.sqrt((tiled ** 2).mean(axis=0))        # by column: its scales
     assert (np.abs(got - tiled) <= 2.0 ** -6 * (np.abs(tiled) + rms)).all()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("group,K,N", [(32, 544, 544), (64, 576, 1088), (96, 672, 576), (128, 1152, 640), (256, 768, 512)])
+def test_scale_table_in_a_large_launch(group, K, N, dtype):
+    """More workgroups than two and a half for every CU: one activation buffer, odd and even numbers of stages and a last one
+    that is short.  The first rows have the bits of a launch of their own, with two buffers, except where the larger launch takes the
+    zero points by row sums as well (bf16, chunk-steps of 64)."""
+    cfg = MoEConfig(name="t64_large", T=9000, K=K, N=N, E=4, topk=1, group=group, dtype=dtype, seed=22)
+    print(f"blocks of 64, large launch {cfg}", flush=True)
+    inp = make_inputs(cfg)
+    few = copy.copy(inp)
+    few.cfg = dataclasses.replace(cfg, T=150)
+    few.x_bits, few.topk_ids, few.topk_weights = inp.x_bits[:150], inp.topk_ids[:150], inp.topk_weights[:150]
+    large, small = _block_64(inp)[:150], _block_64(few)
+    _check(few, large, "large launch")
+    assert torch.equal(large, small) == (dtype == "f16" or group != 64)
