@@ -178,6 +178,34 @@ def test_multi_tile_workgroups(tpw, which):
         M.moe_set_scale_path(0)
 
 
+@pytest.mark.parametrize("K,N,T,tiles", [(2048, 1024, 256, 2),      # 4 stages a tile: one tile would be all start-up
+                                         (4096, 2048, 64, 2)])      # 8 stages: three tiles leave 1584 workgroups, two 2304
+def test_tiles_per_workgroup_with_a_few_rows_per_expert(K, N, T, tiles):
+    """Down product of 256 experts: a third round of workgroups only if each keeps 16 stages; any count has the same bits."""
+    E, topk, dev = 256, 4, "cuda"
+    torch.manual_seed(K)
+    say(f"layer K={K} N={N} T={T} E={E}")
+    draw = lambda rows, red: (torch.randint(-2**31, 2**31, (E, rows, red // 8), dtype=torch.int32, device=dev),
+                              (torch.rand(E, rows, red // 128, device=dev) * 0.02).half(),
+                              torch.randint(0, 16, (E, rows, red // 128), dtype=torch.uint8, device=dev))
+    w1, w2 = draw(2 * N, K), draw(K, N)
+    X = (0.5 * torch.randn(T, K, device=dev)).half()
+    ids = torch.argsort(torch.rand(T, E, device=dev), dim=1)[:, :topk].int().contiguous()
+    wts = torch.full((T, topk), 1.0 / topk, device=dev)
+    ws = torch.empty(M.moe_w4a16_layer_workspace_bytes(T, K, N, E, topk, M.MOE_F16), dtype=torch.uint8, device=dev)
+    outs = [torch.empty(T, K, dtype=torch.float16, device=dev) for _ in range(2)]
+    M.moe_w4a16_layer(X, ids, wts, *w1, *w2, outs[0], 128, ws)
+    plan = M.moe_last_gemm_plan()
+    M.moe_set_tiles_per_workgroup(1)
+    try:
+        M.moe_w4a16_layer(X, ids, wts, *w1, *w2, outs[1], 128, ws)
+    finally:
+        M.moe_set_tiles_per_workgroup(0)
+    torch.cuda.synchronize()
+    assert (plan["mt"], plan["register_scales"], plan["tiles_per_workgroup"]) == (1, 1, tiles)
+    assert torch.equal(outs[0], outs[1]) and bool(outs[0].isfinite().all())
+
+
 def test_scale_paths_agree_bitwise():
     cfg = MoEConfig(name="szr_eq", T=64, K=2048, N=1024, E=6, topk=2, group=128, dtype="f16", seed=13)
     say("layer with LDS-table scales vs register scales")
