@@ -65,11 +65,15 @@ namespace moe {
 #define MOE_ONE_BUFFER(M, F) M(0, 1, F) M(0, 2, F) M(0, 4, F) M(1, 1, F) M(1, 2, F) M(1, 4, F)
 #define MOE_DECL_ONE(DT, KW, F) extern template int launch_w4a16_gemm<DT, 4, 2, 128, KW, F, 0, 0, 4, 1>(const GemmParams&, int, hipStream_t);
 MOE_ONE_BUFFER(MOE_DECL_ONE, 0) MOE_ONE_BUFFER(MOE_DECL_ONE, 1)
+#define MOE_NOT_AHEAD(M) M(1, 0) M(1, 1) M(2, 0) M(2, 1)
+#define MOE_DECL_NOT_AHEAD(KW, F) extern template int launch_w4a16_gemm<0, 2, 2, 256, KW, F, 0, 0, 4, 1, 0>(const GemmParams&, int, hipStream_t);
+MOE_NOT_AHEAD(MOE_DECL_NOT_AHEAD)
 
 typedef int (*GemmLaunchFn)(const GemmParams&, int, hipStream_t);
 // pre: 0 = weight tile staged in LDS, 1 = operand-order (repacked) weights, 2 = row-major weights
-// loaded in operand order; wv = wavefronts per workgroup; one = with one activation buffer where the tile has two
-struct GemmVariant { int dt, mt, nt, ks, kw, fuse, szr, pre, wv; GemmLaunchFn fn; int one = 0; };
+// loaded in operand order; wv = wavefronts per workgroup; alt = the tile's other form:
+// 64x128 with one activation buffer, 32x128 without words read ahead
+struct GemmVariant { int dt, mt, nt, ks, kw, fuse, szr, pre, wv; GemmLaunchFn fn; int alt = 0; };
 #define MOE_ENTRY(DT, MT, NT, KS, KW, F, Z) {DT, MT, NT, KS, KW, F, Z, 0, 4, &launch_w4a16_gemm<DT, MT, NT, KS, KW, F, Z, 0, 4>},
 #define MOE_ENTRY_PRE(DT, MT, NT, KS, F) {DT, MT, NT, KS, 4, F, 1, 1, 4, &launch_w4a16_gemm<DT, MT, NT, KS, 4, F, 1, 1, 4>},
 #define MOE_ENTRY_WIDE(DT, MT, NT, KS, F, WV) {DT, MT, NT, KS, 4, F, 1, 2, WV, &launch_w4a16_gemm<DT, MT, NT, KS, 4, F, 1, 2, WV>},
@@ -88,12 +92,14 @@ static const GemmVariant kVariants[] = {
 #include "gemm_variants_wide.def"
 #define MOE_ENTRY_ONE(DT, KW, F) {DT, 4, 2, 128, KW, F, 0, 0, 4, &launch_w4a16_gemm<DT, 4, 2, 128, KW, F, 0, 0, 4, 1>, 1},
   MOE_ONE_BUFFER(MOE_ENTRY_ONE, 0) MOE_ONE_BUFFER(MOE_ENTRY_ONE, 1)
+#define MOE_ENTRY_NOT_AHEAD(KW, F) {0, 2, 2, 256, KW, F, 0, 0, 4, &launch_w4a16_gemm<0, 2, 2, 256, KW, F, 0, 0, 4, 1, 0>, 1},
+  MOE_NOT_AHEAD(MOE_ENTRY_NOT_AHEAD)
 };
 
-static const GemmVariant* find_variant(int dt, int mt, int nt, int kw, int fuse, int szr, int pre = 0, int wv = 4, int one = 0) {
+static const GemmVariant* find_variant(int dt, int mt, int nt, int kw, int fuse, int szr, int pre = 0, int wv = 4, int alt = 0) {
   for (const GemmVariant& v : kVariants)
     if (v.dt == dt && v.mt == mt && v.nt == nt && v.kw == kw && v.fuse == fuse && v.szr == szr && v.pre == pre &&
-        v.wv == wv && v.one == one)
+        v.wv == wv && v.alt == alt)
       return &v;
   return nullptr;
 }
@@ -196,6 +202,17 @@ static bool one_buffer_pays(int num_slots, int E, int feat, int fuse, int K_in, 
   return fit_one > fit_two && K_in >= 512 && blocks * n_tiles > 320 * fit_two;
 }
 
+// Does the 32x128 tile, which reads its words ahead in fp16 with groups below 128, do better without?  The registers
+// of that (118 and 127 -> 144) leave three workgroups on a CU; up to five groups the LDS holds four.  So with groups of
+// 64 a launch of more than three for every CU does (an estimate: what a uniform routing has); with groups of 32 and
+// reductions this short, one stage that is half empty, any launch.  Layer, time with over time without, 4200 shapes, products of up
+// to five groups by workgroups up to 768 / 768 ... 1024 / above, mean: groups of 32 1.005 / 1.045 / 1.05, of 64 0.987 / 1.03 / 1.03;
+// of six to eight groups, any launch, 0.985.
+static bool read_ahead_costs(int num_slots, int E, int feat, int fuse, int G, int dt, int kw) {
+  const long long blocks = (num_slots + 31) / 32 + (num_slots < E ? num_slots : E) / 2, n_tiles = (feat + (fuse ? 63 : 127)) / (fuse ? 64 : 128);
+  return kReadAhead(dt, 2, 2, kw, 0) && 4 * gemm_lds_bytes(2, 2, 256, G, 0) <= 160 * 1024 && (kw == 1 || blocks * n_tiles > 768);
+}
+
 struct GemmArgs {
   const void* A; int row_div;
   const int32_t* qweight; const void* scales; const uint8_t* zeros;
@@ -248,8 +265,9 @@ static int run_gemm(const GemmArgs& a, hipStream_t stream) {
     return fail(MOE_UNSUPPORTED_SHAPE, "no GEMM tile fits (K_in/group_size = %d, block_m = %d, override %d/%d)",
                 G, a.block_m, g_force_mt, g_force_nt);
   }
-  const int one = mt == 4 && nt == 2 && !szr && one_buffer_pays(a.num_slots, a.E, feat, fuse, a.K_in, G, a.dt, kw);
-  const GemmVariant* v = find_variant(a.dt, mt, nt, kw, fuse, szr, pre, wv, one);
+  const int alt = !szr && nt == 2 && (mt == 4 ? one_buffer_pays(a.num_slots, a.E, feat, fuse, a.K_in, G, a.dt, kw)
+                                              : mt == 2 && read_ahead_costs(a.num_slots, a.E, feat, fuse, G, a.dt, kw));
+  const GemmVariant* v = find_variant(a.dt, mt, nt, kw, fuse, szr, pre, wv, alt);
   if (!v) return fail(MOE_UNSUPPORTED_SHAPE, "GEMM variant mt=%d nt=%d kw=%d fuse=%d szr=%d is not compiled", mt, nt, kw, fuse, szr);
 
   GemmParams p;

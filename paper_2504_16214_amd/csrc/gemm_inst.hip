@@ -11,9 +11,9 @@
 
 namespace moe {
 
-template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE, int WV, int XB>
+template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE, int WV, int XB, int RA>
 int launch_w4a16_gemm(const GemmParams& p, int grid, hipStream_t stream) {
-  auto kern = w4a16_gemm_kernel<DT, MT, NT, KS, KW, FUSE, SZR, PRE, WV, XB>;
+  auto kern = w4a16_gemm_kernel<DT, MT, NT, KS, KW, FUSE, SZR, PRE, WV, XB, RA>;
   const size_t lds = TileGeom<MT, NT, KS, SZR, WV, XB>::lds_bytes(p.G, PRE);
   if (lds > 64 * 1024) {
     // Raise the dynamic LDS limit of this kernel, once per device and size (the attribute is
@@ -43,6 +43,11 @@ int launch_w4a16_gemm(const GemmParams& p, int grid, hipStream_t stream) {
 // one activation buffer
 template int launch_w4a16_gemm<MOE_DT, 4, 2, 128, MOE_KW, 0, 0, 0, 4, 1>(const GemmParams&, int, hipStream_t);
 template int launch_w4a16_gemm<MOE_DT, 4, 2, 128, MOE_KW, 1, 0, 0, 4, 1>(const GemmParams&, int, hipStream_t);
+// words not read ahead
+#if MOE_DT == 0 && MOE_KW < 4
+template int launch_w4a16_gemm<0, 2, 2, 256, MOE_KW, 0, 0, 0, 4, 1, 0>(const GemmParams&, int, hipStream_t);
+template int launch_w4a16_gemm<0, 2, 2, 256, MOE_KW, 1, 0, 0, 4, 1, 0>(const GemmParams&, int, hipStream_t);
+#endif
 
 // register-resident scale variants: group 128 only (KW == 4), small token tiles
 #if MOE_KW == 4

@@ -332,9 +332,19 @@ constexpr int kWRowPad(int ks) { return ks >= 512 ? 16 : 32; }   // 512-k stages
 // third workgroup fit on a CU.  The 64x128 tile with its scales in LDS is compiled with two and with one (65 and
 // 47 KB at 32 groups): XB.  It waits for its LDS reads and barriers, not for a unit that is full: 64 experts,
 // K 2048, N 1408, 1024 tokens of top-6 with half the rows on three experts, group 64, layer with two
-// buffers / one / one and the stage's words read ahead (AHEAD): f16 247 / 229 / 225 us, bf16 (with
+// buffers / one / one and the stage's words read ahead (kReadAhead): f16 247 / 229 / 225 us, bf16 (with
 // ZS) 312 / 282 / 276.  Where the launch has no third workgroup for each CU the second barrier is all it gives (see run_gemm).
 constexpr int kXBufs(int mt, int ks, int wv = 4) { return wv == 8 ? 3 : (mt == 2 || ks >= 512) ? 1 : 2; }
+
+// Are a stage's packed words and scale entries read before its first product, so that a chunk-step does not
+// begin with a wait for them (see kXBufs)?  In the 32-row tile it pays in fp16 with more than one group per 128 k (two to
+// eight chunk-steps a stage hold four to eight waits): 24 rows per expert, groups of 64, layer K 7168, N 2048, 32 experts
+// 303 -> 288 us, K 4096, N 7168, 8 experts 151 -> 143, K 2048, N 1408, 64 experts 130 -> 127, groups of 32 the
+// same; at group 128 it costs 1 %, in bf16 and in the 16-row tile it gives nothing.  That tile is compiled without it
+// too, for the reductions of few groups that would lose their fourth workgroup on a CU by its registers (RA, see run_gemm).
+constexpr int kReadAhead(int dt, int mt, int nt, int kw, int szr) {
+  return !szr && ((mt == 4 && nt == 2) || (mt == 2 && dt == kF16 && kw < 4)) ? 1 : 0;
+}
 
 template <int MT, int NT, int KS, int SZR, int WV = 4, int XB = kXBufs(MT, KS, WV)>
 struct TileGeom {
@@ -399,7 +409,8 @@ __device__ __forceinline__ void feature_of(int n_tile, int wave, int sub, int n,
 //
 // WV = 8: eight wavefronts per workgroup (two per SIMD) share one activation tile; wave w owns
 // features [w*16*NT, (w+1)*16*NT) of a tile of 128*NT features.
-template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE = 0, int WV = 4, int XB = kXBufs(MT, KS, WV)>
+template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE = 0, int WV = 4, int XB = kXBufs(MT, KS, WV),
+          int RA = kReadAhead(DT, MT, NT, KW, SZR)>
 // Minimum workgroups per CU: two wherever the tile's registers fit 256 per lane.  Besides the
 // occupancy this decides where the accumulators live: with a budget above 256 registers the
 // compiler keeps them in accumulation registers, which VALU instructions cannot address, and
@@ -788,15 +799,9 @@ w4a16_gemm_kernel(const GemmParams p) {
     // (the run-time bound also keeps the chunk-steps apart for the scheduler: with a constant bound
     // it interleaves them and needs ~40 more registers, which costs a workgroup per CU)
     const int nu = left < UCH ? left : UCH;   // SZR: whole panels, no partial or dead stage
-    // The stage's packed words and scale entries are read before its first product, so a chunk-step
-    // does not begin with a wait for them (see kXBufs).  In the 32-row tile it pays in fp16 with more than
-    // one group per 128 k (two to eight chunk-steps a stage hold four to eight waits): 24 rows per expert, groups of 64,
-    // layer K 7168, N 2048, 32 experts 303 -> 288 us, K 4096, N 7168, 8 experts 151 -> 143, K 2048, N 1408, 64
-    // experts 130 -> 127, groups of 32 the same; at group 128 it costs 1 %, in bf16 and in the 16-row tile it gives nothing.
-    constexpr int AHEAD = !SZR && ((MT == 4 && NT == 2) || (MT == 2 && DT == kF16 && KW < 4));
-    WordVec<KW> w_st[AHEAD ? UCH : 1][NT];
-    uint32_t e_st[AHEAD ? UCH : 1][NT];
-    if constexpr (AHEAD) {
+    WordVec<KW> w_st[RA ? UCH : 1][NT];
+    uint32_t e_st[RA ? UCH : 1][NT];
+    if constexpr (RA) {
       if (left <= 0) return;
 #pragma unroll
       for (int u = 0; u < UCH; ++u) {
@@ -821,7 +826,7 @@ w4a16_gemm_kernel(const GemmParams p) {
         if constexpr (SZR) {
           const int gp = (UCH * R + u) % PG;   // group inside the panel: constant after unrolling
           ctx[s] = DeqCtx<DT, ZM>::from_panel(gp, s_cur[s][gp >> 1], z_cur[s][gp >> 2], z4_cur[s][gp >> 2], uk);
-        } else if constexpr (AHEAD) {
+        } else if constexpr (RA) {
           ctx[s] = DeqCtx<DT, ZM>(e_st[u][s]);
         } else {
           ctx[s] = DeqCtx<DT, ZM>(sz[gi * N_T + wave * NW + s * 16 + ln]);
@@ -829,7 +834,7 @@ w4a16_gemm_kernel(const GemmParams p) {
         if constexpr (PRE) {
           const u32x4 t = wcur[s * UCH + u];      // the lane's four operand words, straight from the ring
           wv[s].w[0] = t.x; wv[s].w[1] = t.y; wv[s].w[2] = t.z; wv[s].w[3] = t.w;
-        } else if constexpr (AHEAD) {
+        } else if constexpr (RA) {
           wv[s] = w_st[u][s];
         } else {
           wv[s] = lds_read_words<KW>(wsw + (s * 16 + ln) * WP + 16 * KW * u + 4 * KW * lj);
@@ -1277,7 +1282,7 @@ w4a16_gemm_kernel(const GemmParams p) {
 }
 
 // Host-side launcher, one per instantiation.  Returns hipError_t as int.
-template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE, int WV, int XB = kXBufs(MT, KS, WV)>
+template <int DT, int MT, int NT, int KS, int KW, int FUSE, int SZR, int PRE, int WV, int XB = kXBufs(MT, KS, WV), int RA = kReadAhead(DT, MT, NT, KW, SZR)>
 int launch_w4a16_gemm(const GemmParams& p, int grid, hipStream_t stream);
 
 }  // namespace moe

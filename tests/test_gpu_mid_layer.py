@@ -323,3 +323,24 @@ def test_scale_table_in_a_large_launch(group, K, N, dtype):
     large, small = _block_64(inp)[:150], _block_64(few)
     _check(few, large, "large launch")
     assert torch.equal(large, small) == (dtype == "f16" or group != 64)
+
+
+@pytest.mark.parametrize("group,K,N", [(32, 160, 544), (64, 64, 1088), (96, 192, 672), (64, 640, 320)])
+def test_few_groups_in_a_large_launch_of_32_slot_blocks(group, K, N):
+    """fp16, up to five groups and (groups of 64) more than three workgroups for every CU: the tile that does not read its words
+    ahead.  The first rows have the bits of a launch of their own, with groups of 64 on the tile that does."""
+    cfg = MoEConfig(name="t32_large", T=6000, K=K, N=N, E=4, topk=1, group=group, dtype="f16", seed=23)
+    print(f"blocks of 32, large launch {cfg}", flush=True)
+    inp = make_inputs(cfg)
+    few = copy.copy(inp)
+    few.cfg = dataclasses.replace(cfg, T=150)
+    few.x_bits, few.topk_ids, few.topk_weights = inp.x_bits[:150], inp.topk_ids[:150], inp.topk_weights[:150]
+    M.moe_set_block_m_override(32)
+    try:
+        large, small = U.run_layer(U.DevInputs(inp))[:150], U.run_layer(U.DevInputs(few))
+        torch.cuda.synchronize()
+        assert M.moe_last_gemm_plan()["mt"] == 2
+    finally:
+        M.moe_set_block_m_override(0)
+    _check(few, large, "large launch")
+    assert torch.equal(large, small)
