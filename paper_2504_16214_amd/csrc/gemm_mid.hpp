@@ -188,7 +188,9 @@ __device__ __forceinline__ void mid_tile(const MidParams& p, unsigned char* lds,
 
   // ---- scales and zero points: panels of eight groups in registers, one panel ahead.  bf16: for the product of the
   // zero points, at the end of a panel, a lane fetches groups 2 j, 2 j + 1 in the middle of it: scales and
-  // zero points of its features, sums of its rows.
+  // zero points of its features, sums of its rows.  Four parts have no registers for that (they spilled 10 to 21) and
+  // fetch at the end: 3 to 5 % less at 48 to 63 rows per expert, the same or less with fewer parts.  3 to 13 are spilled still,
+  // in fp16 with four parts and the stated layout 4 to 8.
   u32x4 s_cur[2], s_nxt[2];
   u32x2 z_cur[2], z_nxt[2];
   uint32_t sp[2], zp[2];
@@ -372,7 +374,7 @@ __device__ __forceinline__ void mid_tile(const MidParams& p, unsigned char* lds,
          constexpr int buf = Rs & 1;
          MID_FENCE()
          if constexpr (r == 2 && h == 0) {
-           load_zero_operands(c_pan);
+           if constexpr (ML < 4) load_zero_operands(c_pan);
            load_panel();
          }
          dma_x(buf ^ 1);
@@ -398,6 +400,7 @@ __device__ __forceinline__ void mid_tile(const MidParams& p, unsigned char* lds,
        ...);
     }(std::make_integer_sequence<int, 4 * XSTEPS>{});
     if constexpr (DT == kBF16) {
+      if constexpr (ML == 4) load_zero_operands(c_pan);
       // the panel's zero points: four groups per instruction, float32 operands (scale * z / 16 stays in range, see kZeroUnit)
 #pragma unroll
       for (int h = 0; h < 2; ++h)
