@@ -85,15 +85,6 @@ __device__ __forceinline__ floatx4_t mfma16x16x32(const u32x4& a, const u32x4& b
   }
 }
 
-typedef float floatx16_t __attribute__((ext_vector_type(16)));
-template <int DT>
-__device__ __forceinline__ floatx16_t mfma32x32x16(const u32x4& a, const u32x4& b, floatx16_t c) {
-  if constexpr (DT == kF16)
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-}
-
 // ---- int4 -> 16-bit float, in registers ---------------------------------------------------
 // The MFMA never sees a rounded weight.  Two ways of removing the zero point, chosen by ZM:
 //

@@ -10,18 +10,6 @@ namespace moe {
 static int launch(const MidParams& p, int fuse, int pre, int grid, hipStream_t stream) {
   auto kern = fuse ? (pre ? w4a16_mid_kernel<MOE_DT, 1, 1> : w4a16_mid_kernel<MOE_DT, 1, 0>)
                    : (pre ? w4a16_mid_kernel<MOE_DT, 0, 1> : w4a16_mid_kernel<MOE_DT, 0, 0>);
-  // the dynamic LDS limit of each kernel is raised once per device
-  constexpr int kMaxDev = 64;
-  static bool allowed[4][kMaxDev] = {};
-  int dev = 0;
-  hipError_t err = hipGetDevice(&dev);
-  if (err != hipSuccess) return (int)err;
-  bool* const ok = dev >= 0 && dev < kMaxDev ? &allowed[(fuse ? 2 : 0) + (pre ? 1 : 0)][dev] : nullptr;
-  if (!ok || !*ok) {
-    err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kMidLds);
-    if (err != hipSuccess) return (int)err;
-    if (ok) *ok = true;
-  }
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), kMidLds, stream, p);
   return (int)hipGetLastError();
 }

@@ -46,6 +46,7 @@ struct MidParams {
 
 constexpr int kMidRows = 64, kMidXBytes = 32768, kMidWBytes = 4096;      // activations (two buffers), weights per wave
 constexpr int kMidSlots = kMidXBytes + 4 * kMidWBytes, kMidLds = kMidSlots + kMidRows * 4;
+static_assert(kMidLds <= 64 * 1024, "no kernel attribute is needed for this much");
 
 // A word's eight weights in the order of its activations.
 //   fp16: the integers q - z, order 0,4,1,5,2,6,3,7.
@@ -437,9 +438,6 @@ w4a16_mid_kernel(const MidParams p) {
   const int slot = p.sorted_slot_ids[row0 + (threadIdx.x & 63)];
   const unsigned long long any = __ballot(slot >= 0 && slot < p.num_slots);
   const int parts = any ? (64 - __builtin_clzll(any) + 15) / 16 : 0;
-#ifdef MID_ONLY
-  mid_tile<DT, FUSE, PRE, MID_ONLY>(p, smem, row0, e, tile0, ntl, split); return;
-#endif
   switch (__builtin_amdgcn_readfirstlane(parts)) {
     case 1: mid_tile<DT, FUSE, PRE, 1>(p, smem, row0, e, tile0, ntl, split); break;
     case 2: mid_tile<DT, FUSE, PRE, 2>(p, smem, row0, e, tile0, ntl, split); break;
