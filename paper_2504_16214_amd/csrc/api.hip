@@ -820,36 +820,32 @@ static int run_mid(const void* A, const float* sums, int row_div, const int32_t*
 }
 
 // Do the vector-product kernels (few_tokens.hip) take the call?  They have two launches instead of four, but
-// read an expert's weights once for every slot, and their down launch has a workgroup of eight waves for
-// every token and 16 columns (one fits a CU), whose waves idle where a token has few (slot, part)
-// pairs.  So up to 32 slots, and by the time both sides should take, in us with weights that are not in a
-// cache: fitted to 1331 calls of 1 to 32 tokens, K 256 ... 7168, N 512 ... 14336, 8 to 256 experts, top 1 to 8,
-// within 7 % (vector) and 5 % (tiled) on average; operand-order weights suit the tiles better and have a fit of
-// their own (598 calls).  Of 1791 calls near the crossing that the fits had not seen it takes 115 that are slower
-// than on the tiles, cached or not, by 12 % at most; of those it was fitted to, it leaves 34 on the tiles that
-// would be 3 to 18 % faster.  Tiled / vector, weights in memory (in the cache):
-//   7168x2048, 256 experts, top 8: 1 token 59.7 / 48.9 (57.8 / 46.2);   top 1: 4 tokens 48.4 / 43.8 (47.3 / 40.4), 6 52.1 / 66.8
-//   4096x14336, 8, top 2: 1 token 55.7 / 49.1 (54.3 / 44.2);   2048x1408, 64, top 6: 4 tokens 42.1 / 39.6, 5 46.1 / 46.2
-//   2048x2048, 64: top 1, 6 tokens 27.9 / 24.2, 8 28.4 / 28.9, 16 35.6 / 49.7;   top 4, 6 tokens 45.6 / 45.6
-//   1024x1024, 64: top 2, 12 tokens 27.0 / 24.6, 16 27.6 / 29.4;   256x512, 8, top 2: 16 tokens 19.4 / 10.1
-// (The vector figures are from before the gate/up launch wrote act as chunk vectors: one token is now 45.0 for 49.1, the
-// 256x512 layer 17.5 for 20.2 with its router, so calls near the crossing may still be better off there.)
-// The other limits keep slots that share an expert (about S^2 / 2E reads more than the tiles have) and
-// large weights, where nothing is left to gain, on the tiles.
+// read an expert's weights once for every slot.  So up to 32 slots, and by the time both sides should take, in us with
+// weights that are not in a cache: a start, then the vectors by the weights of every slot and by the activations a workgroup of gate/up
+// stages, the tiles by the weights of every expert met, by the reduction that a workgroup walks and by what a reduction that is no multiple
+// of 1024 loses (no register scales, no splits).  The host does not know the routing: the experts met are the mean of
+// what independent tokens meet and of what tokens meet that all choose the same.  Fitted to 5180 calls of 1 to 32 tokens (K 128 ... 8192,
+// N 128 ... 14336, 4 to 256 experts, top 1 to 10), within 10 % (vector) and 6 % (tiled) on average.
+// Calls it takes that are slower than on the tiles by more than 3 %, cached or not / calls it leaves there that would be faster by more:
+// independent tokens 0 / 846 of 8538 (the fits saw 5180 of them), experts weighted as 1 / rank 5 / 116 of 2073, all tokens alike 9 / 72 of
+// 2089 (20 % at most).  Above 128 million weights for all slots there is least to gain (0.8 to 1) and alike tokens cost most (31 of the 2089
+// with twice that).  More than 16 tokens, one expert each, keep the line they had, five rounds of down workgroups; 150 of the calls left
+// are beyond it.
+// Tiled / vector, weights in memory (in the cache), fp16:
+//   7168x2048, 256 experts, top 8: 1 token 58.7 / 41.9 (57.1 / 41.5);   top 1: 4 tokens 45.8 / 24.6 (45.6 / 24.6), 8 52.9 / 39.0
+//   4096x14336, 8, top 2: 1 token 54.9 / 46.4 (54.0 / 42.7);   2048x1408, 64, top 6: 4 tokens 41.3 / 29.9, 5 46.4 / 37.6
+//   2048x2048, 64: top 1, 6 tokens 25.8 / 16.5, 8 27.0 / 17.1, 16 35.7 / 26.9;   top 4, 6 tokens 45.9 / 37.0, 8 55.8 / 47.0
+//   1024x1024, 64: top 2, 12 tokens 27.0 / 16.8, 16 27.5 / 18.1;   256x512, 8, top 2: 16 tokens 19.3 / 8.9
 static bool few_tokens_pay(int T, int topk, int E, int K, int N, int dt, int pre) {
   const long long S = (long long)T * topk, nk = (long long)N * K;
-  if (S > 32 || S * nk > 128000000LL || S * S * nk > 40000000LL * E) return false;
-  const int parts = few_down_parts(topk, N), panels = (N + 1023) / 1024;
-  const double mw = nk / 1e6;                                  // a million weights of one of an expert's three matrices
-  const int serial = (topk * parts + 7) / 8 * ((panels + parts - 1) / parts);        // panels that a down wave works off
-  const double w = (double)T * K / 4096, full = ceil(w), rounds = w <= 1 ? 1 : w + 0.4 * (full - w);      // of down workgroups
-  const double experts = E * (1 - pow(1 - (topk < E ? (double)topk / E : 1.0), T));  // that the batch meets
-  const bool f16 = dt == MOE_F16;
-  if (pre)
-    return 9.7 + 0.331 * S * mw + rounds * (0.92 + (f16 ? 1.92 : 1.49) * serial) < 19.1 + 0.252 * experts * mw + (f16 ? 1.35e-3 : 1.55e-3) * K;
-  // (a reduction that is no multiple of 1024 runs without register scales and splits on the tiles)
-  return 8.5 + (f16 ? 0.331 : 0.303) * S * mw + rounds * (0.68 + 2.06 * serial) <
-         19.1 + 0.271 * experts * mw + (f16 ? 1.58e-3 : 1.87e-3) * K + (K % 1024 ? 1.04e-3 * K : 0) + (N % 1024 ? 1.71e-3 * N : 0);
+  if (S > 32 || S * nk > 128000000LL || (T > 16 && T * (long long)K > 20480)) return false;
+  static const struct { double vector, slot, stage, tiled, expert, walk, odd_k, odd_n; } kFit[2][2] = {      // [operand order][bf16]; sizes in thousands
+      {{8.1, 0.288, 0.85, 18.0, 0.260, 2.17, 0.78, 3.23}, {8.1, 0.268, 0.75, 18.2, 0.253, 2.40, 0.69, 3.29}},
+      {{8.6, 0.293, 0.52, 18.9, 0.265, 1.15, 0, 0}, {8.25, 0.270, 0.68, 18.9, 0.256, 1.48, 0, 0}}};
+  const auto& f = kFit[pre ? 1 : 0][dt == MOE_BF16 ? 1 : 0];
+  const double mw = nk / 1e6, k = K / 1e3, n = N / 1e3;        // a million weights of one of an expert's three matrices
+  const double alike = topk < E ? topk : E, experts = 0.5 * (E * (1 - pow(1 - alike / E, T)) + alike);
+  return f.vector + f.slot * S * mw + f.stage * k < f.tiled + f.expert * experts * mw + f.walk * k + (K % 1024 ? f.odd_k * k : 0) + (N % 1024 ? f.odd_n * n : 0);
 }
 static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_weights,
                       const int32_t* qw1, const void* s1, const uint8_t* z1,

@@ -68,6 +68,20 @@ def test_the_rule_ends_where_many_tokens_have_few_slots(T, few):
     assert ran_without_a_tile() == few
 
 
+@pytest.mark.parametrize("K,N,E,topk,T,dtype,few", [
+    (2048, 1408, 64, 6, 5, "f16", True),       # 38 us where the tiles take 46: what the launches save outweighs weights read twice
+    (2048, 2048, 64, 4, 5, "bf16", True),
+    (7168, 2048, 64, 1, 8, "f16", True),       # 39 and 53; one expert a token
+    (4096, 2048, 8, 2, 7, "f16", False),       # fourteen slots on eight experts
+    (1024, 1024, 24, 1, 20, "bf16", True),     # five rounds of down workgroups
+])
+def test_where_the_vector_products_are_chosen(K, N, E, topk, T, dtype, few):
+    cfg = MoEConfig("few_rule", T=T, K=K, N=N, E=E, topk=topk, group=128, dtype=dtype, seed=T)
+    say(f"rule for a few tokens {cfg}")
+    check_case(make_inputs(cfg), str(cfg))
+    assert ran_without_a_tile() == few
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_few_tokens_in_operand_order_are_the_same_bits(dtype):
     cfg = MoEConfig("few_pre", T=2, K=2048, N=1024, E=6, topk=3, group=128, dtype=dtype, seed=5)
