@@ -6,9 +6,9 @@
 // of 5 to 6 us that hardly use the chip.  Here every slot is a vector product of its own: gate/up with
 // SiLU-and-multiply is one kernel over (slot, columns), the down projection of all of a token's slots
 // with the weighted combine another over (token, columns).  Measured, us, tiled then vector, with the weights in
-// the last-level cache (in memory): that token 57.3 / 45.9 (59.7 / 48.8), bf16 60.6 / 43.8 (63.3 / 48.3); one token of
-// 4096 x 14336 with 8 experts, top 2, 53.7 / 44.1 (55.9 / 49.3); of 2048 x 1408 with 64, top 6, groups of 128, 29.6 / 17.5
-// (31.1 / 21.3); 16 tokens of 256 x 512 with 8, top 2, 18.7 / 9.4 (19.4 / 9.8).
+// the last-level cache (in memory), replayed: that token 57.1 / 41.5 (58.7 / 41.9), bf16 59.0 / 39.6 (59.0 / 39.5); one token of
+// 4096 x 14336 with 8 experts, top 2, 54.0 / 42.7 (54.9 / 46.4); 3 of 2048 x 1408 with 64, top 6, groups of 128, 39.3 / 25.7
+// (40.0 / 26.8); 16 tokens of 256 x 512 with 8, top 2, 18.7 / 8.2 (19.3 / 8.9).
 //
 // What bounds it: two launches (9 us); in the gate/up launch the vector unit (77 instructions a wave and
 // 1 KB of weights, 118 MB in 26 us: 4.5 TB/s), matrix instructions on 4 x 4 x 4 blocks in place of the dot products
@@ -17,7 +17,7 @@
 // of the down launch needs all act vectors of its token, 36 KB at top 8, for 16 columns: they are brought into their final
 // form once, by the gate/up kernel, and copied to LDS directly, and both panels of a 2048-long reduction are sent before
 // the first is waited for (23.9 us when every workgroup scaled the vectors itself and one panel was in flight).
-// That token now 44.0 (was 49.2, replayed), bf16 41.4 (45.4); 4 tokens of 2048 x 1408 30.0 (37.7).
+// With both that token went from 49.2 to 44.0 (another session), bf16 45.4 to 41.4, 4 tokens of 2048 x 1408 37.7 to 30.0.
 //
 // A wave covers 16 weight rows; 8 lanes share a row, lane i takes reduction indices 256 c + 32 i + [0, 32)
 // (16 bytes) of step c: 128 contiguous bytes of a row, or 128-byte runs of the offline repack's blocks

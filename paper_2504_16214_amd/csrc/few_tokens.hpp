@@ -13,6 +13,8 @@ bool few_tokens_fit(int topk, int K, int N);
 // Parts of the reduction that a slot's down product is cut into: about eight (slot, part) pairs for the eight waves.
 int few_down_parts(int topk, int N);
 // Routing inside the gate/up launch: up to kFewRouteE experts and 16 experts a token; fills ids and weights [T, topk].
+// (Sixteen keys a lane instead of four, for 65 to 256 experts, would take 1 to 13 % off such calls: 1 token of 7168 x 2048, 256 experts,
+// 48.9 -> 47.9 us, 128 experts 47.9 -> 46.1, 8 tokens of 256 x 512, 72 experts, 10.6 -> 9.4.  Not built.)
 constexpr int kFewRouteE = 64, kFewRouteTopk = 16;
 struct FewRoute {
   const float* logits;

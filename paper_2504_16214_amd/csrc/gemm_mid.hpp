@@ -4,10 +4,11 @@
 // passing registers (on the 32-slot tile their way through registers was a seventh of the time: 16 of 115 vector
 // instructions for 16 matrix instructions, and a second barrier per stage).
 //
-// A wave owns 32 features for all slots of the block.  A step is 256 reduction indices: 128 bytes of every weight
-// row, fetched two steps ahead into registers, then through a wave-private LDS tile to operand order; the
-// activations one step ahead, straight to LDS; one barrier per step.  The kernel is specialised on the live
-// 16-row parts of a block, so that up to 64 rows of an expert share one fetch and one unpack of its weights
+// A wave owns 32 features for all slots of the block.  A weight stage is 256 reduction indices: 128 bytes of every weight
+// row, fetched into registers, then through a wave-private LDS tile to operand order; the activations one of their
+// stages ahead, straight to LDS, with a barrier after each.  Up to two live parts an activation stage is 256 indices too and the
+// weights run two stages ahead; from three on it is 128 (two buffers of 16 KB), so two barriers per weight stage, and
+// the weights run one ahead (registers).  The kernel is specialised on the live 16-row parts of a block, so that up to 64 rows of an expert share one fetch and one unpack of its weights
 // without paying for padding.  bf16 has no packed subtraction; the other tiles send the zero points through
 // a second matrix instruction for every one.  Here the conversion unit produces the integers q and the zero points
 // cost one float32 matrix instruction per four groups (see mid_tile): half the matrix instructions, 7 vector
@@ -15,11 +16,11 @@
 //
 // Measured, former tiles -> this one, layer of 256 experts (K 7168, N 2048): fp16 512 tokens 1.30 -> 1.23 ms, 1024
 // 1.67 -> 1.51; bf16 512 1.59 -> 1.29, 717 1.70 -> 1.41, 1024 1.89 -> 1.57; 8 experts (K 4096, N 14336), 64 tokens,
-// fp16 184 -> 172 us.  What bounds it: gate/up at 22 rows takes 0.80 ms, without weight loads 0.53, without
+// fp16 175 -> 167 us.  What bounds it: gate/up at 22 rows takes 0.80 ms, without weight loads 0.53, without
 // computation 0.67 (4.3 GB at 6.5 TB/s; a tenth more than the weights, scale lines that are fetched again);
 // vector and matrix instructions of a SIMD share its issue and add up.  Not better: 64 features a wave on 32x32x16
 // instructions with two workgroups on a CU (half the activation reads, 0.78 ms at 22 rows, but 8 % slower at 32
-// and 64 rows), unpacking between the matrix instructions instead of before them (the same).
+// and 64 rows).  Where the unpacking stands makes little difference: see `groups`.
 #pragma once
 #include "gemm_kernel.hpp"
 #include "mid_order.hpp"
@@ -250,9 +251,9 @@ __device__ __forceinline__ void mid_tile(const MidParams& p, unsigned char* lds,
 
   u32x4 wcur[4];            // PRE: the words of the stage being multiplied
   // NG consecutive groups of the panel from GP0 on (one activation stage).  Every word's unpack stands between the
-  // matrix instructions of the word before it, and the sums of a group between those of the next: a wave
-  // issues a matrix instruction and works off vector instructions while it runs.  In separate blocks the two add up,
-  // with two or three waves on a SIMD as well.
+  // matrix instructions of the word before it, and the sums of a group between those of the next.  (Unpacking a word before
+  // its own matrix instructions, in separate blocks, takes the same time at 10 to 30 rows per expert and 1 to 2 %
+  // less at 48 to 63, bf16.)
   auto groups = [&](auto gpc, int xbuf) __attribute__((always_inline)) {
     constexpr int GP0 = decltype(gpc)::value, NG = XS / 128;
     u32x4 w[2][NG];
