@@ -311,16 +311,16 @@ static int run_gemm(const GemmArgs& a, hipStream_t stream) {
     // Enough workgroups for the chip: two rounds of the 768 that are resident, and with a few rows per expert
     // (16-row blocks, a workgroup is all weight streaming) a third one, which evens out the tail, as long as a workgroup keeps
     // 16 stages to make up for its start.  A count that leaves a short last group is lowered to the next that does not, if
-    // that costs less than half of it.  Down projection of 256 experts, 2048 -> 7168 (56 tiles), f16:
+    // that costs less than half of it and leaves 16 stages.  Down projection of 256 experts, 2048 -> 7168 (56 tiles), f16:
     // 128 tokens 4 or 7 tiles 358 us, 10 379, 12 403; 37 tokens on repacked weights 2 tiles 222 us,
     // 4 228, 6 (what 1536 workgroups alone gave) 235.  The whole layer, replayed: 37 to 96 tokens 1 to 3 % less, others within 1.5 %.
-    // Products of 366 layers where two rounds alone choose another count: gate/up 1.4 % less for a reduction of 1024, 1.1 to 2.4 % for longer ones (slowest tenth
-    // 2 % more, 7 of 100 at most), down 0.4 % less; without the 16 stages a reduction of 1024 lost up to 11 %, down 3 % on average.
+    // Products where two rounds alone choose another count: 144 of gate/up 1.8 % less on average (8 % more at most), 7 of down 1 % less;
+    // without the 16 stages a gate/up reduction of 1024 lost up to 11 %, 157 of down 3 % on average.
     const long long est_blocks = (a.num_slots + 16 * mt - 1) / (16 * mt) + (a.num_slots < a.E ? a.num_slots : a.E) / 2;
     auto workgroups = [&](int t) { return est_blocks * ((p.n_tiles + t - 1) / t) * ksp; };
     while (tpw > 1 && workgroups(tpw) < 1536) --tpw;
     while (mt == 1 && (tpw - 1) * nst >= 16 && workgroups(tpw) < 2304) --tpw;
-    for (int t = tpw; mt == 1 && 2 * t > tpw; --t)
+    for (int t = tpw; mt == 1 && 2 * t > tpw && (t == tpw || t * nst >= 16); --t)
       if (p.n_tiles % t == 0) { tpw = t; break; }
   }
   if (g_force_tpw > 0) tpw = szr ? (g_force_tpw < p.n_tiles ? g_force_tpw : p.n_tiles) : 1;

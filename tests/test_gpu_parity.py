@@ -179,6 +179,7 @@ def test_multi_tile_workgroups(tpw, which):
 
 
 @pytest.mark.parametrize("K,N,T,tiles", [(2048, 1024, 256, 2),      # 4 stages a tile: one tile would be all start-up
+                                         (4096, 1024, 128, 3),      # 32 tiles: two leave no short last group, but 8 stages
                                          (4096, 2048, 64, 2)])      # 8 stages: three tiles leave 1584 workgroups, two 2304
 def test_tiles_per_workgroup_with_a_few_rows_per_expert(K, N, T, tiles):
     """Down product of 256 experts: a third round of workgroups only if each keeps 16 stages; any count has the same bits."""
