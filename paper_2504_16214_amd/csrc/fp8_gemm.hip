@@ -6,7 +6,7 @@
 //
 // Mapping.  A workgroup of WM x WN waves owns BM rows of A ("tokens") and BN rows of B ("features").
 // The features are the matrix instruction's row operand and the tokens its column operand, so a
-// lane ends up with one token and 4 NT consecutive features: 16-byte stores, one activation scale
+// lane ends up with one token and runs of its features: 16-byte stores, one activation scale
 // per lane and row block.
 //   * Both operands go global -> LDS with direct-to-LDS loads (global_load_lds_dwordx4: no staging
 //     registers, no ds_write) -> operand registers.  The global side is fully coalesced (eight lanes
@@ -66,6 +66,18 @@ struct Geom {
   static_assert(BN % RPP == 0, "feature tile must be whole passes");
 };
 
+// Which of a wave's 16 NT features LDS row q (operand row q & 15 of sub-tile q >> 4) holds.  Lane group j of a token
+// ends up with operand rows 4 j ... 4 j + 3 of every sub-tile.  The rows are dealt so that the four groups' 16 bytes
+// of one store lie side by side, 64 bytes of a token: float32 stores a sub-tile at a time (the identity), 16-bit types
+// two.  (With 4 NT consecutive features in a lane a store touched every fourth or second 16 bytes: float32 tiles, written
+// only, 3.3 TB/s against 5.4.  Grouped 256 x 256 tile, 256 rows for each of 256 experts, K 2048, N 7168, float32, 1600 ->
+// 1430 us; FP8 layer, 4096 tokens, 256 experts 3.09 -> 3.05 ms, 64 experts, K 2048, N 1408 457 -> 428 us; dense the same.)
+template <int NT>
+__device__ __forceinline__ int feature_of_row(int q, bool f32) {
+  const int nt = q >> 4, l = q & 15;
+  return NT == 1 || f32 ? q : 32 * (nt >> 1) + 8 * (l >> 2) + 4 * (nt & 1) + (l & 3);
+}
+
 // Row block mb and feature block nb of tile L inside a split.  Tiles are walked in groups of group_m row
 // blocks: feature block by feature block inside a group, so that the workgroups that run together share
 // both their A rows and their B rows.  Row blocks of different experts share no B rows: a group without two
@@ -79,6 +91,37 @@ __device__ __forceinline__ void tile_of(const GemmParams& p, bool grouped, int m
   for (int i = 1; i < m_in && !share; ++i) share = p.block_expert_ids[m0 + i] == p.block_expert_ids[m0 + i - 1];
   nb = share ? rem / m_in : rem % n_blocks;
   mb = m0 + (share ? rem % m_in : rem / n_blocks);
+}
+
+// Lane group j's share of a token's 16 NT features (see feature_of_row) in the output type (p.out_bf16: 0 fp16, 1 bf16,
+// 2 float32); at: the first of them.
+template <int NT>
+__device__ __forceinline__ void store_row(const GemmParams& p, size_t at, int j, const f32x4 (&v)[NT]) {
+  if (p.k_splits > 1 || p.out_bf16 == 2) {      // a partial plane, or the result itself
+    float* dst = reinterpret_cast<float*>(p.C) + at + 4 * j;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<f32x4*>(dst + 16 * nt) = v[nt];
+    return;
+  }
+  uint32_t w[2 * NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    if (p.out_bf16 == 1) {
+      w[2 * nt] = pack2<1>(v[nt][0], v[nt][1]);
+      w[2 * nt + 1] = pack2<1>(v[nt][2], v[nt][3]);
+    } else {
+      w[2 * nt] = pack2<0>(v[nt][0], v[nt][1]);
+      w[2 * nt + 1] = pack2<0>(v[nt][2], v[nt][3]);
+    }
+  }
+  uint16_t* dst = reinterpret_cast<uint16_t*>(p.C) + at + (NT == 1 ? 4 : 8) * j;
+  if constexpr (NT == 1) {
+    *reinterpret_cast<u32x2*>(dst) = u32x2{w[0], w[1]};
+  } else {
+#pragma unroll
+    for (int h = 0; h < NT / 2; ++h)
+      *reinterpret_cast<u32x4*>(dst + 32 * h) = u32x4{w[4 * h], w[4 * h + 1], w[4 * h + 2], w[4 * h + 3]};
+  }
 }
 
 template <int WM, int WN, int MT, int NT, int NS>
@@ -147,6 +190,7 @@ fp8_blockwise_gemm_kernel(const GemmParams p) {
     const int g = row0 + r;
     return g >= p.M ? p.M - 1 : g;
   };
+  const bool f32 = p.k_splits > 1 || p.out_bf16 == 2;      // a partial plane, or the result itself
   uint32_t aoff[CHA], boff[CHB];                  // byte offsets from A / B (host checks they fit 32 bits)
 #pragma unroll
   for (int i = 0; i < CHA; ++i) {
@@ -155,20 +199,18 @@ fp8_blockwise_gemm_kernel(const GemmParams p) {
     aoff[i] = (uint32_t)a_row_of(r) * (uint32_t)p.K + 16u * (sc ^ (srow & 7));
   }
 #pragma unroll
-  for (int i = 0; i < CHB; ++i) boff[i] = (uint32_t)(n0 + srow + RPP * i) * (uint32_t)p.K + 16u * (sc ^ (srow & 7));
+  for (int i = 0; i < CHB; ++i) {
+    const int r = srow + RPP * i, q = r % (16 * NT);
+    boff[i] = (uint32_t)(n0 + r - q + feature_of_row<NT>(q, f32)) * (uint32_t)p.K + 16u * (sc ^ (srow & 7));
+  }
   // activation scale of tile row tid (threads past BM repeat the last row)
   const float* assrc = p.a_scale + (size_t)a_row_of(tid < BM ? tid : BM - 1) * KB;
   const float* bssrc = bsmat + (size_t)((n0 + wn * 16 * NT) >> 7) * KB;      // wave-uniform
 
   // ---- operand read positions ----
-  // features: operand row ln of sub-tile nt is feature 4 NT (ln >> 2) + 4 nt + (ln & 3) of the wave's
-  // range, so that a lane ends up with 4 NT consecutive features of its token
   const int xrow = wm * 16 * MT + ln;             // + 16 mt
   const int xpos = 16 * (lj ^ (ln & 7));          // tile rows are multiples of 16 apart: (row & 7) == (ln & 7)
-  // sub-tile nt: rows 4 nt further down; (row & 7) changes by 4 (nt & 1), i.e. the position flips by 64
-  const int wr0 = wn * 16 * NT + 4 * NT * (ln >> 2) + (ln & 3);
-  const int wpos0 = (AROWS + wr0) * 128 + 16 * (lj ^ (wr0 & 7));
-  static_assert(NT == 1 || (4 * NT) % 8 == 0, "the swizzle of the feature rows assumes 4 NT % 8 == 0");
+  const int wpos0 = (AROWS + wn * 16 * NT + ln) * 128 + xpos;      // + 2048 nt
 
   f32x4 acc[MT][NT];
 #pragma unroll
@@ -209,7 +251,7 @@ fp8_blockwise_gemm_kernel(const GemmParams p) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) sp[mt] = ss[16 * mt] * bs;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) wa[nt] = read_op(st, (wpos0 + 512 * nt) ^ (64 * (nt & 1)));
+    for (int nt = 0; nt < NT; ++nt) wa[nt] = read_op(st, wpos0 + 2048 * nt);
   };
   // row blocks [MLO, MHI) of the tile against the wave's NT weight operands
   auto compute = [&](int ring, auto mlo, auto mhi) __attribute__((always_inline)) {
@@ -284,8 +326,7 @@ fp8_blockwise_gemm_kernel(const GemmParams p) {
     if constexpr (NS >= 4) { if (it + 3 < nkb) stage(integral_constant<int, 3>{}, clampk(it + NS + 2)); }
   }
 
-  // ---- epilogue: the lane's token, 4 NT consecutive features ----
-  const int f0 = n0 + wn * 16 * NT + 4 * NT * lj;
+  // ---- epilogue: the lane's token ----
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     int t = row0 + xrow + 16 * mt;               // dense: the token; grouped: the slot behind the tile row
@@ -295,58 +336,8 @@ fp8_blockwise_gemm_kernel(const GemmParams p) {
     } else if (t >= p.M) {
       continue;
     }
-    if (p.k_splits > 1 || p.out_bf16 == 2) {     // float32: a partial plane, or the result itself
-      float* dst = reinterpret_cast<float*>(p.C) + ((size_t)split * p.M + t) * p.N + f0;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<f32x4*>(dst + 4 * nt) = acc[mt][nt];
-    } else {
-      uint16_t* dst = reinterpret_cast<uint16_t*>(p.C) + (size_t)t * p.N + f0;
-      uint32_t w[2 * NT];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        if (p.out_bf16 == 1) {
-          w[2 * nt] = pack2<1>(acc[mt][nt][0], acc[mt][nt][1]);
-          w[2 * nt + 1] = pack2<1>(acc[mt][nt][2], acc[mt][nt][3]);
-        } else {
-          w[2 * nt] = pack2<0>(acc[mt][nt][0], acc[mt][nt][1]);
-          w[2 * nt + 1] = pack2<0>(acc[mt][nt][2], acc[mt][nt][3]);
-        }
-      }
-      if constexpr (NT == 1) {
-        *reinterpret_cast<u32x2*>(dst) = u32x2{w[0], w[1]};
-      } else {
-#pragma unroll
-        for (int h = 0; h < NT / 2; ++h)
-          *reinterpret_cast<u32x4*>(dst + 8 * h) = u32x4{w[4 * h], w[4 * h + 1], w[4 * h + 2], w[4 * h + 3]};
-      }
-    }
+    store_row<NT>(p, ((size_t)split * p.M + t) * p.N + n0 + wn * 16 * NT, lj, acc[mt]);
   }
-}
-
-// One token's 4 NT consecutive features in the output type (p.out_bf16: 0 fp16, 1 bf16, 2 float32).
-template <int NT>
-__device__ __forceinline__ void store_row(const GemmParams& p, size_t at, const f32x4 (&v)[NT]) {
-  if (p.k_splits > 1 || p.out_bf16 == 2) {      // a partial plane, or the result itself
-    float* dst = reinterpret_cast<float*>(p.C) + at;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<f32x4*>(dst + 4 * nt) = v[nt];
-    return;
-  }
-  uint16_t* dst = reinterpret_cast<uint16_t*>(p.C) + at;
-  uint32_t w[2 * NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    if (p.out_bf16 == 1) {
-      w[2 * nt] = pack2<1>(v[nt][0], v[nt][1]);
-      w[2 * nt + 1] = pack2<1>(v[nt][2], v[nt][3]);
-    } else {
-      w[2 * nt] = pack2<0>(v[nt][0], v[nt][1]);
-      w[2 * nt + 1] = pack2<0>(v[nt][2], v[nt][3]);
-    }
-  }
-#pragma unroll
-  for (int h = 0; h < NT / 2; ++h)
-    *reinterpret_cast<u32x4*>(dst + 8 * h) = u32x4{w[4 * h], w[4 * h + 1], w[4 * h + 2], w[4 * h + 3]};
 }
 
 // ---- the 256 x 256 tile: two wave groups in turn on the matrix unit -------------------------------
@@ -382,7 +373,8 @@ struct PingGeom {
   static constexpr int SR = ROWS / 32;                     // scale rows per wave and step
   static constexpr int SOFF = NBUF * STAGE;                // activation scales: ring of four groups of four blocks
   static constexpr int TOFF = SOFF + 4 * ROWS * 16;        // A row behind every tile row
-  static constexpr int LDS = TOFF + ROWS * 4;
+  static constexpr int OOFF = TOFF + ROWS * 4;             // row of C behind every tile row, -1: none
+  static constexpr int LDS = OOFF + ROWS * 4;
   static_assert(LDS <= 160 * 1024, "LDS");
 };
 constexpr int kPingLds = PingGeom<4>::LDS > PingGeom<8>::LDS ? PingGeom<4>::LDS : PingGeom<8>::LDS;
@@ -419,15 +411,19 @@ ping_tile(const GemmParams& p, unsigned char* lds, int row0, int n0, const uint8
   // A row behind a tile row: dense = the row itself (rows past the matrix repeat its last row and are
   // never stored); grouped = slot / row_div (padding rows read row 0)
   int* const atab = reinterpret_cast<int*>(lds + G::TOFF);
+  int* const otab = reinterpret_cast<int*>(lds + G::OOFF);      // (the table's entries: fetched at the end, each store waited for one)
   if (tid < G::ROWS) {
-    int r;
+    int r, o;
     if (grouped) {
       const int slot = p.sorted_slot_ids[row0 + tid];
-      r = (slot >= 0 && slot < p.num_slots) ? slot / p.row_div : 0;
+      o = (slot >= 0 && slot < p.num_slots) ? slot : -1;
+      r = o >= 0 ? slot / p.row_div : 0;
     } else {
-      r = row0 + tid < p.M ? row0 + tid : p.M - 1;
+      o = row0 + tid < p.M ? row0 + tid : -1;
+      r = o >= 0 ? o : p.M - 1;
     }
     atab[tid] = r;
+    otab[tid] = o;
   }
   __syncthreads();
 
@@ -442,8 +438,7 @@ ping_tile(const GemmParams& p, unsigned char* lds, int row0, int n0, const uint8
   for (int c = 0; c < C; ++c) aoff[c] = (uint32_t)atab[64 * c + arow + srow] * (uint32_t)p.K + chunk;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int r = 8 * wave + srow;      // LDS row 64 i + 16 nt + l holds feature 64 i + 16 (l >> 2) + 4 nt + (l & 3)
-    boff[i] = (uint32_t)(n0 + 64 * i + 16 * ((r >> 2) & 3) + 4 * (r >> 4) + (r & 3)) * (uint32_t)p.K + chunk;
+    boff[i] = (uint32_t)(n0 + 64 * i + feature_of_row<NT>(8 * wave + srow, p.k_splits > 1 || p.out_bf16 == 2)) * (uint32_t)p.K + chunk;
   }
   const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)p.A, 0, (int)0xffffffffu, 0x00020000);
   const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc((void*)B, 0, (int)0xffffffffu, 0x00020000);
@@ -612,17 +607,14 @@ ping_tile(const GemmParams& p, unsigned char* lds, int row0, int n0, const uint8
   if (wm == 0) FP8_PHASE_BARRIER()
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, false));      // no direct-to-LDS load outlives the workgroup
 
-  const int f0 = n0 + wn * 64 + 16 * lj;
+  int rows[ML];
+#pragma unroll
+  for (int mt = 0; mt < ML; ++mt) rows[mt] = otab[32 * mt + 16 * wm + ln];
 #pragma unroll
   for (int mt = 0; mt < ML; ++mt) {
-    int t = row0 + 32 * mt + 16 * wm + ln;
-    if (grouped) {
-      t = p.sorted_slot_ids[t];
-      if (t < 0 || t >= p.num_slots) continue;
-    } else if (t >= p.M) {
-      continue;
-    }
-    store_row<NT>(p, ((size_t)split * p.M + t) * p.N + f0, acc[mt]);
+    const int t = rows[mt];
+    if (t < 0) continue;
+    store_row<NT>(p, ((size_t)split * p.M + t) * p.N + n0 + wn * 64, lj, acc[mt]);
   }
 }
 
