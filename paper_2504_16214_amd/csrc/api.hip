@@ -282,6 +282,7 @@ static int run_gemm(const GemmArgs& a, hipStream_t stream) {
   p.cpg = a.group / (32 * kw);
   p.half_n = a.fuse_half_n;
   p.out_f32 = a.out_f32;
+  p.c_bytes = c_plane_bytes(a.num_slots, (long long)a.ldc * (a.out_f32 ? 4 : 2));
   p.sz_vec = sz_vec;
   p.dense = a.dense;
   // Split reduction: whole scale panels (4 pipeline stages) per range, every range non-empty.
@@ -767,6 +768,7 @@ static int run_twogroup(const void* A, const float* bias_rows, int row_div, cons
   p.qweight = qw; p.scales = sc; p.zeros = z;
   p.sorted_slot_ids = sorted; p.block_expert_ids = blocks; p.num_padded = num_padded;
   p.num_slots = num_slots; p.E = E; p.N_out = N_out; p.K_in = K_in; p.C = C; p.pre = pre;
+  p.c_bytes = c_plane_bytes(num_slots, fuse ? N_out : 4LL * N_out);      // 16-bit act of half the columns, or float32
   p.n_tiles = N_out / 256;
   // Several tiles per workgroup where the reduction is short (a tile's start and end cost about as
   // much as four stages), as long as a few rounds over the CUs remain.

@@ -48,6 +48,7 @@ struct GemmParams {
   const int32_t* num_padded;
   int num_slots, E, N_out, K_in, group, block_m;
   void* C;
+  uint32_t c_bytes;   // bytes of a plane of C; 0: too large for 32-bit offsets (see kNoRow)
   int ldc;
   int n_tiles;    // workgroups along the feature dimension
   int G;          // K_in / group
@@ -276,6 +277,36 @@ __device__ __forceinline__ int xcd_contiguous_index(int pid, int total) {
   return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
 }
 
+// Rows of C by 32-bit offsets, for stores without a branch: a padding row's offset lies outside the buffer, and the
+// hardware drops what is stored there.  A branch per row costs its mask and a 64-bit address, and behind stores that may
+// or may not have been sent the compiler no longer knows how many loads are in flight, so it waits for more of
+// them than it has to.  Planes that 32 bits do not reach (c_plane_bytes) are stored with a branch.  The tiles of 64 rows and
+// more use it (layer, 64 experts, K 2048, N 1408, groups of 64: 4096 tokens f16 768 -> 752 us, bf16 844 -> 821, 1024 tokens of skewed
+// routing 219 -> 214 and 242 -> 238; two-group tile: see there); the smaller ones and the 64-slot tile gain nothing.  What their float32 rows
+// cost is the memory's: 59 MB written beside 1.9 GB read take 56 us, 117 MB 75, however they are stored.
+constexpr uint32_t kNoRow = 0xF0000000u;      // (a column's offset is below 2^28: the sum stays in 32 bits)
+inline uint32_t c_plane_bytes(long long rows, long long row_bytes) {
+  return rows * row_bytes <= (long long)kNoRow && row_bytes < (1LL << 28) ? (uint32_t)(rows * row_bytes) : 0u;
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t c_rows(void* plane, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(plane, 0, (int)bytes, 0x00020000);
+}
+// (By value: a bit cast of a vector's element takes the vector's first.)
+__device__ __forceinline__ uint32_t bits32(float v) { return __builtin_bit_cast(uint32_t, v); }
+// The value of the neighbouring lane (lane ^ 1).
+__device__ __forceinline__ uint32_t from_neighbour(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);      // quad_perm(1, 0, 3, 2)
+}
+// The value of lane ^ 2.
+__device__ __forceinline__ uint32_t from_pair(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);      // quad_perm(2, 3, 0, 1)
+}
+// Two 16-bit values of a column in neighbouring lanes, rows r0 and r1: the even lane gets both columns of r0, the odd one of r1.
+__device__ __forceinline__ uint32_t pair_columns(uint32_t v0, uint32_t v1, bool odd) {
+  const uint32_t got = from_neighbour(odd ? v0 : v1);
+  return odd ? got | (v1 << 16) : v0 | (got << 16);
+}
+
 // Packed weights: streamed once per launch in the small-token regime (non-temporal, so they
 // do not displace the activation tiles in L2); with large token tiles the same expert rows are
 // read again by the neighbouring slot blocks and should stay cached.
@@ -453,7 +484,7 @@ w4a16_gemm_kernel(const GemmParams p) {
   constexpr int XBUFS = G_::XBUFS;
   unsigned char* ws_all = xs + XBUFS * M_T * XP;                   // [WV][NW][WP] (absent when PRE)
   uint32_t* sz = reinterpret_cast<uint32_t*>(ws_all + (PRE ? 0 : WV * NW * WP));  // [G][N_T] (absent when SZR)
-  int* slot_s = reinterpret_cast<int*>(sz + (SZR ? 0 : p.G * N_T));  // [M_T]
+  uint32_t* row_s = reinterpret_cast<uint32_t*>(sz + (SZR ? 0 : p.G * N_T));  // [M_T] row of C behind a tile row: offset in bytes, or (c_bytes 0 or a tile below 64 rows) the slot
 
   // A workgroup owns one block of M_T slots and `tiles_per_wg` consecutive feature tiles; it
   // walks them with one continuous load pipeline (no drain between tiles), so the fixed cost of
@@ -621,6 +652,7 @@ w4a16_gemm_kernel(const GemmParams p) {
             ZS ? deal8(XV[ps]) : interleave8(XV[ps]);                                           \
   }
 
+  constexpr bool kByOffset = MT >= 4;      // stores by offset, see kNoRow
   // Flattened step index over (tile, stage).  nst_pad rounds the stages of a tile up to whole
   // trips; stages in [nst, nst_pad) are dead (clamped loads, no compute).
   const int nst_pad = (nst + UNR - 1) / UNR * UNR;
@@ -712,7 +744,10 @@ w4a16_gemm_kernel(const GemmParams p) {
   }
 
   // ---- stage scales / zero points of this tile's rows into LDS ---------------------
-  if (tid < M_T) slot_s[tid] = slot_at(row0 + tid);
+  if (tid < M_T) {
+    const int slot = slot_at(row0 + tid);
+    row_s[tid] = !kByOffset || !p.c_bytes ? (uint32_t)slot : slot >= 0 && slot < p.num_slots ? (uint32_t)slot * ((uint32_t)p.ldc * (p.out_f32 ? 4u : 2u)) : kNoRow;
+  }
   if constexpr (!SZR) {
     const uint16_t* sc = reinterpret_cast<const uint16_t*>(p.scales);
     const int G = p.G, G8 = (G + 7) >> 3;
@@ -1006,12 +1041,60 @@ w4a16_gemm_kernel(const GemmParams p) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) acc[mt][s][i] *= unit[s];
     }
+    if constexpr (kByOffset) {
+      if (p.c_bytes) {
+      // Two rows at a time: neighbouring lanes, which hold the same rows of neighbouring columns, exchange so that the even
+      // one stores the first row and the odd one the second, twice as many columns each.
+      const __amdgpu_buffer_rsrc_t rc = c_rows(reinterpret_cast<float*>(p.C) + (size_t)split * p.split_stride, p.c_bytes);
+      const bool odd = ln & 1;
+#pragma unroll
+      for (int mt = 0; mt < ML; ++mt) {
+#pragma unroll
+        for (int i = 0; i < 4; i += 2) {
+          const uint32_t row = row_s[mt * 16 + lj * 4 + i + (ln & 1)];
+          if constexpr (FUSE == 0) {
+#pragma unroll
+            for (int s = 0; s < NT; s += 2) {
+              int wrow, ocol; bool ok;
+              feature_of<NT, FUSE, WV>(tile, wave, s, ln & ~1, p, wrow, ocol, ok);
+              if (p.out_f32) {
+                const uint32_t a0 = bits32(acc[mt][s][i]), b0 = bits32(acc[mt][s + 1][i]);
+                const uint32_t a1 = bits32(acc[mt][s][i + 1]), b1 = bits32(acc[mt][s + 1][i + 1]);
+                const uint32_t ga = from_neighbour(odd ? a0 : a1), gb = from_neighbour(odd ? b0 : b1);
+                __builtin_amdgcn_raw_buffer_store_b128(odd ? u32x4{ga, gb, a1, b1} : u32x4{a0, b0, ga, gb}, rc, (int)(ok ? row + 4u * ocol : kNoRow), 0, 0);
+              } else {
+                const uint32_t v0 = (uint32_t)to_bits16<DT>(acc[mt][s][i]) | ((uint32_t)to_bits16<DT>(acc[mt][s + 1][i]) << 16);
+                const uint32_t v1 = (uint32_t)to_bits16<DT>(acc[mt][s][i + 1]) | ((uint32_t)to_bits16<DT>(acc[mt][s + 1][i + 1]) << 16);
+                const uint32_t got = from_neighbour(odd ? v0 : v1);
+                __builtin_amdgcn_raw_buffer_store_b64(odd ? u32x2{got, v1} : u32x2{v0, got}, rc, (int)(ok ? row + 2u * ocol : kNoRow), 0, 0);
+              }
+            }
+          } else {
+#pragma unroll
+            for (int s = 0; s < NT; s += 2) {
+              int wrow, ocol; bool ok;
+              feature_of<NT, FUSE, WV>(tile, wave, s, ln & ~1, p, wrow, ocol, ok);
+              uint32_t v[2];
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                // round gate/up to the storage type first so the fused path equals the staged one
+                const float g = from_bits16<DT>(to_bits16<DT>(acc[mt][s][i + h])), u = from_bits16<DT>(to_bits16<DT>(acc[mt][s + 1][i + h]));
+                v[h] = to_bits16<DT>(silu_f32(g) * u);
+              }
+              __builtin_amdgcn_raw_buffer_store_b32(pair_columns(v[0], v[1], odd), rc, (int)(ok ? row + 2u * ocol : kNoRow), 0, 0);
+            }
+          }
+        }
+      }
+      }
+    }
+    if (!kByOffset || !p.c_bytes) {
     uint16_t* C16 = reinterpret_cast<uint16_t*>(p.C);
 #pragma unroll
     for (int mt = 0; mt < ML; ++mt) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int slot = slot_s[mt * 16 + lj * 4 + i];
+        const int slot = (int)row_s[mt * 16 + lj * 4 + i];
         if (slot < 0 || slot >= p.num_slots) continue;
         uint16_t* crow = C16 + (size_t)slot * p.ldc;
         if constexpr (FUSE == 0 && NT == 1) {
@@ -1051,6 +1134,8 @@ w4a16_gemm_kernel(const GemmParams p) {
           }
         }
       }
+    }
+    if (kByOffset) __builtin_amdgcn_s_waitcnt(0x0F70);      // (nothing in flight: what is counted after the other form holds here too)
     }
 #pragma unroll
     for (int mt = 0; mt < ML; ++mt)

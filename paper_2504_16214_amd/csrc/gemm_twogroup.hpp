@@ -24,7 +24,8 @@
 // weight loads likewise (1607 us).
 // Measured, eight-wave 128-slot tile -> this one, gate/up product of 256 experts (K 7168, N 2048), fp16:
 // 128 rows per expert 2.09 -> 1.87 ms (even counts; 2.06 with drawn routing), 160 rows 2.87 -> 2.22, 192 rows
-// 3.23 -> 2.54, 64 rows 1.32 -> 1.17; layer at 4096 tokens fp16 4.03 -> 3.60 ms, bf16 5.44 -> 4.26 ms.
+// 3.23 -> 2.54, 64 rows 1.32 -> 1.17; layer at 4096 tokens fp16 4.03 -> 3.60 ms, bf16 5.44 -> 4.26 ms.  With its
+// stores by offset and four (act: two) columns wide instead of one, with a branch for each: fp16 3.64 -> 3.49 ms, bf16 4.30 -> 4.25.
 #pragma once
 #include "gemm_kernel.hpp"
 
@@ -42,6 +43,7 @@ struct TwoGroupParams {
   const int32_t* num_padded;
   int num_slots, E, N_out, K_in;
   void* C;                   // FUSE: act [num_slots, N_out / 2] 16-bit, runs of eight reordered; else float32 [num_slots, N_out]
+  uint32_t c_bytes;          // bytes of C; 0: rows are stored with a branch (c_plane_bytes)
   int n_tiles;               // 256-feature tiles of a block
   int tiles_per_wg;          // consecutive tiles one workgroup walks
   int pre;                   // 1: qweight in the operand order of the offline repack
@@ -70,7 +72,8 @@ struct TwoGroupGeom {
   static constexpr int SR = RROWS / 32;                     // row sums: rows per wave and step
   static constexpr int ROFF = NBUF * STAGE;                 // ring of four groups of four stages
   static constexpr int TOFF = ROFF + 4 * RROWS * 16;        // slot of every tile row
-  static constexpr int ZOFF = TOFF + 256 * 4;               // zeros, as large as one group of the ring
+  static constexpr int OOFF = TOFF + 256 * 4;               // its offset in C (c_bytes)
+  static constexpr int ZOFF = OOFF + 256 * 4;               // zeros, as large as one group of the ring
   static constexpr int WOFF = ZOFF + RROWS * 16;            // STREAM: three buffers of 256 rows x 128 bytes
   static constexpr int LDS = WOFF + (STREAM ? 3 * 32768 : 0);
   static_assert(LDS <= 160 * 1024, "LDS");
@@ -136,9 +139,11 @@ tg_tile(const TwoGroupParams& p, unsigned char* lds, int row0, int e, int tile0,
   uk.or_lo = vgpr_const(0x54005400u);
 
   int* const slots = reinterpret_cast<int*>(lds + G::TOFF);
+  uint32_t* const out_rows = reinterpret_cast<uint32_t*>(lds + G::OOFF);
   if (tid < 256) {
     const int s = tid < 32 * ML ? p.sorted_slot_ids[row0 + tid] : -1;
     slots[tid] = s >= 0 && s < p.num_slots ? s : -1;
+    out_rows[tid] = s >= 0 && s < p.num_slots ? (uint32_t)s * (uint32_t)p.N_out * (FUSE ? 1u : 4u) : kNoRow;
   }
   if (DT == kBF16 && tid < G::RROWS) *reinterpret_cast<u32x4*>(lds + G::ZOFF + tid * 16) = u32x4{0, 0, 0, 0};
   __syncthreads();
@@ -176,7 +181,9 @@ tg_tile(const TwoGroupParams& p, unsigned char* lds, int row0, int e, int tile0,
   uint32_t woff, sz_row;
   uint32_t wdma[4];                          // STREAM: the lane's rows 8 i + lane / 8 of the wave's 32
   auto wrow_of = [&](int tile, int n) __attribute__((always_inline)) {
-    return FUSE ? (n >> 4) * half_n + tile * 128 + wave * 16 + (n & 15) : tile * 256 + wave * 32 + n;
+    // (fused: lane n & 15 takes the feature whose act lies at that position, runs of eight in operand order: neighbouring lanes
+    // store neighbouring columns)
+    return FUSE ? (n >> 4) * half_n + tile * 128 + wave * 16 + (n & 8) + ((n >> 1) & 3) + 4 * (n & 1) : tile * 256 + wave * 32 + n;
   };
   // 16-byte chunk j (0 .. 3) of a stage of weight row wrow, bytes from wbase
   auto w_at = [&](uint32_t wrow, uint32_t st, uint32_t j) __attribute__((always_inline)) -> uint32_t {
@@ -289,6 +296,42 @@ tg_tile(const TwoGroupParams& p, unsigned char* lds, int row0, int e, int tile0,
 
   // accumulator register c of a lane: row 8 (c >> 2) + 4 h + (c & 3) of the sub-tile, feature n
   auto store_tile = [&](int tile) __attribute__((always_inline)) {
+    if (p.c_bytes) {
+      const __amdgpu_buffer_rsrc_t rc = c_rows(p.C, p.c_bytes);
+      const bool odd = lane & 1;
+#pragma unroll
+      for (int mt = 0; mt < ML; ++mt) {
+#pragma unroll
+        for (int c4 = 0; c4 < 4; ++c4) {
+          const uint32_t* const rows = out_rows + mt * 32 + 8 * c4 + 4 * lh;
+          if constexpr (FUSE) {
+            // (see below; then neighbouring lanes put their columns together: one row of two each)
+            uint32_t v[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const auto sw = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, acc[mt][4 * c4 + 2 * h] * unit),
+                                                               __builtin_bit_cast(uint32_t, acc[mt][4 * c4 + 2 * h + 1] * unit), false, false);
+              const float g = from_bits16<DT>(to_bits16<DT>(__builtin_bit_cast(float, (uint32_t)sw[0])));
+              const float u = from_bits16<DT>(to_bits16<DT>(__builtin_bit_cast(float, (uint32_t)sw[1])));
+              v[h] = to_bits16<DT>(silu_f32(g) * u);
+            }
+            const uint32_t at = rows[2 * (lane & 1) + ((lane >> 4) & 1)] + (uint32_t)(tile * 128 + wave * 16 + (lane & 14)) * 2u;
+            __builtin_amdgcn_raw_buffer_store_b32(pair_columns(v[0], v[1], odd), rc, (int)at, 0, 0);
+          } else {
+            // four lanes exchange four rows of their columns: a lane then stores four columns of one row
+            uint32_t v[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = __builtin_bit_cast(uint32_t, acc[mt][4 * c4 + c] * unit);
+            const bool two = lane & 2;
+            const uint32_t g0 = from_neighbour(odd ? v[0] : v[1]), g1 = from_neighbour(odd ? v[2] : v[3]);
+            const uint32_t r0 = odd ? g0 : v[0], r1 = odd ? v[1] : g0, r2 = odd ? g1 : v[2], r3 = odd ? v[3] : g1;      // columns of a pair: (r0, r1) of row 0 or 1, (r2, r3) of row 2 or 3
+            const uint32_t h0 = from_pair(two ? r0 : r2), h1 = from_pair(two ? r1 : r3);
+            const uint32_t at = rows[lane & 3] + (uint32_t)(tile * 256 + wave * 32 + (ln & ~3)) * 4u;
+            __builtin_amdgcn_raw_buffer_store_b128(two ? u32x4{h0, h1, r2, r3} : u32x4{r0, r1, h0, h1}, rc, (int)at, 0, 0);
+          }
+        }
+      }
+    } else {
 #pragma unroll
     for (int mt = 0; mt < ML; ++mt) {
 #pragma unroll
@@ -305,7 +348,7 @@ tg_tile(const TwoGroupParams& p, unsigned char* lds, int row0, int e, int tile0,
             // round gate/up to the storage type first: the product is a 16-bit tensor by definition
             const float g = from_bits16<DT>(to_bits16<DT>(__builtin_bit_cast(float, (uint32_t)sw[0])));
             const float u = from_bits16<DT>(to_bits16<DT>(__builtin_bit_cast(float, (uint32_t)sw[1])));
-            const int col = tile * 128 + wave * 16 + (lane & 8) + 2 * (lane & 3) + ((lane >> 2) & 1);
+            const int col = tile * 128 + wave * 16 + (lane & 15);
             if (slot >= 0) reinterpret_cast<uint16_t*>(p.C)[(size_t)slot * half_n + col] = to_bits16<DT>(silu_f32(g) * u);
           }
         } else {
@@ -317,6 +360,8 @@ tg_tile(const TwoGroupParams& p, unsigned char* lds, int row0, int e, int tile0,
           }
         }
       }
+    }
+    __builtin_amdgcn_s_waitcnt(tg_waitcnt(0, false));
     }
 #pragma unroll
     for (int mt = 0; mt < ML; ++mt)
