@@ -521,6 +521,38 @@ static void fp8_medium_plan(int M, int N, int KB, int& bm, int& bn, int& splits)
   }
 }
 
+// Up to 64 rows: does the kernel whose workgroups split the reduction among their waves (launch_fp8_kgroups) take the
+// call?  It has no planes and no second launch, but a workgroup reads the activations of its whole reduction for 16 to 64
+// features, where planes give it a part for 64 or 128.  So by the time both should take, mean of weights in the cache and in memory, in
+// us.  Groups: a start; the kilobytes of the fullest CU and of the mean one; the blocks of one group (and by rows); the
+// workgroups of the fullest CU (and by rows); its blocks by rows squared.  Planes: a start; a second launch; the blocks of a
+// workgroup (and by rows); a million weights; outputs of all planes; activations.  Fitted to 7348 random calls (N 64 ... 51200,
+// K 128 ... 28160), mean error 6 to 8 %.  A tenth has to be gained, and beyond 64 million weights there is little to gain: of those
+// calls 2300 are taken, 1.32x on average, 53 of them slower by more than 3 % with weights in one of the two places (0.83 the worst).
+// us, planes then groups, weights in the cache (in memory): 16 x 3968 x 3328 7.8 / 4.8 (9.1 / 6.6), 64 x 6656 x 2688 11.7 / 7.4 (12.3 / 9.5),
+// 1 x 2048 x 7168 8.4 / 5.8 (9.8 / 7.7), 16 x 12800 x 1024 6.9 / 4.7 (7.9 / 5.9), 1 x 10240 x 5120 12.6 / 10.7 (15.7 / 12.9);
+// left with planes 64 x 10240 x 5120 16.6 / 19.7 (23.6 / 28.5), 16 x 5120 x 25600 25.4 / 32.6 (30.6 / 51).
+static bool fp8_groups_pay(int M, int N, int K, const Fp8Plan& pl, int& bn, int& groups) {
+  const int KB = K / 128;
+  if (M > 64 || (long long)N * K > 64000000LL) return false;
+  static const struct { int bn, groups; double start, most, mean, blocks, blocks_rows, wgs, wgs_rows, rows2; } kFit[] = {
+      {16, 4, 1.9, 0.00224, 0.0115, 0.309, 0, 0.18, 0.238, 0.0423}, {16, 8, 1.63, 0.00178, 0.0112, 0.272, 0, 0.93, 0.288, 0.156},
+      {32, 4, 1.87, 0.0042, 0.0139, 0.375, 0, 0.412, 0.353, 0.0322}, {64, 2, 2.29, 0.007, 0.0159, 0.311, 0.0334, 0.0771, 0.246, 0.00115}};
+  const double rows = pl.bm / 16, nk = (double)N * K / 1e6;
+  const int per = (KB + pl.splits - 1) / pl.splits;
+  const double planes = 2.64 + (pl.splits > 1 ? 2.84 : 0) + per * (0.293 + 0.00617 * rows) + 0.114 * nk + 1.18 * pl.splits * (double)M * N / 1e6 + 4.19 * (double)M * K / 1e6;
+  double best = planes / 1.1;
+  bool pays = false;
+  for (const auto& f : kFit) {
+    if (KB < f.groups || (f.groups == 8 && pl.bm > 16)) continue;      // (eight groups of 32 rows are never the best, of 64 they do not fit the LDS)
+    const int pass = f.bn / 2, a_rows = (pl.bm + pass - 1) / pass * pass;      // rows of a load pass; activation rows held
+    const double kb = ((a_rows + f.bn) * 128 + f.bn * 16) / 1e3, wgs = (double)(N / f.bn) / 256, full = ceil(wgs), b = (KB + f.groups - 1) / f.groups;
+    const double us = f.start + f.most * full * KB * kb + f.mean * wgs * KB * kb + b * (f.blocks + f.blocks_rows * rows) + full * (f.wgs + f.wgs_rows * rows) + f.rows2 * full * KB * rows * rows / 10;
+    if (us < best) { best = us; bn = f.bn; groups = f.groups; pays = true; }
+  }
+  return pays;
+}
+
 // The splits a workspace was sized for before the tiles and splits above were chosen by time: up to 768
 // workgroups of the four-wave tiles.  A caller who brings planes for them, by a size kept from an earlier
 // release, still runs: a shape that needed none unsplit, one that needed fewer than it is now given
@@ -1279,6 +1311,13 @@ int fp8_blockwise_gemm(const uint8_t* A, const float* a_scale, const uint8_t* B,
     p.C = workspace;
   } else {
     p.C = C;
+  }
+  int kbn, kgroups;
+  if (!g_fp8_mt && !g_fp8_nt && !g_fp8_splits && fp8_groups_pay(M, N, K, pl, kbn, kgroups)) {
+    p.C = C; p.k_splits = 1; p.kb_per_split = K / 128;
+    const int err = fp8::launch_fp8_kgroups(p, pl.bm, kbn, kgroups, (hipStream_t)stream);
+    if (err != 0) return hip_fail(err, "FP8 GEMM launch");
+    return MOE_OK;
   }
   int err = fp8::launch_fp8_gemm(p, pl.bm, pl.bn, (hipStream_t)stream);
   if (err == -1) return fail(MOE_UNSUPPORTED_SHAPE, "no FP8 GEMM variant for tile %d x %d", pl.bm, pl.bn);

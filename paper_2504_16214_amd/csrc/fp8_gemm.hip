@@ -124,14 +124,18 @@ __device__ __forceinline__ void store_row(const GemmParams& p, size_t at, int j,
   }
 }
 
-template <int WM, int WN, int MT, int NT, int NS>
-__global__ void __launch_bounds__(64 * WM * WN, (WM * WN == 4 && MT * NT <= 16 ? 2 : 1))
+// KG > 1: KG groups of WM x WN waves share the tile, each with a part of the reduction and its own ring of buffers;
+// their sums meet in LDS (dense, unsplit launches).
+template <int WM, int WN, int MT, int NT, int NS, int KG = 1>
+__global__ void __launch_bounds__(64 * WM * WN * KG, (WM * WN * KG == 4 && MT * NT <= 16 ? 2 : 1))
 fp8_blockwise_gemm_kernel(const GemmParams p) {
   using G = Geom<WM, WN, MT, NT, NS>;
   constexpr int T = G::T, BM = G::BM, BN = G::BN, RPP = G::RPP, AROWS = G::AROWS, CHA = G::CHA, CHB = G::CHB;
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  extern __shared__ __attribute__((aligned(16))) unsigned char all_lds[];
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int kgroup = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / T);
+  unsigned char* const lds = all_lds + kgroup * G::LDS;
+  const int tid = KG == 1 ? (int)threadIdx.x : (int)threadIdx.x - kgroup * T, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave - wm * WN;
   const int ln = lane & 15, lj = lane >> 4;
@@ -157,10 +161,11 @@ fp8_blockwise_gemm_kernel(const GemmParams p) {
   const int row0 = mb * BM;                       // first token of the tile
   const int n0 = nb * BN;                         // first feature of the tile
   const int KB = p.K >> 7;
-  const int kb0 = split * p.kb_per_split;
-  int kb1 = kb0 + p.kb_per_split;
+  const int kb0 = KG == 1 ? split * p.kb_per_split : kgroup * KB / KG;
+  int kb1 = KG == 1 ? kb0 + p.kb_per_split : (kgroup + 1) * KB / KG;
   if (kb1 > KB) kb1 = KB;
   const int nkb = kb1 - kb0;                      // >= 1 by construction of the grid
+  const int trips = KG == 1 ? nkb : (KB + KG - 1) / KG;      // (every group meets every barrier)
 
   // ---- global -> LDS: direct-to-LDS loads (no staging registers, no ds_write) ----
   // LDS row r keeps its chunk c at position c ^ (r & 7): the operand reads below (16 rows, one
@@ -190,7 +195,7 @@ fp8_blockwise_gemm_kernel(const GemmParams p) {
     const int g = row0 + r;
     return g >= p.M ? p.M - 1 : g;
   };
-  const bool f32 = p.k_splits > 1 || p.out_bf16 == 2;      // a partial plane, or the result itself
+  const bool f32 = KG > 1 || p.k_splits > 1 || p.out_bf16 == 2;      // a partial sum, or the result itself
   uint32_t aoff[CHA], boff[CHB];                  // byte offsets from A / B (host checks they fit 32 bits)
 #pragma unroll
   for (int i = 0; i < CHA; ++i) {
@@ -300,13 +305,15 @@ fp8_blockwise_gemm_kernel(const GemmParams p) {
   // One block.  Buffer cur is multiplied; the block NS - 1 ahead is sent to the buffer that was
   // multiplied last (every wave is past the barrier that followed it); before the closing barrier
   // each wave waits until its own part of the NEXT block has landed.
-  auto stage = [&](auto cur_c, int kb_far) __attribute__((always_inline)) {
+  auto stage = [&](auto cur_c, int kb_far, bool live) __attribute__((always_inline)) {
     constexpr int cur = decltype(cur_c)::value;
-    read_w(cur);
-    __builtin_amdgcn_sched_barrier(0);       // the LDS reads above are issued before the far block's loads
-    dma_block((cur + NS - 1) % NS, kb_far);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(cur, integral_constant<int, 0>{}, integral_constant<int, MT>{});
+    if (KG == 1 || live) {
+      read_w(cur);
+      __builtin_amdgcn_sched_barrier(0);       // the LDS reads above are issued before the far block's loads
+      dma_block((cur + NS - 1) % NS, kb_far);
+      __builtin_amdgcn_sched_barrier(0);
+      compute(cur, integral_constant<int, 0>{}, integral_constant<int, MT>{});
+    }
     __builtin_amdgcn_s_waitcnt(kLanded);
     __syncthreads();
   };
@@ -319,11 +326,33 @@ fp8_blockwise_gemm_kernel(const GemmParams p) {
   for (int s = 0; s < NS - 1; ++s) dma_block(s, clampk(s));
   __builtin_amdgcn_s_waitcnt(kLanded);
   __syncthreads();
-  for (int it = 0; it < nkb; it += NS) {
-    stage(integral_constant<int, 0>{}, clampk(it + NS - 1));
-    if constexpr (NS >= 2) { if (it + 1 < nkb) stage(integral_constant<int, 1>{}, clampk(it + NS)); }
-    if constexpr (NS >= 3) { if (it + 2 < nkb) stage(integral_constant<int, 2>{}, clampk(it + NS + 1)); }
-    if constexpr (NS >= 4) { if (it + 3 < nkb) stage(integral_constant<int, 3>{}, clampk(it + NS + 2)); }
+  for (int it = 0; it < trips; it += NS) {
+    stage(integral_constant<int, 0>{}, clampk(it + NS - 1), it < nkb);
+    if constexpr (NS >= 2) { if (it + 1 < trips) stage(integral_constant<int, 1>{}, clampk(it + NS), it + 1 < nkb); }
+    if constexpr (NS >= 3) { if (it + 2 < trips) stage(integral_constant<int, 2>{}, clampk(it + NS + 1), it + 2 < nkb); }
+    if constexpr (NS >= 4) { if (it + 3 < trips) stage(integral_constant<int, 3>{}, clampk(it + NS + 2), it + 3 < nkb); }
+  }
+  if constexpr (KG > 1) {
+    // the groups' sums (operand rows are features in order, see f32), added in the order of the reduction
+    static_assert(BM * BN * 4 <= G::LDS, "a group's sums fit in its buffers");
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<f32x4*>(lds + ((xrow + 16 * mt) * BN + wn * 16 * NT + 16 * nt + 4 * lj) * 4) = acc[mt][nt];
+    __syncthreads();
+    for (int q = threadIdx.x; q < BM * BN / 4; q += T * KG) {
+      const int t = q / (BN / 4), f = 4 * (q % (BN / 4));
+      if (row0 + t >= p.M) continue;
+      f32x4 v = *reinterpret_cast<const f32x4*>(all_lds + 16 * q);
+#pragma unroll
+      for (int g = 1; g < KG; ++g) v += *reinterpret_cast<const f32x4*>(all_lds + g * G::LDS + 16 * q);
+      const size_t at = (size_t)(row0 + t) * p.N + n0 + f;
+      if (p.out_bf16 == 2) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(p.C) + at) = v;
+      else
+        *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(p.C) + at) =
+            p.out_bf16 == 1 ? u32x2{pack2<1>(v[0], v[1]), pack2<1>(v[2], v[3])} : u32x2{pack2<0>(v[0], v[1]), pack2<0>(v[2], v[3])};
+    }
+    return;
   }
 
   // ---- epilogue: the lane's token ----
@@ -684,11 +713,12 @@ fp8_split_reduce_kernel(const f32x4* __restrict__ planes, int k_splits, long lon
   }
 }
 
-template <int WM, int WN, int MT, int NT, int NS>
+template <int WM, int WN, int MT, int NT, int NS, int KG = 1>
 static int launch_one(const GemmParams& p, hipStream_t stream) {
   using G = Geom<WM, WN, MT, NT, NS>;
-  auto kern = fp8_blockwise_gemm_kernel<WM, WN, MT, NT, NS>;
-  if (G::LDS > 64 * 1024) {
+  static_assert(G::LDS * KG <= 160 * 1024, "LDS");
+  auto kern = fp8_blockwise_gemm_kernel<WM, WN, MT, NT, NS, KG>;
+  if (G::LDS * KG > 64 * 1024) {
     // raise the dynamic LDS limit of this kernel once per device
     constexpr int kMaxDev = 64;
     static bool allowed[kMaxDev] = {};
@@ -697,13 +727,13 @@ static int launch_one(const GemmParams& p, hipStream_t stream) {
     if (err != hipSuccess) return (int)err;
     if (dev < 0 || dev >= kMaxDev || !allowed[dev]) {
       err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                G::LDS);
+                                G::LDS * KG);
       if (err != hipSuccess) return (int)err;
       if (dev >= 0 && dev < kMaxDev) allowed[dev] = true;
     }
   }
   const int grid = ((p.M + G::BM - 1) / G::BM) * (p.N / G::BN) * p.k_splits;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(G::T), G::LDS, stream, p);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(G::T * KG), G::LDS * KG, stream, p);
   return (int)hipGetLastError();
 }
 
@@ -742,6 +772,20 @@ int launch_fp8_gemm(const GemmParams& p, int bm, int bn, hipStream_t stream) {
   FP8_TILE(256, 128, 2, 4, 8, 2, 2)
 #undef FP8_TILE
   return -1;
+}
+
+// Tiles whose reduction is split among kg groups of waves (bm in {16, 32, 64}; bn, kg below).  Why: up to 64 rows a
+// launch is a chain of loads, and what the planes of a split cost, a second launch (2.5 us of 8 to 12) and their trip through
+// memory, is most of what can be saved; a CU takes in 70 to 90 kB a microsecond from the caches however its waves
+// are dealt, so few fat workgroups stream as fast as many thin ones.  Deeper rings (three and four buffers) measured the same.
+int launch_fp8_kgroups(const GemmParams& p, int bm, int bn, int kg, hipStream_t stream) {
+  if (p.K / 128 < kg || p.sorted_slot_ids || p.k_splits != 1) return (int)hipErrorInvalidValue;      // (every group has a block of the reduction)
+#define FP8_KG(BMv, BNv, WNv, MTv, KGv) if (bm == BMv && bn == BNv && kg == KGv) return launch_one<1, WNv, MTv, 1, 2, KGv>(p, stream);
+  FP8_KG(16, 16, 1, 1, 4) FP8_KG(16, 16, 1, 1, 8) FP8_KG(16, 32, 2, 1, 4) FP8_KG(16, 64, 4, 1, 2)
+  FP8_KG(32, 16, 1, 2, 4) FP8_KG(32, 32, 2, 2, 4) FP8_KG(32, 64, 4, 2, 2)
+  FP8_KG(64, 16, 1, 4, 4) FP8_KG(64, 32, 2, 4, 4) FP8_KG(64, 64, 4, 4, 2)
+#undef FP8_KG
+  return (int)hipErrorInvalidValue;
 }
 
 // Register-resident loop of the FP8 matrix instruction (the achievable matrix-unit roof).
