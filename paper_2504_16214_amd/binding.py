@@ -186,8 +186,27 @@ def _expect_weights(qweight, scales, zeros, group_size: int, act_dtype, what: st
     _expect(zeros, f"{what} zeros", torch.uint8, (E, rows, G))
 
 
+def _layer_is_right(X, topk_ids, topk_weights, qw1, s1, z1, qw2, s2, z2, out, group_size) -> bool:
+    """Everything that _expect_layer asks for, in one expression (1.5 us instead of 5 of a small call's 17)."""
+    try:
+        dt, (T, K), (E, N2, kw1) = X.dtype, X.shape, qw1.shape
+        N, i32, u8 = N2 // 2, torch.int32, torch.uint8
+        return (dt in _F16 and qw1.dtype is i32 and qw2.dtype is i32 and z1.dtype is u8 and z2.dtype is u8 and
+                s1.dtype is dt and s2.dtype is dt and out.dtype is dt and
+                group_size >= 1 and kw1 * 8 == K and N2 % 2 == 0 and N % 8 == 0 and K % group_size == 0 and N % group_size == 0 and
+                s1.shape == (E, N2, K // group_size) and z1.shape == s1.shape and
+                qw2.shape == (E, K, N // 8) and s2.shape == (E, K, N // group_size) and z2.shape == s2.shape and
+                out.shape == (T, K) and
+                (topk_ids is None or (topk_ids.dtype is i32 and topk_weights.dtype is torch.float32 and topk_ids.dim() == 2 and
+                                      topk_ids.shape[0] == T and topk_weights.shape == topk_ids.shape)))
+    except (AttributeError, TypeError, ValueError):
+        return False
+
+
 def _expect_layer(X, topk_ids, topk_weights, qw1, s1, z1, qw2, s2, z2, out, group_size):
-    _expect(X, "X", _F16)
+    if _layer_is_right(X, topk_ids, topk_weights, qw1, s1, z1, qw2, s2, z2, out, group_size):
+        return
+    _expect(X, "X", _F16)                       # (names what is wrong)
     if X.dim() != 2:
         raise ValueError(f"X: expected [T, K], got shape {tuple(X.shape)}")
     T, K = X.shape
@@ -205,8 +224,8 @@ def _expect_layer(X, topk_ids, topk_weights, qw1, s1, z1, qw2, s2, z2, out, grou
 
 
 def _stream(stream) -> int:
-    if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+    if stream is None:       # (torch.cuda.current_stream() makes an object of it: 2.8 us instead of 0.3)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
