@@ -38,6 +38,8 @@ int launch_combine(const void*, int, int, const float*, const int32_t*, int, voi
 namespace fp8 {
 int launch_fp8_quantize(const void*, long long, int, int, int, uint8_t*, float*, hipStream_t);
 }
+static bool few_tokens_pay(int T, int topk, int E, int K, int N, int dt, int pre);
+
 namespace moe {
 
 // ---- table of compiled GEMM variants ------------------------------------------------------
@@ -443,7 +445,7 @@ static int mid_splits(long long S, int E, int K, int N) {
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 
 struct Workspace {
-  size_t counts, offsets, num_padded, sorted, blocks, act, Y, base, sums, mid_splits, total;
+  size_t counts, offsets, num_padded, sorted, blocks, act, Y, base, sums, mid_splits, few_units, few_end, total;
 };
 // Bytes up to the end of `planes` partial planes at Y; the row sums of act lie there.
 static size_t end_of_planes(const Workspace& w, size_t plane, size_t planes) {
@@ -471,6 +473,11 @@ static Workspace carve(long long T, int K, int N, int E, int topk, int dt) {
   const size_t row_sums = (size_t)S * (N / 128) * 4;
   w.sums = dt == MOE_BF16 ? row_sums : 0;
   if (rows_for_two ? dt == MOE_BF16 : mid) o += round_up(row_sums, 256);
+  // The vector products of a few tokens hold act in twice the bytes, from its place on into that of Y.
+  w.few_units = w.act + round_up(few_act_bytes(S, N), 256);
+  w.few_end = w.few_units + few_unit_bytes(S, N);
+  const bool few = S <= 32 && few_tokens_fit(topk, K, N) && (few_tokens_pay((int)T, topk, E, K, N, dt, 0) || few_tokens_pay((int)T, topk, E, K, N, dt, 1));
+  if (few) o = std::max(o, round_up(w.few_end, 256));
   // Planes of the 64-slot tile's split down product.  A workspace without them runs it in fewer splits, whose sums are
   // rounded in another order, so sizes that the built-in array serves get no more of them than it holds: the two
   // calls then have the same bits.
@@ -863,7 +870,8 @@ static int run_mid(const void* A, const float* sums, int row_div, const int32_t*
 // Calls it takes that are slower than on the tiles by more than 3 %, cached or not / calls it leaves there that would be faster by more:
 // independent tokens 0 / 846 of 8538 (the fits saw 5180 of them), experts weighted as 1 / rank 5 / 116 of 2073, all tokens alike 9 / 72 of
 // 2089 (20 % at most).  Above 128 million weights for all slots there is least to gain (0.8 to 1) and alike tokens cost most (31 of the 2089
-// with twice that).  More than 16 tokens, one expert each, keep the line they had, five rounds of down workgroups; 150 of the calls left
+// with twice that).  The fit is older than the products' present form, 2 to 15 % faster: the line errs to the side of the tiles.
+// More than 16 tokens, one expert each, keep the line they had, five rounds of down workgroups; 150 of the calls left
 // are beyond it.
 // Tiled / vector, weights in memory (in the cache), fp16:
 //   7168x2048, 256 experts, top 8: 1 token 58.7 / 41.9 (57.1 / 41.5);   top 1: 4 tokens 45.8 / 24.6 (45.6 / 24.6), 8 52.9 / 39.0
@@ -945,9 +953,9 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   auto mark = [&](int i) { if (ev) (void)hipEventRecord((hipEvent_t)g_events[i], stream); };
   int err;
   // A few tokens: vector products, unless a tuning hook asks for a tile; whole groups of 128, 16-byte
-  // aligned words and activations, 32-bit offsets into an expert, room for the chunks' floats (4 bytes for 32 columns of act) in Y.
+  // aligned words and activations, 32-bit offsets into an expert, room for act's vectors.
   const bool few = few_tokens_pay(T, topk, E, K, N, (int)dt, pre) && group_size == 128 && few_tokens_fit(topk, K, N) && g_force_block_m == 0 &&
-                   (size_t)S * (N / 32) * 4 <= w.base - w.Y &&
+                   w.few_end <= workspace_bytes &&
                    g_force_mt == 0 && g_force_nt == 0 && g_force_ksplit == 0 && g_scale_path == 0 && g_force_tpw == 0 && g_wide_mode == 0 &&
                    (((uintptr_t)X | (uintptr_t)qw1 | (uintptr_t)qw2) % 16) == 0 && (((uintptr_t)s1 | (uintptr_t)s2) % 2) == 0 &&
                    (long long)N * K < (1LL << 31);
@@ -960,10 +968,10 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
       if (err != 0) return hip_fail(err, "router launch");
     }
     mark(1);
-    err = launch_few_gate_up(X, fused ? &inside : nullptr, topk_ids, qw1, s1, z1, act, (float*)Y, T, topk, E, K, N, (int)dt, pre, stream);
+    err = launch_few_gate_up(X, fused ? &inside : nullptr, topk_ids, qw1, s1, z1, act, (float*)(base + w.few_units), T, topk, E, K, N, (int)dt, pre, stream);
     if (err != 0) return hip_fail(err, "few-token gate/up launch");
     mark(2);
-    err = launch_few_down(act, (const float*)Y, topk_ids, topk_weights, qw2, s2, z2, out, T, topk, E, K, N, (int)dt, pre, stream);
+    err = launch_few_down(act, (const float*)(base + w.few_units), topk_ids, topk_weights, qw2, s2, z2, out, T, topk, E, K, N, (int)dt, pre, stream);
     if (err != 0) return hip_fail(err, "few-token down launch");
     for (int& v : g_last_plan) v = 0;       // no tile
     mark(3);

@@ -1,276 +1,315 @@
-// The layer for a few tokens: vector times int4 matrix, no bucketing and no matrix instructions.
+// The layer for a few tokens: vector times int4 matrix, no bucketing and no tile.
 //
 // With a few slots a launch of the tiled GEMM leaves about one wave on a SIMD, and its chain
-// load -> LDS -> unpack -> matrix instruction of a stage is exposed (one token of a 7168 x 2048 layer with
-// 256 experts, top 8: 118 MB of gate/up weights in 29 us); bucketing and combine are two more launches
+// load -> LDS -> unpack -> matrix instruction of a stage is exposed; bucketing and combine are two more launches
 // of 5 to 6 us that hardly use the chip.  Here every slot is a vector product of its own: gate/up with
 // SiLU-and-multiply is one kernel over (slot, columns), the down projection of all of a token's slots
-// with the weighted combine another over (token, columns).  Measured, us, tiled then vector, with the weights in
-// the last-level cache (in memory), replayed: that token 57.1 / 41.5 (58.7 / 41.9), bf16 59.0 / 39.6 (59.0 / 39.5); one token of
-// 4096 x 14336 with 8 experts, top 2, 54.0 / 42.7 (54.9 / 46.4); 3 of 2048 x 1408 with 64, top 6, groups of 128, 39.3 / 25.7
-// (40.0 / 26.8); 16 tokens of 256 x 512 with 8, top 2, 18.7 / 8.2 (19.3 / 8.9).
+// with the weighted combine another over (token, columns).
 //
-// What bounds it: two launches (9 us); in the gate/up launch the vector unit (77 instructions a wave and
-// 1 KB of weights, 118 MB in 26 us: 4.5 TB/s), matrix instructions on 4 x 4 x 4 blocks in place of the dot products
-// measured 5 to 10 % slower, they issue from the same port, and two waves for each range of columns with half of the
-// reduction each 6 % slower; the down launch (59 MB in 18.6 us) its start, about 5 us, and then the same.  Every workgroup
-// of the down launch needs all act vectors of its token, 36 KB at top 8, for 16 columns: they are brought into their final
-// form once, by the gate/up kernel, and copied to LDS directly, and both panels of a 2048-long reduction are sent before
-// the first is waited for (23.9 us when every workgroup scaled the vectors itself and one panel was in flight).
-// With both that token went from 49.2 to 44.0 (another session), bf16 45.4 to 41.4, 4 tokens of 2048 x 1408 37.7 to 30.0.
+// The products are sums of integers.  A chunk of 32 activations is brought to a power of two below 2^30 (its unit) and
+// rounded to integers of four signed bytes, digits to the base 256; nibbles as bytes need two masks and a shift for eight
+// weights.  The int8 matrix instruction multiplies them: its 16 rows are the 4 digits of the 4 chunks of a quantisation
+// group, each zero outside its own chunk, its 16 columns are 16 weight rows.  A lane ends up with the 4 digits' sums of one
+// chunk and one weight row, exact, puts them together in float32, takes the zero point times the chunk's sum away
+// and multiplies by the group's scale.  What it loses: activations below 2^-30 of the largest of their chunk are rounded to that
+// (the sums of float32 products that it replaces lost 2^-24 of theirs).  A chunk with an infinity or a NaN has no such
+// form: its slot goes the long way round, weight by weight (slow_group).
 //
-// A wave covers 16 weight rows; 8 lanes share a row, lane i takes reduction indices 256 c + 32 i + [0, 32)
-// (16 bytes) of step c: 128 contiguous bytes of a row, or 128-byte runs of the offline repack's blocks
-// (256 bytes of 4 rows measured slower: fewer waves fit and a short reduction leaves lanes idle).  A panel
-// of four steps (1024 indices, eight groups of 128) is loaded while the previous one is multiplied; lane i
-// fetches the scale and zero point of the panel's group i and passes them round.  The order in which a
+// What bounds it: two launches of 5 to 6 us each beside the stream of weights (gate/up of one token of 7168 x 2048, 256 experts, top 8, 118 MB from
+// memory, 25.6 us and 4.6 TB/s; down 16.2; 45.0 -> 40.9 the call.  With products of float16 pairs on the vector unit, 77 instructions a KB of
+// weights where there are 40 now, they took 27.8 and 19.4, and no less with the weights in the cache).
+//
+// A wave covers 16 weight rows, four groups (4 KB) in flight, the next four asked for as each is used.  The order in which a
 // row is summed is the same in both weight layouts.  Weights go through the caches: slots that share
-// an expert find them there, and a layer that fits the last-level cache stays in it (2048 x 1408 called again
-// and again: 17 us against 21 with non-temporal loads, the 256-expert layer the same).
+// an expert find them there, and a layer that fits the last-level cache stays in it.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "few_tokens.hpp"
-#include "gemm_kernel.hpp"   // 16-bit conversions, interleave8, unpack constants
+#include "gemm_kernel.hpp"   // 16-bit conversions
 #include "router_device.hpp"
 
 namespace moe {
 
-// A vector: chunks of 32 values, 64 bytes, four runs of eight (each in the order 0,4,1,5,2,6,3,7); run j of
-// chunk m lies at position j ^ run_key(m), so that the 8 lanes of a row, which read 8 chunks at once, hit different
-// banks.  Behind the values one float32 per chunk.
-//   fp16: the unit of the chunk.  The dot product takes subnormal operands as zero, so a chunk is moved up
-//         by the power of two that brings its largest value to [2^15, 2^16); values below 2^-29 of
-//         that largest one (possible only from 64 on) are lost, which is less than a rounding of its float32
-//         sum unless that value's weight is exactly zero.
-//   bf16: the sum of its values, which takes the bias of the weights (128 + z) out again.
-// The gate/up kernel leaves act in this form in memory (a workgroup produces whole chunks), all values of a token first,
-// then its chunks' floats, so that the down kernel copies it to LDS without touching it.
-__host__ __device__ __forceinline__ int vec_bytes(int k) { return 2 * k; }
-__host__ __device__ __forceinline__ int vec_total(int k) { return vec_bytes(k) + (k >> 5) * 4; }
-__device__ __forceinline__ int run_key(int m) { return (m & 3) ^ ((m >> 1) & 2); }
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void* lptr_t;
 
-// The power of two for a chunk whose largest exponent field is m (0x7c00 mask): exponent to add
-__device__ __forceinline__ uint32_t chunk_up(uint32_t m) {
-  const uint32_t e = m >> 10;                                         // 31: an infinity or NaN, nothing moves
-  return e == 31 ? 0u : 30u - (e > 1 ? e : 1u);
+// A vector of k activations: for every group of 128, [half h of a chunk][chunk][digit][16 bytes], the bytes of a half (16
+// activations, two weight words) in the order the nibbles are unpacked to: 0, 2, 4, 6, 1, 3, 5, 7 of either word.
+// Behind it, for every chunk, its unit and the sum of its activations, floats.  A chunk that holds an infinity or a NaN has the unit
+// NaN, and where digits would lie its 16-bit activations as they are, 16 at the start of each half's 64 bytes.
+__host__ __device__ __forceinline__ int vec_bytes(int k) { return 4 * k; }
+__host__ __device__ __forceinline__ int vec_total(int k) { return vec_bytes(k) + (k >> 5) * 8; }
+__device__ __forceinline__ int half_at(int chunk, int h) { return (chunk >> 2) * 512 + h * 256 + (chunk & 3) * 64; }      // + 16 digit
+
+// Exponent to add so that the chunk's largest value (float32 bits, no sign) comes to [2^29, 2^30); 126 at most: the factor and the unit
+// stay normal numbers.
+__device__ __forceinline__ int chunk_up(uint32_t largest) {
+  const int up = 29 + 127 - (int)(largest >> 23);
+  return up < 126 ? up : 126;
+}
+__device__ __forceinline__ float power_of_two(int e) { return __builtin_bit_cast(float, (uint32_t)(127 + e) << 23); }
+// |v| < 2^30 -> its four signed digits as bytes
+__device__ __forceinline__ uint32_t digits(float v) {
+  const uint32_t i = (uint32_t)(int)__builtin_rintf(v);
+  return (i + 0x00808080u) ^ 0x00808080u;
 }
 
-// c + a.x b.x + a.y b.y in float32
-typedef __bf16 bf16_pair __attribute__((ext_vector_type(2)));
-template <int DT>
-__device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
-  if constexpr (DT == kF16)
-    return __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, a), __builtin_bit_cast(half2_t, b), c, false);
-  else
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16_pair, a), __builtin_bit_cast(bf16_pair, b), c, false);
+// Over 4 lanes (a quad), over 8, over the lanes (n, 0 ... 3) of a row: every lane ends up with the result.
+__device__ __forceinline__ float as_float(uint32_t v) { return __builtin_bit_cast(float, v); }      // (of a vector's element, by value)
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true); }
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+template <int CTRL>
+__device__ __forceinline__ void max_and_sum(uint32_t& m, float& s) {
+  const uint32_t o = dpp<CTRL>(m);
+  m = m > o ? m : o;
+  s += as_float(dpp<CTRL>(bits32(s)));
+}
+__device__ __forceinline__ float row_sum(float v) {
+  auto h = __builtin_amdgcn_permlane32_swap(bits32(v), bits32(v), false, false);
+  v = as_float(h[0]) + as_float(h[1]);
+  h = __builtin_amdgcn_permlane16_swap(bits32(v), bits32(v), false, false);
+  return as_float(h[0]) + as_float(h[1]);
 }
 
-struct DotConst {
-  uint32_t hi, lo;           // see UnpackConsts
-};
-// Eight weights against eight values: fp16 operands are the exact q - z, bf16 operands 128 + q.
-template <int DT>
-__device__ __forceinline__ float word_mac(uint32_t v, const u32x4& x, half2_t zA, half2_t zB, const DotConst& dc, float c) {
-  const uint32_t v8 = v >> 8;
-  uint32_t r[4];
-  if constexpr (DT == kF16) {
-    r[0] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, (v & 0x000F000Fu) | dc.hi) - zA);
-    r[1] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, (v & 0x00F000F0u) | dc.lo) - zB);
-    r[2] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, (v8 & 0x000F000Fu) | dc.hi) - zA);
-    r[3] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, (v8 & 0x00F000F0u) | dc.lo) - zB);
-  } else {
-    r[0] = (v & 0x000F000Fu) | dc.hi;
-    r[1] = ((v >> 4) & 0x000F000Fu) | dc.hi;
-    r[2] = (v8 & 0x000F000Fu) | dc.hi;
-    r[3] = ((v >> 12) & 0x000F000Fu) | dc.hi;
-  }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) c = dot2<DT>(r[t], x[t], c);
-  return c;
-}
-
-template <int NR>
-struct Panel {
-  u32x4 w[NR][4];
-  uint32_t s[NR], z[NR];  // the lane's own group: scale bits, zero point (put together at use: here they would be waited for)
-};
-
-// NR weight rows per lane (row[q] = the lane's q-th row of the expert) against a vector of K values.
-template <int DT, int NR>
-struct RowsDot {
+// 16 weight rows against a vector, R groups in flight.  PRE: operand order; register i is group i, lane (n, j) with its own 16 bytes.
+// Otherwise registers 2 i and 2 i + 1 are rows 0 ... 7 and 8 ... 15 of groups 2 i and 2 i + 1, a lane with 16 bytes of row lane / 8: 128 bytes in
+// a line (64 of each of the 16 rows, the order of the operands, had the caches look up every line twice: 46.7 us for the call
+// above where this takes 41.5); pair() brings them to the lanes that want them.
+template <int DT, int R, int PRE>
+struct Rows16 {
+  __amdgpu_buffer_rsrc_t rs, rz;
   const unsigned char* wbase;
-  const uint16_t* sbase;
-  const uint8_t* zbase;
-  uint32_t woff[NR], goff[NR], wstep, half;
-  int K, G, i;
-  DotConst dc;
-  Panel<NR> ring[2];
+  uint32_t woff, soff, wbytes, half, from;
+  int G;
+  u32x4 w[R];
+  uint32_t own[R / 4], nxt_s[R / 4], nxt_z[R / 4];
 
-  __device__ __forceinline__ void init(const unsigned char* wb, const uint16_t* sb, const uint8_t* zb, const uint32_t (&row)[NR],
-                                       int K_, int pre, int paired) {
-    wbase = wb; sbase = sb; zbase = zb; K = K_; G = K_ >> 7; i = threadIdx.x & 7;
-    dc.hi = vgpr_const(DT == kF16 ? 0x64006400u : 0x43004300u);
-    dc.lo = vgpr_const(0x54005400u);
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-      const uint32_t r = row[q];
-      const uint32_t blk = paired ? ((r >> 5) << 1) | (r & 1) : r >> 4, n = paired ? (r >> 1) & 15 : r & 15;
-      goff[q] = r * (uint32_t)G;
-      woff[q] = pre ? (blk * (uint32_t)G + (uint32_t)(i >> 2)) * 1024u + (16u * (i & 3) + n) * 16u : r * (uint32_t)(K >> 1) + 16u * i;
-    }
-    wstep = pre ? 2048u : 128u;
-    half = K % 256 != 0 && i >= 4 ? (pre ? 1024u : 64u) : 0u;        // from a last half step's missing group to the one before
-  }
-  // What lies past the end reads the last step again, or (a lane past the end in a last half step) its first
-  // half; it is not used.
-  __device__ __forceinline__ void load_w(int pn, Panel<NR>& P) const {
-    const int last = (K - 1) >> 8;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int st = 4 * pn + c < last ? 4 * pn + c : last;
-      const unsigned char* const b = wbase + (size_t)st * wstep;
-      const uint32_t back = st == last ? half : 0u;
-#pragma unroll
-      for (int q = 0; q < NR; ++q) P.w[q][c] = *reinterpret_cast<const u32x4*>(b + (uint32_t)(woff[q] - back));
-    }
-  }
-  __device__ __forceinline__ void load_sz(int pn, uint32_t (&s)[NR], uint32_t (&z)[NR]) const {
-    const int g = 8 * pn + i < G ? 8 * pn + i : G - 1;
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-      s[q] = sbase[goff[q] + g];
-      z[q] = zbase[goff[q] + g];
-    }
-  }
-  __device__ __forceinline__ void panel(int pn, const Panel<NR>& cur, const unsigned char* xl, const float* xs, float (&acc)[NR]) const {
-    uint32_t own[NR];
-#pragma unroll
-    for (int q = 0; q < NR; ++q) own[q] = cur.s[q] | ((cur.z[q] & 15) << 16);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      int m = 8 * (4 * pn + c) + i;               // the lane's chunk
-      if (256 * (4 * pn + c) >= K) break;         // (uniform)
-      const bool in = 32 * m < K;
-      if (!in) m = 0;
-      u32x4 x[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) x[j] = *reinterpret_cast<const u32x4*>(xl + 64 * m + 16 * (j ^ run_key(m)));
-      const float xc = xs[m];
-#pragma unroll
-      for (int q = 0; q < NR; ++q) {
-        const uint32_t sz = (uint32_t)__shfl((int)own[q], (int)(threadIdx.x & 56) + 2 * c + (i >> 2), 64), z = sz >> 16;
-        const half2_t zA = __builtin_bit_cast(half2_t, 0x64006400u + z * 0x00010001u), zB = __builtin_bit_cast(half2_t, 0x54005400u + z * 0x00100010u);
-        float d = 0.f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) d = word_mac<DT>(cur.w[q][c][j], x[j], zA, zB, dc, d);
-        const float p = DT == kF16 ? d * xc : __builtin_fmaf(-(128.f + (float)z), xc, d);
-        const float a = __builtin_fmaf(from_bits16<DT>((uint16_t)sz), p, acc[q]);
-        acc[q] = in ? a : acc[q];
-      }
-    }
-  }
-  // Panels [p0, p1).  One or two are sent at the start and worked off.  More: one is sent while the one before it is
-  // multiplied (two panels in flight, with their code unrolled or the last one read again, are no faster there; a loop over the
-  // one or two panels costs 7 us of 19).
-  __device__ __forceinline__ void start(int p0, int p1) {
-    load_sz(p0, ring[0].s, ring[0].z);
-    load_sz(p0 + 1, ring[1].s, ring[1].z);
-    load_w(p0, ring[0]);
-    if (p1 - p0 == 2) load_w(p0 + 1, ring[1]);
-  }
-  __device__ __forceinline__ void run(const unsigned char* xl, const float* xs, int p0, int p1, float (&acc)[NR]) {
-    if (p1 - p0 > 2) {
-      for (int pn = p0; pn < p1; ++pn) {
-        const int nx = pn + 1 < p1 ? pn + 1 : pn;
-        load_sz(nx, ring[1].s, ring[1].z);
-        load_w(nx, ring[1]);
-        panel(pn, ring[0], xl, xs, acc);
-        ring[0] = ring[1];
-      }
+  // rows: those of one matrix (of one expert); row0: the first of 16, apart: rows from the eighth to the ninth
+  __device__ __forceinline__ void init(const unsigned char* wb, const uint16_t* sb, const uint8_t* zb, uint32_t rows, uint32_t row0, uint32_t apart, int K, int paired) {
+    const uint32_t lane = threadIdx.x & 63, j = lane >> 4, row = row0 + (lane & 7) + (lane & 8 ? apart : 0);
+    G = K >> 7;
+    wbytes = rows * (uint32_t)(K >> 1);
+    if constexpr (PRE) {
+      const uint32_t blk = paired ? ((row >> 5) << 1) | (row & 1) : row >> 4, n = paired ? (row >> 1) & 15 : row & 15;
+      woff = blk * (uint32_t)G * 1024u + (16u * j + n) * 16u;
     } else {
-      panel(p0, ring[0], xl, xs, acc);
-      if (p1 - p0 == 2) panel(p0 + 1, ring[1], xl, xs, acc);
+      woff = (row0 + (lane >> 3)) * (uint32_t)(K >> 1) + 16u * (lane & 7);
+      half = apart * (uint32_t)(K >> 1);
+      from = 4u * (8u * (lane & 7) + 4u * ((lane >> 3) & 1) + j);
     }
+    soff = row * (uint32_t)G + j;
+    wbase = wb;
+    rs = __builtin_amdgcn_make_buffer_rsrc((void*)sb, 0, (int)(rows * (uint32_t)G * 2u), 0x00020000);
+    rz = __builtin_amdgcn_make_buffer_rsrc((void*)zb, 0, (int)(rows * (uint32_t)G), 0x00020000);
+  }
+  // Register i, of the pair of groups (g, g + 1) (g even).  A group past the end fetches nothing (a buffer without bytes; the second of an odd
+  // row's last pair: an offset past the buffer), and counts as a load all the same.
+  __device__ __forceinline__ void load_w(int i, int g, int g1) {
+    const bool some = (PRE ? g + (i & 1) : g) < g1;
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)wbase, 0, some ? (int)wbytes : 0, 0x00020000);
+    if constexpr (PRE) w[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)woff, (g + (i & 1)) * 1024, 0);
+    else w[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(g + 1 < G || !(threadIdx.x & 4) ? woff : 0xFFFFFFF0u), g * 64 + (i & 1 ? (int)half : 0), 0);
+  }
+  __device__ __forceinline__ void pair(u32x4& a, u32x4& b) const {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const uint32_t lo = a[t], hi = b[t];
+      const int x = __builtin_amdgcn_ds_bpermute((int)from, (int)lo), y = __builtin_amdgcn_ds_bpermute((int)from, (int)hi);
+      // (row lane & 7, group lane & 8) of either half -> of either group (row lane & 15)
+      a[t] = (uint32_t)__builtin_amdgcn_update_dpp(x, y, 0x128, 0xf, 0xc, false);
+      b[t] = (uint32_t)__builtin_amdgcn_update_dpp(y, x, 0x128, 0xf, 0x3, false);
+    }
+  }
+  // scales and zero points of groups [g, g + R): lane group j those of g + j, g + 4 + j ...  (Past a row's end those of
+  // the next, past the last row's nothing: not used.)
+  __device__ __forceinline__ void load_sz(int g) {
+#pragma unroll
+    for (int q = 0; q < R / 4; ++q) {
+      const uint32_t at = soff + (uint32_t)(g + 4 * q);
+      nxt_s[q] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)(2u * at), 0, 0);
+      nxt_z[q] = (uint32_t)(uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rz, (int)at, 0, 0);
+    }
+  }
+  __device__ __forceinline__ void start(int g0, int g1) {
+    load_sz(g0);
+#pragma unroll
+    for (int i = 0; i < R; ++i) load_w(i, g0 + (i & ~1), g1);
+  }
+  // The rows' sums over groups [g0, g1), g0 even, against the vector at xl: lane (n, j) has row n's over the chunks j.
+  __device__ __forceinline__ float run(const unsigned char* xl, const float* units, const unsigned char* zeros, int g0, int g1) {
+    const int lane = threadIdx.x & 63, n = lane & 15, j = lane >> 4;
+    // lanes of the digits of chunk j read them, the others zeros
+    const bool mine = (n >> 2) == j;
+    const unsigned char* xp = mine ? xl + g0 * 512 + j * 64 + (n & 3) * 16 : zeros;
+    const int xstep = mine ? 512 * R : 0;
+    const float* up = units + (size_t)(g0 * 4 + j) * 2;
+    float acc = 0.f;
+    auto group = [&](int i, const u32x4& v) __attribute__((always_inline)) {
+      const u32x4 x0 = *reinterpret_cast<const u32x4*>(xp + 512 * i), x1 = *reinterpret_cast<const u32x4*>(xp + 512 * i + 256);
+      const floatx2_t u = *reinterpret_cast<const floatx2_t*>(up + 8 * i);
+      const uint32_t sz = (uint32_t)__builtin_amdgcn_ds_bpermute((n + 16 * (i & 3)) * 4, (int)own[i >> 2]);
+      const uint32_t m = 0x0F0F0F0Fu;
+      i32x4 d = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, x0),
+                                                      i32x4{(int)(v.x & m), (int)((v.x >> 4) & m), (int)(v.y & m), (int)((v.y >> 4) & m)}, i32x4{0, 0, 0, 0}, 0, 0, 0);
+      d = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, x1),
+                                                i32x4{(int)(v.z & m), (int)((v.z >> 4) & m), (int)(v.w & m), (int)((v.w >> 4) & m)}, d, 0, 0, 0);
+      // a digit's sum is below 128 * 15 * 32: two of them are exact in float32
+      const float lo = (float)(d[0] + (d[1] << 8)), hi = (float)(d[2] + (d[3] << 8));
+      const float t = __builtin_fmaf(__builtin_fmaf(hi, 65536.f, lo), u[0], -((float)(sz >> 16) * u[1]));
+      acc = __builtin_fmaf(from_bits16<DT>((uint16_t)sz), t, acc);
+    };
+    for (int p = g0; p < g1; p += R) {
+#pragma unroll
+      for (int q = 0; q < R / 4; ++q) own[q] = nxt_s[q] | ((nxt_z[q] & 15) << 16);
+      load_sz(p + R);
+#pragma unroll
+      for (int i = 0; i < R; i += 2) {
+        if (p + i >= g1) return acc;
+        if constexpr (PRE) {
+          group(i, w[i]);
+          load_w(i, p + i + R, g1);
+          if (p + i + 1 < g1) group(i + 1, w[i + 1]);
+          load_w(i + 1, p + i + R, g1);
+        } else {
+          u32x4 a = w[i], b = w[i + 1];
+          pair(a, b);
+          load_w(i, p + i + R, g1);
+          load_w(i + 1, p + i + R, g1);
+          group(i, a);
+          if (p + i + 1 < g1) group(i + 1, b);
+        }
+      }
+      xp += xstep;
+      up += 8 * R;
+    }
+    return acc;
+  }
+  // The same where the vector holds an infinity or a NaN: weight by weight, x(k) the activations.
+  template <typename F>
+  __device__ __forceinline__ float slow(F x, int g0, int g1) {
+    const int j = (threadIdx.x >> 4) & 3;
+    float acc = 0.f;
+#pragma unroll 1
+    for (int g = g0; g < g1; ++g) {
+      const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)wbase, 0, (int)wbytes, 0x00020000);
+      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(PRE ? woff : (soff - j) * 64u + 16u * j), g * (PRE ? 1024 : 64), 0);
+      const int at = (int)(soff + (uint32_t)g) - j;
+      const float s = from_bits16<DT>((uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, 2 * at, 0, 0));
+      const int z = (int)((uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rz, at, 0, 0) & 15);
+      float t = 0.f;
+#pragma unroll 1
+      for (int k = 0; k < 32; ++k) {
+        const uint32_t word = k < 8 ? v.x : k < 16 ? v.y : k < 24 ? v.z : v.w;
+        t = __builtin_fmaf((float)((int)((word >> (4 * (k & 7))) & 15) - z), x(4 * g + j, k), t);
+      }
+      acc = __builtin_fmaf(s, t, acc);
+    }
+    return acc;
   }
 };
 
-// 256 threads bring the K activations of a token into an LDS vector; `between` runs after the first loads
-// are on their way.
-template <int DT, typename F>
-__device__ __forceinline__ void stage_row(const uint16_t* src, int K, unsigned char* xl, F between) {
-  const int vb = vec_bytes(K);
-  u32x4 v[4];
+constexpr int kGateThreads = 512;
+struct FirstValues { u32x4 v[2]; };
+__device__ __forceinline__ FirstValues first_values(const uint16_t* src, int K) {
+  FirstValues f;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const int k = (c * 256 + (int)threadIdx.x) * 8;
-    v[c] = *reinterpret_cast<const u32x4*>(src + (k < K ? k : 0));
+  for (int c = 0; c < 2; ++c) {
+    const int k = (c * kGateThreads + (int)threadIdx.x) * 8;
+    f.v[c] = *reinterpret_cast<const u32x4*>(src + (k < K ? k : 0));
   }
-  between();
-  auto put = [&](int k, u32x4 x) __attribute__((always_inline)) {
+  return f;
+}
+// kGateThreads threads bring the K activations of a token into an LDS vector, the first of them loaded already.
+// Whether one of the thread's chunks holds an infinity or a NaN (it is garbage then).
+template <int DT>
+__device__ __forceinline__ bool stage_row(const uint16_t* src, int K, unsigned char* xl, FirstValues& first) {
+  bool odd = false;
+  float* const units = reinterpret_cast<float*>(xl + vec_bytes(K));
+  constexpr int step = kGateThreads * 8;
+  u32x4 (&v)[2] = first.v;
+  auto put = [&](int k, const u32x4& x) __attribute__((always_inline)) {
+    float f[8];
+    uint32_t m = 0;
     float s = 0.f;
-    if constexpr (DT == kBF16) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) s += from_bits16<DT>((uint16_t)x[t]) + from_bits16<DT>((uint16_t)(x[t] >> 16));
-      s += __shfl_xor(s, 1, 64);
-      s += __shfl_xor(s, 2, 64);
-    } else {
-      uint32_t m = 0;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const uint32_t a = x[t] & 0x7c00u, b = (x[t] >> 16) & 0x7c00u;
-        m = m > a ? m : a;
-        m = m > b ? m : b;
-      }
-      uint32_t o = (uint32_t)__shfl_xor((int)m, 1, 64);
-      m = m > o ? m : o;
-      o = (uint32_t)__shfl_xor((int)m, 2, 64);
-      m = m > o ? m : o;
-      const uint32_t up = chunk_up(m);
-      const float f = __builtin_bit_cast(float, (127u + up) << 23);
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        x[t] = (uint32_t)to_bits16<DT>(from_bits16<DT>((uint16_t)x[t]) * f) |
-               ((uint32_t)to_bits16<DT>(from_bits16<DT>((uint16_t)(x[t] >> 16)) * f) << 16);
-      s = __builtin_bit_cast(float, (127u - up) << 23);
+    for (int t = 0; t < 8; ++t) {
+      f[t] = from_bits16<DT>((uint16_t)(x[t >> 1] >> (16 * (t & 1))));
+      const uint32_t a = bits32(f[t]) & 0x7fffffffu;
+      m = m > a ? m : a;
+      s += f[t];
     }
+    max_and_sum<kXor1>(m, s);
+    max_and_sum<kXor2>(m, s);
     if (k >= K) return;
-    const int m = k >> 5;
-    *reinterpret_cast<u32x4*>(xl + 64 * m + 16 * (((k >> 3) & 3) ^ run_key(m))) = interleave8(x);
-    if ((k & 31) == 0) *reinterpret_cast<float*>(xl + vb + m * 4) = s;
-  };
+    odd |= m >= 0x7f800000u;
+    const int up = chunk_up(m), chunk = k >> 5, word = (k >> 3) & 3;
+    const float factor = power_of_two(up);
+    uint32_t y[8];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) put((c * 256 + (int)threadIdx.x) * 8, v[c]);
-  for (int k0 = 4 * 256 * 8; k0 < K; k0 += 256 * 8) {
+    for (int t = 0; t < 8; ++t) y[t] = digits(f[t] * factor);
+    // digit planes: bytes of values 0, 2, 4, 6 and of 1, 3, 5, 7
+    unsigned char* const at = xl + half_at(chunk, word >> 1) + 8 * (word & 1);
+    uint32_t plane[4][2];
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      const uint32_t a = __builtin_amdgcn_perm(y[2 + o], y[o], 0x05010400u), b = __builtin_amdgcn_perm(y[2 + o], y[o], 0x07030602u);
+      const uint32_t c = __builtin_amdgcn_perm(y[6 + o], y[4 + o], 0x05010400u), d = __builtin_amdgcn_perm(y[6 + o], y[4 + o], 0x07030602u);
+      plane[0][o] = __builtin_amdgcn_perm(c, a, 0x05040100u);
+      plane[1][o] = __builtin_amdgcn_perm(c, a, 0x07060302u);
+      plane[2][o] = __builtin_amdgcn_perm(d, b, 0x05040100u);
+      plane[3][o] = __builtin_amdgcn_perm(d, b, 0x07060302u);
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) *reinterpret_cast<u32x2*>(at + 16 * d) = u32x2{plane[d][0], plane[d][1]};
+    if (word == 0) *reinterpret_cast<floatx2_t*>(units + 2 * chunk) = floatx2_t{power_of_two(-up), s};
+  };
+  // (one copy of the code for all four: what a short kernel runs once comes from memory)
+#pragma unroll 1
+  for (int c = 0; c < 2 && c * step < K; ++c) {
+    put(c * step + (int)threadIdx.x * 8, v[0]);
+    v[0] = v[1];
+  }
+#pragma unroll 1
+  for (int k0 = 2 * step; k0 < K; k0 += step) {
     const int k = k0 + (int)threadIdx.x * 8;
     put(k, *reinterpret_cast<const u32x4*>(src + (k < K ? k : 0)));
   }
+  return odd;
 }
 
-// sum over the 8 lanes of a row (every lane ends up with it)
-__device__ __forceinline__ float row_sum(float v) {
-  v += __shfl_xor(v, 1, 64);
-  v += __shfl_xor(v, 2, 64);
-  v += __shfl_xor(v, 4, 64);
-  return v;
+// Zeros, as long as R groups, that the lanes of the other chunks read.
+__host__ __device__ constexpr int zero_bytes(int R) { return 512 * R; }
+template <int R>
+__device__ __forceinline__ void clear(unsigned char* zeros, int threads) {
+  for (int o = 16 * (int)threadIdx.x; o < zero_bytes(R); o += 16 * threads) *reinterpret_cast<u32x4*>(zeros + o) = u32x4{0, 0, 0, 0};
 }
 
-// act[slot, :] = round(silu(gate) * up) with gate / up rounded first, as vectors for the down kernel: the values of
-// slot s at vals + s N, the floats of its chunks at units + s N / 32.
-// grid (N / 32, slots), 4 waves, 8 columns each: a chunk.  LDS: the token's K activations, a word for each wave, ROUTE:
-// the token's ids and weights.
+// act[slot, :] = round(silu(gate) * up) with gate / up rounded first, as vectors for the down kernel: digits of slot s at
+// vals + 4 s N, its chunks' floats at units + 2 s N / 32.
+// KP 1: grid (N / 64, slots), 8 waves, 8 columns each; KP 2: (N / 32, slots), four times 8 columns, two halves of the reduction.  LDS: the
+// token's K activations, zeros, a flag for every wave, the columns' sums, ROUTE: the token's ids and weights.
 // ROUTE: the ids come from the token's logits; every wave works them out for itself (at most 64 experts: four keys a lane, half
 // a microsecond against a launch of 3.5 us), and the first workgroup of a token stores them for the down kernel.
-template <int DT, int ROUTE>
-__global__ void __launch_bounds__(256, 4)
+template <int DT, int ROUTE, int R, int PRE, int KP>
+__global__ void __launch_bounds__(kGateThreads, 4)
 few_gate_up_kernel(const uint16_t* __restrict__ X, FewRoute route, const int32_t* __restrict__ ids, const unsigned char* __restrict__ qw,
-                   const uint16_t* __restrict__ sc, const uint8_t* __restrict__ zp, uint16_t* __restrict__ vals,
-                   float* __restrict__ units, int topk, int E, int K, int N, int pre) {
+                   const uint16_t* __restrict__ sc, const uint8_t* __restrict__ zp, unsigned char* __restrict__ vals,
+                   float* __restrict__ units, int topk, int E, int K, int N) {
   extern __shared__ __align__(16) unsigned char xl[];
-  const int slot = blockIdx.y, lane = threadIdx.x & 63, r = lane >> 3;
+  unsigned char* const zeros = xl + vec_total(K);
+  uint32_t* const bad = reinterpret_cast<uint32_t*>(zeros + zero_bytes(R));
+  constexpr int COLS = 64 / KP;
+  float* const col = reinterpret_cast<float*>(bad + 8);
+  const int slot = blockIdx.y, lane = threadIdx.x & 63;
+  const uint16_t* const x = X + (size_t)(slot / topk) * K;
+  FirstValues first = first_values(x, K);
   int e;
   if constexpr (ROUTE) {
-    int32_t* const rid = reinterpret_cast<int32_t*>(xl + vec_total(K) + 16);
+    int32_t* const rid = reinterpret_cast<int32_t*>(col + 128);
     float* const rw = reinterpret_cast<float*>(rid + kRouter16MaxTopk);
     const int t = slot / topk, j = slot - t * topk;
     route_token_row16<kFewRouteE / 16>(route.logits + (size_t)t * E, route.bias, E, topk, lane, rid, rw);      // (every wave writes the same)
@@ -283,102 +322,131 @@ few_gate_up_kernel(const uint16_t* __restrict__ X, FewRoute route, const int32_t
     e = ids[slot];
   }
   if (e < 0 || e >= E) return;                     // (uniform over the workgroup)
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), chunk = blockIdx.x;
-  const int c = 32 * chunk + 8 * wave + r;         // (N is a multiple of 32)
-  const uint32_t row[2] = {(uint32_t)c, (uint32_t)(N + c)};
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), part = KP == 2 ? wave >> 2 : 0, cw = 8 * (KP == 2 ? wave & 3 : wave);
   const size_t eb = (size_t)e * 2 * N;
-  const int np = (K + 1023) >> 10;
-  RowsDot<DT, 2> rd;
-  rd.init(qw + eb * (size_t)(K >> 1), sc + eb * (K >> 7), zp + eb * (K >> 7), row, K, pre, 0);
-  stage_row<DT>(X + (size_t)(slot / topk) * K, K, xl, [&]() __attribute__((always_inline)) { rd.start(0, np); });
+  const int G = K >> 7, mid = KP == 2 ? 2 * ((G + 2) >> 2) : G, g0 = part ? mid : 0, g1 = part ? G : mid;
+  Rows16<DT, R, PRE> rd;       // eight gate rows, the eight up rows of the same columns (N is a multiple of 32)
+  rd.init(qw + eb * (size_t)(K >> 1), sc + eb * G, zp + eb * G, 2u * (uint32_t)N, (uint32_t)(COLS * (int)blockIdx.x + cw), (uint32_t)N, K, 0);
+  rd.start(g0, g1);
+  clear<R>(zeros, kGateThreads);
+  const bool odd = stage_row<DT>(x, K, xl, first);
+  if (lane == 0) bad[wave] = 0u;
+  if (odd) bad[wave] = 1u;
   __syncthreads();
-  float acc[2] = {0.f, 0.f};
-  rd.run(xl, reinterpret_cast<const float*>(xl + vec_bytes(K)), 0, np, acc);
-  const float g = from_bits16<DT>(to_bits16<DT>(row_sum(acc[0])));
-  const float u = from_bits16<DT>(to_bits16<DT>(row_sum(acc[1])));
-  const uint16_t a = to_bits16<DT>(silu_f32(g) * u);      // (all 8 lanes of the row hold it)
-  // the chunk's float: over the wave's 8 columns, then over the four waves
-  uint32_t* const red = reinterpret_cast<uint32_t*>(xl + vec_total(K));
-  uint32_t m = a & 0x7c00u;
-  float sum = from_bits16<DT>(a);
+  const u32x4 b0 = *reinterpret_cast<const u32x4*>(bad), b1 = *reinterpret_cast<const u32x4*>(bad + 4);
+  float r;
+  if (__builtin_expect((b0[0] | b0[1] | b0[2] | b0[3] | b1[0] | b1[1] | b1[2] | b1[3]) != 0u, 0))
+    r = rd.slow([&](int ch, int k) { return from_bits16<DT>(x[32 * ch + k]); }, g0, g1);
+  else r = rd.run(xl, reinterpret_cast<const float*>(xl + vec_bytes(K)), zeros, g0, g1);
+  // [part][gate, up][column]
+  const float y = row_sum(r);
+  if (lane < 16) col[(2 * part + (lane >> 3)) * COLS + cw + (lane & 7)] = y;
+  __syncthreads();
+  if ((int)threadIdx.x >= COLS) return;
+  float gate = col[threadIdx.x], upper = col[COLS + threadIdx.x];
+  if constexpr (KP == 2) {
+    gate += col[2 * COLS + threadIdx.x];
+    upper += col[3 * COLS + threadIdx.x];
+  }
+  const float a = from_bits16<DT>(to_bits16<DT>(silu_f32(from_bits16<DT>(to_bits16<DT>(gate))) * from_bits16<DT>(to_bits16<DT>(upper))));
+  uint32_t m = bits32(a) & 0x7fffffffu;
+  float sum = a;
+  max_and_sum<kXor1>(m, sum);
+  max_and_sum<kXor2>(m, sum);
+  max_and_sum<kHalfMirror>(m, sum);
+  max_and_sum<kMirror>(m, sum);
+  const uint32_t o = (uint32_t)__shfl_xor((int)m, 16, 64);
+  m = m > o ? m : o;
+  sum += __shfl_xor(sum, 16, 64);
+  const bool finite = m < 0x7f800000u;
+  const int up = chunk_up(m), k = threadIdx.x & 31, chunk = (int)(blockIdx.x * COLS + threadIdx.x) >> 5;
+  unsigned char* const at = vals + (size_t)slot * vec_bytes(N) + half_at(chunk, k >> 4);
+  if (finite) {
+    const uint32_t y = digits(a * power_of_two(up));
+    const int pos = (k & 8) + 4 * (k & 1) + ((k >> 1) & 3);
 #pragma unroll
-  for (int d = 8; d <= 32; d <<= 1) {
-    const uint32_t o = (uint32_t)__shfl_xor((int)m, d, 64);
-    m = m > o ? m : o;
-    sum += __shfl_xor(sum, d, 64);
-  }
-  if (lane == 0) red[wave] = DT == kF16 ? m : __builtin_bit_cast(uint32_t, sum);
-  __syncthreads();
-  const u32x4 all = *reinterpret_cast<const u32x4*>(red);
-  uint16_t v = a;
-  float unit;
-  if constexpr (DT == kF16) {
-    const uint32_t m0 = all[0] > all[1] ? all[0] : all[1], m1 = all[2] > all[3] ? all[2] : all[3];
-    const uint32_t up = chunk_up(m0 > m1 ? m0 : m1);
-    v = to_bits16<DT>(from_bits16<DT>(a) * __builtin_bit_cast(float, (127u + up) << 23));
-    unit = __builtin_bit_cast(float, (127u - up) << 23);
+    for (int d = 0; d < 4; ++d) at[16 * d + pos] = (unsigned char)(y >> (8 * d));
   } else {
-    const floatx4_t f = __builtin_bit_cast(floatx4_t, all);
-    unit = (f[0] + f[1]) + (f[2] + f[3]);
+    reinterpret_cast<uint16_t*>(at)[k & 15] = to_bits16<DT>(a);
   }
-  if ((lane & 7) == 0) vals[(size_t)slot * N + 32 * chunk + 8 * (wave ^ run_key(chunk)) + 2 * (r & 3) + (r >> 2)] = v;
-  if (threadIdx.x == 0) units[(size_t)slot * (N >> 5) + chunk] = unit;
+  if (k == 0)
+    *reinterpret_cast<floatx2_t*>(units + ((size_t)slot * (N >> 5) + chunk) * 2) = floatx2_t{finite ? power_of_two(-up) : __builtin_nanf(""), sum};
 }
 
 // out[t, :] = sum over j of w[t, j] * (act[slot] . W2[e]), the products unrounded.  grid (K / 16, T), up to 8 waves,
-// 16 columns; a wave takes (slot, part of the reduction) pairs.  LDS: the token's act values, their chunks'
-// floats, the pairs' results.
-template <int DT>
+// 16 columns; a wave takes (slot, part of the reduction) pairs.  LDS: the token's act vectors, their chunks' floats, zeros, the pairs' results.
+template <int DT, int R, int PRE>
 __global__ void __launch_bounds__(512, 4)
-few_down_kernel(const uint16_t* vals, const float* units, const int32_t* __restrict__ ids,
+few_down_kernel(const unsigned char* vals, const float* units, const int32_t* __restrict__ ids,
                 const float* wts, const unsigned char* qw, const uint16_t* sc,
-                const uint8_t* zp, uint16_t* out, int topk, int E, int K, int N, int parts, int pre) {
+                const uint8_t* zp, uint16_t* out, int topk, int E, int K, int N, int parts) {
   extern __shared__ __align__(16) unsigned char xl[];
-  const int vbytes = topk * vec_bytes(N), ubytes = topk * (N >> 5) * 4;
-  float* const ys = reinterpret_cast<float*>(xl + vbytes + ubytes);          // [topk * parts][16]
+  const int vbytes = topk * vec_bytes(N), ubytes = topk * (N >> 5) * 8;
+  unsigned char* const zeros = xl + vbytes + ubytes;
+  float* const ys = reinterpret_cast<float*>(zeros + zero_bytes(R));          // [topk * parts][16]
   const int t = blockIdx.y, lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int np = (N + 1023) >> 10;
-  const int c0 = blockIdx.x * 16, r = lane >> 3;
-  const uint32_t row[2] = {(uint32_t)(c0 + 2 * r), (uint32_t)(c0 + 2 * r + 1)};
+  const int G = N >> 7;
+  const int c0 = blockIdx.x * 16;
   const int nw = (int)blockDim.x >> 6;              // at most eight waves, and as many pairs
   const int e0 = ids[t * topk + wave / parts];
-  // act straight to LDS (both arrays are whole runs of 16 bytes).  (The weights are no __restrict__ pointers: their first
-  // loads would be moved behind the barrier.)
-  typedef __attribute__((address_space(3))) void* lptr_t;
-  const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)(vals + (size_t)t * topk * N), 0, vbytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t ru = __builtin_amdgcn_make_buffer_rsrc((void*)(units + (size_t)t * topk * (N >> 5)), 0, ubytes, 0x00020000);
+  // act straight to LDS (both arrays are whole runs of 16 bytes)
+  const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)(vals + (size_t)t * vbytes), 0, vbytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t ru = __builtin_amdgcn_make_buffer_rsrc((void*)((const unsigned char*)units + (size_t)t * ubytes), 0, ubytes, 0x00020000);
   for (int o = wave * 1024; o < vbytes; o += nw * 1024)
     if (o + lane * 16 < vbytes) __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lptr_t)(xl + o), 16, lane * 16, o, 0, 0);
   for (int o = wave * 1024; o < ubytes; o += nw * 1024)
     if (o + lane * 16 < ubytes) __builtin_amdgcn_raw_ptr_buffer_load_lds(ru, (lptr_t)(xl + vbytes + o), 16, lane * 16, o, 0, 0);
+  clear<R>(zeros, 64 * nw);
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("" ::: "memory");
-  RowsDot<DT, 2> rd;
-  // The pair's first panels, e its expert; false: none, nothing to do.  (The loads are sent all the same, for expert 0: with a
-  // branch around them the compiler waits where its paths meet, 23 us instead of 19.5 for one 7168 x 2048 token.)
+  Rows16<DT, R, PRE> rd;
+  auto range = [&](int part, int& g0, int& g1) __attribute__((always_inline)) {
+    const int pairs = (G + 1) >> 1;
+    g0 = 2 * (part * pairs / parts);
+    g1 = part + 1 == parts ? G : 2 * ((part + 1) * pairs / parts);
+  };
+  // The pair's first groups, e its expert; false: none, nothing to do.  (The loads are sent all the same, for expert 0: with a
+  // branch around them the compiler waits where its paths meet.)
   auto start = [&](int u, int e) __attribute__((always_inline)) {
-    const int j = u / parts, part = u - j * parts;
-    const int p1 = (part + 1) * np / parts, p0 = part * np / parts;
+    int g0, g1;
+    range(u % parts, g0, g1);
     const bool some = e >= 0 && e < E;
     const size_t eb = (size_t)(some ? e : 0) * K;
-    rd.init(qw + eb * (size_t)(N >> 1), sc + eb * (N >> 7), zp + eb * (N >> 7), row, N, pre, 1);
-    rd.start(p0, p1);
+    rd.init(qw + eb * (size_t)(N >> 1), sc + eb * G, zp + eb * G, (uint32_t)K, (uint32_t)c0, 8u, N, 1);
+    rd.start(g0, g1);
     return some;
   };
   bool some = start(wave, e0);
   __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): act has landed (and the first panels, which are next)
+  __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): act has landed (and the first groups, which are next)
   asm volatile("" ::: "memory");
   __syncthreads();
   for (int u = wave; u < topk * parts; u += nw) {
-    const int j = u / parts, part = u - j * parts;
+    const int j = u / parts;
+    int g0, g1;
+    range(u - j * parts, g0, g1);
     if (u != wave) some = start(u, ids[t * topk + j]);
-    float acc[2] = {0.f, 0.f};
-    if (some)
-      rd.run(xl + (size_t)j * vec_bytes(N), reinterpret_cast<const float*>(xl + vbytes) + (size_t)j * (N >> 5), part * np / parts, (part + 1) * np / parts, acc);
-    const float y0 = row_sum(acc[0]), y1 = row_sum(acc[1]);
-    if ((lane & 7) == 0) { ys[u * 16 + 2 * r] = y0; ys[u * 16 + 2 * r + 1] = y1; }
+    float r = 0.f;
+    if (some) {
+      const unsigned char* const xv = xl + (size_t)j * vec_bytes(N);
+      const float* const xu = reinterpret_cast<const float*>(xl + vbytes) + (size_t)j * (N >> 5) * 2;
+      bool odd = false;
+      for (int i = 4 * g0 + lane; i < 4 * g1; i += 64) odd |= xu[2 * i] != xu[2 * i];
+      if (__builtin_expect(__ballot(odd) != 0ull, 0)) {
+        r = rd.slow([&](int ch, int k) {
+          const unsigned char* const at = xv + half_at(ch, k >> 4);
+          const float unit = xu[2 * ch];
+          if (unit != unit) return from_bits16<DT>(reinterpret_cast<const uint16_t*>(at)[k & 15]);
+          const signed char* const b = reinterpret_cast<const signed char*>(at) + (k & 8) + 4 * (k & 1) + ((k >> 1) & 3);
+          return (float)(((b[48] * 256 + b[32]) * 256 + b[16]) * 256 + b[0]) * unit;
+        }, g0, g1);
+      } else {
+        r = rd.run(xv, xu, zeros, g0, g1);
+      }
+    }
+    const float y = row_sum(r);
+    if (lane < 16) ys[u * 16 + lane] = y;
   }
   __syncthreads();
   if (threadIdx.x < 16) {
@@ -394,41 +462,86 @@ few_down_kernel(const uint16_t* vals, const float* units, const int32_t* __restr
   }
 }
 
+// Groups in flight a wave.  Eight would have more on its way, and twice the code: a kernel of ten to twenty us fetches its
+// instructions from memory once, and loses as much on that (1 token of 7168 x 2048, 256 experts, top 8: 40.9 us with four, 42.5 with eight
+// in the down kernel; 12 tokens of 1024 x 1024, 64 experts, top 2: 13.4, 14.6 with eight in gate/up).
+constexpr int kDeep = 4;
+using Zero = std::integral_constant<int, 0>;
+using One = std::integral_constant<int, 1>;
+using Two = std::integral_constant<int, 2>;
+
+static size_t gate_up_lds(int K, bool route, int R) { return (size_t)vec_total(K) + zero_bytes(R) + 32 + 512 + (route ? kRouter16MaxTopk * 8 : 0); }
+static size_t down_lds(int topk, int N, int parts, int R) { return (size_t)topk * (vec_total(N) + parts * 64) + zero_bytes(R); }
+
 bool few_tokens_fit(int topk, int K, int N) {
-  return K % 128 == 0 && N % 128 == 0 && (size_t)vec_total(K) + 16 + kRouter16MaxTopk * 8 <= kFewLds && (size_t)topk * (vec_total(N) + 8 * 64) <= kFewLds;
+  return K % 128 == 0 && N % 128 == 0 && gate_up_lds(K, true, kDeep) <= kFewLds && down_lds(topk, N, 8, kDeep) <= kFewLds;
 }
+
+size_t few_act_bytes(long long slots, int N) { return (size_t)slots * vec_bytes(N); }
+size_t few_unit_bytes(long long slots, int N) { return (size_t)slots * (N >> 5) * 8; }
 
 int few_down_parts(int topk, int N) {
   const int parts = topk >= 8 ? 1 : topk >= 4 ? 2 : topk >= 2 ? 4 : 8, panels = (N + 1023) / 1024;
   return parts < panels ? parts : panels;
 }
 
+// Dynamic LDS beyond 64 KB needs the kernel's attribute, remembered per device.
+static int allow_lds(const void* kern, size_t lds, bool (&allowed)[64]) {
+  if (lds <= 64 * 1024) return 0;
+  int dev = 0;
+  hipError_t err = hipGetDevice(&dev);
+  if (err != hipSuccess) return (int)err;
+  if (dev >= 0 && dev < 64 && allowed[dev]) return 0;
+  err = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFewLds);
+  if (err == hipSuccess && dev >= 0 && dev < 64) allowed[dev] = true;
+  return (int)err;
+}
+
+template <int DT, int ROUTE, int R, int PRE, int KP>
+static int gate_up(const void* X, const FewRoute& route, const int32_t* ids, const int32_t* qw, const void* s, const uint8_t* z, void* act,
+                   float* units, int T, int topk, int E, int K, int N, hipStream_t stream) {
+  static bool allowed[64] = {};
+  const size_t lds = gate_up_lds(K, ROUTE, R);
+  const int err = allow_lds(reinterpret_cast<const void*>(few_gate_up_kernel<DT, ROUTE, R, PRE, KP>), lds, allowed);
+  if (err != 0) return err;
+  hipLaunchKernelGGL((few_gate_up_kernel<DT, ROUTE, R, PRE, KP>), dim3(N / (64 / KP), T * topk), dim3(kGateThreads), lds, stream, (const uint16_t*)X, route, ids,
+                     (const unsigned char*)qw, (const uint16_t*)s, z, (unsigned char*)act, units, topk, E, K, N);
+  return (int)hipGetLastError();
+}
+
+template <int DT, int R, int PRE>
+static int down(const void* act, const float* units, const int32_t* ids, const float* w, const int32_t* qw, const void* s, const uint8_t* z,
+                void* out, int T, int topk, int E, int K, int N, hipStream_t stream) {
+  static bool allowed[64] = {};
+  const int parts = few_down_parts(topk, N), pairs = topk * parts;
+  const size_t lds = down_lds(topk, N, parts, R);
+  const int err = allow_lds(reinterpret_cast<const void*>(few_down_kernel<DT, R, PRE>), lds, allowed);
+  if (err != 0) return err;
+  hipLaunchKernelGGL((few_down_kernel<DT, R, PRE>), dim3(K / 16, T), dim3(64 * (pairs < 8 ? pairs : 8)), lds, stream, (const unsigned char*)act, units, ids, w,
+                     (const unsigned char*)qw, (const uint16_t*)s, z, (uint16_t*)out, topk, E, K, N, parts);
+  return (int)hipGetLastError();
+}
+
 int launch_few_gate_up(const void* X, const FewRoute* route, const int32_t* ids, const int32_t* qw, const void* s, const uint8_t* z, void* act,
                        float* units, int T, int topk, int E, int K, int N, int dt, int pre, hipStream_t stream) {
-  const dim3 grid(N / 32, T * topk), block(256);
-  const size_t lds = (size_t)vec_total(K) + 16 + (route ? kRouter16MaxTopk * 8 : 0);
-#define MOE_LAUNCH_FEW(DT, ROUTE) \
-  hipLaunchKernelGGL((few_gate_up_kernel<DT, ROUTE>), grid, block, lds, stream, (const uint16_t*)X, route ? *route : FewRoute{}, ids, \
-                     (const unsigned char*)qw, (const uint16_t*)s, z, (uint16_t*)act, units, topk, E, K, N, pre)
-  if (dt == kF16) { if (route) MOE_LAUNCH_FEW(kF16, 1); else MOE_LAUNCH_FEW(kF16, 0); }
-  else { if (route) MOE_LAUNCH_FEW(kBF16, 1); else MOE_LAUNCH_FEW(kBF16, 0); }
-#undef MOE_LAUNCH_FEW
-  return (int)hipGetLastError();
+  const FewRoute r = route ? *route : FewRoute{};
+  auto with = [&](auto route_in, auto ordered, auto parts) {
+    constexpr int RT = decltype(route_in)::value, PRE = decltype(ordered)::value, KP = decltype(parts)::value;
+    return (dt == kF16 ? gate_up<kF16, RT, kDeep, PRE, KP> : gate_up<kBF16, RT, kDeep, PRE, KP>)(X, r, ids, qw, s, z, act, units, T, topk, E, K, N, stream);
+  };
+  auto pick = [&](auto route_in, auto parts) { return pre ? with(route_in, One{}, parts) : with(route_in, Zero{}, parts); };
+  // 64 columns a workgroup, unless that leaves CUs without one: then 32, and the reduction in halves.  (4 tokens of 7168 x 2048, top 1, 128 workgroups
+  // of 64 columns: 25.5 -> 24.0 us; 16 tokens of 256 x 512, top 2, 256 of them: 8.2, in halves 9.1.  A half of less than two groups is not
+  // worth its waves: 11 tokens of 256 x 512, 8.1, in halves 8.7; 4 tokens of 768 x 512, 8.0, in halves 7.5.)
+  const bool halves = K >= 512 && (long long)N / 64 * T * topk < 256;
+  if (route) return halves ? pick(One{}, Two{}) : pick(One{}, One{});
+  return halves ? pick(Zero{}, Two{}) : pick(Zero{}, One{});
 }
 
 int launch_few_down(const void* act, const float* units, const int32_t* ids, const float* w, const int32_t* qw, const void* s, const uint8_t* z,
                     void* out, int T, int topk, int E, int K, int N, int dt, int pre, hipStream_t stream) {
-  const int parts = few_down_parts(topk, N);
-  const int pairs = topk * parts;
-  const dim3 grid(K / 16, T), block(64 * (pairs < 8 ? pairs : 8));
-  const size_t lds = (size_t)topk * (vec_total(N) + parts * 64);
-  if (dt == kF16)
-    hipLaunchKernelGGL(few_down_kernel<kF16>, grid, block, lds, stream, (const uint16_t*)act, units, ids, w, (const unsigned char*)qw,
-                       (const uint16_t*)s, z, (uint16_t*)out, topk, E, K, N, parts, pre);
-  else
-    hipLaunchKernelGGL(few_down_kernel<kBF16>, grid, block, lds, stream, (const uint16_t*)act, units, ids, w, (const unsigned char*)qw,
-                       (const uint16_t*)s, z, (uint16_t*)out, topk, E, K, N, parts, pre);
-  return (int)hipGetLastError();
+  auto go = dt == kF16 ? (pre ? down<kF16, kDeep, 1> : down<kF16, kDeep, 0>) : (pre ? down<kBF16, kDeep, 1> : down<kBF16, kDeep, 0>);
+  return go(act, units, ids, w, qw, s, z, out, T, topk, E, K, N, stream);
 }
 
 }  // namespace moe

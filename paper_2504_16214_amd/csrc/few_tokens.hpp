@@ -6,7 +6,7 @@
 
 namespace moe {
 
-constexpr size_t kFewLds = 64 * 1024;      // LDS either kernel may take (no attribute needed up to here)
+constexpr size_t kFewLds = 136 * 1024;     // LDS either kernel may take
 
 // K and N whole groups of 128, the vectors within the LDS budget.
 bool few_tokens_fit(int topk, int K, int N);
@@ -22,7 +22,10 @@ struct FewRoute {
   int32_t* ids;
   float* weights;
 };
-// act [T * topk, N] as vectors of the down kernel (16-byte aligned) with their chunks' floats in units [T * topk, N / 32],
+// What act and its chunks' floats take.
+size_t few_act_bytes(long long slots, int N);
+size_t few_unit_bytes(long long slots, int N);
+// act as vectors of the down kernel (few_act_bytes, 16-byte aligned) with their chunks' floats in units (few_unit_bytes, 16-byte aligned),
 // then out [T, K]; ids outside [0, E) contribute zero.  route (may be null): the ids come from there.  Group 128; X, act, out
 // and the packed words 16-byte aligned; pre: the words are in operand order.
 int launch_few_gate_up(const void* X, const FewRoute* route, const int32_t* ids, const int32_t* qw, const void* s, const uint8_t* z, void* act,
