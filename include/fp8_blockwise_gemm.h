@@ -98,7 +98,8 @@ int fp8_moe_grouped_gemm(const uint8_t* A, const float* a_scale, int row_div,
  * fp8_set_layer_block_m: force the token tile of the layer's two grouped products (0 = choose);
  * thread-local tuning hook.  With moe_set_stage_events(events, 7) the layer records seven events:
  * before the bucketing, the quantiser, the first product, the SiLU quantiser, the second
- * product, the combine, and after it.
+ * product, the combine, and after it.  (Up to T * K = 2^23 the quantiser runs in the launch of the bucketing: the
+ * time of both lies between the first and the second, nothing between the second and the third.)
  */
 int fp8_quantize_rows(const void* X, int rows, int K, int dt, uint8_t* codes, float* scales, void* stream);
 int fp8_silu_mul_quantize(const void* H, int S, int N, int dt, uint8_t* codes, float* scales, void* stream);

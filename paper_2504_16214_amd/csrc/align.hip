@@ -17,10 +17,13 @@
 // 16 waves first routes its share of the tokens (top-k ids and softmax weights, written for the
 // later steps of the layer), then the bucketing runs on the ids the workgroup has just written.
 // One launch instead of two; the ids and tables are bit for bit those of the separate kernels.
+//
+// Either launch can have a pass over the activations beside it (RowsJob), in further workgroups.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "router_device.hpp"
+#include "rows_device.hpp"
 
 namespace moe {
 
@@ -150,11 +153,22 @@ align_body(const int32_t* topk_ids, int S, int E, int block_m, int capacity, int
   }
 }
 
+// Workgroups behind the first: a pass over the activations that the first product needs as well (0 of them: none).
+__device__ __forceinline__ void run_beside(const RowsJob& job) {
+  run_job(job, (long long)(blockIdx.x - 1) * kAlignThreads + threadIdx.x, (long long)(gridDim.x - 1) * kAlignThreads);
+}
+static unsigned grid_beside(const RowsJob* job) {
+  if (!job || job->kind == RowsJob::kNone) return 1;
+  const long long blocks = (job->groups() * 16 + kAlignThreads - 1) / kAlignThreads;
+  return 1u + (unsigned)(blocks < 2048 ? blocks : 2048);
+}
+
 __global__ void __launch_bounds__(kAlignThreads)
 align_kernel(const int32_t* __restrict__ topk_ids, int S, int E, int block_m, int capacity, int id_bits,
              int32_t* __restrict__ expert_counts, int32_t* __restrict__ expert_offsets,
              int32_t* __restrict__ sorted_slot_ids, int32_t* __restrict__ block_expert_ids,
-             int32_t* __restrict__ num_padded) {
+             int32_t* __restrict__ num_padded, RowsJob job) {
+  if (blockIdx.x != 0) { run_beside(job); return; }
   align_body(topk_ids, S, E, block_m, capacity, id_bits, expert_counts, expert_offsets, sorted_slot_ids,
              block_expert_ids, num_padded);
 }
@@ -164,7 +178,8 @@ route_align_kernel(const float* __restrict__ logits, const float* __restrict__ b
                    int32_t* topk_ids, float* __restrict__ topk_weights, int block_m, int capacity, int id_bits,
                    int32_t* __restrict__ expert_counts, int32_t* __restrict__ expert_offsets,
                    int32_t* __restrict__ sorted_slot_ids, int32_t* __restrict__ block_expert_ids,
-                   int32_t* __restrict__ num_padded) {
+                   int32_t* __restrict__ num_padded, RowsJob job) {
+  if (blockIdx.x != 0) { run_beside(job); return; }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (E <= kRouter16MaxE && topk <= kRouter16MaxTopk) {
     // one token per 16-lane row: 64 tokens of the workgroup in flight at a time
@@ -213,29 +228,29 @@ static int prepare_align_lds(int which, const void* kern, size_t lds) {
 int launch_route_align(const float* logits, const float* bias, int T, int E, int topk, int32_t* topk_ids,
                        float* topk_weights, int block_m, int capacity, int32_t* expert_counts,
                        int32_t* expert_offsets, int32_t* sorted_slot_ids, int32_t* block_expert_ids,
-                       int32_t* num_padded, hipStream_t stream) {
+                       int32_t* num_padded, const RowsJob* job, hipStream_t stream) {
   int id_bits = 0;
   while ((1 << id_bits) < E) ++id_bits;
   const size_t lds = (size_t)(kAlignWaves * E + E + 1) * sizeof(int);
   const int perr = prepare_align_lds(1, reinterpret_cast<const void*>(route_align_kernel), lds);
   if (perr != 0) return perr;
-  hipLaunchKernelGGL(route_align_kernel, dim3(1), dim3(kAlignThreads), lds, stream, logits, bias, T, E, topk,
+  hipLaunchKernelGGL(route_align_kernel, dim3(grid_beside(job)), dim3(kAlignThreads), lds, stream, logits, bias, T, E, topk,
                      topk_ids, topk_weights, block_m, capacity, id_bits, expert_counts, expert_offsets,
-                     sorted_slot_ids, block_expert_ids, num_padded);
+                     sorted_slot_ids, block_expert_ids, num_padded, job ? *job : RowsJob{});
   return (int)hipGetLastError();
 }
 
 int launch_align(const int32_t* topk_ids, int S, int E, int block_m, int capacity,
                  int32_t* expert_counts, int32_t* expert_offsets, int32_t* sorted_slot_ids,
-                 int32_t* block_expert_ids, int32_t* num_padded, hipStream_t stream) {
+                 int32_t* block_expert_ids, int32_t* num_padded, const RowsJob* job, hipStream_t stream) {
   int id_bits = 0;
   while ((1 << id_bits) < E) ++id_bits;
   const size_t lds = (size_t)(kAlignWaves * E + E + 1) * sizeof(int);
   const int perr = prepare_align_lds(0, reinterpret_cast<const void*>(align_kernel), lds);
   if (perr != 0) return perr;
-  hipLaunchKernelGGL(align_kernel, dim3(1), dim3(kAlignThreads), lds, stream, topk_ids, S, E, block_m,
+  hipLaunchKernelGGL(align_kernel, dim3(grid_beside(job)), dim3(kAlignThreads), lds, stream, topk_ids, S, E, block_m,
                      capacity, id_bits, expert_counts, expert_offsets, sorted_slot_ids,
-                     block_expert_ids, num_padded);
+                     block_expert_ids, num_padded, job ? *job : RowsJob{});
   return (int)hipGetLastError();
 }
 

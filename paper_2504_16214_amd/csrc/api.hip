@@ -15,12 +15,13 @@
 #include "gemm_kernel.hpp"
 #include "gemm_mid.hpp"
 #include "gemm_twogroup.hpp"
+#include "rows_device.hpp"
 
 
 namespace moe {
 
 int launch_align(const int32_t*, int, int, int, int, int32_t*, int32_t*, int32_t*, int32_t*, int32_t*,
-                 hipStream_t);
+                 const RowsJob*, hipStream_t);
 int launch_silu_mul(const void*, void*, long long, int, int, hipStream_t);
 int launch_prepare_rows(const void*, long long, int, int, int, void*, float*, float, hipStream_t);
 int launch_repack(const int32_t*, int, int, int, int, int32_t*, hipStream_t);
@@ -28,7 +29,7 @@ int launch_awq_import(const int32_t*, const int32_t*, const void*, int, int, int
                       hipStream_t);
 int launch_route_topk(const float*, const float*, int, int, int, int32_t*, float*, hipStream_t);
 int launch_route_align(const float*, const float*, int, int, int, int32_t*, float*, int, int, int32_t*, int32_t*,
-                       int32_t*, int32_t*, int32_t*, hipStream_t);
+                       int32_t*, int32_t*, int32_t*, const RowsJob*, hipStream_t);
 int launch_stream_read(const void*, size_t, uint32_t*, int, hipStream_t);
 int launch_mfma_loop(float*, int, int, hipStream_t);
 int launch_issue_mix(float*, int, int, int, hipStream_t);
@@ -648,7 +649,7 @@ int moe_align_by_expert(const int32_t* topk_ids, int T, int topk, int E, int blo
     return fail(MOE_INVALID_ARGUMENT, "null pointer argument");
   const size_t cap = align_capacity(S, E, block_m);
   const int err = launch_align(topk_ids, (int)S, E, block_m, (int)cap, expert_counts, expert_offsets,
-                               sorted_slot_ids, block_expert_ids, num_padded, (hipStream_t)stream);
+                               sorted_slot_ids, block_expert_ids, num_padded, nullptr, (hipStream_t)stream);
   if (err != 0) return hip_fail(err, "align launch");
   return MOE_OK;
 }
@@ -779,21 +780,27 @@ struct RouteArgs {            // routed layer: the layer's first step computes i
   float* weights = nullptr;
 };
 
+// Does the pass over the activations run in the launch of the bucketing?  A launch and its gap less, 2.5 us (64 tokens of 4096 x 14336
+// 167.0 -> 164.6, 512 of 2048 x 2048 147.5 -> 144.9, FP8 64 of 2048 x 1408 129.2 -> 126.6).  Where the pass is long the bucketing, one workgroup that
+// now shares its CU and the caches with it, takes longer: 4096 tokens of 7168 3405 -> 3429 us, FP8 the same either way; 4096 of 2048
+// in FP8 419 -> 415.
+static bool runs_beside(long long T, int K) { return T * K <= 1LL << 23; }
+
 // router (+ bucketing): one launch for small batches, two otherwise
 static int route_and_align(const RouteArgs& r, int T, int E, int topk, int block_m, int32_t* counts, int32_t* offsets,
-                           int32_t* sorted, int32_t* blocks, int32_t* num_padded, hipStream_t stream) {
+                           int32_t* sorted, int32_t* blocks, int32_t* num_padded, const RowsJob* job, hipStream_t stream) {
   const long long S = (long long)T * topk;
   const int cap = (int)align_capacity(S, E, block_m);
   int err;
   if (T <= kFusedRouteMaxTokens) {
     err = launch_route_align(r.logits, r.bias, T, E, topk, r.ids, r.weights, block_m, cap, counts, offsets, sorted,
-                             blocks, num_padded, stream);
+                             blocks, num_padded, job, stream);
     if (err != 0) return hip_fail(err, "router + align launch");
     return MOE_OK;
   }
   err = launch_route_topk(r.logits, r.bias, T, E, topk, r.ids, r.weights, stream);
   if (err != 0) return hip_fail(err, "router launch");
-  err = launch_align(r.ids, (int)S, E, block_m, cap, counts, offsets, sorted, blocks, num_padded, stream);
+  err = launch_align(r.ids, (int)S, E, block_m, cap, counts, offsets, sorted, blocks, num_padded, job, stream);
   if (err != 0) return hip_fail(err, "align launch");
   return MOE_OK;
 }
@@ -979,22 +986,30 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
     return MOE_OK;
   }
 
+  // The two-group and the 64-slot tile read the rows of X in another order (bf16: and their sums); they live where Y will be
+  // written: Y is written last.
+  float* const xsum = dt == MOE_BF16 ? (float*)((unsigned char*)Y + round_up((size_t)T * K * 2, 256)) : nullptr;
+  const bool reorder = two_group || mid, beside = reorder && runs_beside(T, K);
+  const int deal = two_group ? 0 : 1;
+  const float factor = two_group ? 47.f : kZeroUnit;
+  RowsJob job;
+  if (beside) job = prepare_job(X, T, K, (int)dt, deal, Y, xsum, factor);
   mark(0);
   if (route) {
-    const int rst = route_and_align(*route, T, E, topk, block_m, counts, offsets, sorted, blocks, num_padded, stream);
+    const int rst = route_and_align(*route, T, E, topk, block_m, counts, offsets, sorted, blocks, num_padded, &job, stream);
     if (rst != MOE_OK) return rst;
   } else {
     err = launch_align(topk_ids, (int)S, E, block_m, (int)align_capacity(S, E, block_m), counts, offsets,
-                       sorted, blocks, num_padded, stream);
+                       sorted, blocks, num_padded, &job, stream);
     if (err != 0) return hip_fail(err, "align launch");
+  }
+  if (reorder && !beside) {
+    err = launch_prepare_rows(X, T, K, (int)dt, deal, Y, xsum, factor, stream);
+    if (err != 0) return hip_fail(err, "activation reorder launch");
   }
 
   if (two_group) {
-    // the reordered rows of X and their sums live where Y will be written: Y is written last
-    float* const xsum = dt == MOE_BF16 ? (float*)((unsigned char*)Y + round_up((size_t)T * K * 2, 256)) : nullptr;
     float* const asum = dt == MOE_BF16 ? (float*)(base + w.base) : nullptr;
-    err = launch_prepare_rows(X, T, K, (int)dt, 0, Y, xsum, 47.f, stream);
-    if (err != 0) return hip_fail(err, "activation reorder launch");
     mark(1);
     int st = run_twogroup(Y, xsum, topk, qw1, s1, z1, sorted, blocks, num_padded, (int)S, E, 2 * N, K, (int)dt, 1, pre, act, stream);
     if (st != MOE_OK) return st;
@@ -1012,14 +1027,11 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
     return MOE_OK;
   }
   if (mid) {
-    float* const xsum = dt == MOE_BF16 ? (float*)((unsigned char*)Y + round_up((size_t)T * K * 2, 256)) : nullptr;
     // reduction splits of the down product: as many partial planes as the caller's workspace holds
     const size_t plane = (size_t)S * K * 4;
     size_t want = g_force_ksplit > 0 ? (size_t)g_force_ksplit : w.mid_splits;
     while (want > 1 && end_of_planes(w, plane, want) + w.sums > workspace_bytes) --want;
     float* const asum = dt == MOE_BF16 ? (float*)(base + end_of_planes(w, plane, want)) : nullptr;
-    err = launch_prepare_rows(X, T, K, (int)dt, 1, Y, xsum, kZeroUnit, stream);
-    if (err != 0) return hip_fail(err, "activation reorder launch");
     mark(1);
     int st = run_mid(Y, xsum, topk, qw1, s1, z1, sorted, blocks, num_padded, (int)S, E, 2 * N, K, (int)dt, 1, pre, 1, act, nullptr, stream);
     if (st != MOE_OK) return st;
@@ -1212,7 +1224,7 @@ int moe_route_align(const float* logits, const float* bias, int T, int E, int to
   RouteArgs r;
   r.logits = logits; r.bias = bias; r.ids = topk_ids; r.weights = topk_weights;
   return route_and_align(r, T, E, topk, block_m, expert_counts, expert_offsets, sorted_slot_ids, block_expert_ids,
-                         num_padded, (hipStream_t)stream);
+                         num_padded, nullptr, (hipStream_t)stream);
 }
 
 int moe_set_stage_events(void* const* events, int n) {
@@ -1500,12 +1512,16 @@ int fp8_moe_layer(const void* X, const int32_t* topk_ids, const float* topk_weig
   auto mark = [&](int i) { if (ev) (void)hipEventRecord((hipEvent_t)g_events[i], stream); };
 
   mark(0);
+  const bool beside = runs_beside(T, K);
+  const RowsJob job = beside ? quantize_job(X, T, K, (int)dt, xq, sx) : RowsJob{};
   int err = launch_align(topk_ids, (int)S, E, block_m, (int)align_capacity(S, E, block_m), counts, offsets, sorted,
-                         blocks, num_padded, stream);
-  if (err != 0) return hip_fail(err, "align launch");
+                         blocks, num_padded, &job, stream);
+  if (err != 0) return hip_fail(err, "align and quantiser launch");
   mark(1);
-  err = fp8::launch_fp8_quantize(X, T, K, (int)dt, 0, xq, sx, stream);
-  if (err != 0) return hip_fail(err, "activation quantiser launch");
+  if (!beside) {
+    err = fp8::launch_fp8_quantize(X, T, K, (int)dt, 0, xq, sx, stream);
+    if (err != 0) return hip_fail(err, "activation quantiser launch");
+  }
   mark(2);
   int st = fp8_moe_grouped_gemm(xq, sx, topk, w1, w1_scale, sorted, blocks, num_padded, (int)S, E, 2 * N, K, block_m,
                                 (int)dt, H, stream);

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "gemm_kernel.hpp"   // 16-bit conversions and silu_f32 only
+#include "rows_device.hpp"
 
 namespace moe {
 
@@ -103,26 +104,10 @@ combine_kernel(const void* __restrict__ Yv, const float* __restrict__ w, const i
   }
 }
 
-// Activations for the two-group and the 64-slot GEMM.  out (may be null): every run of eight reduction indices in
-// the order 0,4,1,5,2,6,3,7 (DEAL: 0,2,4,6,1,3,5,7).  sums (may be null): factor * (sum of the row's 128-index group), float32
-// (two-group, bf16: 47, the constant its operands carry; 64-slot, bf16: 16, kZeroUnit).  16 lanes per group, 8 elements each;
-// a pure stream (4096 x 7168: 117 MB moved in 24 us).
 template <int DT, int DEAL>
 __global__ void __launch_bounds__(256)
 prepare_rows_kernel(const uint16_t* __restrict__ X, long long groups, uint16_t* __restrict__ out, float* __restrict__ sums, float factor) {
-  for (long long g = ((long long)blockIdx.x * 256 + threadIdx.x) >> 4; g < groups; g += ((long long)gridDim.x * 256) >> 4) {
-    const long long at = g * 128 + (threadIdx.x & 15) * 8;
-    const u32x4 v = *reinterpret_cast<const u32x4*>(X + at);
-    if (out) *reinterpret_cast<u32x4*>(out + at) = DEAL ? deal8(v) : interleave8(v);
-    if (sums) {
-      float s = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) s += from_bits16<DT>((uint16_t)v[i]) + from_bits16<DT>((uint16_t)(v[i] >> 16));
-#pragma unroll
-      for (int d = 8; d >= 1; d >>= 1) s += __shfl_xor(s, d, 16);
-      if ((threadIdx.x & 15) == 0) sums[g] = factor * s;
-    }
-  }
+  prepare_rows<DT, DEAL>(X, groups, out, sums, factor, (long long)blockIdx.x * 256 + threadIdx.x, (long long)gridDim.x * 256);
 }
 
 static int grid_for(long long work_items) {

@@ -13,73 +13,15 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "gemm_kernel.hpp"   // 16-bit conversions and silu_f32 only
+#include "rows_device.hpp"
 
 namespace fp8 {
 
-typedef uint32_t q_u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t q_u32x2 __attribute__((ext_vector_type(2)));
-
-// two float32 -> two e4m3 codes in the low or high half of a word (round to nearest even; the
-// matrix unit's own converter, OCP flavour on this chip)
-__device__ __forceinline__ uint32_t pack_e4m3(float a, float b, uint32_t old, bool high) {
-  return high ? (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(a, b, (int)old, true)
-              : (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(a, b, (int)old, false);
-}
-
-// FUSE = 0: X [rows, K] -> codes [rows, K], scales [rows, K / 128]
-// FUSE = 1: H [rows, 2K] (columns [0, K) gate, [K, 2K) up) -> the same for act = rnd(silu(gate) * up)
 template <int DT, int FUSE>
 __global__ void __launch_bounds__(256)
 quantize_rows_kernel(const uint16_t* __restrict__ X, long long rows, int K, uint8_t* __restrict__ codes,
                      float* __restrict__ scales) {
-  const int KB = K >> 7;
-  const long long tiles = rows * KB;
-  const int lane16 = threadIdx.x & 15;
-  const long long group0 = ((long long)blockIdx.x * 256 + threadIdx.x) >> 4;      // 16-lane group index
-  const long long ngroups = ((long long)gridDim.x * 256) >> 4;
-  for (long long t = group0; t < tiles; t += ngroups) {                           // uniform per 16-lane group
-    const long long row = t / KB;
-    const int kb = (int)(t - row * KB);
-    const int col = kb * 128 + lane16 * 8;
-    float x[8];
-    if constexpr (FUSE) {
-      const uint16_t* hrow = X + row * 2 * (long long)K;
-      const q_u32x4 g = *reinterpret_cast<const q_u32x4*>(hrow + col);
-      const q_u32x4 u = *reinterpret_cast<const q_u32x4*>(hrow + K + col);
-      const uint32_t gw[4] = {g.x, g.y, g.z, g.w}, uw[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float g0 = moe::from_bits16<DT>((uint16_t)gw[i]), g1 = moe::from_bits16<DT>((uint16_t)(gw[i] >> 16));
-        const float u0 = moe::from_bits16<DT>((uint16_t)uw[i]), u1 = moe::from_bits16<DT>((uint16_t)(uw[i] >> 16));
-        // the activation is a 16-bit tensor: round it before it is quantised
-        x[2 * i] = moe::from_bits16<DT>(moe::to_bits16<DT>(moe::silu_f32(g0) * u0));
-        x[2 * i + 1] = moe::from_bits16<DT>(moe::to_bits16<DT>(moe::silu_f32(g1) * u1));
-      }
-    } else {
-      const q_u32x4 v = *reinterpret_cast<const q_u32x4*>(X + row * (long long)K + col);
-      const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        x[2 * i] = moe::from_bits16<DT>((uint16_t)vw[i]);
-        x[2 * i + 1] = moe::from_bits16<DT>((uint16_t)(vw[i] >> 16));
-      }
-    }
-    float m = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(x[i]));
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 16));
-    m = fmaxf(m, 1e-4f);
-    const float ratio = 448.0f / m;          // correctly rounded float32 division
-    uint32_t lo = 0u, hi = 0u;
-    lo = pack_e4m3(x[0] * ratio, x[1] * ratio, lo, false);
-    lo = pack_e4m3(x[2] * ratio, x[3] * ratio, lo, true);
-    hi = pack_e4m3(x[4] * ratio, x[5] * ratio, hi, false);
-    hi = pack_e4m3(x[6] * ratio, x[7] * ratio, hi, true);
-    *reinterpret_cast<q_u32x2*>(codes + row * (long long)K + col) = q_u32x2{lo, hi};
-    if (lane16 == 0) scales[t] = m / 448.0f;
-  }
+  quantize_rows<DT, FUSE>(X, rows, K, codes, scales, (long long)blockIdx.x * 256 + threadIdx.x, (long long)gridDim.x * 256);
 }
 
 // rows * K / 128 tiles, 16 per workgroup; returns a hipError_t
