@@ -652,7 +652,11 @@ w4a16_gemm_kernel(const GemmParams p) {
             ZS ? deal8(XV[ps]) : interleave8(XV[ps]);                                           \
   }
 
-  constexpr bool kByOffset = MT >= 4;      // stores by offset, see kNoRow
+  // Stores by offset, see kNoRow.  Not where a group fills a stage (128 and more), fp16 128-slot tiles apart: too few registers are left (bf16, 64 slots,
+  // 6 spilled instead of 2).  With them / without: bf16 2086 rows of 5760 x 21488 dense 848 / 801 us, 2915 tokens of 2560 x 3584, 49 experts, top 2
+  // 603 / 576, 128-slot tile 6536 of 3072 x 3072, 19 experts, top 1 663 / 617; fp16 13401 tokens of 512 x 2176, 107 experts, top 4 709 / 689,
+  // 128-slot tile 6536 of 3072 x 3072 485 / 491; groups of 64: 1024 tokens of 2048 x 1408, 64 experts, top 6, bf16 243 / 246.
+  constexpr bool kByOffset = MT >= 4 && !(KW == 4 && (DT == kBF16 || MT == 4));
   // Flattened step index over (tile, stage).  nst_pad rounds the stages of a tile up to whole
   // trips; stages in [nst, nst_pad) are dead (clamped loads, no compute).
   const int nst_pad = (nst + UNR - 1) / UNR * UNR;
