@@ -16,7 +16,7 @@
 // form: its slot goes the long way round, weight by weight (slow_group).
 //
 // What bounds it: two launches of 5 to 6 us each beside the stream of weights (gate/up of one token of 7168 x 2048, 256 experts, top 8, 118 MB from
-// memory, 25.6 us and 4.6 TB/s; down 16.2; 45.0 -> 40.9 the call.  With products of float16 pairs on the vector unit, 77 instructions a KB of
+// memory, 24.9 us and 4.7 TB/s; down 16.0; 44.5 -> 40.5 the call.  With products of float16 pairs on the vector unit, 77 instructions a KB of
 // weights where there are 40 now, they took 27.8 and 19.4, and no less with the weights in the cache).
 //
 // A wave covers 16 weight rows, four groups (4 KB) in flight, the next four asked for as each is used.  The order in which a
