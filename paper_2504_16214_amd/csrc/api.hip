@@ -975,10 +975,10 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
       if (err != 0) return hip_fail(err, "router launch");
     }
     mark(1);
-    err = launch_few_gate_up(X, fused ? &inside : nullptr, topk_ids, qw1, s1, z1, act, (float*)(base + w.few_units), T, topk, E, K, N, (int)dt, pre, stream);
+    err = launch_few_gate_up(X, fused ? &inside : nullptr, topk_ids, qw1, s1, z1, act, (uint32_t*)(base + w.few_units), T, topk, E, K, N, (int)dt, pre, stream);
     if (err != 0) return hip_fail(err, "few-token gate/up launch");
     mark(2);
-    err = launch_few_down(act, (const float*)(base + w.few_units), topk_ids, topk_weights, qw2, s2, z2, out, T, topk, E, K, N, (int)dt, pre, stream);
+    err = launch_few_down(act, (const uint32_t*)(base + w.few_units), topk_ids, topk_weights, qw2, s2, z2, out, T, topk, E, K, N, (int)dt, pre, stream);
     if (err != 0) return hip_fail(err, "few-token down launch");
     for (int& v : g_last_plan) v = 0;       // no tile
     mark(3);

@@ -6,18 +6,24 @@
 // SiLU-and-multiply is one kernel over (slot, columns), the down projection of all of a token's slots
 // with the weighted combine another over (token, columns).
 //
-// The products are sums of integers.  A chunk of 32 activations is brought to a power of two below 2^30 (its unit) and
-// rounded to integers of four signed bytes, digits to the base 256; nibbles as bytes need two masks and a shift for eight
+// The products are sums of integers.  A chunk of 32 activations is brought to whole numbers below 2^30 by a power of two
+// (its unit), four signed bytes each, digits to the base 256; nibbles as bytes need two masks and a shift for eight
 // weights.  The int8 matrix instruction multiplies them: its 16 rows are the 4 digits of the 4 chunks of a quantisation
 // group, each zero outside its own chunk, its 16 columns are 16 weight rows.  A lane ends up with the 4 digits' sums of one
-// chunk and one weight row, exact, puts them together in float32, takes the zero point times the chunk's sum away
-// and multiplies by the group's scale.  What it loses: activations below 2^-30 of the largest of their chunk are rounded to that
-// (the sums of float32 products that it replaces lost 2^-24 of theirs).  A chunk with an infinity or a NaN has no such
-// form: its slot goes the long way round, weight by weight (slow_group).
+// chunk and one weight row and takes the zero point times the chunk's own sums from them, digits 0 and 1 and digits 2 and 3
+// together: whole numbers that float32 holds.  So a chunk's sum of (q - z) x is rounded once, when its halves are put
+// together; a weight that is its zero point contributes nothing, however large its activation.  Then it multiplies by the
+// group's scale.  Some chunks have no such form: fp16 with a value that is no multiple of its unit (only beside one of 64
+// and more, 2^19 times as large), bf16 with nothing above 2^-97, either with an infinity or a NaN.  They are kept as
+// they are and their weights multiplied one by one in float32 (by_values).  bf16 values below 2^-22 of the largest of their
+// chunk lose what is below 2^-29 of it: one in a thousand chunks of act has one, and kept as they are they cost 2 to 3 us a
+// call; the products with 128 + q that this form replaced lost 2^-24 of 143 times the largest.
 //
 // What bounds it: two launches of 5 to 6 us each beside the stream of weights (gate/up of one token of 7168 x 2048, 256 experts, top 8, 118 MB from
 // memory, 24.9 us and 4.7 TB/s; down 16.0; 44.5 -> 40.5 the call.  With products of float16 pairs on the vector unit, 77 instructions a KB of
-// weights where there are 40 now, they took 27.8 and 19.4, and no less with the weights in the cache).
+// weights where there are 40 now, they took 27.8 and 19.4, and no less with the weights in the cache).  Zero points taken out in whole numbers, and
+// the chunks kept as they are, cost 1 % (that call with its weights in the cache 34.2 -> 34.5 us; 12 tokens of 1024 x 1024, 64 experts, top 2, 12.5 -> 12.8),
+// where act is so large that most fp16 chunks are kept, more (one token of 28672 x 1024, 8 experts, top 2, 37.2 -> 50.7; with float16 pairs 56.4).
 //
 // A wave covers 16 weight rows, four groups (4 KB) in flight, the next four asked for as each is used.  The order in which a
 // row is summed is the same in both weight layouts.  Weights go through the caches: slots that share
@@ -34,12 +40,16 @@
 namespace moe {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 // A vector of k activations: for every group of 128, [half h of a chunk][chunk][digit][16 bytes], the bytes of a half (16
 // activations, two weight words) in the order the nibbles are unpacked to: 0, 2, 4, 6, 1, 3, 5, 7 of either word.
-// Behind it, for every chunk, its unit and the sum of its activations, floats.  A chunk that holds an infinity or a NaN has the unit
-// NaN, and where digits would lie its 16-bit activations as they are, 16 at the start of each half's 64 bytes.
+// Behind it, two words for every chunk: in the low 24 bits the sum of its digits 0 + 256 digits 1 and that of its digits 2
+// + 256 digits 3, in the first one's upper 8 the exponent of its unit.  A chunk that is kept as it is has kAsIs for
+// an exponent, and where digits would lie its 16-bit activations, 16 at the start of each half's 64 bytes.
+constexpr int kAsIs = -128;
+constexpr uint32_t kLossFrom = 0x42800000u;      // 64: below it every fp16 value is a multiple of its chunk's unit
 __host__ __device__ __forceinline__ int vec_bytes(int k) { return 4 * k; }
 __host__ __device__ __forceinline__ int vec_total(int k) { return vec_bytes(k) + (k >> 5) * 8; }
 __device__ __forceinline__ int half_at(int chunk, int h) { return (chunk >> 2) * 512 + h * 256 + (chunk & 3) * 64; }      // + 16 digit
@@ -51,11 +61,17 @@ __device__ __forceinline__ int chunk_up(uint32_t largest) {
   return up < 126 ? up : 126;
 }
 __device__ __forceinline__ float power_of_two(int e) { return __builtin_bit_cast(float, (uint32_t)(127 + e) << 23); }
-// |v| < 2^30 -> its four signed digits as bytes
-__device__ __forceinline__ uint32_t digits(float v) {
-  const uint32_t i = (uint32_t)(int)__builtin_rintf(v);
-  return (i + 0x00808080u) ^ 0x00808080u;
+// |v| < 2^30, towards zero to a whole number -> its four signed digits as bytes, each of the first three plus 128
+__device__ __forceinline__ uint32_t biased_digits(float v) { return (uint32_t)(int)v + 0x00808080u; }
+template <int DT>
+__device__ __forceinline__ bool no_digits(uint32_t largest) {      // float32 bits, no sign
+  return largest >= 0x7f800000u || (DT == kBF16 && largest - 1u < ((uint32_t)(127 - 97) << 23) - 1u);
 }
+__device__ __forceinline__ u32x2 chunk_words(bool as_is, int up, int s01, int s23) {
+  return as_is ? u32x2{(uint32_t)kAsIs << 24, 0u} : u32x2{((uint32_t)-up << 24) | ((uint32_t)s01 & 0x00FFFFFFu), (uint32_t)s23};
+}
+// a * (the low 24 bits of b) + c
+__device__ __forceinline__ int mad24(int a, uint32_t b, int c) { return a * ((int)(b << 8) >> 8) + c; }
 
 // Over 4 lanes (a quad), over 8, over the lanes (n, 0 ... 3) of a row: every lane ends up with the result.
 __device__ __forceinline__ float as_float(uint32_t v) { return __builtin_bit_cast(float, v); }      // (of a vector's element, by value)
@@ -63,11 +79,12 @@ template <int CTRL>
 __device__ __forceinline__ uint32_t dpp(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true); }
 constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
 template <int CTRL>
-__device__ __forceinline__ void max_and_sum(uint32_t& m, float& s) {
+__device__ __forceinline__ uint32_t max_over(uint32_t m) {
   const uint32_t o = dpp<CTRL>(m);
-  m = m > o ? m : o;
-  s += as_float(dpp<CTRL>(bits32(s)));
+  return m > o ? m : o;
 }
+template <int CTRL>
+__device__ __forceinline__ int sum_over(int v) { return v + (int)dpp<CTRL>((uint32_t)v); }
 __device__ __forceinline__ float row_sum(float v) {
   auto h = __builtin_amdgcn_permlane32_swap(bits32(v), bits32(v), false, false);
   v = as_float(h[0]) + as_float(h[1]);
@@ -140,47 +157,51 @@ struct Rows16 {
     for (int i = 0; i < R; ++i) load_w(i, g0 + (i & ~1), g1);
   }
   // The rows' sums over groups [g0, g1), g0 even, against the vector at xl: lane (n, j) has row n's over the chunks j.
-  __device__ __forceinline__ float run(const unsigned char* xl, const float* units, const unsigned char* zeros, int g0, int g1) {
+  // as_is (uniform): some chunk of the vector may be kept as it is.
+  __device__ __forceinline__ float run(const unsigned char* xl, const uint32_t* units, const unsigned char* zeros, int g0, int g1, bool as_is) {
     const int lane = threadIdx.x & 63, n = lane & 15, j = lane >> 4;
     // lanes of the digits of chunk j read them, the others zeros
     const bool mine = (n >> 2) == j;
     const unsigned char* xp = mine ? xl + g0 * 512 + j * 64 + (n & 3) * 16 : zeros;
     const int xstep = mine ? 512 * R : 0;
-    const float* up = units + (size_t)(g0 * 4 + j) * 2;
+    const uint32_t* up = units + (size_t)(g0 * 4 + j) * 2;
     float acc = 0.f;
-    auto group = [&](int i, const u32x4& v) __attribute__((always_inline)) {
+    auto group = [&](int i, int g, const u32x4& v) __attribute__((always_inline)) {
       const u32x4 x0 = *reinterpret_cast<const u32x4*>(xp + 512 * i), x1 = *reinterpret_cast<const u32x4*>(xp + 512 * i + 256);
-      const floatx2_t u = *reinterpret_cast<const floatx2_t*>(up + 8 * i);
+      const u32x2 u = *reinterpret_cast<const u32x2*>(up + 8 * i);
       const uint32_t sz = (uint32_t)__builtin_amdgcn_ds_bpermute((n + 16 * (i & 3)) * 4, (int)own[i >> 2]);
       const uint32_t m = 0x0F0F0F0Fu;
       i32x4 d = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, x0),
                                                       i32x4{(int)(v.x & m), (int)((v.x >> 4) & m), (int)(v.y & m), (int)((v.y >> 4) & m)}, i32x4{0, 0, 0, 0}, 0, 0, 0);
       d = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, x1),
                                                 i32x4{(int)(v.z & m), (int)((v.z >> 4) & m), (int)(v.w & m), (int)((v.w >> 4) & m)}, d, 0, 0, 0);
-      // a digit's sum is below 128 * 15 * 32: two of them are exact in float32
-      const float lo = (float)(d[0] + (d[1] << 8)), hi = (float)(d[2] + (d[3] << 8));
-      const float t = __builtin_fmaf(__builtin_fmaf(hi, 65536.f, lo), u[0], -((float)(sz >> 16) * u[1]));
+      // |q - z| <= 15, |digit 0 + 256 digit 1| <= 32896, |digit 2 + 256 digit 3| <= 2^14: over 32 weights below 2^24
+      const int nz = (int)sz >> 16, exponent = (int)u[0] >> 24;
+      const float lo = (float)mad24(nz, u[0], d[0] + (d[1] << 8)), hi = (float)mad24(nz, u[1], d[2] + (d[3] << 8));
+      float t = __builtin_ldexpf(__builtin_fmaf(hi, 65536.f, lo), exponent);
+      if (__builtin_expect(as_is, 0))
+        if (exponent == kAsIs) t = by_values(v, xl + g * 512 + j * 64, nz);
       acc = __builtin_fmaf(from_bits16<DT>((uint16_t)sz), t, acc);
     };
     for (int p = g0; p < g1; p += R) {
 #pragma unroll
-      for (int q = 0; q < R / 4; ++q) own[q] = nxt_s[q] | ((nxt_z[q] & 15) << 16);
+      for (int q = 0; q < R / 4; ++q) own[q] = nxt_s[q] | ((0u - (nxt_z[q] & 15)) << 16);
       load_sz(p + R);
 #pragma unroll
       for (int i = 0; i < R; i += 2) {
         if (p + i >= g1) return acc;
         if constexpr (PRE) {
-          group(i, w[i]);
+          group(i, p + i, w[i]);
           load_w(i, p + i + R, g1);
-          if (p + i + 1 < g1) group(i + 1, w[i + 1]);
+          if (p + i + 1 < g1) group(i + 1, p + i + 1, w[i + 1]);
           load_w(i + 1, p + i + R, g1);
         } else {
           u32x4 a = w[i], b = w[i + 1];
           pair(a, b);
           load_w(i, p + i + R, g1);
           load_w(i + 1, p + i + R, g1);
-          group(i, a);
-          if (p + i + 1 < g1) group(i + 1, b);
+          group(i, p + i, a);
+          if (p + i + 1 < g1) group(i + 1, p + i + 1, b);
         }
       }
       xp += xstep;
@@ -188,27 +209,19 @@ struct Rows16 {
     }
     return acc;
   }
-  // The same where the vector holds an infinity or a NaN: weight by weight, x(k) the activations.
-  template <typename F>
-  __device__ __forceinline__ float slow(F x, int g0, int g1) {
-    const int j = (threadIdx.x >> 4) & 3;
-    float acc = 0.f;
+  // A chunk's sum weight by weight, at: its activations as they are, nz: minus the zero point.
+  static __device__ __forceinline__ float by_values(const u32x4& v, const unsigned char* at, int nz) {
+    const float z = (float)nz;
+    float t = 0.f;
 #pragma unroll 1
-    for (int g = g0; g < g1; ++g) {
-      const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)wbase, 0, (int)wbytes, 0x00020000);
-      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(PRE ? woff : (soff - j) * 64u + 16u * j), g * (PRE ? 1024 : 64), 0);
-      const int at = (int)(soff + (uint32_t)g) - j;
-      const float s = from_bits16<DT>((uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, 2 * at, 0, 0));
-      const int z = (int)((uint8_t)__builtin_amdgcn_raw_buffer_load_b8(rz, at, 0, 0) & 15);
-      float t = 0.f;
-#pragma unroll 1
-      for (int k = 0; k < 32; ++k) {
-        const uint32_t word = k < 8 ? v.x : k < 16 ? v.y : k < 24 ? v.z : v.w;
-        t = __builtin_fmaf((float)((int)((word >> (4 * (k & 7))) & 15) - z), x(4 * g + j, k), t);
-      }
-      acc = __builtin_fmaf(s, t, acc);
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t word = (i < 2 ? v.x : i < 4 ? v.y : i < 6 ? v.z : v.w) >> (16 * (i & 1)), even = word & 0x0F0Fu, odd = (word >> 4) & 0x0F0Fu;
+      const u32x2 x = *reinterpret_cast<const u32x2*>(at + 256 * (i >> 2) + 8 * (i & 3));
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        t = __builtin_fmaf((float)(uint8_t)((k & 1 ? odd : even) >> (8 * (k >> 1))) + z, from_bits16<DT>((uint16_t)(x[k >> 1] >> (16 * (k & 1)))), t);
     }
-    return acc;
+    return t;
   }
 };
 
@@ -224,33 +237,34 @@ __device__ __forceinline__ FirstValues first_values(const uint16_t* src, int K) 
   return f;
 }
 // kGateThreads threads bring the K activations of a token into an LDS vector, the first of them loaded already.
-// Whether one of the thread's chunks holds an infinity or a NaN (it is garbage then).
+// Whether one of the thread's chunks is kept as it is.
 template <int DT>
 __device__ __forceinline__ bool stage_row(const uint16_t* src, int K, unsigned char* xl, FirstValues& first) {
   bool odd = false;
-  float* const units = reinterpret_cast<float*>(xl + vec_bytes(K));
+  uint32_t* const units = reinterpret_cast<uint32_t*>(xl + vec_bytes(K));
   constexpr int step = kGateThreads * 8;
   u32x4 (&v)[2] = first.v;
   auto put = [&](int k, const u32x4& x) __attribute__((always_inline)) {
-    float f[8];
-    uint32_t m = 0;
-    float s = 0.f;
+    // the largest of the chunk, on the 16-bit patterns
+    u16x2 top = {0, 0};
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      f[t] = from_bits16<DT>((uint16_t)(x[t >> 1] >> (16 * (t & 1))));
-      const uint32_t a = bits32(f[t]) & 0x7fffffffu;
-      m = m > a ? m : a;
-      s += f[t];
-    }
-    max_and_sum<kXor1>(m, s);
-    max_and_sum<kXor2>(m, s);
-    if (k >= K) return;
-    odd |= m >= 0x7f800000u;
+    for (int t = 0; t < 4; ++t) top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, x[t] & 0x7fff7fffu));
+    const uint32_t larger = top.x > top.y ? top.x : top.y;
+    const uint32_t m = bits32(from_bits16<DT>((uint16_t)max_over<kXor2>(max_over<kXor1>(larger))));
+    if (k >= K) return;                            // (K is a multiple of 32: a chunk's four lanes stay together)
     const int up = chunk_up(m), chunk = k >> 5, word = (k >> 3) & 3;
     const float factor = power_of_two(up);
+    auto scaled = [&](int t) __attribute__((always_inline)) { return __builtin_fmaf(from_bits16<DT>((uint16_t)(x[t >> 1] >> (16 * (t & 1)))), factor, 0.f); };
     uint32_t y[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) y[t] = digits(f[t] * factor);
+    for (int t = 0; t < 8; ++t) y[t] = biased_digits(scaled(t));
+    bool as_is = no_digits<DT>(m);
+    if (DT == kF16 && m >= kLossFrom) {
+      uint32_t rest = 0u;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) rest |= bits32(scaled(t) - __builtin_truncf(scaled(t)));
+      as_is |= max_over<kXor2>(max_over<kXor1>(rest << 1)) != 0u;      // (no sign: what is whole leaves a zero)
+    }
     // digit planes: bytes of values 0, 2, 4, 6 and of 1, 3, 5, 7
     unsigned char* const at = xl + half_at(chunk, word >> 1) + 8 * (word & 1);
     uint32_t plane[4][2];
@@ -258,25 +272,36 @@ __device__ __forceinline__ bool stage_row(const uint16_t* src, int K, unsigned c
     for (int o = 0; o < 2; ++o) {
       const uint32_t a = __builtin_amdgcn_perm(y[2 + o], y[o], 0x05010400u), b = __builtin_amdgcn_perm(y[2 + o], y[o], 0x07030602u);
       const uint32_t c = __builtin_amdgcn_perm(y[6 + o], y[4 + o], 0x05010400u), d = __builtin_amdgcn_perm(y[6 + o], y[4 + o], 0x07030602u);
-      plane[0][o] = __builtin_amdgcn_perm(c, a, 0x05040100u);
-      plane[1][o] = __builtin_amdgcn_perm(c, a, 0x07060302u);
-      plane[2][o] = __builtin_amdgcn_perm(d, b, 0x05040100u);
+      plane[0][o] = __builtin_amdgcn_perm(c, a, 0x05040100u) ^ 0x80808080u;
+      plane[1][o] = __builtin_amdgcn_perm(c, a, 0x07060302u) ^ 0x80808080u;
+      plane[2][o] = __builtin_amdgcn_perm(d, b, 0x05040100u) ^ 0x80808080u;
       plane[3][o] = __builtin_amdgcn_perm(d, b, 0x07060302u);
     }
+    int sum[4];
 #pragma unroll
-    for (int d = 0; d < 4; ++d) *reinterpret_cast<u32x2*>(at + 16 * d) = u32x2{plane[d][0], plane[d][1]};
-    if (word == 0) *reinterpret_cast<floatx2_t*>(units + 2 * chunk) = floatx2_t{power_of_two(-up), s};
+    for (int d = 0; d < 4; ++d)
+      sum[d] = __builtin_amdgcn_sdot4((int)plane[d][0], 0x01010101, __builtin_amdgcn_sdot4((int)plane[d][1], 0x01010101, 0, false), false);
+    const int s01 = sum_over<kXor2>(sum_over<kXor1>(sum[0] + (sum[1] << 8)));
+    const int s23 = sum_over<kXor2>(sum_over<kXor1>(sum[2] + (sum[3] << 8)));
+    odd |= as_is;
+    if (__builtin_expect(as_is, 0)) {
+      *reinterpret_cast<u32x4*>(xl + half_at(chunk, word >> 1) + 16 * (word & 1)) = x;
+    } else {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) *reinterpret_cast<u32x2*>(at + 16 * d) = u32x2{plane[d][0], plane[d][1]};
+    }
+    if (word == 0) *reinterpret_cast<u32x2*>(units + 2 * chunk) = chunk_words(as_is, up, s01, s23);
   };
-  // (one copy of the code for all four: what a short kernel runs once comes from memory)
+  // (one copy of the code for all: what a short kernel runs once comes from memory)
 #pragma unroll 1
-  for (int c = 0; c < 2 && c * step < K; ++c) {
-    put(c * step + (int)threadIdx.x * 8, v[0]);
+  for (int c = 0; c * step < K; ++c) {
+    const int k = c * step + (int)threadIdx.x * 8;
+    if (c >= 2) {
+      v[0] = *reinterpret_cast<const u32x4*>(src + (k < K ? k : 0));
+      __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0), here: behind the branch it would hold for the first loads as well
+    }
+    put(k, v[0]);
     v[0] = v[1];
-  }
-#pragma unroll 1
-  for (int k0 = 2 * step; k0 < K; k0 += step) {
-    const int k = k0 + (int)threadIdx.x * 8;
-    put(k, *reinterpret_cast<const u32x4*>(src + (k < K ? k : 0)));
   }
   return odd;
 }
@@ -289,16 +314,17 @@ __device__ __forceinline__ void clear(unsigned char* zeros, int threads) {
 }
 
 // act[slot, :] = round(silu(gate) * up) with gate / up rounded first, as vectors for the down kernel: digits of slot s at
-// vals + 4 s N, its chunks' floats at units + 2 s N / 32.
+// vals + 4 s N, its chunks' words at units + 2 s N / 32.
 // KP 1: grid (N / 64, slots), 8 waves, 8 columns each; KP 2: (N / 32, slots), four times 8 columns, two halves of the reduction.  LDS: the
 // token's K activations, zeros, a flag for every wave, the columns' sums, ROUTE: the token's ids and weights.
 // ROUTE: the ids come from the token's logits; every wave works them out for itself (at most 64 experts: four keys a lane, half
 // a microsecond against a launch of 3.5 us), and the first workgroup of a token stores them for the down kernel.
+// (64 registers: four workgroups a CU.)
 template <int DT, int ROUTE, int R, int PRE, int KP>
-__global__ void __launch_bounds__(kGateThreads, 4)
+__global__ void __launch_bounds__(kGateThreads, 8)
 few_gate_up_kernel(const uint16_t* __restrict__ X, FewRoute route, const int32_t* __restrict__ ids, const unsigned char* __restrict__ qw,
                    const uint16_t* __restrict__ sc, const uint8_t* __restrict__ zp, unsigned char* __restrict__ vals,
-                   float* __restrict__ units, int topk, int E, int K, int N) {
+                   uint32_t* __restrict__ units, int topk, int E, int K, int N) {
   extern __shared__ __align__(16) unsigned char xl[];
   unsigned char* const zeros = xl + vec_total(K);
   uint32_t* const bad = reinterpret_cast<uint32_t*>(zeros + zero_bytes(R));
@@ -334,10 +360,8 @@ few_gate_up_kernel(const uint16_t* __restrict__ X, FewRoute route, const int32_t
   if (odd) bad[wave] = 1u;
   __syncthreads();
   const u32x4 b0 = *reinterpret_cast<const u32x4*>(bad), b1 = *reinterpret_cast<const u32x4*>(bad + 4);
-  float r;
-  if (__builtin_expect((b0[0] | b0[1] | b0[2] | b0[3] | b1[0] | b1[1] | b1[2] | b1[3]) != 0u, 0))
-    r = rd.slow([&](int ch, int k) { return from_bits16<DT>(x[32 * ch + k]); }, g0, g1);
-  else r = rd.run(xl, reinterpret_cast<const float*>(xl + vec_bytes(K)), zeros, g0, g1);
+  const bool odd_row = __builtin_amdgcn_readfirstlane((int)(b0[0] | b0[1] | b0[2] | b0[3] | b1[0] | b1[1] | b1[2] | b1[3])) != 0;
+  const float r = rd.run(xl, reinterpret_cast<const uint32_t*>(xl + vec_bytes(K)), zeros, g0, g1, odd_row);
   // [part][gate, up][column]
   const float y = row_sum(r);
   if (lane < 16) col[(2 * part + (lane >> 3)) * COLS + cw + (lane & 7)] = y;
@@ -349,35 +373,37 @@ few_gate_up_kernel(const uint16_t* __restrict__ X, FewRoute route, const int32_t
     upper += col[3 * COLS + threadIdx.x];
   }
   const float a = from_bits16<DT>(to_bits16<DT>(silu_f32(from_bits16<DT>(to_bits16<DT>(gate))) * from_bits16<DT>(to_bits16<DT>(upper))));
-  uint32_t m = bits32(a) & 0x7fffffffu;
-  float sum = a;
-  max_and_sum<kXor1>(m, sum);
-  max_and_sum<kXor2>(m, sum);
-  max_and_sum<kHalfMirror>(m, sum);
-  max_and_sum<kMirror>(m, sum);
-  const uint32_t o = (uint32_t)__shfl_xor((int)m, 16, 64);
-  m = m > o ? m : o;
-  sum += __shfl_xor(sum, 16, 64);
-  const bool finite = m < 0x7f800000u;
+  uint32_t m = max_over<kMirror>(max_over<kHalfMirror>(max_over<kXor2>(max_over<kXor1>(bits32(a) & 0x7fffffffu))));
+  const auto both = __builtin_amdgcn_permlane16_swap(m, m, false, false);      // rows 0 and 1 (2 and 3) of 16 lanes
+  m = both[0] > both[1] ? both[0] : both[1];
   const int up = chunk_up(m), k = threadIdx.x & 31, chunk = (int)(blockIdx.x * COLS + threadIdx.x) >> 5;
+  const float v = a * power_of_two(up);
+  bool as_is = no_digits<DT>(m);
+  if (DT == kF16) as_is |= (uint32_t)(__ballot(v != __builtin_truncf(v)) >> (threadIdx.x & 32)) != 0u;
+  const uint32_t d = biased_digits(v) ^ 0x00808080u;
+  int s01 = ((int)(d << 24) >> 24) + (((int)(d << 16) >> 24) << 8), s23 = ((int)(d << 8) >> 24) + (((int)d >> 24) << 8);
+  s01 = sum_over<kMirror>(sum_over<kHalfMirror>(sum_over<kXor2>(sum_over<kXor1>(s01))));
+  s23 = sum_over<kMirror>(sum_over<kHalfMirror>(sum_over<kXor2>(sum_over<kXor1>(s23))));
+  const auto both01 = __builtin_amdgcn_permlane16_swap((uint32_t)s01, (uint32_t)s01, false, false);
+  const auto both23 = __builtin_amdgcn_permlane16_swap((uint32_t)s23, (uint32_t)s23, false, false);
+  s01 = (int)(both01[0] + both01[1]);
+  s23 = (int)(both23[0] + both23[1]);
   unsigned char* const at = vals + (size_t)slot * vec_bytes(N) + half_at(chunk, k >> 4);
-  if (finite) {
-    const uint32_t y = digits(a * power_of_two(up));
+  if (__builtin_expect(as_is, 0)) {
+    reinterpret_cast<uint16_t*>(at)[k & 15] = to_bits16<DT>(a);
+  } else {
     const int pos = (k & 8) + 4 * (k & 1) + ((k >> 1) & 3);
 #pragma unroll
-    for (int d = 0; d < 4; ++d) at[16 * d + pos] = (unsigned char)(y >> (8 * d));
-  } else {
-    reinterpret_cast<uint16_t*>(at)[k & 15] = to_bits16<DT>(a);
+    for (int i = 0; i < 4; ++i) at[16 * i + pos] = (unsigned char)(d >> (8 * i));
   }
-  if (k == 0)
-    *reinterpret_cast<floatx2_t*>(units + ((size_t)slot * (N >> 5) + chunk) * 2) = floatx2_t{finite ? power_of_two(-up) : __builtin_nanf(""), sum};
+  if (k == 0) *reinterpret_cast<u32x2*>(units + ((size_t)slot * (N >> 5) + chunk) * 2) = chunk_words(as_is, up, s01, s23);
 }
 
 // out[t, :] = sum over j of w[t, j] * (act[slot] . W2[e]), the products unrounded.  grid (K / 16, T), up to 8 waves,
-// 16 columns; a wave takes (slot, part of the reduction) pairs.  LDS: the token's act vectors, their chunks' floats, zeros, the pairs' results.
+// 16 columns; a wave takes (slot, part of the reduction) pairs.  LDS: the token's act vectors, their chunks' words, zeros, the pairs' results.
 template <int DT, int R, int PRE>
 __global__ void __launch_bounds__(512, 4)
-few_down_kernel(const unsigned char* vals, const float* units, const int32_t* __restrict__ ids,
+few_down_kernel(const unsigned char* vals, const uint32_t* units, const int32_t* __restrict__ ids,
                 const float* wts, const unsigned char* qw, const uint16_t* sc,
                 const uint8_t* zp, uint16_t* out, int topk, int E, int K, int N, int parts) {
   extern __shared__ __align__(16) unsigned char xl[];
@@ -430,20 +456,10 @@ few_down_kernel(const unsigned char* vals, const float* units, const int32_t* __
     float r = 0.f;
     if (some) {
       const unsigned char* const xv = xl + (size_t)j * vec_bytes(N);
-      const float* const xu = reinterpret_cast<const float*>(xl + vbytes) + (size_t)j * (N >> 5) * 2;
+      const uint32_t* const xu = reinterpret_cast<const uint32_t*>(xl + vbytes) + (size_t)j * (N >> 5) * 2;
       bool odd = false;
-      for (int i = 4 * g0 + lane; i < 4 * g1; i += 64) odd |= xu[2 * i] != xu[2 * i];
-      if (__builtin_expect(__ballot(odd) != 0ull, 0)) {
-        r = rd.slow([&](int ch, int k) {
-          const unsigned char* const at = xv + half_at(ch, k >> 4);
-          const float unit = xu[2 * ch];
-          if (unit != unit) return from_bits16<DT>(reinterpret_cast<const uint16_t*>(at)[k & 15]);
-          const signed char* const b = reinterpret_cast<const signed char*>(at) + (k & 8) + 4 * (k & 1) + ((k >> 1) & 3);
-          return (float)(((b[48] * 256 + b[32]) * 256 + b[16]) * 256 + b[0]) * unit;
-        }, g0, g1);
-      } else {
-        r = rd.run(xv, xu, zeros, g0, g1);
-      }
+      for (int i = 4 * g0 + lane; i < 4 * g1; i += 64) odd |= (int)xu[2 * i] >> 24 == kAsIs;
+      r = rd.run(xv, xu, zeros, g0, g1, __ballot(odd) != 0ull);
     }
     const float y = row_sum(r);
     if (lane < 16) ys[u * 16 + lane] = y;
@@ -499,7 +515,7 @@ static int allow_lds(const void* kern, size_t lds, bool (&allowed)[64]) {
 
 template <int DT, int ROUTE, int R, int PRE, int KP>
 static int gate_up(const void* X, const FewRoute& route, const int32_t* ids, const int32_t* qw, const void* s, const uint8_t* z, void* act,
-                   float* units, int T, int topk, int E, int K, int N, hipStream_t stream) {
+                   uint32_t* units, int T, int topk, int E, int K, int N, hipStream_t stream) {
   static bool allowed[64] = {};
   const size_t lds = gate_up_lds(K, ROUTE, R);
   const int err = allow_lds(reinterpret_cast<const void*>(few_gate_up_kernel<DT, ROUTE, R, PRE, KP>), lds, allowed);
@@ -510,7 +526,7 @@ static int gate_up(const void* X, const FewRoute& route, const int32_t* ids, con
 }
 
 template <int DT, int R, int PRE>
-static int down(const void* act, const float* units, const int32_t* ids, const float* w, const int32_t* qw, const void* s, const uint8_t* z,
+static int down(const void* act, const uint32_t* units, const int32_t* ids, const float* w, const int32_t* qw, const void* s, const uint8_t* z,
                 void* out, int T, int topk, int E, int K, int N, hipStream_t stream) {
   static bool allowed[64] = {};
   const int parts = few_down_parts(topk, N), pairs = topk * parts;
@@ -523,7 +539,7 @@ static int down(const void* act, const float* units, const int32_t* ids, const f
 }
 
 int launch_few_gate_up(const void* X, const FewRoute* route, const int32_t* ids, const int32_t* qw, const void* s, const uint8_t* z, void* act,
-                       float* units, int T, int topk, int E, int K, int N, int dt, int pre, hipStream_t stream) {
+                       uint32_t* units, int T, int topk, int E, int K, int N, int dt, int pre, hipStream_t stream) {
   const FewRoute r = route ? *route : FewRoute{};
   auto with = [&](auto route_in, auto ordered, auto parts) {
     constexpr int RT = decltype(route_in)::value, PRE = decltype(ordered)::value, KP = decltype(parts)::value;
@@ -538,7 +554,7 @@ int launch_few_gate_up(const void* X, const FewRoute* route, const int32_t* ids,
   return halves ? pick(Zero{}, Two{}) : pick(Zero{}, One{});
 }
 
-int launch_few_down(const void* act, const float* units, const int32_t* ids, const float* w, const int32_t* qw, const void* s, const uint8_t* z,
+int launch_few_down(const void* act, const uint32_t* units, const int32_t* ids, const float* w, const int32_t* qw, const void* s, const uint8_t* z,
                     void* out, int T, int topk, int E, int K, int N, int dt, int pre, hipStream_t stream) {
   auto go = dt == kF16 ? (pre ? down<kF16, kDeep, 1> : down<kF16, kDeep, 0>) : (pre ? down<kBF16, kDeep, 1> : down<kBF16, kDeep, 0>);
   return go(act, units, ids, w, qw, s, z, out, T, topk, E, K, N, stream);

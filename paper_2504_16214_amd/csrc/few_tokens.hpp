@@ -22,15 +22,15 @@ struct FewRoute {
   int32_t* ids;
   float* weights;
 };
-// What act and its chunks' floats take.
+// What act and its chunks' words take.
 size_t few_act_bytes(long long slots, int N);
 size_t few_unit_bytes(long long slots, int N);
-// act as vectors of the down kernel (few_act_bytes, 16-byte aligned) with their chunks' floats in units (few_unit_bytes, 16-byte aligned),
+// act as vectors of the down kernel (few_act_bytes, 16-byte aligned) with their chunks' words in units (few_unit_bytes, 16-byte aligned),
 // then out [T, K]; ids outside [0, E) contribute zero.  route (may be null): the ids come from there.  Group 128; X, act, out
 // and the packed words 16-byte aligned; pre: the words are in operand order.
 int launch_few_gate_up(const void* X, const FewRoute* route, const int32_t* ids, const int32_t* qw, const void* s, const uint8_t* z, void* act,
-                       float* units, int T, int topk, int E, int K, int N, int dt, int pre, hipStream_t stream);
-int launch_few_down(const void* act, const float* units, const int32_t* ids, const float* w, const int32_t* qw, const void* s, const uint8_t* z,
+                       uint32_t* units, int T, int topk, int E, int K, int N, int dt, int pre, hipStream_t stream);
+int launch_few_down(const void* act, const uint32_t* units, const int32_t* ids, const float* w, const int32_t* qw, const void* s, const uint8_t* z,
                     void* out, int T, int topk, int E, int K, int N, int dt, int pre, hipStream_t stream);
 
 }  // namespace moe
