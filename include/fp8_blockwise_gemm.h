@@ -27,7 +27,8 @@
  * Nothing is allocated and nothing synchronises with the host: kernels go to `stream`
  * (a hipStream_t; NULL = the default stream).  `workspace`: at least
  * fp8_blockwise_gemm_workspace_bytes(M, N, K) bytes, 256-byte aligned (float32 partial planes
- * when the reduction is split over workgroups; may be NULL when that size is 0).  Some shapes of more
+ * when the reduction is split over workgroups; may be NULL when that size is 0).  Up to 64 rows it is asked
+ * for where a reduction would be split, also where the kernel that then runs needs no planes and leaves it untouched.  Some shapes of more
  * than 64 rows also run with less, or with none, in fewer splits and more time; the float32 sums of
  * such a call are then rounded in another order than with the full workspace.
  * Returns a moe_status value (0 = ok, 1 = invalid argument, 2 = unsupported shape,

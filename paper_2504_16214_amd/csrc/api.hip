@@ -535,9 +535,11 @@ static void fp8_medium_plan(int M, int N, int KB, int& bm, int& bn, int& splits)
 // us.  Groups: a start; the kilobytes of the fullest CU and of the mean one; the blocks of one group (and by rows); the
 // workgroups of the fullest CU (and by rows); its blocks by rows squared.  Planes: a start; a second launch; the blocks of a
 // workgroup (and by rows); a million weights; outputs of all planes; activations.  Fitted to 7348 random calls (N 64 ... 51200,
-// K 128 ... 28160), mean error 6 to 8 %.  A tenth has to be gained, and beyond 64 million weights there is little to gain: of those
-// calls 2300 are taken, 1.32x on average, 53 of them slower by more than 3 % with weights in one of the two places (0.83 the worst).
-// us, planes then groups, weights in the cache (in memory): 16 x 3968 x 3328 7.8 / 4.8 (9.1 / 6.6), 64 x 6656 x 2688 11.7 / 7.4 (12.3 / 9.5),
+// K 128 ... 28160), mean error 6 to 8 %.  Beyond 64 million weights there is little to gain.  A tenth has to be gained, a quarter where the planes
+// are one and no second launch goes away, or where the activations are large: below that 23 of 1600 calls were slower by more than 3 % with weights
+// in one of the two places (15 x 2432 x 13952, from memory 17.2 / 20.3 the worst; 5 % at unsplit ones, from the cache), and now one is (0.969) of the 2565 of 2800
+// random calls that are still taken, 1.41x on average from the cache and 1.44x from memory.  The plan is that of a full workspace: up to 64 rows none is accepted with fewer planes.
+// us, planes then groups, weights in the cache (in memory): 16 x 3968 x 3328 7.8 / 4.8 (9.1 / 6.6), 54 x 6016 x 1408 7.6 / 5.8 (11.6 / 9.1),
 // 1 x 2048 x 7168 8.4 / 5.8 (9.8 / 7.7), 16 x 12800 x 1024 6.9 / 4.7 (7.9 / 5.9), 1 x 10240 x 5120 12.6 / 10.7 (15.7 / 12.9);
 // left with planes 64 x 10240 x 5120 16.6 / 19.7 (23.6 / 28.5), 16 x 5120 x 25600 25.4 / 32.6 (30.6 / 51).
 static bool fp8_groups_pay(int M, int N, int K, const Fp8Plan& pl, int& bn, int& groups) {
@@ -549,10 +551,11 @@ static bool fp8_groups_pay(int M, int N, int K, const Fp8Plan& pl, int& bn, int&
   const double rows = pl.bm / 16, nk = (double)N * K / 1e6;
   const int per = (KB + pl.splits - 1) / pl.splits;
   const double planes = 2.64 + (pl.splits > 1 ? 2.84 : 0) + per * (0.293 + 0.00617 * rows) + 0.114 * nk + 1.18 * pl.splits * (double)M * N / 1e6 + 4.19 * (double)M * K / 1e6;
-  double best = planes / 1.1;
+  double best = planes / (pl.splits == 1 || (long long)M * K >= 65536 ? 1.25 : 1.1);
   bool pays = false;
   for (const auto& f : kFit) {
-    if (KB < f.groups || (f.groups == 8 && pl.bm > 16)) continue;      // (eight groups of 32 rows are never the best, of 64 they do not fit the LDS)
+    // (eight groups of 32 rows are never the best, of 64 they do not fit the LDS; 64 features of 16 rows gain too little)
+    if (KB < f.groups || (f.groups == 8 && pl.bm > 16) || (f.bn == 64 && pl.bm == 16)) continue;
     const int pass = f.bn / 2, a_rows = (pl.bm + pass - 1) / pass * pass;      // rows of a load pass; activation rows held
     const double kb = ((a_rows + f.bn) * 128 + f.bn * 16) / 1e3, wgs = (double)(N / f.bn) / 256, full = ceil(wgs), b = (KB + f.groups - 1) / f.groups;
     const double us = f.start + f.most * full * KB * kb + f.mean * wgs * KB * kb + b * (f.blocks + f.blocks_rows * rows) + full * (f.wgs + f.wgs_rows * rows) + f.rows2 * full * KB * rows * rows / 10;

@@ -781,7 +781,7 @@ int launch_fp8_gemm(const GemmParams& p, int bm, int bn, hipStream_t stream) {
 int launch_fp8_kgroups(const GemmParams& p, int bm, int bn, int kg, hipStream_t stream) {
   if (p.K / 128 < kg || p.sorted_slot_ids || p.k_splits != 1) return (int)hipErrorInvalidValue;      // (every group has a block of the reduction)
 #define FP8_KG(BMv, BNv, WNv, MTv, KGv) if (bm == BMv && bn == BNv && kg == KGv) return launch_one<1, WNv, MTv, 1, 2, KGv>(p, stream);
-  FP8_KG(16, 16, 1, 1, 4) FP8_KG(16, 16, 1, 1, 8) FP8_KG(16, 32, 2, 1, 4) FP8_KG(16, 64, 4, 1, 2)
+  FP8_KG(16, 16, 1, 1, 4) FP8_KG(16, 16, 1, 1, 8) FP8_KG(16, 32, 2, 1, 4)
   FP8_KG(32, 16, 1, 2, 4) FP8_KG(32, 32, 2, 2, 4) FP8_KG(32, 64, 4, 2, 2)
   FP8_KG(64, 16, 1, 4, 4) FP8_KG(64, 32, 2, 4, 4) FP8_KG(64, 64, 4, 4, 2)
 #undef FP8_KG

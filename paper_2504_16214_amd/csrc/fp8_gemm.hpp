@@ -38,7 +38,7 @@ int launch_fp8_split_reduce(const float* planes, int k_splits, long long mn, voi
                             hipStream_t stream);
 
 // Dense, unsplit, up to 64 rows: workgroups of bn features whose kg groups of waves share the reduction (K / 128 >= kg);
-// (bn, kg) in {(16, 4), (16, 8), (32, 4), (64, 2)}, (16, 8) only with bm 16.
+// (bn, kg) in {(16, 4), (16, 8), (32, 4), (64, 2)}, (16, 8) only with bm 16, (64, 2) not with it.
 int launch_fp8_kgroups(const GemmParams& p, int bm, int bn, int kg, hipStream_t stream);
 
 int launch_fp8_mfma_loop(float* sink, int grid, int iters, hipStream_t stream);

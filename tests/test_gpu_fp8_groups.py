@@ -17,7 +17,8 @@ if torch.cuda.is_available():
 SHAPES = [  # rows, features, reduction: 16 features and 4 groups, 16 and 8, 32 and 4, 64 and 2, by row tile
     (1, 64, 512), (15, 320, 640), (16, 192, 1920), (9, 2048, 7168), (16, 6656, 512),
     (17, 64, 512), (31, 640, 1152), (32, 1472, 2688), (32, 6656, 640), (21, 14400, 1152), (15, 13952, 512),
-    (33, 64, 896), (63, 192, 1152), (64, 1472, 1152), (33, 6656, 1152), (64, 12800, 1024)]
+    (33, 64, 896), (63, 192, 1152), (64, 1472, 1152), (33, 6656, 1152), (64, 12800, 1024),
+    (16, 7744, 1024), (21, 4160, 1024), (32, 8256, 1024), (33, 4160, 1024)]
 
 
 @pytest.mark.parametrize("rows,n,k", SHAPES)
@@ -50,3 +51,19 @@ def test_groups_match_the_oracle(rows, n, k):
     finally:
         M_.fp8_set_plan_override(0, 0, 0, 0)
     assert float((tiles - out[torch.float32]).norm() / tiles.norm()) <= 2.0 ** -24 * (k // 128 + 8)
+
+
+@pytest.mark.parametrize("rows,n,k", [(15, 2432, 13952), (24, 192, 4608), (33, 1024, 4096)])
+def test_calls_left_to_the_planes(rows, n, k):
+    """Splits that lie too close to call, or are faster: the planes are written."""
+    say(f"fp8 gemm planes M={rows} N={n} K={k}")
+    inp = make_fp8_inputs(Fp8GemmConfig("p", M=rows, N=n, K=k, seed=rows + n + k))
+    A, sa, B, sb = (torch.from_numpy(x).cuda() for x in (inp.a_codes, inp.a_scale, inp.b_codes, inp.b_scale))
+    ws = torch.full((M_.fp8_blockwise_gemm_workspace_bytes(rows, n, k),), 255, dtype=torch.uint8, device="cuda")
+    out = torch.empty(rows, n, dtype=torch.bfloat16, device="cuda")
+    M_.fp8_blockwise_gemm(A, sa, B, sb, out, ws)
+    torch.cuda.synchronize()
+    assert bool((ws[:rows * n * 4] != 255).any()), "another kernel ran"
+    want = F.blockwise_gemm(inp.a_codes, inp.a_scale, inp.b_codes, inp.b_scale, "bf16")
+    bound = error_bound(want, inp.a_codes, inp.a_scale, inp.b_codes, inp.b_scale)
+    assert float((np.abs(out.double().cpu().numpy() - want) / bound).max()) <= 1.0
