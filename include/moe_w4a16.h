@@ -154,7 +154,13 @@ int moe_combine(const void* Y, const float* topk_weights, void* out,
 int moe_combine_masked(const void* Y, const float* topk_weights, const int32_t* topk_ids, int E, void* out,
                        int T, int topk, int K, moe_dtype dt, void* stream);
 
-/* Bytes of workspace moe_w4a16_layer needs for these sizes (0 if invalid). */
+/*
+ * Bytes of workspace moe_w4a16_layer needs for these sizes (0 if invalid); enough for its best
+ * kernels at T tokens and for the few-token kernels at fewer.  Ask again after an update of the library: a layer
+ * call also takes what an earlier one answered, but where act is long beside the output (N above about 1.8 K)
+ * the few-token kernels need more, and with less the call runs on a tile, in 1.2 to 2 times the time and with
+ * float32 sums in another order.
+ */
 size_t moe_w4a16_layer_workspace_bytes(int T, int K, int N, int E, int topk, moe_dtype dt);
 
 /*

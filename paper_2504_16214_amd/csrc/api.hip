@@ -477,8 +477,6 @@ static Workspace carve(long long T, int K, int N, int E, int topk, int dt) {
   // The vector products of a few tokens hold act in twice the bytes, from its place on into that of Y.
   w.few_units = w.act + round_up(few_act_bytes(S, N), 256);
   w.few_end = w.few_units + few_unit_bytes(S, N);
-  const bool few = S <= 32 && few_tokens_fit(topk, K, N) && (few_tokens_pay((int)T, topk, E, K, N, dt, 0) || few_tokens_pay((int)T, topk, E, K, N, dt, 1));
-  if (few) o = std::max(o, round_up(w.few_end, 256));
   // Planes of the 64-slot tile's split down product.  A workspace without them runs it in fewer splits, whose sums are
   // rounded in another order, so sizes that the built-in array serves get no more of them than it holds: the two
   // calls then have the same bits.
@@ -489,6 +487,16 @@ static Workspace carve(long long T, int K, int N, int E, int topk, int dt) {
   while (w.mid_splits > 1 && (mid ? with_planes(w.mid_splits) > most : w.Y + plane * w.mid_splits > w.base)) --w.mid_splits;
   w.total = mid ? std::max(o, with_planes(w.mid_splits)) : o;
   return w;
+}
+// What the size query answers: room for T tokens, and for the most of fewer tokens that run as vector products, whose act
+// may be longer than everything the tiles need for T (13 to 16 tokens of 256 x 1024, 8 experts, top 2, with the size of 17 to 22).
+static size_t layer_workspace(int T, int K, int N, int E, int topk, int dt) {
+  size_t o = carve(T, K, N, E, topk, dt).total;
+  if (few_tokens_fit(topk, K, N))
+    for (int t = std::min(T, 32 / topk); t > 0; --t)
+      if (few_tokens_pay(t, topk, E, K, N, dt, 0) || few_tokens_pay(t, topk, E, K, N, dt, 1))
+        return std::max(o, round_up(carve(t, K, N, E, topk, dt).few_end, 256));
+  return o;
 }
 
 }  // namespace moe
@@ -754,7 +762,7 @@ int moe_combine_masked(const void* Y, const float* topk_weights, const int32_t* 
 
 size_t moe_w4a16_layer_workspace_bytes(int T, int K, int N, int E, int topk, moe_dtype dt) {
   if (T < 0 || K < 1 || N < 1 || E < 1 || topk < 1) return 0;
-  return carve(T, K, N, E, topk, (int)dt).total;
+  return layer_workspace(T, K, N, E, topk, (int)dt);
 }
 
 int moe_layer_block_m(int T, int E, int topk) {
@@ -922,7 +930,7 @@ static int layer_impl(const void* X, const int32_t* topk_ids, const float* topk_
   if (((uintptr_t)out % 16) != 0) return fail(MOE_INVALID_ARGUMENT, "out must be 16-byte aligned");
   const Workspace w = carve(T, K, N, E, topk, (int)dt);
   if (workspace_bytes < w.base)
-    return fail(MOE_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", workspace_bytes, w.total);
+    return fail(MOE_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", workspace_bytes, layer_workspace(T, K, N, E, topk, (int)dt));
   const long long S = (long long)T * topk;
   if (S > 0x7fffffffLL / 2) return fail(MOE_UNSUPPORTED_SHAPE, "T*topk too large");
   // Operand-order weights: the same shapes and alignments at every token number, whichever kernel runs.
@@ -1497,7 +1505,7 @@ int fp8_moe_layer(const void* X, const int32_t* topk_ids, const float* topk_weig
   if (S > 0x7fffffffLL / 2) return fail(MOE_UNSUPPORTED_SHAPE, "T*topk too large");
   const Fp8Workspace w = fp8_carve(T, K, N, E, topk);
   if (workspace_bytes < w.total)
-    return fail(MOE_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", workspace_bytes, w.total);
+    return fail(MOE_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", workspace_bytes, layer_workspace(T, K, N, E, topk, (int)dt));
   unsigned char* base = (unsigned char*)workspace;
   int32_t* counts = (int32_t*)(base + w.counts);
   int32_t* offsets = (int32_t*)(base + w.offsets);

@@ -85,6 +85,15 @@ def test_row_sums_are_reserved_where_the_two_group_tile_is_chosen(binding, T, K,
     assert extra == (-(-S * (N // 128) * 4 // 256) * 256 if row_sums else 0)
 
 
+@pytest.mark.parametrize("K,N,E,topk", [(256, 1024, 8, 2), (512, 8192, 4, 1)])
+@pytest.mark.parametrize("dt", [0, 1])
+def test_a_workspace_serves_fewer_tokens_too(binding, K, N, E, topk, dt):
+    """act of a few tokens can be longer than what the tiles need for a few more: the query's answer holds it all the same
+    (4 bytes a value and 8 for 32, behind the tables)."""
+    sizes = [binding.moe_w4a16_layer_workspace_bytes(T, K, N, E, topk, dt) for T in range(1, 41)]
+    assert sizes == sorted(sizes)
+
+
 def test_layer_block_choice_tracks_rows_per_expert(binding):
     assert binding.moe_layer_block_m(128, 256, 8) == 16      # about 4 rows per expert
     assert binding.moe_layer_block_m(64, 8, 2) == 32         # 16 rows per expert
