@@ -313,22 +313,25 @@ def test_float32_output_matches_unrounded_oracle(splits):
     assert worst <= 1.0
 
 
-def test_gemm_with_split_reduction_is_graph_capturable():
-    """Nothing is allocated, nothing synchronises and both kernels go to the given stream, so the
-    call (GEMM into float32 planes + plane reduction) can be recorded into a HIP graph; every replay,
+@pytest.mark.parametrize("rows,n,k,planes", [(24, 1024, 2048, False), (33, 1024, 4096, True)])
+def test_gemm_with_split_reduction_is_graph_capturable(rows, n, k, planes):
+    """Nothing is allocated, nothing synchronises and every kernel goes to the given stream, so the
+    call (GEMM into float32 planes + plane reduction, or one kernel whose waves split the reduction and that leaves the
+    planes alone) can be recorded into a HIP graph; every replay,
     with eager work and synchronisations in between and with the workspace overwritten, equals the
     eager result bit for bit."""
-    cfg = Fp8GemmConfig("graph", M=24, N=1024, K=2048, seed=71)
+    cfg = Fp8GemmConfig("graph", M=rows, N=n, K=k, seed=71)
     say(f"fp8 gemm graph capture {cfg}")
     inp = make_fp8_inputs(cfg)
     A, B = torch.from_numpy(inp.a_codes).cuda(), torch.from_numpy(inp.b_codes).cuda()
     sa, sb = torch.from_numpy(inp.a_scale).cuda(), torch.from_numpy(inp.b_scale).cuda()
     nbytes = M_.fp8_blockwise_gemm_workspace_bytes(cfg.M, cfg.N, cfg.K)
     assert nbytes > 0, "the shape is meant to take the split-reduction path"
-    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    ws = torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda")
     eager = torch.full((cfg.M, cfg.N), float("nan"), dtype=torch.bfloat16, device="cuda")
     M_.fp8_blockwise_gemm(A, sa, B, sb, eager, ws)
     torch.cuda.synchronize()
+    assert bool((ws != 255).any()) == planes
     out = torch.zeros_like(eager)
     side = torch.cuda.Stream()
     graph = torch.cuda.CUDAGraph()
