@@ -184,14 +184,14 @@ def test_routing_inside_the_gate_up_launch(E, topk, T):
 
 @pytest.mark.parametrize("K,N,E,topk,T", [(128, 30592, 4, 1, 1), (128, 30592, 4, 1, 2), (128, 15104, 4, 2, 1), (256, 30592, 4, 1, 2)])
 def test_the_chunk_floats_stay_within_the_workspace(K, N, E, topk, T):
-    """The longest rows against the shortest outputs: the floats of act's chunks, kept where the down product's planes
-    are on the other paths, take nearly all of them.  Nothing behind the workspace of the size query is written."""
+    """The longest rows against the shortest outputs: act's digits and its chunks' words, from where act lies on the other
+    paths on, need more than those do.  Nothing behind the workspace of the size query is written."""
     cfg = MoEConfig("few_room", T=T, K=K, N=N, E=E, topk=topk, group=128, dtype="f16", seed=K + T)
     say(f"room for the chunk floats {cfg}")
     inp = make_inputs(cfg)
     d = U.DevInputs(inp)
     need = M.moe_w4a16_layer_workspace_bytes(T, K, N, E, topk, M.MOE_F16)
-    assert cfg.S * (N // 32) * 4 <= need - cfg.S * N * 2
+    assert cfg.S * (N * 4 + N // 32 * 8) <= need
     buf = torch.full((need + 4096,), 255, dtype=torch.uint8, device="cuda")
     out = torch.full((T, K), float("nan"), dtype=torch.float16, device="cuda")
     M.moe_w4a16_layer(d.X, d.ids, d.w, d.qw1, d.s1, d.z1, d.qw2, d.s2, d.z2, out, 128, buf[:need])

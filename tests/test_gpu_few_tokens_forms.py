@@ -17,7 +17,7 @@ if torch.cuda.is_available():
     import gpu_util as U
 
 
-# Workgroups of 64 columns (N / 64 * T * topk): 254 | 256; K 384 (never halved), 512 and 640 (2 + 2, 4 + 1 groups), 896 (4 + 3);
+# Workgroups of 64 columns (N / 64 * T * topk): 252 | 256; K 384 (never halved), 512 and 640 (2 + 2, 2 + 3 groups), 896 (4 + 3);
 # K 4224, 8320 and 8448: more activations than the first loads bring (1, 2 rounds)
 @pytest.mark.parametrize("K,N,E,topk,T", [(512, 8064, 4, 1, 2), (512, 8192, 4, 1, 2), (384, 128, 4, 2, 3), (640, 384, 8, 3, 2), (896, 896, 8, 1, 5),
                                           (4224, 256, 4, 2, 1), (8320, 128, 4, 1, 1), (8448, 1024, 16, 4, 1)])
