@@ -21,9 +21,11 @@
 //
 // What bounds it: two launches of 5 to 6 us each beside the stream of weights (gate/up of one token of 7168 x 2048, 256 experts, top 8, 118 MB from
 // memory, 24.9 us and 4.7 TB/s; down 16.0; 44.5 -> 40.5 the call.  With products of float16 pairs on the vector unit, 77 instructions a KB of
-// weights where there are 40 now, they took 27.8 and 19.4, and no less with the weights in the cache).  Zero points taken out in whole numbers, and
-// the chunks kept as they are, cost 1 % (that call with its weights in the cache 34.2 -> 34.5 us; 12 tokens of 1024 x 1024, 64 experts, top 2, 12.5 -> 12.8),
-// where act is so large that most fp16 chunks are kept, more (one token of 28672 x 1024, 8 experts, top 2, 37.2 -> 50.7; with float16 pairs 56.4).
+// weights where there are 40 now, they took 27.8 and 19.4, and no less with the weights in the cache).  Zero points taken out in whole numbers
+// cost 1 % (that call with its weights in the cache 34.2 -> 34.5 us; 12 tokens of 1024 x 1024, 64 experts, top 2, 12.5 -> 12.8).  A group with a chunk kept
+// as it is takes 76 instructions a lane more.  Activations as wide as x e^(1.5 y), act in the hundreds, so that most fp16 chunks are kept: 120 random
+// calls of 8 to 100 us take 1.01 times what float16 pairs took with weights in the cache, 1.04 times with them in memory, the worst 1.37 (in loops of four weights
+// with a wait in each they took 1.19, the worst 2).
 //
 // A wave covers 16 weight rows, four groups (4 KB) in flight, the next four asked for as each is used.  The order in which a
 // row is summed is the same in both weight layouts.  Weights go through the caches: slots that share
@@ -41,6 +43,7 @@ namespace moe {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 // A vector of k activations: for every group of 128, [half h of a chunk][chunk][digit][16 bytes], the bytes of a half (16
@@ -211,8 +214,29 @@ struct Rows16 {
   }
   // A chunk's sum weight by weight, at: its activations as they are, nz: minus the zero point.
   static __device__ __forceinline__ float by_values(const u32x4& v, const unsigned char* at, int nz) {
-    const float z = (float)nz;
     float t = 0.f;
+    if constexpr (DT == kF16) {
+      // q - z as two float16 at a time (1024 + q less 1024 + z: whole numbers that float16 holds), the products in float32
+      const f16x2 z = {(_Float16)(nz - 1024), (_Float16)(nz - 1024)};
+#pragma unroll 1
+      for (int h = 0; h < 2; ++h) {
+        const u32x4 x0 = *reinterpret_cast<const u32x4*>(at + 256 * h), x1 = *reinterpret_cast<const u32x4*>(at + 256 * h + 16);
+#pragma unroll
+        for (int word = 0; word < 2; ++word) {
+          const uint32_t nibbles = h == 0 ? (word == 0 ? v.x : v.y) : word == 0 ? v.z : v.w;
+          const u32x4& x = word == 0 ? x0 : x1;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {      // weights k and k + 4 of the word's eight
+            const f16x2 w = __builtin_bit_cast(f16x2, ((nibbles >> (4 * k)) & 0x000F000Fu) | 0x64006400u) + z;
+            const f16x2 a = __builtin_bit_cast(f16x2, (uint32_t)x[k >> 1]), b = __builtin_bit_cast(f16x2, (uint32_t)x[2 + (k >> 1)]);
+            t = __builtin_fmaf((float)w.x, (float)(k & 1 ? a.y : a.x), t);
+            t = __builtin_fmaf((float)w.y, (float)(k & 1 ? b.y : b.x), t);
+          }
+        }
+      }
+      return t;
+    }
+    const float z = (float)nz;
 #pragma unroll 1
     for (int i = 0; i < 8; ++i) {
       const uint32_t word = (i < 2 ? v.x : i < 4 ? v.y : i < 6 ? v.z : v.w) >> (16 * (i & 1)), even = word & 0x0F0Fu, odd = (word >> 4) & 0x0F0Fu;
