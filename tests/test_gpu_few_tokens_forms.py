@@ -34,6 +34,37 @@ def test_forms_of_the_gate_up_product(K, N, E, topk, T, dtype):
     assert M.moe_last_gemm_plan()["mt"] == 0
 
 
+# act vectors of more than 80 KB beside more than 256 workgroups: two rounds of 4 slots, 2 + 1, 5 + 4, three rounds of one, and either side of both lines
+@pytest.mark.parametrize("K,N,E,topk,T", [(4224, 2432, 8, 8, 1), (4224, 6528, 4, 3, 1), (2176, 2304, 16, 9, 2), (4224, 7680, 4, 3, 1),
+                                          (4096, 2432, 8, 8, 1), (4224, 2304, 8, 8, 1)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_act_in_rounds(K, N, E, topk, T, dtype):
+    cfg = MoEConfig("few_rounds", T=T, K=K, N=N, E=E, topk=topk, group=128, dtype=dtype, seed=K + N + T)
+    inp = make_inputs(cfg)
+    inp.topk_ids[-1, -2] = -1                 # a slot without an expert, in the last round
+    say(f"rounds {cfg}")
+    check_case(inp, str(cfg))
+    assert M.moe_last_gemm_plan()["mt"] == 0
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_act_in_rounds_has_the_same_bits_in_operand_order(dtype):
+    """4 + 3 slots."""
+    cfg = MoEConfig("few_rounds", T=1, K=5120, N=3072, E=8, topk=7, group=128, dtype=dtype, seed=12)
+    say(f"rounds, operand order {cfg}")
+    d = U.DevInputs(make_inputs(cfg))
+    plain = U.run_layer(d)
+    assert M.moe_last_gemm_plan()["mt"] == 0
+    p1, p2 = torch.empty_like(d.qw1), torch.empty_like(d.qw2)
+    M.moe_repack_qweight(d.qw1, False, p1)
+    M.moe_repack_qweight(d.qw2, True, p2)
+    out = torch.full_like(plain, float("nan"))
+    ws = torch.full((M.moe_w4a16_layer_workspace_bytes(1, 5120, 3072, 8, 7, M.MOE_F16 if dtype == "f16" else M.MOE_BF16),), 255, dtype=torch.uint8, device="cuda")
+    M.moe_w4a16_layer_prepacked(d.X, d.ids, d.w, p1, d.s1, d.z1, p2, d.s2, d.z2, out, 128, ws)
+    torch.cuda.synchronize()
+    assert M.moe_last_gemm_plan()["mt"] == 0 and bool(plain.isfinite().all()) and torch.equal(out.view(torch.int16), plain.view(torch.int16))
+
+
 def test_a_workspace_without_room_for_the_digits_runs_on_a_tile():
     """A long act beside a short output: the bytes that the tiles need do not hold act as digits, and one block
     less than the size query names is between the two.  Accepted
