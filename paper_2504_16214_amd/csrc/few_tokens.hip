@@ -15,17 +15,19 @@
 // together; a weight that is its zero point contributes nothing, however large its activation.  Then it multiplies by the
 // group's scale.  Some chunks have no such form: fp16 with a value that is no multiple of its unit (only beside one of 64
 // and more, 2^19 times as large), bf16 with nothing above 2^-97, either with an infinity or a NaN.  They are kept as
-// they are and their weights multiplied one by one in float32 (by_values).  bf16 values below 2^-22 of the largest of their
+// they are and their weights multiplied one by one in float32 (by_values), unless they are fp16 with kMany values of a 32nd of the largest and more:
+// those lose 2^-29 of the largest where a float32 sum that meets but one of the many rounds at 2^-24 of it (simulated on 2048 values, silu(g) u, with
+// standard deviations of 4 to 100 and weights of which 3 to 97 % are zero: the same error as float32 sums of all, 5e-9 to 1.5e-8).  Without that most chunks are
+// kept where act is in the hundreds, as gates of -10 and less leave a millionth beside it.  bf16 values below 2^-22 of the largest of their
 // chunk lose what is below 2^-29 of it: one in a thousand chunks of act has one, and kept as they are they cost 2 to 3 us a
 // call; the products with 128 + q that this form replaced lost 2^-24 of 143 times the largest.
 //
 // What bounds it: two launches of 5 to 6 us each beside the stream of weights (gate/up of one token of 7168 x 2048, 256 experts, top 8, 118 MB from
 // memory, 24.9 us and 4.7 TB/s; down 16.0; 44.5 -> 40.5 the call.  With products of float16 pairs on the vector unit, 77 instructions a KB of
 // weights where there are 40 now, they took 27.8 and 19.4, and no less with the weights in the cache).  Zero points taken out in whole numbers
-// cost 1 % (that call with its weights in the cache 34.2 -> 34.5 us; 12 tokens of 1024 x 1024, 64 experts, top 2, 12.5 -> 12.8).  A group with a chunk kept
-// as it is takes 76 instructions a lane more.  Activations as wide as x e^(1.5 y), act in the hundreds, so that most fp16 chunks are kept: 120 random
-// calls of 8 to 100 us take 1.01 times what float16 pairs took with weights in the cache, 1.04 times with them in memory, the worst 1.37 (in loops of four weights
-// with a wait in each they took 1.19, the worst 2).
+// cost 1 % (that call with its weights in the cache 34.4 -> 34.7 us, from memory 43.9 -> 44.7; 12 tokens of 1024 x 1024, 64 experts, top 2, 12.1 -> 12.3 and 18.4).
+// Activations as wide as x e^(1.5 y), act in the hundreds: 20 calls of 15 to 100 us that were the slowest beside the float16 pairs while every chunk with
+// a loss was kept (0.63 of their speed from the cache, 0.66 from memory) are 1.25 and 1.14 times as fast.
 //
 // A wave covers 16 weight rows, four groups (4 KB) in flight, the next four asked for as each is used.  The order in which a
 // row is summed is the same in both weight layouts.  Weights go through the caches: slots that share
@@ -43,7 +45,6 @@ namespace moe {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 // A vector of k activations: for every group of 128, [half h of a chunk][chunk][digit][16 bytes], the bytes of a half (16
@@ -53,6 +54,8 @@ typedef __attribute__((address_space(3))) void* lptr_t;
 // an exponent, and where digits would lie its 16-bit activations, 16 at the start of each half's 64 bytes.
 constexpr int kAsIs = -128;
 constexpr uint32_t kLossFrom = 0x42800000u;      // 64: below it every fp16 value is a multiple of its chunk's unit
+constexpr uint32_t kLarge = 5u << 23;            // (an exponent's difference: a 32nd of the largest)
+constexpr int kMany = 4;
 __host__ __device__ __forceinline__ int vec_bytes(int k) { return 4 * k; }
 __host__ __device__ __forceinline__ int vec_total(int k) { return vec_bytes(k) + (k >> 5) * 8; }
 __device__ __forceinline__ int half_at(int chunk, int h) { return (chunk >> 2) * 512 + h * 256 + (chunk & 3) * 64; }      // + 16 digit
@@ -212,31 +215,11 @@ struct Rows16 {
     }
     return acc;
   }
-  // A chunk's sum weight by weight, at: its activations as they are, nz: minus the zero point.
+  // A chunk's sum weight by weight, at: its activations as they are, nz: minus the zero point.  (A short loop: straight-line code, 1.4 times as fast where
+  // every chunk is kept, cost the calls without one 2 %, cold as a short kernel's instructions are.)
   static __device__ __forceinline__ float by_values(const u32x4& v, const unsigned char* at, int nz) {
-    float t = 0.f;
-    if constexpr (DT == kF16) {
-      // q - z as two float16 at a time (1024 + q less 1024 + z: whole numbers that float16 holds), the products in float32
-      const f16x2 z = {(_Float16)(nz - 1024), (_Float16)(nz - 1024)};
-#pragma unroll 1
-      for (int h = 0; h < 2; ++h) {
-        const u32x4 x0 = *reinterpret_cast<const u32x4*>(at + 256 * h), x1 = *reinterpret_cast<const u32x4*>(at + 256 * h + 16);
-#pragma unroll
-        for (int word = 0; word < 2; ++word) {
-          const uint32_t nibbles = h == 0 ? (word == 0 ? v.x : v.y) : word == 0 ? v.z : v.w;
-          const u32x4& x = word == 0 ? x0 : x1;
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {      // weights k and k + 4 of the word's eight
-            const f16x2 w = __builtin_bit_cast(f16x2, ((nibbles >> (4 * k)) & 0x000F000Fu) | 0x64006400u) + z;
-            const f16x2 a = __builtin_bit_cast(f16x2, (uint32_t)x[k >> 1]), b = __builtin_bit_cast(f16x2, (uint32_t)x[2 + (k >> 1)]);
-            t = __builtin_fmaf((float)w.x, (float)(k & 1 ? a.y : a.x), t);
-            t = __builtin_fmaf((float)w.y, (float)(k & 1 ? b.y : b.x), t);
-          }
-        }
-      }
-      return t;
-    }
     const float z = (float)nz;
+    float t = 0.f;
 #pragma unroll 1
     for (int i = 0; i < 8; ++i) {
       const uint32_t word = (i < 2 ? v.x : i < 4 ? v.y : i < 6 ? v.z : v.w) >> (16 * (i & 1)), even = word & 0x0F0Fu, odd = (word >> 4) & 0x0F0Fu;
@@ -284,10 +267,16 @@ __device__ __forceinline__ bool stage_row(const uint16_t* src, int K, unsigned c
     for (int t = 0; t < 8; ++t) y[t] = biased_digits(scaled(t));
     bool as_is = no_digits<DT>(m);
     if (DT == kF16 && m >= kLossFrom) {
+      const uint32_t large = m + ((uint32_t)up << 23) - kLarge;
       uint32_t rest = 0u;
+      int many = 0;
 #pragma unroll
-      for (int t = 0; t < 8; ++t) rest |= bits32(scaled(t) - __builtin_truncf(scaled(t)));
-      as_is |= max_over<kXor2>(max_over<kXor1>(rest << 1)) != 0u;      // (no sign: what is whole leaves a zero)
+      for (int t = 0; t < 8; ++t) {
+        rest |= bits32(scaled(t) - __builtin_truncf(scaled(t)));
+        many += (bits32(scaled(t)) & 0x7fffffffu) >= large;
+      }
+      rest = max_over<kXor2>(max_over<kXor1>(rest << 1));              // (no sign: what is whole leaves a zero)
+      as_is |= rest != 0u && sum_over<kXor2>(sum_over<kXor1>(many)) < kMany;
     }
     // digit planes: bytes of values 0, 2, 4, 6 and of 1, 3, 5, 7
     unsigned char* const at = xl + half_at(chunk, word >> 1) + 8 * (word & 1);
@@ -403,7 +392,11 @@ few_gate_up_kernel(const uint16_t* __restrict__ X, FewRoute route, const int32_t
   const int up = chunk_up(m), k = threadIdx.x & 31, chunk = (int)(blockIdx.x * COLS + threadIdx.x) >> 5;
   const float v = a * power_of_two(up);
   bool as_is = no_digits<DT>(m);
-  if (DT == kF16) as_is |= (uint32_t)(__ballot(v != __builtin_truncf(v)) >> (threadIdx.x & 32)) != 0u;
+  if (DT == kF16) {
+    const int half = threadIdx.x & 32;
+    const uint32_t rest = (uint32_t)(__ballot(v != __builtin_truncf(v)) >> half), large = (uint32_t)(__ballot((bits32(a) & 0x7fffffffu) >= m - kLarge) >> half);
+    as_is |= rest != 0u && __builtin_popcount(large) < kMany;      // (a rest: the largest is 64 or more)
+  }
   const uint32_t d = biased_digits(v) ^ 0x00808080u;
   int s01 = ((int)(d << 24) >> 24) + (((int)(d << 16) >> 24) << 8), s23 = ((int)(d << 8) >> 24) + (((int)d >> 24) << 8);
   s01 = sum_over<kMirror>(sum_over<kHalfMirror>(sum_over<kXor2>(sum_over<kXor1>(s01))));

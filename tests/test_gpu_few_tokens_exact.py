@@ -83,6 +83,28 @@ def test_a_large_activation_whose_weights_are_zero(dtype, ratio, order):
 
 
 @pytest.mark.parametrize("order", ["plain", "operand"])
+def test_three_large_activations_whose_weights_are_zero(order):
+    """The most large values of a chunk beside which small ones are kept, 2^-24 of them: nothing else is left of the chunk."""
+    inp, rng = inputs("f16", 24)
+    where = np.concatenate([32 * c + rng.permutation(32)[:3] for c in range(K // 32)])
+    small = 2.0 ** (15 - 24)
+    x = rng.normal(size=(2, K)).clip(-3, 3) * small / 4
+    x[:, where] = np.where(rng.random((2, where.size)) < 0.5, -1, 1) * small * 2.0 ** 24
+    inp.qw1 = near_zero_points(rng, inp.z1, K, where)
+    s1 = np.full(inp.s1_bits.shape, 0.1 / small) * rng.uniform(0.7, 1.3, inp.s1_bits.shape)
+    inp.qw2 = near_zero_points(rng, inp.z2, N, np.array([], dtype=int))
+    check(inp, x, s1, rng.uniform(0.05, 0.1, inp.s2_bits.shape), order, "three")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_wide_activations(dtype):
+    """Values over eight decades and act in the hundreds, any weights: chunks of every kind."""
+    inp, rng = inputs(dtype, 10)
+    x = rng.normal(size=(2, K)) * np.exp(1.5 * rng.normal(size=(2, K)))
+    check(inp, x, rng.uniform(0.02, 0.06, inp.s1_bits.shape) / 4, rng.uniform(0.002, 0.004, inp.s2_bits.shape), "plain", "wide")
+
+
+@pytest.mark.parametrize("order", ["plain", "operand"])
 @pytest.mark.parametrize("dtype,ratio", [("f16", 14), ("f16", 24), ("bf16", 14), ("bf16", 20)])
 def test_a_large_act_whose_weights_are_zero(dtype, ratio, order):
     """The same for the down product: one column of act in every chunk has up scales 2^ratio times the others'."""
@@ -123,5 +145,5 @@ def test_values_beside_digits_in_one_group(dtype):
     inp, rng = inputs(dtype, 9)
     x = rng.normal(size=(2, K)).clip(-3, 3)
     for c in (0, 5, 6, 17, 31):
-        x[:, 32 * c:32 * c + 32] = rng.normal(size=(2, 32)) * np.where(rng.random((2, 32)) < 0.5, 100.0, 3e-6 if dtype == "f16" else 1e-9)
+        x[:, 32 * c:32 * c + 32] = rng.normal(size=(2, 32)) * np.where(np.arange(32) % 11 == 0, 100.0, 3e-6 if dtype == "f16" else 1e-9)
     check(inp, x, rng.uniform(0.002, 0.004, inp.s1_bits.shape), rng.uniform(0.002, 0.02, inp.s2_bits.shape), "plain", "mixed")
