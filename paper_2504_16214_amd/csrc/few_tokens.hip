@@ -589,10 +589,13 @@ int launch_few_gate_up(const void* X, const FewRoute* route, const int32_t* ids,
     return (dt == kF16 ? gate_up<kF16, RT, kDeep, PRE, KP> : gate_up<kBF16, RT, kDeep, PRE, KP>)(X, r, ids, qw, s, z, act, units, T, topk, E, K, N, stream);
   };
   auto pick = [&](auto route_in, auto parts) { return pre ? with(route_in, One{}, parts) : with(route_in, Zero{}, parts); };
-  // 64 columns a workgroup, unless that leaves CUs without one: then 32, and the reduction in halves.  (4 tokens of 7168 x 2048, top 1, 128 workgroups
-  // of 64 columns: 25.5 -> 24.0 us; 16 tokens of 256 x 512, top 2, 256 of them: 8.2, in halves 9.1.  A half of less than two groups is not
-  // worth its waves: 11 tokens of 256 x 512, 8.1, in halves 8.7; 4 tokens of 768 x 512, 8.0, in halves 7.5.)
-  const bool halves = K >= 512 && (long long)N / 64 * T * topk < 256;
+  // 64 columns a workgroup, unless that leaves CUs without one, or a few with one more than the rest: then 32, and the reduction in halves.  (4 tokens of
+  // 7168 x 2048, top 1, 128 workgroups of 64 columns: 25.5 -> 24.0 us; 16 tokens of 256 x 512, top 2, 256 of them: 8.2, in halves 9.1.  A half of less than
+  // two groups is not worth its waves: 11 tokens of 256 x 512, 8.1, in halves 8.7; 4 tokens of 768 x 512, 8.0, in halves 7.5.  257 to 383 and 513 to 639 of
+  // them, K 1024 and more: 180 random calls 1.05 times as fast from memory and 1.04 from the cache, 3 % slower at the worst (one token of 5248 x 7040, top 3, 330 of
+  // them, 63.7 -> 55.1); 384 to 512 of them 0.98, with K below 1024 1.00 and from the cache 0.95.)
+  const long long columns = (long long)N / 64 * T * topk;      // workgroups of 64
+  const bool halves = columns < 256 ? K >= 512 : K >= 1024 && columns > 256 && columns < 640 && (columns - 1) % 256 < 127;
   if (route) return halves ? pick(One{}, Two{}) : pick(One{}, One{});
   return halves ? pick(Zero{}, Two{}) : pick(Zero{}, One{});
 }

@@ -18,9 +18,10 @@ if torch.cuda.is_available():
 
 
 # Workgroups of 64 columns (N / 64 * T * topk): 252 | 256; K 384 (never halved), 512 and 640 (2 + 2, 2 + 3 groups), 896 (4 + 3);
-# K 4224, 8320 and 8448: more activations than the first loads bring (1, 2 rounds)
+# K 4224, 8320 and 8448: more activations than the first loads bring (1, 2 rounds); 256 | 378 | 384, 528 | 640 workgroups, K 1024 and more
 @pytest.mark.parametrize("K,N,E,topk,T", [(512, 8064, 4, 1, 2), (512, 8192, 4, 1, 2), (384, 128, 4, 2, 3), (640, 384, 8, 3, 2), (896, 896, 8, 1, 5),
-                                          (4224, 256, 4, 2, 1), (8320, 128, 4, 1, 1), (8448, 1024, 16, 4, 1)])
+                                          (4224, 256, 4, 2, 1), (8320, 128, 4, 1, 1), (8448, 1024, 16, 4, 1),
+                                          (1024, 8192, 2, 1, 2), (1152, 8064, 2, 1, 3), (1024, 8192, 2, 1, 3), (1024, 2816, 4, 1, 12), (1024, 2560, 4, 1, 16)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_forms_of_the_gate_up_product(K, N, E, topk, T, dtype):
     cfg = MoEConfig("few_forms", T=T, K=K, N=N, E=E, topk=topk, group=128, dtype=dtype, seed=K + N + T)
