@@ -72,8 +72,11 @@ struct TwoGroupGeom {
   static constexpr int SR = RROWS / 32;                     // row sums: rows per wave and step
   static constexpr int ROFF = NBUF * STAGE;                 // ring of four groups of four stages
   static constexpr int TOFF = ROFF + 4 * RROWS * 16;        // slot of every tile row
-  static constexpr int OOFF = TOFF + 256 * 4;               // its offset in C (c_bytes)
-  static constexpr int ZOFF = OOFF + 256 * 4;               // zeros, as large as one group of the ring
+  // Stores by offset hold on to more registers than a block of six parts or more has left (91 spilled instead of 9 at eight: gate/up of 2921 slots
+  // by 3 on 120 experts, K 1024, N 6144, 456 -> 562 us).
+  static constexpr bool BY_OFFSET = ML <= 5;
+  static constexpr int OOFF = TOFF + 256 * 4;               // BY_OFFSET: its offset in C (c_bytes)
+  static constexpr int ZOFF = OOFF + (BY_OFFSET ? 256 * 4 : 0);      // zeros, as large as one group of the ring
   static constexpr int WOFF = ZOFF + RROWS * 16;            // STREAM: three buffers of 256 rows x 128 bytes
   static constexpr int LDS = WOFF + (STREAM ? 3 * 32768 : 0);
   static_assert(LDS <= 160 * 1024, "LDS");
@@ -143,7 +146,7 @@ tg_tile(const TwoGroupParams& p, unsigned char* lds, int row0, int e, int tile0,
   if (tid < 256) {
     const int s = tid < 32 * ML ? p.sorted_slot_ids[row0 + tid] : -1;
     slots[tid] = s >= 0 && s < p.num_slots ? s : -1;
-    out_rows[tid] = s >= 0 && s < p.num_slots ? (uint32_t)s * (uint32_t)p.N_out * (FUSE ? 1u : 4u) : kNoRow;
+    if constexpr (G::BY_OFFSET) out_rows[tid] = s >= 0 && s < p.num_slots ? (uint32_t)s * (uint32_t)p.N_out * (FUSE ? 1u : 4u) : kNoRow;
   }
   if (DT == kBF16 && tid < G::RROWS) *reinterpret_cast<u32x4*>(lds + G::ZOFF + tid * 16) = u32x4{0, 0, 0, 0};
   __syncthreads();
@@ -295,11 +298,8 @@ tg_tile(const TwoGroupParams& p, unsigned char* lds, int row0, int e, int tile0,
   int gst = 0;                                      // flattened stage
 
   // accumulator register c of a lane: row 8 (c >> 2) + 4 h + (c & 3) of the sub-tile, feature n
-  // Stores by offset hold on to more registers than a block of six parts or more has left (91 spilled instead of 9 at eight: gate/up of 2921 slots
-  // by 3 on 120 experts, K 1024, N 6144, 456 -> 562 us).
-  constexpr bool kByOffset = ML <= 5;
   auto store_tile = [&](int tile) __attribute__((always_inline)) {
-    if (kByOffset && p.c_bytes) {
+    if (G::BY_OFFSET && p.c_bytes) {
       const __amdgpu_buffer_rsrc_t rc = c_rows(p.C, p.c_bytes);
       const bool odd = lane & 1;
 #pragma unroll
