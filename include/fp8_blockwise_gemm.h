@@ -91,8 +91,8 @@ int fp8_moe_grouped_gemm(const uint8_t* A, const float* a_scale, int row_div,
  *       -> grouped FP8 product with W2 [E, K, N] (w2_scale [E, K/128, N/128]) kept in float32 ->
  *       weighted combine in j order, one rounding to dt.  X [T, K] dt, topk_ids [T, topk] int32,
  *       topk_weights [T, topk] float32, out [T, K] dt.  Slots with an expert id outside [0, E)
- *       contribute zero.  K % 128 == 0, N % 128 == 0, E <= 1024.  Six launches on `stream`, no
- *       allocation; `workspace`: at least fp8_moe_layer_workspace_bytes(...) bytes, 256-byte aligned.
+ *       contribute zero.  K % 128 == 0, N % 128 == 0, E <= 1024.  Six launches on `stream`, five
+ *       up to T * K = 2^23 (the first two are one), no allocation; `workspace`: at least fp8_moe_layer_workspace_bytes(...) bytes, 256-byte aligned.
  *
  * All pointers are caller-owned device memory; X, H, out and the weight tensors 16-byte aligned.
  * dt is a moe_dtype (0 = fp16, 1 = bf16).  Each returns a moe_status.

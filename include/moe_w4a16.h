@@ -260,8 +260,8 @@ int moe_route_align(const float* logits, const float* bias, int T, int E, int to
 
 /*
  * Router + layer on one stream: moe_route_align into tables held in the workspace, then the two
- * grouped GEMMs and the combine of moe_w4a16_layer: four launches up to 64 tokens, five beyond, one (fp16) or
- * two (bf16) more for batches on the two-group or the 64-slot tile, two (at most 64 experts, 16 a token) or three for the few tokens that need no bucketing.
+ * grouped GEMMs and the combine of moe_w4a16_layer: four launches up to 64 tokens, five beyond; on the
+ * two-group or the 64-slot tile one more in bf16, and one more from T * K > 2^23 on; two (at most 64 experts, 16 a token) or three for the few tokens that need no bucketing.
  * Arguments as for the two; `workspace` of at least moe_w4a16_routed_layer_workspace_bytes(...)
  * bytes, 256-byte aligned.
  */

@@ -405,9 +405,10 @@ static bool twogroup_pays(long long S, int E, int K, int N, int dt, int pre) {
 }
 
 // Does the layer run on the 64-slot tile (gemm_mid.hpp)?  It reads an expert's weights once for up to 64 rows, works
-// off whole 16-row parts only, and takes activations that were put in order by a launch of their own (4 us; bf16:
-// two, with the sums of act), so the launch has to be large: a quarter of a billion weights in each of an expert's
-// matrices together and two workgroups for each of three on a CU.  Former choice over this tile, lower of two draws, by rows per
+// off whole 16-row parts only, and takes activations that were put in order first (beside the bucketing, or from 2^23 of them on by a launch of
+// their own; in bf16 act's sums are another launch), so the launch has to be large: a quarter of a billion weights in each of an expert's
+// matrices together and two workgroups for each of three on a CU.  (All figures were taken when the reorder was always a launch of 4 us: the line errs
+// to the side of the other tiles, as that of twogroup_pays does.)  Former choice over this tile, lower of two draws, by rows per
 // expert: even routing / experts weighted as 1 / rank / as rank ** -2.4 (2900 calls, 11 shapes, both layouts), stated layout:
 //   256 experts, K 7168, N 2048,  fp16  9: 1.18/1.28/1.12  16: 1.09/1.23/1.23  28: 1.14/1.27/1.28  40: 1.12/1.56/0.97  54: 0.99/1.41/0.93
 //                                 bf16  9: 1.39/1.49/1.43  16: 1.26/1.47/1.38  28: 1.19/1.84/1.09  48: 1.13/1.63/1.01  60: 1.00/1.50/0.96  72: 0.93/1.48/0.93
@@ -887,15 +888,16 @@ static int run_mid(const void* A, const float* sums, int row_div, const int32_t*
 // N 128 ... 14336, 4 to 256 experts, top 1 to 10), within 10 % (vector) and 6 % (tiled) on average.
 // Calls it takes that are slower than on the tiles by more than 3 %, cached or not / calls it leaves there that would be faster by more:
 // independent tokens 0 / 846 of 8538 (the fits saw 5180 of them), experts weighted as 1 / rank 5 / 116 of 2073, all tokens alike 9 / 72 of
-// 2089 (20 % at most).  Above 128 million weights for all slots there is least to gain (0.8 to 1) and alike tokens cost most (31 of the 2089
-// with twice that).  The fit is older than the products' present form, 2 to 15 % faster: the line errs to the side of the tiles.
-// More than 16 tokens, one expert each, keep the line they had, five rounds of down workgroups; 150 of the calls left
+// 2089 (20 % at most), all counted with the products' former times.  Above 128 million weights for all slots there is least to gain (0.8 to 1) and alike tokens
+// cost most (31 of the 2089 with twice that).  The products' present form is 2 to 15 % faster, so the line errs to the side of the tiles: of 4440 random calls that it
+// takes (independent tokens, a third of them with wide activations, plain layout) all are faster than on the tiles, 1.08x the least, 2.3x on average with weights in the cache and
+// 2.0x in memory.  More than 16 tokens, one expert each, keep the line they had, five rounds of down workgroups; 150 of the calls left
 // are beyond it.
-// Tiled / vector, weights in memory (in the cache), fp16:
-//   7168x2048, 256 experts, top 8: 1 token 58.7 / 41.9 (57.1 / 41.5);   top 1: 4 tokens 45.8 / 24.6 (45.6 / 24.6), 8 52.9 / 39.0
-//   4096x14336, 8, top 2: 1 token 54.9 / 46.4 (54.0 / 42.7);   2048x1408, 64, top 6: 4 tokens 41.3 / 29.9, 5 46.4 / 37.6
-//   2048x2048, 64: top 1, 6 tokens 25.8 / 16.5, 8 27.0 / 17.1, 16 35.7 / 26.9;   top 4, 6 tokens 45.9 / 37.0, 8 55.8 / 47.0
-//   1024x1024, 64: top 2, 12 tokens 27.0 / 16.8, 16 27.5 / 18.1;   256x512, 8, top 2: 16 tokens 19.3 / 8.9
+// Tiled / vector, weights in memory (in the cache), fp16, experts drawn from 64 where there are 256:
+//   7168x2048, 256 experts, top 8: 1 token 62.1 / 44.9 (56.5 / 35.0);   top 1: 4 tokens 47.6 / 27.6 (43.5 / 19.7), 8 57.6 / 42.6
+//   4096x14336, 8, top 2: 1 token 57.9 / 46.1 (52.1 / 35.5);   2048x1408, 64, top 6: 4 tokens 43.9 / 33.6, 5 48.5 / 38.2
+//   2048x2048, 64: top 1, 6 tokens 28.2 / 18.7, 8 29.1 / 20.5, 16 38.7 / 28.5
+//   1024x1024, 64: top 2, 12 tokens 28.0 / 18.3, 16 29.0 / 19.3;   256x512, 8, top 2: 16 tokens 22.0 / 9.1
 static bool few_tokens_pay(int T, int topk, int E, int K, int N, int dt, int pre) {
   const long long S = (long long)T * topk, nk = (long long)N * K;
   if (S > 32 || S * nk > 128000000LL || (T > 16 && T * (long long)K > 20480)) return false;

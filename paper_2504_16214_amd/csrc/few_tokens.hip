@@ -23,7 +23,7 @@
 // call; the products with 128 + q that this form replaced lost 2^-24 of 143 times the largest.
 //
 // What bounds it: two launches of 5 to 6 us each beside the stream of weights (gate/up of one token of 7168 x 2048, 256 experts, top 8, 118 MB from
-// memory, 24.9 us and 4.7 TB/s; down 16.0; 44.5 -> 40.5 the call.  With products of float16 pairs on the vector unit, 77 instructions a KB of
+// memory, 25.6 us and 4.6 TB/s; down 15.9; 44.6 -> 41.5 the call.  With products of float16 pairs on the vector unit, 77 instructions a KB of
 // weights where there are 40 now, they took 27.8 and 19.4, and no less with the weights in the cache).  Zero points taken out in whole numbers
 // cost 1 % (that call with its weights in the cache 34.4 -> 34.7 us, from memory 43.9 -> 44.7; 12 tokens of 1024 x 1024, 64 experts, top 2, 12.1 -> 12.3 and 18.4).
 // Activations as wide as x e^(1.5 y), act in the hundreds: 20 calls of 15 to 100 us that were the slowest beside the float16 pairs while every chunk with

@@ -281,8 +281,9 @@ __device__ __forceinline__ int xcd_contiguous_index(int pid, int total) {
 // hardware drops what is stored there.  A branch per row costs its mask and a 64-bit address, and behind stores that may
 // or may not have been sent the compiler no longer knows how many loads are in flight, so it waits for more of
 // them than it has to.  Planes that 32 bits do not reach (c_plane_bytes) are stored with a branch.  The tiles of 64 rows and
-// more use it (layer, 64 experts, K 2048, N 1408, groups of 64: 4096 tokens f16 768 -> 752 us, bf16 844 -> 821, 1024 tokens of skewed
-// routing 219 -> 214 and 242 -> 238; two-group tile: see there); the smaller ones and the 64-slot tile gain nothing.  What their float32 rows
+// more use it, 64-row tiles only with groups below 128, bf16 ones of 128 rows likewise (see kByOffset), and two-group blocks of up to five parts (layer, 64 experts,
+// K 2048, N 1408, groups of 64: 4096 tokens f16 768 -> 752 us, bf16 844 -> 821, 1024 tokens of skewed
+// routing 219 -> 214 and 242 -> 238 in replayed graphs, within the spread when called one by one); the smaller ones and the 64-slot tile gain nothing.  What their float32 rows
 // cost is the memory's: 59 MB written beside 1.9 GB read take 56 us, 117 MB 75, however they are stored.
 constexpr uint32_t kNoRow = 0xF0000000u;      // (a column's offset is below 2^28: the sum stays in 32 bits)
 inline uint32_t c_plane_bytes(long long rows, long long row_bytes) {
